@@ -54,10 +54,9 @@ def kernel_shares(w):
         "grad_q": (U + proj, 2 * ds),                # dphi_Q, projection of Q again (tanh and its derivative), dQ = dz . W
         "grad_k": (U + proj, 3 * ds),                # dphi_K, same
         "stream_totals_kv": (0.0, 0.0), "stream_totals_qg": (0.0, 0.0), "segment_scan": (0.0, 0.0),
-        # generic family: one replay kernel forward; the key/value kernel forms dV and dK
+        # generic family: hashing and read-out are credited to the output kernel; one kernel forms all three gradients
         "simple_fwd_replay": (proj + 2 * U, 4 * ds + 4),
-        "simple_bwd_keyvalue": (proj + 2 * U + U + proj / 2, 6 * ds + 4),
-        "simple_bwd_query": (U + proj / 2, 2 * ds),
+        "simple_grads": (2 * proj + 4 * U, 8 * ds + 4),
     }
 
 

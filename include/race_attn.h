@@ -152,7 +152,7 @@ race_status_t race_attn_bwd_beta(const race_attn_desc_t *desc, const void *Q, co
  * nothing has written to it since, and this call is stream-ordered after that forward.  A workspace that does not
  * hold that forward's data gives wrong gradients, never an out-of-bounds access.  Arguments, outputs, dbeta
  * (may be NULL) and error behaviour are those of race_attn_bwd_beta, whose results it reproduces bit for bit.
- * Kernel families that keep no such statistics recompute them (the call is then race_attn_bwd_beta). */
+ * Both kernel families keep them. */
 race_status_t race_attn_bwd_saved(const race_attn_desc_t *desc, const void *Q, const void *K, const void *V,
                                   const void *O, const float *den, const void *dO,
                                   const uint64_t *proj_seeds, void *dQ, void *dK, void *dV, float *dbeta,
@@ -219,9 +219,9 @@ const char *race_attn_last_error(void);
 
 /* Which kernel family a descriptor is served by: 0 = invalid/unsupported, 1 = generic fp32-math
  * kernels, 2 = bf16 MFMA kernels.  Informational (benchmarks and tests report it).
- * The generic kernels serve fp32 tensors and every bf16 shape without an MFMA instantiation; they keep per-table
- * partial results of every token in the workspace (3 * B*H*L*N*d floats for the backward pass), and a descriptor whose
- * partial results would exceed 16 GiB is RACE_ERR_UNSUPPORTED (e.g. fp32, d = 64, L = 4: B*H*N beyond 5.6 million).
+ * The generic kernels serve fp32 tensors and every bf16 shape without an MFMA instantiation; they are not a long-context
+ * path, and a descriptor with 3 * B*H*L*N*d floats beyond 16 GiB is RACE_ERR_UNSUPPORTED (e.g. fp32, d = 64, L = 4: B*H*N
+ * beyond 5.6 million).
  * Test switch: with RACE_ATTN_FORCE_GENERIC=1 in the environment every descriptor is planned on the generic kernels
  * (the tests use it to run one problem on both families; it is read at every call). */
 int race_attn_kernel_family(const race_attn_desc_t *desc);

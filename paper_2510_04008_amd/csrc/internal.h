@@ -36,10 +36,14 @@ struct Plan {
     size_t off_stateA;  // per-segment bucket statistics, (BH, nseg, ...) fp32
     size_t off_stateB;  // second set (backward only: cotangent statistics)
     size_t bytes_state;
-    size_t off_part;    // per-table partial results (simple family only)
+    int rt;             // generic family: 16-token row tiles per tile (tiles of 16 rt tokens)
+    size_t off_part;    // generic family: 1 / |x| of the rows of Q and K (unit-norm option)
     size_t bytes_part;
-    size_t off_massQ;   // MFMA family: the hashed rows of Q and of K, (BH, N, Lc * Pc) fp32 each (one float per token,
-    size_t off_massK;   // table and hyperplane: the per-bit soft-hash masses every pass rebuilds phi from)
+    size_t off_carry;   // generic family: running statistics inside segments of several tiles
+    size_t bytes_carry;
+    size_t off_massQ;   // the hashed rows of Q and of K, (BH, N, Lc * Pc) fp32 each (one float per token, table and
+    size_t off_massK;   // hyperplane: the per-bit soft-hash masses every pass rebuilds phi from); generic family: followed
+                        // by the projections themselves, in the same layout
     size_t bytes_mass;
     size_t fwd_bytes;   // the leading part of the workspace that the forward pass uses
     size_t off_dbeta;   // partial cotangents of beta: (2 sides, BH, dbeta_parts) fp32, backward only
@@ -76,6 +80,10 @@ struct ProfileScope {
     hipStream_t st_;
 };
 
+// In-place scan of per-segment states (BH, nseg, stride) fp32, stride a multiple of 4 (generic_kernels.hip).  mode 0: exclusive
+// prefix over the segments, 1: exclusive suffix, 2: the total over all segments, into segment 0 only.
+hipError_t scan_states(const char *name, float *state, int nseg, int BH, size_t stride, int mode, hipStream_t st);
+
 // dbeta[bh] = sum over the two sides and the dbeta_parts partial sums of part, in index order (simple_kernels.hip).
 hipError_t reduce_dbeta(const Plan &p, const float *part, float *dbeta, hipStream_t st);
 
@@ -84,7 +92,9 @@ hipError_t calibration_copy(void *dst, const void *src, size_t bytes, hipStream_
 // Dense bf16 MFMA loop on register operands (mfma_kernels.hip).
 hipError_t calibration_mfma(int workgroups, int iters, int vector_ops, float *sink, hipStream_t st);
 
-// ---- simple family (simple_kernels.hip)
+// ---- generic family (generic_kernels.hip; taps and decoding in simple_kernels.hip)
+void generic_geometry(int64_t chunk, Plan *p);         // tile and segment length (rt, seg_len)
+size_t generic_state_floats(const Plan &p);            // floats per segment state
 hipError_t simple_fwd(const Plan &p, const void *Q, const void *K, const void *V, void *O, float *den,
                       char *ws, hipStream_t st);
 hipError_t simple_bwd(const Plan &p, const void *Q, const void *K, const void *V, const void *O,

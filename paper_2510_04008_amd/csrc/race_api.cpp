@@ -20,7 +20,7 @@ namespace {
 
 thread_local std::string g_last_error;
 
-// largest per-table partial-result area the generic kernels are offered (their workspace grows like L * N * d)
+// largest problem the generic kernels are offered, as the bytes of one fp32 gradient row per token and table, three times
 constexpr size_t kGenericPartialLimit = static_cast<size_t>(16) << 30;
 
 size_t align256(size_t x) { return (x + 255) & ~static_cast<size_t>(255); }
@@ -206,24 +206,19 @@ race_status_t make_plan(const race_attn_desc_t *desc, Plan *pl)
 
     const int64_t n = p.N > 0 ? p.N : 1;
     if (p.family == kFamilySimple) {
-        // enough workgroups to fill 256 CUs a few times over, segments of at least 16 tokens (the kernels take the
-        // tokens of a segment one after the other: short sequences want many short segments)
-        int64_t want = (2048 + static_cast<int64_t>(p.BH) * p.L - 1) / (static_cast<int64_t>(p.BH) * p.L);
-        int64_t len = desc->chunk > 0 ? desc->chunk : (n + want - 1) / want;
-        if (desc->chunk == 0 && len < 16) len = 16;
-        len = (len + 7) / 8 * 8;
-        p.seg_len = len;
-        p.nseg = static_cast<int>((n + len - 1) / len);
-        if ((n + len - 1) / len > 65535) return RACE_ERR_UNSUPPORTED;
+        generic_geometry(desc->chunk, &p);
+        p.nseg = static_cast<int>((n + p.seg_len - 1) / p.seg_len);
+        if ((n + p.seg_len - 1) / p.seg_len > 65535) return RACE_ERR_UNSUPPORTED;
         p.bytes_W = align256(static_cast<size_t>(p.H) * p.LP * p.d * sizeof(float));
-        p.bytes_state = align256(static_cast<size_t>(p.BH) * p.L * p.nseg * p.R * (p.d + 1) * sizeof(float));
-        const size_t fwd_part = static_cast<size_t>(p.BH) * p.L * n * (p.d + 1) * sizeof(float);
-        const size_t bwd_part = static_cast<size_t>(p.BH) * p.L * n * p.d * sizeof(float) * 3;
-        p.bytes_part = align256(fwd_part > bwd_part ? fwd_part : bwd_part);
-        // these kernels keep per-table partial results of every token in the workspace (L * N * d floats): they are
-        // the fp32 reference path, not a long-context path
-        if (p.bytes_part > kGenericPartialLimit) return RACE_ERR_UNSUPPORTED;
-        p.dbeta_parts = p.L * p.nseg;
+        p.bytes_state = align256(static_cast<size_t>(p.BH) * p.nseg * generic_state_floats(p) * sizeof(float));
+        p.bytes_mass = align256(static_cast<size_t>(p.BH) * n * p.LP * 2 * sizeof(float));
+        p.bytes_part = align256(static_cast<size_t>(p.BH) * n * 2 * sizeof(float));
+        p.bytes_carry = (p.causal && p.seg_len > 16 * p.rt) ? p.bytes_state : 0;
+        // the fp32 path is not a long-context path: problems beyond this size are refused
+        const size_t per_table = static_cast<size_t>(p.BH) * p.L * n * sizeof(float);
+        const size_t fwd_part = per_table * (p.d + 1), bwd_part = per_table * p.d * 3;
+        if (align256(fwd_part > bwd_part ? fwd_part : bwd_part) > kGenericPartialLimit) return RACE_ERR_UNSUPPORTED;
+        p.dbeta_parts = p.nseg;
     } else {
         // two workgroups' worth of segments per CU and head-batch; multiples of the 32-token tile
         int64_t want = (512 + p.BH - 1) / p.BH;
@@ -240,17 +235,18 @@ race_status_t make_plan(const race_attn_desc_t *desc, Plan *pl)
         p.dbeta_parts = mfma_dbeta_parts(p);
     }
     p.bytes_dbeta = align256(static_cast<size_t>(2) * p.BH * p.dbeta_parts * sizeof(float));
-    // [W | key/value statistics | hashed Q | hashed K] is what the forward pass uses (and leaves behind);
-    // [cotangent statistics | per-table partial results | parts of dbeta] follow
+    // [W | key/value statistics | hashed Q | hashed K | row norms | carry] is what the forward pass uses (and leaves
+    // behind); [cotangent statistics | parts of dbeta] follow
     p.off_W = 0;
     p.off_stateA = p.off_W + p.bytes_W;
     p.off_massQ = p.off_stateA + p.bytes_state;
     p.off_massK = p.off_massQ + p.bytes_mass;
-    p.off_stateB = p.off_massK + p.bytes_mass;
-    p.off_part = p.off_stateB + p.bytes_state;
-    p.off_dbeta = p.off_part + p.bytes_part;
+    p.off_part = p.off_massK + p.bytes_mass;
+    p.off_carry = p.off_part + p.bytes_part;
+    p.off_stateB = p.off_carry + p.bytes_carry;
+    p.off_dbeta = p.off_stateB + p.bytes_state;
     p.total = p.off_dbeta + p.bytes_dbeta;
-    p.fwd_bytes = (p.family == kFamilyMfma) ? p.off_stateB : p.off_dbeta;
+    p.fwd_bytes = p.off_stateB;
     *pl = p;
     return RACE_OK;
 }
@@ -428,9 +424,8 @@ race_status_t backward(const race_attn_desc_t *desc, const void *Q, const void *
     if ((s = check_workspace(p, workspace, workspace_bytes, p.total)) != RACE_OK) return s;
     char *ws = static_cast<char *>(workspace);
     hipStream_t st = reinterpret_cast<hipStream_t>(stream);
-    // the MFMA family's forward leaves its projection image and segment-start statistics where the backward
-    // pass looks for them; the generic family's forward reuses that area for other things and starts over
-    p.fwd_state_kept = (saved && p.family == kFamilyMfma) ? 1 : 0;
+    // the forward leaves its projection image, hashed rows and segment-start statistics where the backward pass looks for them
+    p.fwd_state_kept = saved ? 1 : 0;
     if (!p.fwd_state_kept && (s = upload_projection(p, proj_seeds, ws, st)) != RACE_OK) return s;
     hipError_t e = (p.family == kFamilyMfma) ? mfma_bwd(p, Q, K, V, O, den, dO, dQ, dK, dV, dbeta, ws, st)
                                              : simple_bwd(p, Q, K, V, O, den, dO, dQ, dK, dV, dbeta, ws, st);
