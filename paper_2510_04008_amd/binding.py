@@ -1,5 +1,6 @@
-"""Thin ctypes binding of librace_attn.so: argument marshalling only.  Every step of the path runs in
-the library's HIP kernels; torch is used for device memory and streams.  Names follow include/race_attn.h.
+"""Thin binding of librace_attn.so: argument marshalling only.  Every step of the path runs in the library's HIP kernels;
+torch is used for device memory and streams.  Names follow include/race_attn.h.  The calls of a training or serving loop go
+through the extension module _native (csrc/native_binding.cpp), the rest through ctypes.
 """
 from __future__ import annotations
 
@@ -33,6 +34,7 @@ class RaceAttnError(RuntimeError):
 
 
 _lib = None
+_native_module = None
 
 
 def lib() -> ctypes.CDLL:
@@ -90,6 +92,20 @@ def lib() -> ctypes.CDLL:
         L.race_attn_last_error.restype = ctypes.c_char_p
         _lib = L
     return _lib
+
+
+def _native():
+    """The extension module (which needs torch's libraries in the process, hence not at import)."""
+    global _native_module
+    if _native_module is None:
+        _torch()
+        lib()
+        if not os.path.exists(os.path.join(_HERE, "_native.so")):
+            from . import build as _build
+            _build.build()
+        from . import _native as module
+        _native_module = module
+    return _native_module
 
 
 def make_desc(B: int, H: int, N: int, d: int, L: int, P: int, sharpening: float, causal: bool,
@@ -157,18 +173,16 @@ def race_attn_expand_projection(desc: RaceAttnDesc, proj_seeds: Sequence[int]) -
 
 def race_attn_fwd(desc: RaceAttnDesc, Q, K, V, proj_seeds: Sequence[int], O=None, den=None,
                   workspace=None, stream=None):
-    torch = _torch()
-    for t, n in ((Q, "Q"), (K, "K"), (V, "V")):
-        _check_tensor(t, desc, n)
-    if O is None:
-        O = torch.empty_like(V)
-    if den is None:
-        den = torch.empty((desc.B, desc.H, desc.N), dtype=torch.float32, device=V.device)
-    _check_tensor(O, desc, "O")
-    _check_tensor(den, desc, "den", (desc.B, desc.H, desc.N), torch.float32)
-    workspace, nbytes = _workspace(desc, workspace, V.device)
-    st = lib().race_attn_fwd(ctypes.byref(desc), Q.data_ptr(), K.data_ptr(), V.data_ptr(), _seeds(proj_seeds),
-                             O.data_ptr(), den.data_ptr(), workspace.data_ptr(), nbytes, _stream(stream))
+    if O is None or den is None or workspace is None:
+        torch = _torch()
+        for t, n in ((Q, "Q"), (K, "K"), (V, "V")):
+            _check_tensor(t, desc, n)
+        if O is None:
+            O = torch.empty_like(V)
+        if den is None:
+            den = torch.empty((desc.B, desc.H, desc.N), dtype=torch.float32, device=V.device)
+        workspace, _ = _workspace(desc, workspace, V.device)
+    st = (_native_module or _native()).fwd(desc, Q, K, V, proj_seeds, O, den, workspace, stream)
     if st != RACE_OK:
         raise RaceAttnError(st, "race_attn_fwd")
     return O, den
@@ -176,86 +190,55 @@ def race_attn_fwd(desc: RaceAttnDesc, Q, K, V, proj_seeds: Sequence[int], O=None
 
 def race_attn_fwd_static(desc: RaceAttnDesc, Q, K, V, proj_seeds: Sequence[int], O, den, stream=None):
     """race_attn_fwd on the library's built-in scratch array; the caller passes every output (nothing is allocated)."""
-    torch = _torch()
-    for t, n in ((Q, "Q"), (K, "K"), (V, "V"), (O, "O")):
-        _check_tensor(t, desc, n)
-    _check_tensor(den, desc, "den", (desc.B, desc.H, desc.N), torch.float32)
-    st = lib().race_attn_fwd_static(ctypes.byref(desc), Q.data_ptr(), K.data_ptr(), V.data_ptr(), _seeds(proj_seeds),
-                                    O.data_ptr(), den.data_ptr(), _stream(stream))
+    st = (_native_module or _native()).fwd(desc, Q, K, V, proj_seeds, O, den, None, stream)
     if st != RACE_OK:
         raise RaceAttnError(st, "race_attn_fwd_static")
     return O, den
 
 
+def _backward(where, saved, desc, Q, K, V, O, den, dO, proj_seeds, dQ, dK, dV, dbeta, workspace, stream):
+    if dQ is None or dK is None or dV is None or workspace is None:
+        torch = _torch()
+        for t, n in ((Q, "Q"), (K, "K"), (V, "V"), (O, "O"), (dO, "dO")):
+            _check_tensor(t, desc, n)
+        dQ = torch.empty_like(Q) if dQ is None else dQ
+        dK = torch.empty_like(K) if dK is None else dK
+        dV = torch.empty_like(V) if dV is None else dV
+        workspace, _ = _workspace(desc, workspace, V.device)
+    st = (_native_module or _native()).bwd(desc, Q, K, V, O, den, dO, proj_seeds, dQ, dK, dV, dbeta, workspace, stream, saved)
+    if st != RACE_OK:
+        raise RaceAttnError(st, where)
+    return dQ, dK, dV
+
+
+def _new_dbeta(desc, V):
+    torch = _torch()
+    return torch.empty((desc.B, desc.H), dtype=torch.float32, device=V.device)
+
+
 def race_attn_bwd(desc: RaceAttnDesc, Q, K, V, O, den, dO, proj_seeds: Sequence[int], dQ=None, dK=None, dV=None,
                   workspace=None, stream=None):
-    torch = _torch()
-    for t, n in ((Q, "Q"), (K, "K"), (V, "V"), (O, "O"), (dO, "dO")):
-        _check_tensor(t, desc, n)
-    _check_tensor(den, desc, "den", (desc.B, desc.H, desc.N), torch.float32)
-    dQ = torch.empty_like(Q) if dQ is None else dQ
-    dK = torch.empty_like(K) if dK is None else dK
-    dV = torch.empty_like(V) if dV is None else dV
-    for t, n in ((dQ, "dQ"), (dK, "dK"), (dV, "dV")):
-        _check_tensor(t, desc, n)
-    workspace, nbytes = _workspace(desc, workspace, V.device)
-    st = lib().race_attn_bwd(ctypes.byref(desc), Q.data_ptr(), K.data_ptr(), V.data_ptr(), O.data_ptr(),
-                             den.data_ptr(), dO.data_ptr(), _seeds(proj_seeds), dQ.data_ptr(), dK.data_ptr(),
-                             dV.data_ptr(), workspace.data_ptr(), nbytes, _stream(stream))
-    if st != RACE_OK:
-        raise RaceAttnError(st, "race_attn_bwd")
-    return dQ, dK, dV
+    return _backward("race_attn_bwd", False, desc, Q, K, V, O, den, dO, proj_seeds, dQ, dK, dV, None, workspace, stream)
 
 
 def race_attn_bwd_beta(desc: RaceAttnDesc, Q, K, V, O, den, dO, proj_seeds: Sequence[int], dQ=None, dK=None, dV=None,
                        dbeta=None, workspace=None, stream=None):
     """race_attn_bwd plus the cotangent of the temperature per (batch, head): returns dQ, dK, dV, dbeta (B, H)."""
-    torch = _torch()
-    for t, n in ((Q, "Q"), (K, "K"), (V, "V"), (O, "O"), (dO, "dO")):
-        _check_tensor(t, desc, n)
-    _check_tensor(den, desc, "den", (desc.B, desc.H, desc.N), torch.float32)
-    dQ = torch.empty_like(Q) if dQ is None else dQ
-    dK = torch.empty_like(K) if dK is None else dK
-    dV = torch.empty_like(V) if dV is None else dV
-    for t, n in ((dQ, "dQ"), (dK, "dK"), (dV, "dV")):
-        _check_tensor(t, desc, n)
-    dbeta = torch.empty((desc.B, desc.H), dtype=torch.float32, device=V.device) if dbeta is None else dbeta
-    _check_tensor(dbeta, desc, "dbeta", (desc.B, desc.H), torch.float32)
-    workspace, nbytes = _workspace(desc, workspace, V.device)
-    st = lib().race_attn_bwd_beta(ctypes.byref(desc), Q.data_ptr(), K.data_ptr(), V.data_ptr(), O.data_ptr(),
-                                  den.data_ptr(), dO.data_ptr(), _seeds(proj_seeds), dQ.data_ptr(), dK.data_ptr(),
-                                  dV.data_ptr(), dbeta.data_ptr(), workspace.data_ptr(), nbytes, _stream(stream))
-    if st != RACE_OK:
-        raise RaceAttnError(st, "race_attn_bwd_beta")
-    return dQ, dK, dV, dbeta
+    dbeta = _new_dbeta(desc, V) if dbeta is None else dbeta
+    return _backward("race_attn_bwd_beta", False, desc, Q, K, V, O, den, dO, proj_seeds, dQ, dK, dV, dbeta, workspace,
+                     stream) + (dbeta,)
 
 
 def race_attn_bwd_saved(desc: RaceAttnDesc, Q, K, V, O, den, dO, proj_seeds: Sequence[int], workspace, dQ=None, dK=None,
                         dV=None, dbeta=None, want_dbeta: bool = False, stream=None):
     """The backward pass on the workspace that race_attn_fwd of the same inputs left behind (required argument).
     Returns dQ, dK, dV and, if want_dbeta or dbeta is given, dbeta (B, H)."""
-    torch = _torch()
-    for t, n in ((Q, "Q"), (K, "K"), (V, "V"), (O, "O"), (dO, "dO")):
-        _check_tensor(t, desc, n)
-    _check_tensor(den, desc, "den", (desc.B, desc.H, desc.N), torch.float32)
-    dQ = torch.empty_like(Q) if dQ is None else dQ
-    dK = torch.empty_like(K) if dK is None else dK
-    dV = torch.empty_like(V) if dV is None else dV
-    for t, n in ((dQ, "dQ"), (dK, "dK"), (dV, "dV")):
-        _check_tensor(t, desc, n)
-    if dbeta is None and want_dbeta:
-        dbeta = torch.empty((desc.B, desc.H), dtype=torch.float32, device=V.device)
-    if dbeta is not None:
-        _check_tensor(dbeta, desc, "dbeta", (desc.B, desc.H), torch.float32)
     if workspace is None:
         raise ValueError("race_attn_bwd_saved needs the workspace the forward pass wrote")
-    st = lib().race_attn_bwd_saved(ctypes.byref(desc), Q.data_ptr(), K.data_ptr(), V.data_ptr(), O.data_ptr(),
-                                   den.data_ptr(), dO.data_ptr(), _seeds(proj_seeds), dQ.data_ptr(), dK.data_ptr(),
-                                   dV.data_ptr(), dbeta.data_ptr() if dbeta is not None else None,
-                                   workspace.data_ptr(), workspace.numel(), _stream(stream))
-    if st != RACE_OK:
-        raise RaceAttnError(st, "race_attn_bwd_saved")
-    return (dQ, dK, dV, dbeta) if dbeta is not None else (dQ, dK, dV)
+    if dbeta is None and want_dbeta:
+        dbeta = _new_dbeta(desc, V)
+    grads = _backward("race_attn_bwd_saved", True, desc, Q, K, V, O, den, dO, proj_seeds, dQ, dK, dV, dbeta, workspace, stream)
+    return grads + (dbeta,) if dbeta is not None else grads
 
 
 def race_attn_debug_hash(desc: RaceAttnDesc, X, proj_seeds: Sequence[int], want_phi: bool = False,
@@ -299,17 +282,11 @@ def race_attn_state_init(desc: RaceAttnDesc, K, V, proj_seeds: Sequence[int], st
     shape = (desc.B, desc.H, desc.L, 1 << desc.P, desc.d + 1)
     device = K.device if K is not None else (state.device if state is not None else "cuda")
     state = torch.empty(shape, dtype=torch.float32, device=device) if state is None else state
-    _check_tensor(state, desc, "state", shape, torch.float32)
-    if desc.N > 0:
+    if desc.N > 0 and workspace is None:
         _check_tensor(K, desc, "K")
         _check_tensor(V, desc, "V")
-        workspace, nbytes = _workspace(desc, workspace, K.device)
-        wptr = workspace.data_ptr()
-    else:
-        nbytes, wptr = 0, None
-    st = lib().race_attn_state_init(ctypes.byref(desc), K.data_ptr() if desc.N > 0 else None,
-                                    V.data_ptr() if desc.N > 0 else None, _seeds(proj_seeds), state.data_ptr(),
-                                    wptr, nbytes, _stream(stream))
+        workspace, _ = _workspace(desc, workspace, K.device)
+    st = (_native_module or _native()).state_init(desc, K, V, proj_seeds, state, workspace if desc.N > 0 else None, stream)
     if st != RACE_OK:
         raise RaceAttnError(st, "race_attn_state_init")
     return state
@@ -323,24 +300,18 @@ def race_attn_step(desc: RaceAttnDesc, q, k, v, proj_seeds: Sequence[int], state
                    stream=None):
     """One decoding step: q, k, v (B, H, d); state updated in place; returns o (B, H, d) and den (B, H).
     proj_seeds = None: the workspace (then a required argument) still holds W from an earlier step."""
-    torch = _torch()
-    row = (desc.B, desc.H, desc.d)
-    for t, n in ((q, "q"), (k, "k"), (v, "v")):
-        _check_tensor(t, desc, n, row)
-    _check_tensor(state, desc, "state", (desc.B, desc.H, desc.L, 1 << desc.P, desc.d + 1), torch.float32)
-    o = torch.empty_like(v) if o is None else o
-    den = torch.empty((desc.B, desc.H), dtype=torch.float32, device=v.device) if den is None else den
-    _check_tensor(o, desc, "o", row)
-    _check_tensor(den, desc, "den", (desc.B, desc.H), torch.float32)
-    need = race_attn_step_workspace_bytes(desc)
-    if workspace is None:
-        if proj_seeds is None:
-            raise ValueError("race_attn_step without seeds needs the workspace of an earlier step")
-        workspace = torch.empty(need, dtype=torch.uint8, device=v.device)
-    st = lib().race_attn_step(ctypes.byref(desc), q.data_ptr(), k.data_ptr(), v.data_ptr(),
-                              _seeds(proj_seeds) if proj_seeds is not None else None,
-                              state.data_ptr(), o.data_ptr(), den.data_ptr(), workspace.data_ptr(),
-                              workspace.numel() * workspace.element_size(), _stream(stream))
+    if o is None or den is None or workspace is None:
+        torch = _torch()
+        row = (desc.B, desc.H, desc.d)
+        for t, n in ((q, "q"), (k, "k"), (v, "v")):
+            _check_tensor(t, desc, n, row)
+        o = torch.empty_like(v) if o is None else o
+        den = torch.empty((desc.B, desc.H), dtype=torch.float32, device=v.device) if den is None else den
+        if workspace is None:
+            if proj_seeds is None:
+                raise ValueError("race_attn_step without seeds needs the workspace of an earlier step")
+            workspace = torch.empty(race_attn_step_workspace_bytes(desc), dtype=torch.uint8, device=v.device)
+    st = (_native_module or _native()).step(desc, q, k, v, proj_seeds, state, o, den, workspace, stream)
     if st != RACE_OK:
         raise RaceAttnError(st, "race_attn_step")
     return o, den

@@ -1010,14 +1010,6 @@ __global__ __launch_bounds__(1024) void scan_states_kernel(float *state, int nse
         if (e_ != hipSuccess) return e_;                 \
     } while (0)
 
-template <typename K>
-hipError_t allow_lds(K kernel, size_t bytes)
-{
-    if (bytes <= 64 * 1024) return hipSuccess;
-    return hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
-                               static_cast<int>(bytes));
-}
-
 GArgs make_args(const Plan &p, char *ws)
 {
     GArgs a;

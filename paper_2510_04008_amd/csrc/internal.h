@@ -64,7 +64,14 @@ race_status_t make_plan(const race_attn_desc_t *desc, Plan *plan);
 // if the cache is full (kMaxProjectionImages distinct keys) or if pinned memory cannot be allocated; *why then
 // names the reason (static string).
 constexpr size_t kMaxProjectionImages = 4096;
+// The address returned is the device's view of the image.
 const void *projection_image(const Plan &plan, const uint64_t *seeds, size_t *bytes, bool may_allocate, const char **why);
+// Copies `bytes` (a multiple of 16) from mapped pinned host memory to the device with one kernel (simple_kernels.hip).
+hipError_t upload(void *dst, const void *src, size_t bytes, hipStream_t st);
+// Lets `kernel` use `bytes` of dynamic LDS on the current device; asks the runtime once per thread, kernel and device.
+hipError_t allow_lds_bytes(const void *kernel, size_t bytes);
+template <class K>
+inline hipError_t allow_lds(K kernel, size_t bytes) { return allow_lds_bytes(reinterpret_cast<const void *>(kernel), bytes); }
 
 // The library's own device scratch for race_attn_fwd_static (static_scratch.hip): a fixed array in the code object.
 constexpr size_t kStaticScratchBytes = static_cast<size_t>(32) << 20;

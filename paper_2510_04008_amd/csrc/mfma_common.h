@@ -124,7 +124,6 @@ struct KArgs {
     int L_real, P_real;    // the problem's tables and hyperplanes (<= the compiled shape's)
     __host__ __device__ Soft soft() const { return Soft{beta, L_real, P_real}; }
     const bf16raw *Wp;     // (H, LPP, D) bf16, rows in projection-group order
-    const bf16raw *WpT;    // (H, D, LPP) bf16
     float *state;          // (BH, nseg, STATE) fp32
     float *Mq, *Mk;        // (BH, N, L * P) fp32: the hashed rows of Q and K (hash_kernel writes them, every later pass reads them)
     float *dbeta_part;     // (2, BH, workgroups per head-batch) fp32: partial cotangents of beta (backward only)

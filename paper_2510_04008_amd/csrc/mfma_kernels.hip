@@ -684,13 +684,6 @@ using namespace mfma;
         if (e_ != hipSuccess) return e_;                 \
     } while (0)
 
-template <class K>
-hipError_t allow_lds(K kernel, size_t bytes)
-{
-    return hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
-                               static_cast<int>(bytes));
-}
-
 template <class C>
 KArgs make_kargs(const Plan &p, char *ws)
 {
@@ -698,7 +691,6 @@ KArgs make_kargs(const Plan &p, char *ws)
     a.H = p.H; a.nseg = p.nseg; a.causal = p.causal; a.N = p.N; a.seg_len = p.seg_len; a.beta = p.beta;
     a.L_real = p.L; a.P_real = p.P;
     a.Wp = reinterpret_cast<const bf16raw *>(ws + p.off_W);
-    a.WpT = a.Wp + static_cast<size_t>(p.H) * C::LPP * C::D;
     a.state = reinterpret_cast<float *>(ws + p.off_stateA);
     a.Mq = reinterpret_cast<float *>(ws + p.off_massQ);
     a.Mk = reinterpret_cast<float *>(ws + p.off_massK);
@@ -837,7 +829,7 @@ uint16_t host_bf16(float x)
     return static_cast<uint16_t>(b >> 16);
 }
 
-// W (H, L*P, D) -> Wp (H, LPP, D) and WpT (H, D, LPP) in projection-group order: row rho of group g
+// W (H, L*P, D) -> Wp (H, LPP, D) in projection-group order: row rho of group g
 // belongs to the lane half hh = (rho / 4) % 2; with a = rho / 8 and b = rho % 4 the half's slots (a, b)
 // hold, for 8-padded tables, the half's table a/2 and hyperplane 4*(a%2) + b; for 4-padded tables, the half's
 // table a and hyperplane b; the half's table j is table TPL*hh + j of the group.  Rows of padding (slots beyond
@@ -846,7 +838,6 @@ template <class C>
 void pack_t(const Plan &p, const float *W, void *image)
 {
     uint16_t *wp = static_cast<uint16_t *>(image);
-    uint16_t *wpt = wp + static_cast<size_t>(p.H) * C::LPP * C::D;
     for (int hd = 0; hd < p.H; ++hd) {
         for (int row = 0; row < C::LPP; ++row) {
             const int g = row / 32, rho = row % 32, a = rho / 8, hh = (rho / 4) % 2, b = rho % 4;
@@ -858,7 +849,6 @@ void pack_t(const Plan &p, const float *W, void *image)
                 if (j < C::TPL && table < p.L && t < p.P) v = W[(static_cast<size_t>(hd) * p.LP + table * p.P + t) * C::D + c];
                 const uint16_t bits = host_bf16(v);
                 wp[(static_cast<size_t>(hd) * C::LPP + row) * C::D + c] = bits;
-                wpt[(static_cast<size_t>(hd) * C::D + c) * C::LPP + row] = bits;
             }
         }
     }
@@ -912,7 +902,7 @@ size_t mfma_hashed_bytes(const Plan &p)
 
 size_t mfma_projection_bytes(const Plan &p)
 {
-#define X(DD, PP_, LL, PD) if (p.d == DD && p.Pc == PP_ && p.Lc == LL && p.pad == PD) return static_cast<size_t>(p.H) * Cfg<DD, PP_, LL, PD != 0>::LPP * DD * 2 * 2;
+#define X(DD, PP_, LL, PD) if (p.d == DD && p.Pc == PP_ && p.Lc == LL && p.pad == PD) return static_cast<size_t>(p.H) * Cfg<DD, PP_, LL, PD != 0>::LPP * DD * 2;
     RACE_SHAPES(X)
 #undef X
     return 0;

@@ -80,7 +80,7 @@ struct CacheKey {
         return seeds < o.seeds;
     }
 };
-struct CacheEntry { void *pinned; size_t bytes; };
+struct CacheEntry { void *pinned; const void *device_view; size_t bytes; };
 std::mutex g_cache_mutex;
 std::map<CacheKey, CacheEntry> g_cache;
 
@@ -130,12 +130,33 @@ const void *projection_image(const Plan &p, const uint64_t *seeds, size_t *bytes
             *why = "hipHostMalloc(projection image) failed";
             return nullptr;
         }
+        void *view = nullptr;
+        if (hipHostGetDevicePointer(&view, e.pinned, 0) != hipSuccess) {
+            (void)hipHostFree(e.pinned);
+            *why = "hipHostGetDevicePointer(projection image) failed";
+            return nullptr;
+        }
+        e.device_view = view;
         if (p.family == kFamilyMfma) mfma_pack_projection(p, W.data(), e.pinned);
         else std::memcpy(e.pinned, W.data(), W.size() * sizeof(float));
         it = g_cache.emplace(std::move(key), e).first;
     }
     *bytes = it->second.bytes;
-    return it->second.pinned;
+    return it->second.device_view;
+}
+
+hipError_t allow_lds_bytes(const void *kernel, size_t bytes)
+{
+    if (bytes <= 64 * 1024) return hipSuccess;         // what every kernel may use
+    thread_local std::map<std::pair<int, const void *>, size_t> allowed;
+    int dev = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return e;
+    size_t &have = allowed[{dev, kernel}];
+    if (bytes <= have) return hipSuccess;
+    e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(bytes));
+    if (e == hipSuccess) have = bytes;
+    return e;
 }
 
 // ---------------------------------------------------------------- per-kernel timing (benchmark aid)
@@ -285,8 +306,8 @@ race_status_t upload_projection(const Plan &p, const uint64_t *seeds, char *ws, 
         g_last_error = why;
         return may_allocate ? RACE_ERR_HIP : RACE_ERR_NOT_READY;
     }
-    hipError_t e = hipMemcpyAsync(ws + p.off_W, img, bytes, hipMemcpyHostToDevice, st);
-    if (e != hipSuccess) return hip_failed(e, "hipMemcpyAsync(projection image)");
+    hipError_t e = upload(ws + p.off_W, img, bytes, st);
+    if (e != hipSuccess) return hip_failed(e, "upload of the projection image");
     return RACE_OK;
 }
 

@@ -272,6 +272,23 @@ hipError_t decode_step(const Plan &p, const float *W, const void *q, const void 
     return hipGetLastError();
 }
 
+// A few tens of KB over PCIe: every thread has one 16-byte read in flight.  (As a stream-ordered copy through the runtime
+// the same bytes cost a hand-over to a copy engine and back: 8 us of copy between gaps of 10 and 16 us, 35 us in front of
+// every pass, against 3-4 us for this kernel.)
+__global__ __launch_bounds__(256) void upload_kernel(uint4 *dst, const uint4 *src, size_t n16)
+{
+    const size_t i = static_cast<size_t>(blockIdx.x) * 256 + threadIdx.x;
+    if (i < n16) dst[i] = src[i];
+}
+
+hipError_t upload(void *dst, const void *src, size_t bytes, hipStream_t st)
+{
+    const size_t n16 = bytes / 16;
+    hipLaunchKernelGGL(upload_kernel, dim3(static_cast<unsigned>((n16 + 255) / 256)), dim3(256), 0, st, static_cast<uint4 *>(dst),
+                       static_cast<const uint4 *>(src), n16);
+    return hipGetLastError();
+}
+
 // One 16-byte load and one 16-byte store per element, grid-stride: every byte is read once and written once.
 __global__ void __launch_bounds__(256) calibration_copy_kernel(uint4 *__restrict__ dst, const uint4 *__restrict__ src,
                                                                 size_t n16)
