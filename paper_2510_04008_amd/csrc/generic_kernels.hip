@@ -618,8 +618,9 @@ struct GradLds {
     }
 };
 
+// (One workgroup per CU where the accumulators need more than 256 registers; LDS allows no more there either.)
 template <typename T, int RT, int NCT>
-__global__ __launch_bounds__(kThreads, 2) void generic_grads(GArgs a, int sides, const T *Q, const T *K, const T *V, const T *O,
+__global__ __launch_bounds__(kThreads, RT * NCT > 2 ? 1 : 2) void generic_grads(GArgs a, int sides, const T *Q, const T *K, const T *V, const T *O,
                                                              const float *den, const T *dO, const float *stateS, const float *stateD,
                                                              T *dQ, T *dK, T *dV, float *dbeta_part)
 {

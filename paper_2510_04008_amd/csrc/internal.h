@@ -66,8 +66,9 @@ race_status_t make_plan(const race_attn_desc_t *desc, Plan *plan);
 constexpr size_t kMaxProjectionImages = 4096;
 // The address returned is the device's view of the image.
 const void *projection_image(const Plan &plan, const uint64_t *seeds, size_t *bytes, bool may_allocate, const char **why);
-// Copies `bytes` (a multiple of 16) from mapped pinned host memory to the device with one kernel (simple_kernels.hip).
-hipError_t upload(void *dst, const void *src, size_t bytes, hipStream_t st);
+// Copies `bytes` from mapped pinned host memory to the device and zeroes `clear_bytes` at `clear` (both multiples of 16),
+// in one kernel (simple_kernels.hip).
+hipError_t upload(void *dst, const void *src, size_t bytes, void *clear, size_t clear_bytes, hipStream_t st);
 // Lets `kernel` use `bytes` of dynamic LDS on the current device; asks the runtime once per thread, kernel and device.
 hipError_t allow_lds_bytes(const void *kernel, size_t bytes);
 template <class K>
@@ -112,9 +113,11 @@ hipError_t simple_hash(const Plan &p, const void *X, uint8_t *codes, float *phi,
 // interleaved (B, H, L, R, d+1) state (A = state + d, Bsum = state, both strides d+1)
 hipError_t simple_buckets(const Plan &p, const void *K, const void *V, float *A, float *Bsum, int a_stride,
                           int b_stride, char *ws, hipStream_t st);
-// One decoding step (simple_kernels.hip): W fp32 (H, L*P, d) and partial (BH, L, d+1) in the workspace.
-hipError_t decode_step(const Plan &p, const float *W, const void *q, const void *k, const void *v, float *state,
-                       void *o, float *den, hipStream_t st);
+// One decoding step (simple_kernels.hip).  Workspace: W fp32 (H, L*P, d) | shares (BH, decode_shares, d+1) fp32 at off_part | arrival
+// counters (BH) at off_carry, zero between steps.
+int decode_shares(const Plan &p);              // workgroups per (batch, head)
+hipError_t decode_step(const Plan &p, const void *q, const void *k, const void *v, float *state, void *o, float *den, char *ws,
+                       hipStream_t st);
 hipError_t zero_floats(float *dst, size_t n, hipStream_t st);
 
 // ---- MFMA family (mfma_kernels.hip, mfma_grad.hip).  Compiled shapes: X(d, P, L)

@@ -297,7 +297,9 @@ bool any_equal(std::initializer_list<const void *> outs, std::initializer_list<c
     return false;
 }
 
-race_status_t upload_projection(const Plan &p, const uint64_t *seeds, char *ws, hipStream_t st, bool may_allocate = true)
+// Copies the image of W to its place in the workspace (and zeroes `clear_bytes` at `clear` on the way).
+race_status_t upload_projection(const Plan &p, const uint64_t *seeds, char *ws, hipStream_t st, bool may_allocate = true,
+                                void *clear = nullptr, size_t clear_bytes = 0)
 {
     size_t bytes = 0;
     const char *why = "";
@@ -306,7 +308,7 @@ race_status_t upload_projection(const Plan &p, const uint64_t *seeds, char *ws, 
         g_last_error = why;
         return may_allocate ? RACE_ERR_HIP : RACE_ERR_NOT_READY;
     }
-    hipError_t e = upload(ws + p.off_W, img, bytes, st);
+    hipError_t e = upload(ws + p.off_W, img, bytes, clear, clear_bytes, st);
     if (e != hipSuccess) return hip_failed(e, "upload of the projection image");
     return RACE_OK;
 }
@@ -551,8 +553,10 @@ race_status_t make_step_plan(const race_attn_desc_t *desc, Plan *pl)
     pl->off_W = 0;
     pl->bytes_W = align256(static_cast<size_t>(pl->H) * pl->LP * pl->d * sizeof(float));
     pl->off_part = pl->bytes_W;
-    pl->bytes_part = 0;
-    pl->total = pl->off_part + pl->bytes_part;
+    pl->bytes_part = align256(static_cast<size_t>(pl->BH) * decode_shares(*pl) * (pl->d + 1) * sizeof(float));
+    pl->off_carry = pl->off_part + pl->bytes_part;
+    pl->bytes_carry = align256(static_cast<size_t>(pl->BH) * sizeof(unsigned));
+    pl->total = pl->off_carry + pl->bytes_carry;
     return RACE_OK;
 }
 }  // namespace
@@ -575,9 +579,9 @@ race_status_t race_attn_step(const race_attn_desc_t *desc, const void *q, const 
     if ((s = check_workspace(p, workspace, workspace_bytes, p.total)) != RACE_OK) return s;
     char *ws = static_cast<char *>(workspace);
     hipStream_t st = reinterpret_cast<hipStream_t>(stream);
-    // no seeds: the workspace still holds the W that an earlier step put there
-    if (proj_seeds && (s = upload_projection(p, proj_seeds, ws, st)) != RACE_OK) return s;
-    hipError_t e = decode_step(p, reinterpret_cast<const float *>(ws + p.off_W), q, k, v, state, o, den, st);
+    // no seeds: the workspace still holds the W and the cleared counters that an earlier step left there
+    if (proj_seeds && (s = upload_projection(p, proj_seeds, ws, st, true, ws + p.off_carry, p.bytes_carry)) != RACE_OK) return s;
+    hipError_t e = decode_step(p, q, k, v, state, o, den, ws, st);
     return e == hipSuccess ? RACE_OK : hip_failed(e, "race_attn_step launch");
 }
 

@@ -86,105 +86,160 @@ __global__ void simple_hash_tap(Args a, int BH, const T *X, uint8_t *codes, floa
 }
 
 // ------------------------------------------------------------------ incremental decoding
-// One decoding step, one workgroup of 1024 threads per (batch, head).  Threads form TF = 1024 / TL slots of
-// TL = 64 ceil(d / 64) threads; a slot takes the tables slot, slot + TF, ... one after the other, thread c of a slot
-// owning column c: it hashes the new key and query against the table's hyperplanes with its slot-mates (Algorithm 1,
-// steps 2-4), adds the key/value to the table's statistics and reads them with the query, column by column
-// (Algorithm 2's loop body; coalesced rows of d+1 floats).  The sums over tables and the normalisation follow in the
-// same kernel (Algorithm 1, steps 7-8): numerators over the slots in slot order, the normaliser over the wavefronts.
-constexpr int kDecodeThreads = 1024;
+// One decoding step.  A workgroup of 256 threads owns up to 32 G bucket rows of one table of one (batch*head): its threads
+// form G = 256 / (64 ceil(d / 64)) groups, thread c of group g holding column c of rows g, g + G, ... in registers, and one
+// row of the mass column each.  All operands are requested up front, the hyperplanes and the new rows before the statistics
+// (loads return in order), so the hashing of the new key and query (Algorithm 1, steps 2-4: 16 threads per dot product) runs
+// while the statistics arrive; then update, read-out (Algorithm 2's loop body) and the workgroup's share of numerator and
+// normaliser.  The workgroup that finishes last for its (batch*head) adds the shares in order (steps 7-8; bit-reproducible),
+// so a step is one launch.  Bound by the latency of that one chain for a few sequences, by the traffic of the states (read
+// and written once) for many.  d = 128, L = 8, P = 6, against one workgroup of 1024 threads per (batch*head) that took the
+// tables one after the other: B H = 4: 17.5 -> 5.7 us; B H = 256: 36.5 -> 25.3 us (135 MB at 5.4 TB/s; a plain in-place
+// update of as many bytes takes 20 us).
+//
+// The shares cross workgroups (and the XCDs' separate L2s): they are written and read with device-scope accesses, which go
+// to the coherence point, and the counter is bumped only when a workgroup's own writes have completed.  The last workgroup
+// sets the counter back to zero for the next step; the upload of W clears it in the first place.
+constexpr int kDecodeThreads = 256;
+constexpr int kDecodeMaxRows = 32;      // bucket rows of a thread
 
-template <typename T>
-__global__ __launch_bounds__(kDecodeThreads) void decode_step_kernel(int H, int L, int P, int d, float beta, int unit, const float *W,
-                                                                     const T *q, const T *k, const T *v, float *state,
-                                                                     T *o, float *den)
+__device__ __forceinline__ float4 load_quad(const float *p) { return *reinterpret_cast<const float4 *>(p); }
+__device__ __forceinline__ float4 load_quad(const bf16_t *p)
 {
-    extern __shared__ float lds[];
+    const uint2 w = *reinterpret_cast<const uint2 *>(p);
+    return float4{__uint_as_float(w.x << 16), __uint_as_float(w.x & 0xffff0000u), __uint_as_float(w.y << 16),
+                  __uint_as_float(w.y & 0xffff0000u)};
+}
+
+// ROWS: bucket rows per thread (R = ROWS G shares-per-table, or R < G and ROWS = 1); NC: 64-column pieces of d.
+template <typename T, int ROWS, int NC>
+__global__ __launch_bounds__(kDecodeThreads, NC <= 2 && ROWS <= 16 ? 8 : 4) void decode_step_kernel(
+    int H, int L, int P, int d, float beta, int unit, const float *W, const T *q, const T *k, const T *v, float *state, float *part,
+    unsigned *arrived, T *o, float *den)
+{
+    __shared__ float zs[18];                        // projections of q (2 t) and k (2 t + 1), then the squared lengths
+    __shared__ float2 bits[16];                     // masses (-1 side, +1 side) of bit t of k (t) and q (P + t)
+    __shared__ float2 phi[256];                     // assignments (key, query) of the workgroup's rows
+    __shared__ float nred[kDecodeThreads], dred[kDecodeThreads / 64];
+    __shared__ unsigned last;
+    constexpr int TL = 64 * NC, G = kDecodeThreads / TL;
     const int R = 1 << P, d1 = d + 1;
-    const int TL = (d + 63) & ~63, TF = kDecodeThreads / TL, NWV = TL / 64;
-    const int tid = threadIdx.x, slot = tid / TL, c = tid % TL, lane = tid & 63, wv = c >> 6;
-    const int bh = blockIdx.x, h = bh % H;
-    float *zred = lds;                              // [TF][2P+2][NWV] partial projections, then the rows' squared lengths
-    float *pq = zred + TF * (2 * P + 2) * NWV;      // [TF][2P][2]   per-bit masses (+1 side, -1 side)
-    float *phi = pq + TF * 2 * P * 2;               // [TF][2][R]    assignments of the query (0) and the key (1)
-    float *numred = phi + TF * 2 * R;               // [TF][d]       numerators per slot
-    float *dred = numred + TF * d;                  // [16]          normaliser per wavefront
-    const bool active = slot < TF, colok = active && c < d;
-    const float xq = colok ? load_elem(q, static_cast<size_t>(bh) * d + c) : 0.f;
-    const float xk = colok ? load_elem(k, static_cast<size_t>(bh) * d + c) : 0.f;
-    const float vv = colok ? load_elem(v, static_cast<size_t>(bh) * d + c) : 0.f;
-    float num = 0.f, dn = 0.f;
-    for (int l0 = 0; l0 < L; l0 += TF) {
-        const int l = l0 + slot;
-        const bool on = active && l < L;
-        const float *Wl = W + (static_cast<size_t>(h) * L + (on ? l : 0)) * P * d;
-        for (int t = 0; t <= P; ++t) {              // t = P: the squared lengths |q|^2, |k|^2 instead of a projection
-            const float w = (on && c < d) ? (t < P ? Wl[t * d + c] : 1.f) : 0.f;
-            float a = w * xq * (t < P ? 1.f : xq), b = w * xk * (t < P ? 1.f : xk);
+    const int tid = threadIdx.x, g = tid / TL, c = tid - g * TL, l = blockIdx.x, bh = blockIdx.y;
+    const int r0 = blockIdx.z * (G * ROWS), nr = R - r0 < G * ROWS ? R - r0 : G * ROWS, shares = L * gridDim.z;
+    const bool on = g < G && g < nr && c < d;
+    const size_t row = static_cast<size_t>(bh) * d;
+    float *S = state + ((static_cast<size_t>(bh) * L + l) * R + r0) * d1;
+    const float *Wl = W + (static_cast<size_t>(bh % H) * L + l) * P * d;
+    // ---- operands, every lane an in-range address: dot product tid / 16 (the first 16 of them), then the statistics
+    const int sub = tid & 15, ndots = 2 * (P + unit), dot0 = tid >> 4 < ndots ? tid >> 4 : 0;
+    auto operands = [&](int i, float4 (&w4)[NC], float4 (&x4)[NC]) __attribute__((always_inline)) {
+        const T *x = ((i & 1) ? k : q) + row;
+        const float *w = Wl + ((i >> 1) < P ? (i >> 1) : 0) * d;
 #pragma unroll
-            for (int m = 32; m >= 1; m >>= 1) {
-                a += __shfl_xor(a, m, 64);
-                b += __shfl_xor(b, m, 64);
-            }
-            if (active && lane == 0) {
-                zred[(slot * (2 * P + 2) + 2 * t) * NWV + wv] = a;
-                zred[(slot * (2 * P + 2) + 2 * t + 1) * NWV + wv] = b;
-            }
+        for (int e = 0; e < NC; ++e) {
+            const int at = 64 * e + 4 * sub < d ? 64 * e + 4 * sub : 0;
+            w4[e] = load_quad(w + at);
+            x4[e] = load_quad(x + at);
         }
-        __syncthreads();
-        if (on && c < 2 * P) {                      // per-bit masses of the query (c < P) and of the key
-            const int side = c / P, t = c % P;
-            float z = 0.f, ss = 0.f;
-            for (int i = 0; i < NWV; ++i) {
-                z += zred[(slot * (2 * P + 2) + 2 * t + side) * NWV + i];
-                ss += zred[(slot * (2 * P + 2) + 2 * P + side) * NWV + i];
-            }
-            if (unit) z *= unit_scale(ss);
-            const float u = tanhf(z);
-            const float e = mass_ratio(beta, u);
-            const float big = 1.0f / (1.0f + e), small = e / (1.0f + e);
-            pq[(slot * 2 * P + c) * 2] = (u >= 0.f) ? big : small;          // mass on the +1 side
-            pq[(slot * 2 * P + c) * 2 + 1] = (u >= 0.f) ? small : big;
+    };
+    float4 w4[NC], x4[NC];
+    operands(dot0, w4, x4);
+    const float vv = load_elem(v, row + (c < d ? c : 0));
+    const uint32_t own = on ? static_cast<uint32_t>(g * d1 + c) : 0u;
+    float s[ROWS];
+#pragma unroll
+    for (int i = 0; i < ROWS; ++i) s[i] = (S + i * G * d1)[own];
+    const float sm = S[static_cast<uint32_t>((tid < nr ? tid : 0) * d1 + d)];
+    // ---- hash
+    for (int i = dot0; i < ndots; i += kDecodeThreads / 16) {
+        if (i != dot0) operands(i, w4, x4);
+        float a = 0.f;
+#pragma unroll
+        for (int e = 0; e < NC; ++e) {
+            if (64 * e + 4 * sub >= d) continue;
+            const float4 x = x4[e], y = (i >> 1) < P ? w4[e] : x;
+            a = fmaf(y.x, x.x, fmaf(y.y, x.y, fmaf(y.z, x.z, fmaf(y.w, x.w, a))));
         }
-        __syncthreads();
-        if (on) {
-            for (int r = c; r < 2 * R; r += TL) {
-                const int side = r / R, cr = r % R;
-                float f = 1.f;
-                for (int t = 0; t < P; ++t) f *= pq[(slot * 2 * P + side * P + t) * 2 + (((cr >> t) & 1) ? 0 : 1)];
-                phi[(slot * 2 + side) * R + cr] = f;
-            }
-        }
-        __syncthreads();
-        if (on) {
-            const float *pqv = phi + (slot * 2) * R, *pk = pqv + R;
-            float *S = state + (static_cast<size_t>(bh) * L + l) * R * d1;
-            if (c < d) {
-#pragma unroll 8
-                for (int r = 0; r < R; ++r) {
-                    const float sv = fmaf(pk[r], vv, S[r * d1 + c]);
-                    S[r * d1 + c] = sv;
-                    num = fmaf(pqv[r], sv, num);
-                }
-            }
-            for (int r = c; r < R; r += TL) {       // the mass column
-                const float sv = S[r * d1 + d] + pk[r];
-                S[r * d1 + d] = sv;
-                dn = fmaf(pqv[r], sv, dn);
-            }
-        }
-        __syncthreads();
+#pragma unroll
+        for (int m = 1; m < 16; m <<= 1) a += __shfl_xor(a, m, 64);
+        if (sub == 0) zs[i] = a;
     }
-    if (colok) numred[slot * d + c] = num;
+    __syncthreads();
+    if (tid < 2 * P) {
+        const int side = tid < P ? 1 : 0, t = tid < P ? tid : tid - P;
+        float z = zs[2 * t + side];
+        if (unit) z *= unit_scale(zs[2 * P + side]);
+        const float u = tanhf(z);
+        const float e = mass_ratio(beta, u);
+        const float big = 1.0f / (1.0f + e), small = e / (1.0f + e);
+        bits[tid] = u >= 0.f ? float2{small, big} : float2{big, small};
+    }
+    __syncthreads();
+    if (tid < nr) {
+        float fk = 1.f, fq = 1.f;
+        for (int t = 0; t < P; ++t) {
+            const float2 bk = bits[t], bq = bits[P + t];
+            const bool set = ((r0 + tid) >> t) & 1;
+            fk *= set ? bk.y : bk.x;
+            fq *= set ? bq.y : bq.x;
+        }
+        phi[tid] = float2{fk, fq};
+    }
+    __syncthreads();
+    // ---- update and read-out
+    float num = 0.f, dn = 0.f;
+    if (on) {
+#pragma unroll
+        for (int i = 0; i < ROWS; ++i) {
+            const float2 f = phi[g + G * i];
+            const float y = fmaf(f.x, vv, s[i]);
+            (S + i * G * d1)[own] = y;
+            num = fmaf(f.y, y, num);
+        }
+    }
+    if (tid < nr) {                                 // the mass column
+        const float2 f = phi[tid];
+        const float y = sm + f.x;
+        S[static_cast<uint32_t>(tid * d1 + d)] = y;
+        dn = f.y * y;
+    }
+    nred[tid] = num;
 #pragma unroll
     for (int m = 32; m >= 1; m >>= 1) dn += __shfl_xor(dn, m, 64);
-    if (lane == 0) dred[tid >> 6] = dn;
+    if ((tid & 63) == 0) dred[tid >> 6] = dn;
     __syncthreads();
+    float *mine = part + (static_cast<size_t>(bh) * shares + l * gridDim.z + blockIdx.z) * d1;
     if (tid < d) {
+        float x = nred[tid];
+#pragma unroll
+        for (int i = 1; i < G; ++i) x += nred[i * TL + tid];
+        __hip_atomic_store(mine + tid, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    if (tid == 0) __hip_atomic_store(mine + d, (dred[0] + dred[1]) + (dred[2] + dred[3]), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");     // this thread's share has reached the coherence point
+    __syncthreads();
+    if (tid == 0) last = __hip_atomic_fetch_add(arrived + bh, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == static_cast<unsigned>(shares - 1);
+    __syncthreads();
+    if (!last) return;
+    if (tid == 0) __hip_atomic_store(arrived + bh, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (tid < d) {
+        const float *all = part + static_cast<size_t>(bh) * shares * d1;
         float tot = 0.f, dnt = 0.f;
-        for (int sl = 0; sl < TF; ++sl) tot += numred[sl * d + tid];
-        for (int i = 0; i < kDecodeThreads / 64; ++i) dnt += dred[i];
-        store_elem(o, static_cast<size_t>(bh) * d + tid, dnt > 0.f ? tot / dnt : 0.f);
+        for (int s0 = 0; s0 < shares; s0 += 8) {
+            float x[8], y[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const int at = s0 + i < shares ? s0 + i : s0;
+                x[i] = __hip_atomic_load(all + at * d1 + tid, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                y[i] = __hip_atomic_load(all + at * d1 + d, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                tot += s0 + i < shares ? x[i] : 0.f;
+                dnt += s0 + i < shares ? y[i] : 0.f;
+            }
+        }
+        store_elem(o, row + tid, dnt > 0.f ? tot / dnt : 0.f);
         if (tid == 0) den[bh] = dnt / static_cast<float>(L);
     }
 }
@@ -258,34 +313,74 @@ hipError_t zero_floats(float *dst, size_t n, hipStream_t st)
     return hipGetLastError();
 }
 
-hipError_t decode_step(const Plan &p, const float *W, const void *q, const void *k, const void *v, float *state,
-                       void *o, float *den, hipStream_t st)
+namespace {
+// bucket rows per thread: all of the table's, at most 32 (8, 16, 32 measured: 31.4, 26.4, 25.3 us at B H = 256)
+int decode_rows(const Plan &p)
 {
-    const int TL = (p.d + 63) & ~63, TF = kDecodeThreads / TL;
-    const size_t lds = (static_cast<size_t>(TF) * (2 * p.P + 2) * (TL / 64) + TF * 4 * p.P + TF * 2 * p.R + TF * p.d + 16) * sizeof(float);
-    if (p.dtype == RACE_F32)
-        hipLaunchKernelGGL((decode_step_kernel<float>), dim3(p.BH), dim3(kDecodeThreads), lds, st, p.H, p.L, p.P, p.d, p.beta, p.unit_qk, W,
-                           (const float *)q, (const float *)k, (const float *)v, state, (float *)o, den);
-    else
-        hipLaunchKernelGGL((decode_step_kernel<bf16_t>), dim3(p.BH), dim3(kDecodeThreads), lds, st, p.H, p.L, p.P, p.d, p.beta, p.unit_qk, W,
-                           (const bf16_t *)q, (const bf16_t *)k, (const bf16_t *)v, state, (bf16_t *)o, den);
+    const int G = kDecodeThreads / ((p.d + 63) & ~63), rows = p.R / G;
+    return rows < 1 ? 1 : (rows > kDecodeMaxRows ? kDecodeMaxRows : rows);
+}
+
+template <typename T, int ROWS, int NC>
+void launch_decode(const Plan &p, const T *q, const T *k, const T *v, float *state, T *o, float *den, char *ws, hipStream_t st)
+{
+    hipLaunchKernelGGL((decode_step_kernel<T, ROWS, NC>), dim3(p.L, p.BH, decode_shares(p) / p.L), dim3(kDecodeThreads), 0, st, p.H, p.L,
+                       p.P, p.d, p.beta, p.unit_qk, reinterpret_cast<const float *>(ws + p.off_W), q, k, v, state,
+                       reinterpret_cast<float *>(ws + p.off_part), reinterpret_cast<unsigned *>(ws + p.off_carry), o, den);
+}
+template <typename T, int ROWS>
+void decode_columns(const Plan &p, const T *q, const T *k, const T *v, float *state, T *o, float *den, char *ws, hipStream_t st)
+{
+    switch ((p.d + 63) / 64) {
+    case 1: return launch_decode<T, ROWS, 1>(p, q, k, v, state, o, den, ws, st);
+    case 2: return launch_decode<T, ROWS, 2>(p, q, k, v, state, o, den, ws, st);
+    case 3: return launch_decode<T, ROWS, 3>(p, q, k, v, state, o, den, ws, st);
+    default: return launch_decode<T, ROWS, 4>(p, q, k, v, state, o, den, ws, st);
+    }
+}
+template <typename T>
+void decode_t(const Plan &p, const T *q, const T *k, const T *v, float *state, T *o, float *den, char *ws, hipStream_t st)
+{
+    switch (decode_rows(p)) {
+    case 1: return decode_columns<T, 1>(p, q, k, v, state, o, den, ws, st);
+    case 2: return decode_columns<T, 2>(p, q, k, v, state, o, den, ws, st);
+    case 4: return decode_columns<T, 4>(p, q, k, v, state, o, den, ws, st);
+    case 8: return decode_columns<T, 8>(p, q, k, v, state, o, den, ws, st);
+    case 16: return decode_columns<T, 16>(p, q, k, v, state, o, den, ws, st);
+    default: return decode_columns<T, 32>(p, q, k, v, state, o, den, ws, st);
+    }
+}
+}  // namespace
+
+int decode_shares(const Plan &p)
+{
+    const int per = kDecodeThreads / ((p.d + 63) & ~63) * decode_rows(p);
+    return p.L * ((p.R + per - 1) / per);
+}
+
+hipError_t decode_step(const Plan &p, const void *q, const void *k, const void *v, float *state, void *o, float *den, char *ws,
+                       hipStream_t st)
+{
+    if (p.dtype == RACE_F32) decode_t(p, (const float *)q, (const float *)k, (const float *)v, state, (float *)o, den, ws, st);
+    else decode_t(p, (const bf16_t *)q, (const bf16_t *)k, (const bf16_t *)v, state, (bf16_t *)o, den, ws, st);
     return hipGetLastError();
 }
 
 // A few tens of KB over PCIe: every thread has one 16-byte read in flight.  (As a stream-ordered copy through the runtime
 // the same bytes cost a hand-over to a copy engine and back: 8 us of copy between gaps of 10 and 16 us, 35 us in front of
 // every pass, against 3-4 us for this kernel.)
-__global__ __launch_bounds__(256) void upload_kernel(uint4 *dst, const uint4 *src, size_t n16)
+__global__ __launch_bounds__(256) void upload_kernel(uint4 *dst, const uint4 *src, size_t n16, uint4 *clear, size_t c16)
 {
     const size_t i = static_cast<size_t>(blockIdx.x) * 256 + threadIdx.x;
     if (i < n16) dst[i] = src[i];
+    if (i < c16) clear[i] = uint4{0u, 0u, 0u, 0u};
 }
 
-hipError_t upload(void *dst, const void *src, size_t bytes, hipStream_t st)
+hipError_t upload(void *dst, const void *src, size_t bytes, void *clear, size_t clear_bytes, hipStream_t st)
 {
-    const size_t n16 = bytes / 16;
-    hipLaunchKernelGGL(upload_kernel, dim3(static_cast<unsigned>((n16 + 255) / 256)), dim3(256), 0, st, static_cast<uint4 *>(dst),
-                       static_cast<const uint4 *>(src), n16);
+    const size_t n16 = bytes / 16, c16 = clear_bytes / 16, n = n16 > c16 ? n16 : c16;
+    hipLaunchKernelGGL(upload_kernel, dim3(static_cast<unsigned>((n + 255) / 256)), dim3(256), 0, st, static_cast<uint4 *>(dst),
+                       static_cast<const uint4 *>(src), n16, static_cast<uint4 *>(clear), c16);
     return hipGetLastError();
 }
 

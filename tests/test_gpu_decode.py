@@ -73,6 +73,13 @@ def test_decode_odd_shapes_fp32(d, L, P):
     _decode_against_oracle(Workload("dec-odd-d%d-L%d-P%d" % (d, L, P), 1, 2, 0, d, L, P, 4.0, True, "f32"), 0, 6)
 
 
+@pytest.mark.parametrize("d,L,P,dtype", [(8, 1, 1, "f32"), (64, 3, 1, "bf16"), (128, 2, 8, "f32"), (136, 1, 7, "f32"), (200, 2, 3, "bf16"),
+                                         (64, 2, 2, "f32"), (128, 1, 7, "bf16")])
+def test_decode_row_and_column_splits(d, L, P, dtype):
+    # fewer bucket rows than thread groups, tables cut over several workgroups, one thread group, every count of rows per thread
+    _decode_against_oracle(Workload("dec-split-d%d-L%d-P%d-%s" % (d, L, P, dtype), 2, 2, 0, d, L, P, 3.0, True, dtype, normalize_qk=True), 0, 5)
+
+
 def test_later_steps_may_reuse_the_projection_in_the_workspace():
     w = Workload("dec-reuse", 2, 2, 10, 128, 8, 6, 8.0, True, "bf16", normalize_qk=True)
     Q, K, V, _ = synth.make_inputs(w, "cuda")

@@ -43,6 +43,18 @@ def test_shape_extremes(L, P, d):
     check_case(Workload("shape", 1, 2, 300, d, L, P, 3.0, True, "f32", normalize_qk=True))
 
 
+@pytest.mark.parametrize("N,chunk,L,P,d,dtype", [
+    (15, 0, 3, 2, 24, "f32"), (16, 0, 3, 2, 24, "f32"), (17, 0, 3, 2, 24, "f32"),       # edges of a 16-token tile; partial blocks
+    (333, 80, 2, 7, 40, "f32"), (200, 0, 1, 8, 128, "f32"),                              # tables over two and four blocks
+    (100, 48, 33, 1, 8, "f32"), (100, 0, 40, 3, 16, "bf16"),                             # many small tables per block
+    (9000, 0, 2, 4, 72, "f32"), (8600, 96, 1, 6, 200, "bf16"), (8200, 64, 2, 5, 48, "f32"),   # 32-token tiles, segments of several tiles
+])
+@pytest.mark.parametrize("causal", [True, False])
+@pytest.mark.parametrize("unit", [False, True])
+def test_tile_and_block_edges(N, chunk, L, P, d, dtype, causal, unit):
+    check_case(Workload("edges", 1, 2, N, d, L, P, 2.0, causal, dtype, normalize_qk=not unit, chunk=chunk, unit_qk=unit), saved=True)
+
+
 def test_saturated_regime_raw_gaussian_inputs():
     # rows of norm ~ sqrt(d): |z| ~ 8, tanh saturates, phi is almost one-hot
     check_case(Workload("saturated", 1, 2, 777, 64, 4, 4, 8.0, True, "f32", chunk=128))
