@@ -1144,7 +1144,7 @@ hipError_t scan_states(const char *name, float *state, int nseg, int BH, size_t 
 {
     ProfileScope prof(name, st);
     int groups = 1;
-    while (groups < 16 && groups * kScanRun / 2 < nseg) groups *= 2;
+    while (groups < 16 && groups * kScanRun < nseg) groups *= 2;
     const int n4 = static_cast<int>(stride / 4);
     hipLaunchKernelGGL(scan_states_kernel, dim3((n4 + 63) / 64, BH), dim3(64, groups), 0, st, state, nseg, n4, stride, mode);
     return hipGetLastError();

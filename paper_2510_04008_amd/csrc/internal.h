@@ -128,6 +128,7 @@ hipError_t zero_floats(float *dst, size_t n, hipStream_t st);
 // The exact shape if compiled, else the padded instantiation with the fewest bucket rows that covers (d, L, P).
 bool mfma_pick(int d, int L, int P, int *Lc, int *Pc, int *pad);
 size_t mfma_hashed_bytes(const Plan &p);       // bytes of the hashed rows of one tensor
+int mfma_workgroups_per_cu(const Plan &p);     // of the stream kernels
 size_t mfma_projection_bytes(const Plan &p);
 void mfma_pack_projection(const Plan &p, const float *W, void *image);   // host
 hipError_t mfma_fwd(const Plan &p, const void *Q, const void *K, const void *V, void *O, float *den,

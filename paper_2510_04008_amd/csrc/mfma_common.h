@@ -119,6 +119,7 @@ struct Soft {
 // kernel arguments common to the family
 struct KArgs {
     int H, nseg, causal;
+    int hash_tokens;       // tokens per workgroup of the hashing kernel
     int64_t N, seg_len;
     float beta;
     int L_real, P_real;    // the problem's tables and hyperplanes (<= the compiled shape's)

@@ -189,7 +189,7 @@ void grad_kernel(KArgs a, const bf16raw *Q, const bf16raw *K, const bf16raw *V, 
     den += static_cast<size_t>(bh) * a.N;
     const bf16raw *Xr = SIDE == 0 ? Q : K;
     const float *Mw = (SIDE == 0 ? a.Mk : a.Mq) + static_cast<size_t>(bh) * a.N * C::LP;
-    const float *st = a.state + (static_cast<size_t>(bh) * a.nseg + seg) * C::STATE;
+    const float *st = a.state + (static_cast<size_t>(bh) * a.nseg + (INTRA ? seg : 0)) * C::STATE;     // (not causal: the totals)
 
     {
         const bf16raw *src = a.Wp + static_cast<size_t>(head) * C::LPP * C::D;

@@ -3,8 +3,8 @@
 // Kernels
 //   hash_kernel      projection and per-bit soft-hash masses of every row of Q and K, once per call: the "hashed rows"
 //                    (one float per token, table and hyperplane) that every later pass rebuilds phi from.
-//   scan_kernel      "totals" of the statistics per segment, then an exclusive prefix (forward) or
-//                    suffix (backward) scan over segments turns them into segment-start states.
+//   totals_kernel    statistics of every segment from a zero start; an exclusive prefix (forward) or suffix (backward)
+//                    scan over segments (scan_states) turns them into segment-start states.
 //   stream_kernel    one pass over a segment carrying statistics [L*R][d] in accumulator registers
 //                    as tiles (bucket rows x head columns).  Modes:
 //                      kTotalsKV  statistics of (phi_K, [V | 1])          (Algorithm 1, step 5)
@@ -69,7 +69,7 @@ struct HashLds {
     static constexpr int total = nx + TT * 4;
 };
 constexpr int kHashThreads = 256;
-constexpr int kHashTokens = 512;        // tokens per workgroup (amortises the load of W)
+constexpr int kHashTokens = 512;        // most tokens per workgroup (amortises the load of W)
 
 template <class C, bool UNIT>
 __global__ __launch_bounds__(kHashThreads) void hash_kernel(KArgs a, const bf16raw *Xq, const bf16raw *Xk, int first)
@@ -93,8 +93,8 @@ __global__ __launch_bounds__(kHashThreads) void hash_kernel(KArgs a, const bf16r
             *reinterpret_cast<u32x4 *>(wp + row * C::XS + ch * 8) = *reinterpret_cast<const u32x4 *>(src + row * C::D + ch * 8);
         }
     }
-    const int64_t t_begin = static_cast<int64_t>(blockIdx.x) * kHashTokens;
-    const int64_t t_end = (t_begin + kHashTokens < a.N) ? t_begin + kHashTokens : a.N;
+    const int64_t t_begin = static_cast<int64_t>(blockIdx.x) * a.hash_tokens;
+    const int64_t t_end = (t_begin + a.hash_tokens < a.N) ? t_begin + a.hash_tokens : a.N;
     const Soft sf = a.soft();
     for (int64_t t0 = t_begin; t0 < t_end; t0 += TT) {
         const int nv = (t_end - t0 < TT) ? static_cast<int>(t_end - t0) : TT;
@@ -320,9 +320,9 @@ void stream_kernel(KArgs a, const float *Mr, const float *Mw, const bf16raw *Y, 
     Y += base; Out += base;
     if (MODE == kGradV) { Oin += base; den_in += static_cast<size_t>(bh) * a.N; }
     if (MODE == kForward) den_out += static_cast<size_t>(bh) * a.N;
-    const float *st = a.state + (static_cast<size_t>(bh) * a.nseg + seg) * C::STATE;
+    // statistics at the start of the segment (not causal: the totals, which the scan leaves in the first segment's place)
+    const float *st = a.state + (static_cast<size_t>(bh) * a.nseg + (NC ? 0 : (a.causal ? seg : 0))) * C::STATE;
 
-    // statistics at the start of the segment
     f32x16 Sacc[C::MT][C::NTW];
     float macc[C::MT];                 // bucket masses (tiles mt % 2 == cg): per-half partial sums, lane n <-> row
 #pragma unroll
@@ -533,37 +533,6 @@ void stream_kernel(KArgs a, const float *Mr, const float *Mw, const bf16raw *Y, 
     RACE_PHASE_PRINT("stream")
 }
 
-// In-place scan over the segments of one (batch*head).  mode 0: exclusive prefix, 1: exclusive suffix,
-// 2: every segment gets the total (non-causal).
-__global__ void scan_kernel(float *state, int nseg, int elems, int mode)
-{
-    const int e = blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= elems) return;
-    float *base = state + static_cast<size_t>(blockIdx.y) * nseg * elems + e;
-    const size_t stride = static_cast<size_t>(elems);
-    constexpr int U = 8;                 // segments in flight per thread: the loads of a group do not depend on the running sum
-    float run = 0.f;
-    if (mode == 2) {
-        for (int s = 0; s < nseg; ++s) run += base[s * stride];
-        for (int s = 0; s < nseg; ++s) base[s * stride] = run;
-        return;
-    }
-    for (int s0 = 0; s0 < nseg; s0 += U) {
-        float v[U];
-#pragma unroll
-        for (int k = 0; k < U; ++k) {
-            const int s = mode == 0 ? s0 + k : nseg - 1 - (s0 + k);
-            v[k] = (s0 + k < nseg) ? base[s * stride] : 0.f;
-        }
-#pragma unroll
-        for (int k = 0; k < U; ++k) {
-            const int s = mode == 0 ? s0 + k : nseg - 1 - (s0 + k);
-            if (s0 + k < nseg) base[s * stride] = run;
-            run += v[k];
-        }
-    }
-}
-
 // Totals over all segments of the problem's own buckets, written as A[row * a_stride] and
 // Bsum[row * b_stride + c] with row = (bh * L_real + l) * R_real + r.  Real corner r of a real table sits at
 // the compiled corner with all padding bits set.
@@ -704,8 +673,12 @@ hipError_t launch_hash(const Plan &p, KArgs a, const void *Q, const void *K, int
 {
     auto kern = p.unit_qk ? hash_kernel<C, true> : hash_kernel<C, false>;
     RACE_TRY(allow_lds(kern, HashLds<C>::total));
+    // short sequences: fewer tokens per workgroup, down to one step, until there are four workgroups per CU
+    a.hash_tokens = kHashTokens;
+    while (a.hash_tokens > HashLds<C>::TT && static_cast<int64_t>(p.BH) * count * ((p.N + a.hash_tokens - 1) / a.hash_tokens) < 1024)
+        a.hash_tokens /= 2;
     ProfileScope prof("hash_rows", st);
-    hipLaunchKernelGGL(kern, dim3(static_cast<unsigned>((p.N + kHashTokens - 1) / kHashTokens), p.BH, count), dim3(kHashThreads),
+    hipLaunchKernelGGL(kern, dim3(static_cast<unsigned>((p.N + a.hash_tokens - 1) / a.hash_tokens), p.BH, count), dim3(kHashThreads),
                        HashLds<C>::total, st, a, static_cast<const bf16raw *>(Q), static_cast<const bf16raw *>(K), first);
     return hipGetLastError();
 }
@@ -736,20 +709,13 @@ hipError_t launch_stream(const Plan &p, KArgs a, const float *Mr, const float *M
     return hipGetLastError();
 }
 
-hipError_t launch_scan(const Plan &p, float *state, int elems, int mode, hipStream_t st)
-{
-    ProfileScope prof("segment_scan", st);
-    hipLaunchKernelGGL(scan_kernel, dim3((elems + 255) / 256, p.BH), dim3(256), 0, st, state, p.nseg, elems, mode);
-    return hipGetLastError();
-}
-
 template <class C>
 hipError_t fwd_t(const Plan &p, const void *Q, const void *K, const void *V, void *O, float *den, char *ws, hipStream_t st)
 {
     KArgs a = make_kargs<C>(p, ws);
     RACE_TRY((launch_hash<C>(p, a, Q, K, 0, 2, st)));
     RACE_TRY((launch_totals<C, 0>(p, a, a.Mk, V, nullptr, nullptr, st)));
-    RACE_TRY(launch_scan(p, a.state, C::STATE, p.causal ? 0 : 2, st));
+    RACE_TRY(scan_states("segment_scan", a.state, p.nseg, p.BH, C::STATE, p.causal ? 0 : 2, st));
     RACE_TRY((launch_stream<C, kForward>(p, a, a.Mq, a.Mk, V, nullptr, nullptr, O, den, st)));
     return hipSuccess;
 }
@@ -785,10 +751,10 @@ hipError_t bwd_t(const Plan &p, const void *Q, const void *K, const void *V, con
     if (!p.fwd_state_kept) {
         RACE_TRY((launch_hash<C>(p, a, Q, K, 0, 2, st)));
         RACE_TRY((launch_totals<C, 0>(p, a, a.Mk, V, nullptr, nullptr, st)));
-        RACE_TRY(launch_scan(p, a.state, C::STATE, p.causal ? 0 : 2, st));
+        RACE_TRY(scan_states("segment_scan", a.state, p.nseg, p.BH, C::STATE, p.causal ? 0 : 2, st));
     }
     RACE_TRY((launch_totals<C, 1>(p, b, a.Mq, dO, O, den, st)));
-    RACE_TRY(launch_scan(p, b.state, C::STATE, p.causal ? 1 : 2, st));
+    RACE_TRY(scan_states("segment_scan", b.state, p.nseg, p.BH, C::STATE, p.causal ? 1 : 2, st));
     RACE_TRY((launch_stream<C, kGradV>(p, b, a.Mk, a.Mq, dO, O, den, dV, nullptr, st)));
     RACE_TRY((launch_grad<C, 0>(p, a, Q, K, V, O, den, dO, dQ, st)));
     RACE_TRY((launch_grad<C, 1>(p, b, Q, K, V, O, den, dO, dK, st)));
@@ -898,6 +864,14 @@ size_t mfma_hashed_bytes(const Plan &p)
     RACE_SHAPES(X)
 #undef X
     return 0;
+}
+
+int mfma_workgroups_per_cu(const Plan &p)
+{
+#define X(DD, PP_, LL, PD) if (p.d == DD && p.Pc == PP_ && p.Lc == LL && p.pad == PD) return Cfg<DD, PP_, LL, PD != 0>::STREAM_WAVES_PER_SIMD / 2;
+    RACE_SHAPES(X)
+#undef X
+    return 1;
 }
 
 size_t mfma_projection_bytes(const Plan &p)

@@ -196,6 +196,38 @@ ProfileScope::~ProfileScope()
     if (i < g_profile_records.size()) (void)hipEventRecord(g_profile_records[i].stop, st_);
 }
 
+// Segment length the MFMA family chooses, in its 32-token tiles: the k that makes
+//     rounds * k * (time of a tile in all passes) + (workgroups) * (time to move a state through passes and scans)
+// smallest.  A round is one workgroup per CU (256).  Long sequences come out at one round with as few, long segments as fill
+// the chip (two rounds with half the segment take as long and move twice the states; more rounds only where B H divides the
+// chip badly), short ones at the balance of the two terms.  The two times are fits to sweeps over segment lengths of training
+// steps, us: at 512 bucket rows of 128 columns 22 and 0.31 (B H = 16, N = 1000: 279, 197, 167, 170, 180 us at 11, 6, 4, 3, 2
+// tiles), at 64 bucket rows 11.5 and 0.04.  Shapes whose stream kernels fit a CU twice take two workgroups per CU once those
+// have a dozen tiles each (64 bucket rows, B H = 64, N = 16384: 1619 -> 1470 us); before that the gradient kernels, which fit
+// once, would run a second, nearly empty round.
+static int64_t mfma_segment_tokens(const Plan &p)
+{
+    const int64_t n = p.N > 0 ? p.N : 1, tiles = (n + 31) / 32;
+    const double state_us = static_cast<double>(p.LRc) * (p.d + 1) * 1.2e-6 * 4, tile_us = 10.0 + 12.0 * p.LRc / 512.0;
+    const int64_t slots = (mfma_workgroups_per_cu(p) == 2 && tiles * p.BH >= 512 * 12) ? 512 : 256;
+    int64_t best_k = tiles;
+    double best = 1e300;
+    auto consider = [&](int64_t k) {
+        if (k < 1 || k > tiles) return;
+        const int64_t groups = p.BH * ((tiles + k - 1) / k);
+        const double t = static_cast<double>((groups + slots - 1) / slots * k) * tile_us + static_cast<double>(groups) * state_us;
+        if (t < best) { best = t; best_k = k; }
+    };
+    for (int64_t rounds = 1; rounds <= 4; ++rounds) {
+        const int64_t nseg = slots * rounds / p.BH;
+        if (nseg > 0) consider((tiles + nseg - 1) / nseg);
+    }
+    const int64_t balance = static_cast<int64_t>(std::sqrt(state_us * static_cast<double>(tiles) * p.BH / tile_us));
+    for (int64_t k = balance; k <= balance + 2; ++k) consider(k);
+    consider(tiles);
+    return best_k * 32;
+}
+
 race_status_t make_plan(const race_attn_desc_t *desc, Plan *pl)
 {
     if (!desc) return RACE_ERR_INVALID_ARG;
@@ -241,10 +273,7 @@ race_status_t make_plan(const race_attn_desc_t *desc, Plan *pl)
         if (align256(fwd_part > bwd_part ? fwd_part : bwd_part) > kGenericPartialLimit) return RACE_ERR_UNSUPPORTED;
         p.dbeta_parts = p.nseg;
     } else {
-        // two workgroups' worth of segments per CU and head-batch; multiples of the 32-token tile
-        int64_t want = (512 + p.BH - 1) / p.BH;
-        int64_t len = desc->chunk > 0 ? desc->chunk : (n + want - 1) / want;
-        if (desc->chunk == 0 && len < 256) len = 256;
+        int64_t len = desc->chunk > 0 ? desc->chunk : mfma_segment_tokens(p);
         len = (len + 31) / 32 * 32;
         p.seg_len = len;
         if ((n + len - 1) / len > 65535) return RACE_ERR_UNSUPPORTED;
