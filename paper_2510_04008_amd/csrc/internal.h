@@ -45,6 +45,8 @@ struct Plan {
     size_t off_massK;   // hyperplane: the per-bit soft-hash masses every pass rebuilds phi from); generic family: followed
                         // by the projections themselves, in the same layout
     size_t bytes_mass;
+    size_t off_ge;      // MFMA family: extra column of the read-out cotangents, (BH, N) fp32, backward only
+    size_t bytes_ge;
     size_t fwd_bytes;   // the leading part of the workspace that the forward pass uses
     size_t off_dbeta;   // partial cotangents of beta: (2 sides, BH, dbeta_parts) fp32, backward only
     size_t bytes_dbeta;

@@ -7,9 +7,11 @@
 // wavefront holds an eighth of them as 32x32 MFMA accumulator tiles (stream kernels: a quarter of the
 // bucket rows x half of the columns; grad kernel: an eighth of the bucket rows x all columns, transposed).
 // Per tile the workgroup
-//   1. projects the 32 query and key rows on all L*P hyperplanes (MFMA) and turns the projections
-//      into soft assignments phi (vector ALU), written as bf16 tiles to LDS;
+//   1. turns the hashed rows of the tile's queries and keys (hash_kernel) into soft assignments phi (vector ALU), written
+//      as bf16 tiles to LDS;
 //   2. contracts them with the register-resident statistics and with each other (MFMA).
+// Two barriers per tile: whatever goes to LDS for a tile is written in the first half (next to the output of the previous
+// tile), whatever reads it runs in the second.
 // MFMA 32x32x16 bf16 register layouts used throughout (lane = 32*h + n):
 //   A operand: row n of A, columns 8h..8h+7 of the 16-wide k-step;   B operand: column n of B, rows 8h..8h+7;
 //   C/D      : column n, rows 8*(v/4) + 4h + v%4 for register v = 0..15.
@@ -49,13 +51,11 @@ struct Cfg {
     static constexpr int D = D_, P = P_, L = L_;
     static constexpr bool PAD = PAD_;
     static constexpr int R = 1 << P, LR = L * R;
-    static constexpr int PP = P > 4 ? 8 : 4;            // hyperplanes per table, padded
-    // tables per 32-row projection group: as many as fit, or (shapes with fewer tables) the tables there are, spread
-    // over both lane halves; the group's remaining rows are padding
-    static constexpr int TPG = (32 / PP < L + (L & 1)) ? 32 / PP : L + (L & 1);
-    static constexpr int TPL = TPG / 2;                 // tables per lane (per half-wave)
-    static constexpr int NG = (L + TPG - 1) / TPG;      // projection groups
-    static constexpr int LPP = NG * 32;                 // padded projection rows
+    static constexpr int PP = P > 4 ? 8 : 4;            // hyperplanes per table, padded; row l * PP + t of the packed W is
+                                                        // hyperplane t of table l
+    static constexpr int NG = (L * PP + 31) / 32;       // groups of 32 packed rows
+    static constexpr int LPP = NG * 32;                 // packed rows (padding rows are zero)
+    static constexpr int PT = (L * PP + 15) / 16;       // 16-row tiles of them that hold hyperplanes
     // stream kernels: wavefront w owns bucket-row group w % RG and column group w / RG (four row groups x two
     // column groups, or two x four when there are only 64 bucket rows)
     static constexpr int RG = LR / 32 >= kRowGroups ? kRowGroups : LR / 32;
@@ -72,7 +72,6 @@ struct Cfg {
     static constexpr int STREAM_WAVES_PER_SIMD = (MT * NTW <= 2 && NTW == 1) ? 4 : 2;
     static constexpr int LRG = LR / kWaves;             // bucket rows per wavefront (grad kernel)
     static constexpr int MTG = LRG / 32;                // 32-row tiles per wavefront (grad kernel)
-    static constexpr int JSTEP = 4 / NG;                // wavefronts that share one projection group
     static constexpr int PLO = P < 3 ? P : 3, PHI = P - PLO;
     static constexpr int CPR = D / 8;                   // 16-byte chunks per row
     // LDS row strides, in bf16 elements (rows stay 16-byte aligned; the pad staggers banks)
@@ -81,17 +80,18 @@ struct Cfg {
     static constexpr int PS = LR + 8;                   // [token][L*R] assignment tiles, read by rows
     static constexpr int PST = LR + 16;                 // ... read through transposing loads only (a compromise:
                                                         // 16-byte row writes and transposing reads both 2-way at most)
-    static constexpr int ZS = LPP + 8;                  // [token][padded projection] tiles
     static constexpr int STATE = LR * (D + 1);          // floats per saved state: B [LR][D] then A [LR]
-    // hashed form of a row (see bit_code()): one float per (table, hyperplane), L * P per token
+    // hashed form of a row (see bit_code()): one float per (table, hyperplane).  In memory a tile of 32 tokens is
+    // [table][32 tokens][4 hyperplanes], for P = 6 followed per table by [32 tokens][2 hyperplanes], so that a half
+    // wavefront whose lanes are the tile's tokens reads and writes a table's hyperplanes as contiguous pieces: every pass
+    // loads them straight into the lanes that rebuild the assignments, without a stop in LDS.
     static constexpr int LP = L * P;
-    static constexpr int MS = LP + 2;                   // [token][LP] tiles of them in LDS: an even stride whose half is odd keeps the 8-byte
-                                                        // reads of 32 consecutive tokens on distinct banks
-    static constexpr int MCH = LP / 4;                  // 16-byte chunks per token
-    static_assert(P % 2 == 0 && LP % 4 == 0 && (MS / 2) % 2 == 1, "hashed rows are read as pairs of floats");
+    static constexpr int HT = kTile * P;                // floats of one table of a tile
+    static_assert(P == 4 || P == 6, "hashed rows are quads, or a quad and a pair");
+    static_assert(L == 4 || L % 8 == 0, "tables over the eight half wavefronts of a side");
     static_assert(RG >= 1 && LR % (32 * RG) == 0 && NT % CG == 0 && NTW >= 1, "bucket rows and columns over the wavefronts");
     static_assert(D % 64 == 0 && P >= 4, "shape (assignments are written for pairs of high-bit indices)");
-    static_assert(4 % NG == 0 && NG <= 4, "projection groups must divide four wavefronts");
+    static_assert(4 % NG == 0 && NG <= 4 && PT <= 4, "groups of packed rows must divide four wavefronts");
 };
 
 // Scheduling fence: keeps the instruction scheduler from hoisting the loads and conversions of later
@@ -126,7 +126,9 @@ struct KArgs {
     __host__ __device__ Soft soft() const { return Soft{beta, L_real, P_real}; }
     const bf16raw *Wp;     // (H, LPP, D) bf16, rows in projection-group order
     float *state;          // (BH, nseg, STATE) fp32
-    float *Mq, *Mk;        // (BH, N, L * P) fp32: the hashed rows of Q and K (hash_kernel writes them, every later pass reads them)
+    float *Mq, *Mk;        // (BH, ceil(N / 32), 32 * L * P) fp32: the hashed rows of Q and K, tile by tile (see Cfg::HT)
+    float *ge;             // (BH, N) fp32: extra column of the read-out cotangents (backward only)
+    int want_dbeta;
     float *dbeta_part;     // (2, BH, workgroups per head-batch) fp32: partial cotangents of beta (backward only)
 };
 
@@ -217,42 +219,78 @@ __device__ __forceinline__ u32x4 lds_tr_acc(const bf16raw *M, int stride, int k0
     return lds_tr8<IL>(M, stride, k0 + 4 * h, k0 + 8 + 4 * h, n0, ln);
 }
 
+// Operands of 16 x 16 x 32 products along the ROWS of a tile: lane (n = lane % 16, q = lane / 16) gets column n of the 16
+// columns whose blocks of four start at the given chunk positions, rows ka .. ka+3 then kb .. kb+3.  chunk: position of the
+// lane's block (lane % 4) of the row that it addresses (lane % 16 / 4).
+__device__ __forceinline__ u32x4 lds_tr16(const bf16raw *M, int stride, int ka, int kb, int chunk, int lane)
+{
+    const bf16raw *p = M + ((lane & 15) >> 2) * stride + chunk;
+    const s16x4 a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(p + ka * stride));
+    const s16x4 b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(p + kb * stride));
+    const u32x2 ua = __builtin_bit_cast(u32x2, a), ub = __builtin_bit_cast(u32x2, b);
+    return u32x4{ua.x, ua.y, ub.x, ub.y};
+}
+
+// Sum over the two halves of the wavefront / over the four rows of 16 lanes, in every lane (register swaps, no LDS).
+__device__ __forceinline__ float sum_halves(float x)
+{
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+__device__ __forceinline__ float sum_rows(float x)
+{
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return sum_halves(__uint_as_float(r[0]) + __uint_as_float(r[1]));
+}
+
+// Four sums over the rows of 16 lanes at once: row i of lanes gets the sum of x_i.
+__device__ __forceinline__ float sum_rows4(float x0, float x1, float x2, float x3)
+{
+    const auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(x0), __float_as_uint(x2), false, false);
+    const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(x1), __float_as_uint(x3), false, false);
+    const float x02 = __uint_as_float(a[0]) + __uint_as_float(a[1]), x13 = __uint_as_float(b[0]) + __uint_as_float(b[1]);
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x02), __float_as_uint(x13), false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+
 // ---------------------------------------------------------------- global -> registers -> LDS tiles
 // A tile of ROWS rows is ROWS*CPR chunks of 16 bytes; thread t owns chunks t, t + 512, ...  Loads are
 // issued ahead of use (fetch) and written to LDS later (store), so that HBM latency overlaps arithmetic.
-// (NTHR: the threads that share the tile, the first NTHR of the workgroup)
-template <class C, int ROWS, int NTHR = kThreads>
+template <class C, int ROWS>
 struct RowChunks {
-    static constexpr int N = (ROWS * C::CPR + NTHR - 1) / NTHR;
+    static constexpr int N = (ROWS * C::CPR + kThreads - 1) / kThreads;
     u32x4 v[N];
 };
 
-// Every lane loads, unconditionally: rows past the end of the tile (nvalid >= 1 rows are real) re-read the last real
-// row and are zeroed when they are stored.  (A load under a condition, into registers cleared first, makes the
+// Every lane loads, unconditionally: rows past the end of the tile (nvalid >= 1 rows are real) re-read the last real row.
+// Such rows stay in the tiles as they are: their assignments are zeros, so they reach neither statistics nor other
+// tokens, and their own results are not stored.  (A load under a condition, into registers cleared first, makes the
 // compiler wait for every load in flight before the clearing moves: the loads of a tile would complete one by one.)
-// SBASE: the address as a uniform base plus a 32-bit byte offset per lane, which lets the loads take their base from
-// scalar registers (10-15 vector registers fewer in the gradient kernel, which needs them; the stream and totals
-// kernels measured 1-4 % slower with it and keep the plain form).
-template <class C, int ROWS, bool SBASE = false, int NTHR = kThreads>
-__device__ __forceinline__ void fetch_rows(const bf16raw *X, int64_t t0, int nvalid, RowChunks<C, ROWS, NTHR> &r)
+// The address is a uniform base plus a 32-bit byte offset per lane, which lets the loads take their base from scalar
+// registers.
+template <class C, int ROWS>
+__device__ __forceinline__ void fetch_rows(const bf16raw *X, int64_t t0, int nvalid, RowChunks<C, ROWS> &r)
 {
     const char *base = reinterpret_cast<const char *>(X + t0 * C::D);
 #pragma unroll
-    for (int k = 0; k < RowChunks<C, ROWS, NTHR>::N; ++k) {
-        const int c = threadIdx.x + k * NTHR, row = c / C::CPR, ch = c % C::CPR;
+    for (int k = 0; k < RowChunks<C, ROWS>::N; ++k) {
+        const int c = threadIdx.x + k * kThreads, row = c / C::CPR, ch = c % C::CPR;
         const int rr = row < nvalid ? row : nvalid - 1;
-        if (SBASE) r.v[k] = *reinterpret_cast<const u32x4 *>(base + static_cast<uint32_t>((rr * C::D + ch * 8) * 2));
-        else r.v[k] = *reinterpret_cast<const u32x4 *>(X + (t0 + rr) * C::D + ch * 8);
+        r.v[k] = *reinterpret_cast<const u32x4 *>(base + static_cast<uint32_t>((rr * C::D + ch * 8) * 2));
     }
 }
 
-// One 16-byte chunk (columns 8ch .. 8ch+7) into row-major tile `dst` with row stride STRIDE; IL: pair-interleaved
-// columns (the chunk's two blocks of 4 land 8 positions apart).
-template <int STRIDE, bool IL>
+// Column order of a row-major tile: as they are; pair-interleaved in groups of 16 (il()); or in groups of 32, where the
+// eight features {4q .. 4q+3, 16 + 4q .. 16 + 4q+3} that a lane of a 16 x 16 x 32 product holds in two accumulator tiles are
+// neighbours (position 8 q + 4 (c / 16) + c % 4).
+enum Order { kPlain = 0, kPairs16 = 1, kPairs32 = 2 };
+// One 16-byte chunk (columns 8ch .. 8ch+7) into row-major tile `dst` with row stride STRIDE; in either interleaved order the
+// chunk's two blocks of 4 land 8 positions apart.
+template <int STRIDE, int IL>
 __device__ __forceinline__ void store_chunk(bf16raw *dst, int row, int ch, u32x4 v)
 {
     if (IL) {
-        bf16raw *p = dst + row * STRIDE + 16 * (ch >> 1) + 4 * (ch & 1);
+        bf16raw *p = dst + row * STRIDE + (IL == kPairs16 ? 16 * (ch >> 1) + 4 * (ch & 1) : 32 * (ch >> 2) + 16 * (ch & 1) + 4 * ((ch >> 1) & 1));
         *reinterpret_cast<u32x2 *>(p) = u32x2{v.x, v.y};
         *reinterpret_cast<u32x2 *>(p + 8) = u32x2{v.z, v.w};
     } else {
@@ -260,52 +298,14 @@ __device__ __forceinline__ void store_chunk(bf16raw *dst, int row, int ch, u32x4
     }
 }
 
-// nvalid: rows of the tile that exist; the others are stored as zeros.
-template <class C, int ROWS, int STRIDE = C::XS, bool IL = false, int NTHR = kThreads>
-__device__ __forceinline__ void store_rows(const RowChunks<C, ROWS, NTHR> &r, bf16raw *dst, int nvalid)
+template <class C, int ROWS, int STRIDE = C::XS, int IL = kPlain>
+__device__ __forceinline__ void store_rows(const RowChunks<C, ROWS> &r, bf16raw *dst)
 {
     const int tid = opaque(static_cast<int>(threadIdx.x));       // keeps the tile addresses out of long-lived registers
 #pragma unroll
-    for (int k = 0; k < RowChunks<C, ROWS, NTHR>::N; ++k) {
-        const int c = tid + k * NTHR, row = c / C::CPR, ch = c % C::CPR;
-        const bool real = row < nvalid;
-        const u32x4 v = {real ? r.v[k].x : 0u, real ? r.v[k].y : 0u, real ? r.v[k].z : 0u, real ? r.v[k].w : 0u};
-        if (row < ROWS) store_chunk<STRIDE, IL>(dst, row, ch, v);
-    }
-}
-
-// Hashed rows: a tile of ROWS tokens is ROWS * C::MCH chunks of 16 bytes, contiguous in memory; thread t owns chunks
-// t, t + 512, ... (most shapes: one, and not every thread has one).
-template <class C, int ROWS, int NTHR = kThreads>
-struct MassChunks {
-    static constexpr int N = (ROWS * C::MCH + NTHR - 1) / NTHR;
-    u32x4 v[N];
-};
-// SBASE: a uniform base plus a 32-bit byte offset per lane (see fetch_rows).
-template <class C, int ROWS, bool SBASE = false, int NTHR = kThreads>
-__device__ __forceinline__ void fetch_masses(const float *M, int64_t t0, int nvalid, MassChunks<C, ROWS, NTHR> &r)
-{
-    const char *base = reinterpret_cast<const char *>(M + t0 * C::LP);
-#pragma unroll
-    for (int k = 0; k < MassChunks<C, ROWS, NTHR>::N; ++k) {
-        const int c = threadIdx.x + k * NTHR, row = c / C::MCH, ch = c % C::MCH;
-        const int rr = row < nvalid ? row : nvalid - 1;         // (rows past the end re-read the last real row; their phi is zeroed)
-        if (SBASE) r.v[k] = *reinterpret_cast<const u32x4 *>(base + static_cast<uint32_t>((rr * C::LP + ch * 4) * 4));
-        else r.v[k] = *reinterpret_cast<const u32x4 *>(M + (t0 + rr) * C::LP + ch * 4);
-    }
-}
-template <class C, int ROWS, int NTHR = kThreads>
-__device__ __forceinline__ void store_masses(const MassChunks<C, ROWS, NTHR> &r, float *dst)
-{
-    const int tid = opaque(static_cast<int>(threadIdx.x));
-#pragma unroll
-    for (int k = 0; k < MassChunks<C, ROWS, NTHR>::N; ++k) {
-        const int c = tid + k * NTHR, row = c / C::MCH, ch = c % C::MCH;
-        if (row < ROWS) {
-            u32x2 *p = reinterpret_cast<u32x2 *>(dst + row * C::MS + ch * 4);
-            p[0] = u32x2{r.v[k].x, r.v[k].y};
-            p[1] = u32x2{r.v[k].z, r.v[k].w};
-        }
+    for (int k = 0; k < RowChunks<C, ROWS>::N; ++k) {
+        const int c = tid + k * kThreads, row = c / C::CPR, ch = c % C::CPR;
+        if (row < ROWS) store_chunk<STRIDE, IL>(dst, row, ch, r.v[k]);
     }
 }
 
@@ -331,37 +331,39 @@ __device__ __forceinline__ void store_row_scales(const RowChunks<C, ROWS> &r, fl
 }
 
 // Read-out cotangent rows: gn = dO / e (e = L * Den) as bf16 rows, ge[row] = -(gn . O) as fp32 (= -(dO . O) / e).
-template <class C, int ROWS, int NTHR = kThreads>
+template <class C, int ROWS>
 struct CotChunks {
-    RowChunks<C, ROWS, NTHR> g, o;
-    float den[RowChunks<C, ROWS, NTHR>::N];
+    RowChunks<C, ROWS> g, o;
+    float den[RowChunks<C, ROWS>::N];
 };
 
-template <class C, int ROWS, bool SBASE = false, int NTHR = kThreads>
+template <class C, int ROWS>
 __device__ __forceinline__ void fetch_cotangent(const bf16raw *dO, const bf16raw *O, const float *den, int64_t t0,
-                                                int nvalid, CotChunks<C, ROWS, NTHR> &r)
+                                                int nvalid, CotChunks<C, ROWS> &r)
 {
-    fetch_rows<C, ROWS, SBASE, NTHR>(dO, t0, nvalid, r.g);
-    fetch_rows<C, ROWS, SBASE, NTHR>(O, t0, nvalid, r.o);
+    fetch_rows<C, ROWS>(dO, t0, nvalid, r.g);
+    fetch_rows<C, ROWS>(O, t0, nvalid, r.o);
     const char *dbase = reinterpret_cast<const char *>(den + t0);
 #pragma unroll
-    for (int k = 0; k < RowChunks<C, ROWS, NTHR>::N; ++k) {
-        const int row = (threadIdx.x + k * NTHR) / C::CPR;
+    for (int k = 0; k < RowChunks<C, ROWS>::N; ++k) {
+        const int row = (threadIdx.x + k * kThreads) / C::CPR;
         const int rr = row < nvalid ? row : nvalid - 1;
-        if (SBASE) r.den[k] = *reinterpret_cast<const float *>(dbase + static_cast<uint32_t>(rr * 4));
-        else r.den[k] = den[t0 + rr];
+        r.den[k] = *reinterpret_cast<const float *>(dbase + static_cast<uint32_t>(rr * 4));
     }
 }
 
-template <class C, int ROWS, int STRIDE = C::XS, bool IL = false, int NTHR = kThreads>
-__device__ __forceinline__ void store_cotangent(const CotChunks<C, ROWS, NTHR> &r, bf16raw *dst, float *ge, int L_real, int nvalid)
+// Forms the cotangent rows of a tile, into LDS (dst, ge) and into memory (Gout, ge_out: rows from t0 on), where the later
+// passes read them back as plain rows.
+template <class C, int ROWS, int STRIDE>
+__device__ __forceinline__ void store_cotangent(const CotChunks<C, ROWS> &r, bf16raw *dst, float *ge, int L_real, int nvalid,
+                                                bf16raw *Gout, float *ge_out, int64_t t0)
 {
     const int tid = opaque(static_cast<int>(threadIdx.x));
+    char *gbase = reinterpret_cast<char *>(Gout + t0 * C::D);
 #pragma unroll
-    for (int k = 0; k < RowChunks<C, ROWS, NTHR>::N; ++k) {
-        const int c = tid + k * NTHR, row = c / C::CPR, ch = c % C::CPR;
-        // rows past the end of the tile hold a copy of the last real row: they get zero cotangents
-        const float inv = (row < nvalid && r.den[k] > 0.f) ? __builtin_amdgcn_rcpf(r.den[k] * static_cast<float>(L_real)) : 0.f;
+    for (int k = 0; k < RowChunks<C, ROWS>::N; ++k) {
+        const int c = tid + k * kThreads, row = c / C::CPR, ch = c % C::CPR;
+        const float inv = r.den[k] > 0.f ? __builtin_amdgcn_rcpf(r.den[k] * static_cast<float>(L_real)) : 0.f;
         const uint32_t gw[4] = {r.g.v[k].x, r.g.v[k].y, r.g.v[k].z, r.g.v[k].w};
         const uint32_t ow[4] = {r.o.v[k].x, r.o.v[k].y, r.o.v[k].z, r.o.v[k].w};
         uint32_t out[4];
@@ -373,72 +375,24 @@ __device__ __forceinline__ void store_cotangent(const CotChunks<C, ROWS, NTHR> &
             // statistics made of few keys, V_j . gn + ge = (V_j - O_i) . gn then cancels as it does in exact arithmetic
             dot = dot2(out[e], ow[e], dot);
         }
-        if (row < ROWS) store_chunk<STRIDE, IL>(dst, row, ch, u32x4{out[0], out[1], out[2], out[3]});
-        if (ge) {
-            // the CPR threads of one row are consecutive lanes
+        const u32x4 v = {out[0], out[1], out[2], out[3]};
+        if (row < ROWS) store_chunk<STRIDE, kPlain>(dst, row, ch, v);
+        if (row < nvalid) *reinterpret_cast<u32x4 *>(gbase + static_cast<uint32_t>((row * C::D + ch * 8) * 2)) = v;
+        // the CPR threads of one row are consecutive lanes
 #pragma unroll
-            for (int m = C::CPR / 2; m >= 1; m >>= 1) dot += __shfl_xor(dot, m, 64);
-            if (ch == 0 && row < ROWS) ge[row] = -dot;
-        }
+        for (int m = C::CPR / 2; m >= 1; m >>= 1) dot += __shfl_xor(dot, m, 64);
+        if (ch == 0 && row < ROWS) ge[row] = -dot;
+        if (ch == 0 && row < nvalid) ge_out[t0 + row] = -dot;
     }
 }
 
 // ---------------------------------------------------------------- projection + soft assignment
-// z^T (32 projection rows of group g) x (32 tokens) = Wg . X^T, contraction over d (Algorithm 1, step 4:
-// the argument of tanh).  Lane (n, h) ends up with the projections of token n for the TPL tables
-// {g*TPG + h*TPL + j}: the host stores W's rows in that order (see pack_projection()).
-// scale != null: the projections of token n are multiplied by scale[n] (W (x / |x|) = (W x) / |x|).
-template <class C>
-__device__ __forceinline__ f32x16 project(const bf16raw *wp, const bf16raw *x, int g, int ln, int h,
-                                          const float *scale = nullptr)
-{
-    // two accumulators halve the chain of dependent MFMAs
-    f32x16 z0 = {0}, z1 = {0};
-#pragma unroll
-    for (int s = 0; s < C::D / 16; s += 2) {
-        z0 = mma(lds128(wp + (g * 32 + ln) * C::XS + 16 * s + 8 * h), lds128(x + ln * C::XS + 16 * s + 8 * h), z0);
-        z1 = mma(lds128(wp + (g * 32 + ln) * C::XS + 16 * s + 16 + 8 * h), lds128(x + ln * C::XS + 16 * s + 16 + 8 * h), z1);
-    }
-    f32x16 z = z0 + z1;
-    if (scale) z = z * scale[ln];
-    return z;
-}
-// projection t of the lane's j-th table inside the accumulator
-template <class C>
-__device__ __forceinline__ constexpr int zslot(int j, int t)
-{
-    return C::PP == 8 ? 4 * (2 * j + t / 4) + t % 4 : 4 * j + t;
-}
+typedef __attribute__((ext_vector_type(4))) float f32x4;
 
-// Per-bit masses of one table: p[t] = sigmoid(2 beta tanh z_t) (mass on the +1 side), q[t] = 1 - p[t],
-// computed without cancellation; sech2[t] = 1 - tanh^2 z_t; u[t] = tanh z_t.  Padding bits (t >= sf.P): all the
-// mass on the +1 side, no dependence on the input.
-template <class C>
-__device__ __forceinline__ void bit_masses(const f32x16 &z, int j, const Soft &sf, float *p, float *q, float *sech2,
-                                           float *u = nullptr)
+// 16 x 16 x 32 product: A row / B column lane % 16, k-slots 8 (lane / 16) ..; D column lane % 16, rows 4 (lane / 16) + v.
+__device__ __forceinline__ f32x4 mma16(u32x4 a, u32x4 b, f32x4 c)
 {
-    const float beta = sf.beta;
-#pragma unroll
-    for (int t = 0; t < C::P; ++t) {
-        if (C::PAD && t >= sf.P) {
-            p[t] = 1.f; q[t] = 0.f;
-            if (sech2) sech2[t] = 0.f;
-            if (u) u[t] = 0.f;
-            continue;
-        }
-        const float zt = z[zslot<C>(j, t)];
-        const float e2 = __expf(-2.0f * fabsf(zt));
-        const float inv = __builtin_amdgcn_rcpf(1.0f + e2);
-        const float ua = (1.0f - e2) * inv;                    // |tanh z|
-        // beta = +infinity is the hard hash: e = 0, and at z = 0 (-inf * 0 = NaN; fmaxf returns its other argument) the bit is set
-        const float e = __expf(fmaxf(-2.0f * beta * ua, -1e30f));
-        const float big = __builtin_amdgcn_rcpf(1.0f + e), small = e * big;
-        const bool pos = zt >= 0.f;
-        p[t] = pos ? big : small;
-        q[t] = pos ? small : big;
-        if (sech2) sech2[t] = 4.0f * e2 * inv * inv;
-        if (u) u[t] = pos ? ua : -ua;
-    }
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
 }
 
 // The hashed form of one projection: c = +small or -small, where small = sigmoid(-2 beta |tanh z|) is the mass of the
@@ -463,90 +417,98 @@ __device__ __forceinline__ void code_masses(float c, float &p, float &q)
     q = pos ? small : big;
 }
 
-// phi over the low PLO bits (lo) and the high PHI bits (hi): phi[a * 2^PLO + b] = hi[a] * lo[b]
-// (the corner softmax is a product of per-bit two-point distributions).
+// Hashed rows of NTAB tables for one token per lane.
+template <class C, int NTAB>
+struct Codes {
+    float c[NTAB][C::P];
+};
+// Mt: uniform; lane_off: table_offset() of the lane's table and token, worked out once per kernel
 template <class C>
-__device__ __forceinline__ void kron_factors(const float *p, const float *q, float *lo, float *hi)
+__device__ __forceinline__ uint32_t table_offset(int table, int ln) { return static_cast<uint32_t>(table * C::HT + 4 * ln) * 4u; }
+template <class C>
+__device__ __forceinline__ void load_table_codes(const float *Mt, uint32_t lane_off, int ln, float *c)
 {
-    lo[0] = 1.f;
-#pragma unroll
-    for (int t = 0; t < C::PLO; ++t) {
-#pragma unroll
-        for (int b = 0; b < (1 << t); ++b) {
-            lo[b + (1 << t)] = lo[b] * p[t];
-            lo[b] = lo[b] * q[t];
-        }
-    }
-    hi[0] = 1.f;
-#pragma unroll
-    for (int t = 0; t < C::PHI; ++t) {
-#pragma unroll
-        for (int b = 0; b < (1 << t); ++b) {
-            hi[b + (1 << t)] = hi[b] * p[C::PLO + t];
-            hi[b] = hi[b] * q[C::PLO + t];
-        }
+    const char *src = reinterpret_cast<const char *>(Mt);
+    const float4 a = *reinterpret_cast<const float4 *>(src + lane_off);
+    c[0] = a.x; c[1] = a.y; c[2] = a.z; c[3] = a.w;
+    if (C::P == 6) {
+        const float2 b = *reinterpret_cast<const float2 *>(src + 16 * kTile + (lane_off - 8u * ln));
+        c[4] = b.x; c[5] = b.y;
     }
 }
 
-// Writes the assignment of the lane's token as bf16 into row `row` of ph [token][L*R] (row stride STRIDE),
-// corners pair-interleaved: the 16 corners of high-bit indices (a, a+1), a even, are stored as
+// Production: SLOTS half wavefronts share the tables of a tile of 32 tokens (lane = token).  Half wavefront `slot` takes
+// tables slot, slot + SLOTS, ...; with fewer tables than slots, two share a table (the lower and upper half of its
+// 16-byte pieces) and the rest are idle.
+template <class C, int SLOTS>
+struct Share {
+    static constexpr int NTAB = C::L >= SLOTS ? C::L / SLOTS : 1;
+    static constexpr int PARTS = C::L >= SLOTS ? 1 : 2;
+    static_assert(C::L >= SLOTS ? C::L % SLOTS == 0 : SLOTS % C::L == 0, "tables over half wavefronts");
+    __device__ static __forceinline__ int table(int slot, int i) { return PARTS == 1 ? slot + i * SLOTS : slot % C::L; }
+    __device__ static __forceinline__ int part(int slot) { return PARTS == 1 ? 0 : slot / C::L; }       // >= PARTS: idle
+    typedef Codes<C, NTAB> Regs;
+    // Mt: the tile's hashed rows; lane_off: table_offset() of table(slot, 0)
+    __device__ static __forceinline__ void load(const float *Mt, uint32_t lane_off, int ln, Regs &r)
+    {
+#pragma unroll
+        for (int i = 0; i < NTAB; ++i) load_table_codes<C>(Mt + i * SLOTS * C::HT, lane_off, ln, r.c[i]);
+    }
+};
+
+// Writes the half wavefront's share of the assignments of the lane's token as bf16 into row `row` of ph [token][L*R] (row
+// stride STRIDE): phi[a * 8 + b] = hi[a] * lo[b] (the corner softmax is a product of per-bit two-point distributions; a: bits
+// 3.., b: bits 0..2), corners pair-interleaved: the 16 corners of high-bit indices (a, a+1), a even, are stored as
 // [a: b 0..3 | a+1: b 0..3 | a: b 4..7 | a+1: b 4..7].
 // valid == false writes zeros (a token past the end of the sequence must not reach the statistics).
-// Only the lane's tables j = j0, j0 + jstep, ... and the high-bit indices a0 <= a < a1 (both even) are
-// written, which lets several wavefronts share the tables of one projection group.
-// If mass != null (bucket masses in the same pair-interleaved order), returns sum_r phi[r] * mass[r] over
-// what was written (the read-out of the bucket masses A by this token, i.e. its share of the normaliser).
-// Two sources: the projections z of the lane's token (an accumulator of project()), or, if mrow != null, the hashed
-// row of the lane's token (C::LP floats, see bit_code()).
-// FENCE: a scheduling fence after every pair of high-bit indices (bounds the registers the compiler may spend on
-// interleaving them; kernels with registers to spare turn it off).
-template <class C, int STRIDE = C::PS, bool FENCE = true>
-__device__ __forceinline__ float write_assignments(const f32x16 &z, int g, int row, int h, const Soft &sf, bool valid,
-                                                   bf16raw *ph, int j0 = 0, int jstep = 1, int a0 = 0,
-                                                   int a1 = 1 << C::PHI, const float *mass = nullptr,
-                                                   const float *mrow = nullptr)
+// If mass != null (bucket masses in the same pair-interleaved order), returns sum_r phi[r] * mass[r] over what was written
+// (the read-out of the bucket masses A by this token, i.e. its share of the normaliser).
+template <class C, int SLOTS, int STRIDE>
+__device__ __forceinline__ float produce(const typename Share<C, SLOTS>::Regs &codes, int slot, int row, const Soft &sf, bool valid,
+                                         bf16raw *ph, const float *mass = nullptr)
 {
+    using Sh = Share<C, SLOTS>;
     static_assert(C::PLO == 3 && C::PHI >= 1, "eight low corners per high-bit index, indices in pairs");
+    constexpr int NA = 1 << C::PHI;
+    // two shares of a table: halves of the high-bit indices if there are two pairs of them, else of the low corners
+    constexpr bool kSplitA = Sh::PARTS == 2 && C::PHI >= 2;
+    const int part = Sh::part(slot);
     float dn = 0.f;
+    if (part >= Sh::PARTS) return dn;
 #pragma unroll
-    for (int j = 0; j < C::TPL; ++j) {
-        const int table = g * C::TPG + h * C::TPL + j;
-        if (table >= C::L) break;
-        if (j < j0 || (j - j0) % jstep != 0) continue;
+    for (int i = 0; i < Sh::NTAB; ++i) {
+        const int table = Sh::table(slot, i);
+        const bool live = valid && (!C::PAD || table < sf.L);     // (a padding table: zero assignments)
         const int tbase = opaque(table * C::R);                   // one base register, constants folded into offsets
         bf16raw *prow = ph + opaque(row * STRIDE);
-        if (C::PAD && table >= sf.L) {                            // a padding table: zero assignments
+        float p[C::P], q[C::P], lo[8], hi[NA];
 #pragma unroll
-            for (int a = 0; a < (1 << C::PHI); a += 2) {
-                if (a < a0 || a >= a1) continue;
-                *reinterpret_cast<u32x4 *>(prow + tbase + a * 8) = u32x4{0u, 0u, 0u, 0u};
-                *reinterpret_cast<u32x4 *>(prow + tbase + a * 8 + 8) = u32x4{0u, 0u, 0u, 0u};
+        for (int t = 0; t < C::P; ++t) code_masses(codes.c[i][t], p[t], q[t]);
+        lo[0] = q[0] * q[1]; lo[1] = p[0] * q[1]; lo[2] = q[0] * p[1]; lo[3] = p[0] * p[1];
+#pragma unroll
+        for (int b = 0; b < 4; ++b) { lo[4 + b] = lo[b] * p[2]; lo[b] = lo[b] * q[2]; }
+        // with a split over the high-bit indices the top bit is this share's
+        constexpr int kTop = kSplitA ? C::P - 1 : C::P;
+        hi[0] = !live ? 0.f : (kSplitA ? (part ? p[C::P - 1] : q[C::P - 1]) : 1.f);
+#pragma unroll
+        for (int t = 3; t < kTop; ++t) {
+#pragma unroll
+            for (int b = 0; b < (1 << (t - 3)); ++b) {
+                hi[b + (1 << (t - 3))] = hi[b] * p[t];
+                hi[b] = hi[b] * q[t];
             }
-            continue;
         }
-        float p[C::P], q[C::P], lo[1 << C::PLO], hi[1 << C::PHI];
-        if (mrow) {
-            const float *src = mrow + opaque(table * C::P);
+        constexpr int kA = kSplitA ? NA / 2 : NA;
+        const int abase = kSplitA ? part * (NA / 2) * 8 : 0;
 #pragma unroll
-            for (int t = 0; t < C::P; t += 2) {
-                const float2 c2 = *reinterpret_cast<const float2 *>(src + t);
-                code_masses(c2.x, p[t], q[t]);
-                code_masses(c2.y, p[t + 1], q[t + 1]);
-            }
-        } else {
-            bit_masses<C>(z, j, sf, p, q, nullptr);
-        }
-        kron_factors<C>(p, q, lo, hi);
-#pragma unroll
-        for (int a = 0; a < (1 << C::PHI); a += 2) {
-            if (a < a0 || a >= a1) continue;
-            const float ha = valid ? hi[a] : 0.f, hb = valid ? hi[a + 1] : 0.f;
+        for (int a = 0; a < kA; a += 2) {
 #pragma unroll
             for (int half = 0; half < 2; ++half) {
-                const int pos = tbase + a * 8 + 8 * half;
+                if (Sh::PARTS == 2 && !kSplitA && half != part) continue;
+                const int pos = tbase + abase + a * 8 + 8 * half;
                 float f[8];
 #pragma unroll
-                for (int b = 0; b < 4; ++b) { f[b] = ha * lo[4 * half + b]; f[4 + b] = hb * lo[4 * half + b]; }
+                for (int b = 0; b < 4; ++b) { f[b] = hi[a] * lo[4 * half + b]; f[4 + b] = hi[a + 1] * lo[4 * half + b]; }
                 if (mass) {
                     const float4 m0 = *reinterpret_cast<const float4 *>(mass + pos);
                     const float4 m1 = *reinterpret_cast<const float4 *>(mass + pos + 4);
@@ -556,7 +518,7 @@ __device__ __forceinline__ float write_assignments(const f32x16 &z, int g, int r
                 *reinterpret_cast<u32x4 *>(prow + pos) =
                     u32x4{pack2(f[0], f[1]), pack2(f[2], f[3]), pack2(f[4], f[5]), pack2(f[6], f[7])};
             }
-            if (FENCE) RACE_SCHED_FENCE();
+            RACE_SCHED_FENCE();
         }
     }
     return dn;

@@ -8,187 +8,142 @@
 //   SIDE 1 (dK), right to left, statistics dS = (dB | dA) of (phi_Q, read-out cotangents) of tokens >= j:
 //       dphi_K(j)[r] = dS[r,:] . [V_j | 1]
 // followed in both cases by the chain rule through the corner softmax, tanh and W:  dx = W^T dz.
-// "reader" is the tensor whose gradient is produced, "writer" the tensor that feeds the statistics.  The writer's
-// assignments are rebuilt from its hashed rows (hash_kernel); the reader's rows are projected here, because the chain
-// rule needs tanh and its derivative next to the per-bit masses.
+// "reader" is the tensor whose gradient is produced, "writer" the tensor that feeds the statistics.  The assignments of
+// both are rebuilt from their hashed rows (hash_kernel); the chain rule through tanh needs tanh z and its derivative as
+// well, for which the reader's rows are projected here, a 16 x 16 tile per wavefront.
 //
 // The statistics are held transposed, tiles S^T[head column][bucket row], so that a tile's accumulator
 // registers are the B operand of the contraction over columns (lane = bucket row).  The in-tile part
 // uses T^T[b][a] = Yw_b . Yr_a (+ the product of the two extra columns), masked to b <= a (b >= a
-// right to left), whose accumulator is directly the A operand of  T . phi_writer.
+// right to left), which goes to LDS as the A operand of  T . phi_writer.
+//
+// Two barriers per tile.  First half: the following tile's rows -> LDS (two buffers), the writer's assignments, the
+// derivative of tanh, the in-tile term, and dX of the previous tile; second half: dphi, the corner softmax backwards, dz,
+// and the update of the statistics.  (With a third barrier between the staging of a tile's own rows and everything that reads
+// them, the projection on two wavefronts and its masses through LDS to the others: 10.4 ms for 16.8 million rows of
+// 128 columns at L = 8, P = 6.)
 #pragma once
 #include "mfma_common.h"
 
 namespace race {
 namespace mfma {
 
-// Developer aid: per-phase cycle counts of one workgroup (build with -DRACE_PHASE_TIMING).
-#ifdef RACE_PHASE_TIMING
-#define GRAD_PHASE_DECL long long ph_t[13] = {0}; long long ph_last = clock64();
-#define GRAD_PHASE(i) { long long now_ = clock64(); ph_t[i] += now_ - ph_last; ph_last = now_; }
-#define GRAD_PHASE_PRINT() if (blockIdx.x == 1 && blockIdx.y == 0 && (threadIdx.x & 63) == 0) \
-    printf("grad side %d wave %d tiles %d: load %lld prod %lld tt %lld dP %lld upd %lld dphiw %lld smbwd %lld dX %lld | waits %lld %lld %lld %lld %lld\n", SIDE, (int)(threadIdx.x >> 6), ntiles, \
-           ph_t[0], ph_t[2], ph_t[4], ph_t[5], ph_t[6], ph_t[8], ph_t[10], ph_t[12], ph_t[1], ph_t[3], ph_t[7], ph_t[9], ph_t[11]);
-#else
-#define GRAD_PHASE_DECL
-#define GRAD_PHASE(i)
-#define GRAD_PHASE_PRINT()
-#endif
-
-// Row tiles per wavefront: all of LR / 256 if that is at most two (128 registers of statistics per lane is what
-// fits next to the working set); beyond that the bucket rows are split over TSPLIT workgroups by tables.
-template <class C> constexpr int grad_row_tiles() { return C::LR / (32 * kWaves) >= 2 ? 2 : 1; }
-
+// Two forms of the second half.  R = 64 (P = 6): a wavefront owns the 64 bucket rows of one table as 32 x 32 tiles.  R = 16
+// (P = 4): 16 x 16 tiles, one table per tile of bucket rows: eight tables or more are shared out over the wavefronts, four
+// go to two wavefronts each, which take half of the tile's tokens each (and both keep the table's statistics).  Both
+// gradients of 4.2 million rows of 128 columns at L = P = 4 take 2.16 ms; with 32 x 32 tiles, which kept two of the eight
+// wavefronts busy in the second half, 3.05 ms.
 template <class C>
 struct GradCfg {
-    static constexpr int MTG = grad_row_tiles<C>();                     // 32-row tiles of bucket rows per wavefront
-    static constexpr int RW = 32 * MTG;                                 // bucket rows per wavefront
-    static constexpr int NRW = C::LR / RW >= kWaves ? kWaves : C::LR / RW;   // wavefronts that own bucket rows (the first NRW)
-    static constexpr int TSPLIT = C::LR / (RW * NRW);                   // workgroups per (segment, head)
-    static constexpr int NGW = C::NG / TSPLIT;                          // projection groups per workgroup
-    static constexpr int ROWS = C::LR / TSPLIT;                         // bucket rows per workgroup
-    static constexpr int TABLES = NGW * C::TPG;                         // tables per workgroup
-    // a wavefront's rows are TWW whole tables (R <= RW) or a 1/WPT share of one table (R > RW);
-    // a 32-row tile holds TW whole tables (R <= 32) or part of one
-    static constexpr int TWW = C::R >= RW ? 1 : RW / C::R;              // tables per wavefront
-    static constexpr int WPT = C::R >= RW ? C::R / RW : 1;              // wavefronts per table
-    static constexpr int TW = C::R >= 32 ? 1 : 32 / C::R;               // tables per tile
-    static constexpr int KM = (C::R >= 32 ? 32 : C::R) / 8;             // groups of 8 corners per table and tile
-    static constexpr int MB = KM == 4 ? 2 : (KM == 2 ? 1 : 0);          // corner bits 3.. that vary inside a tile
-    static_assert(MTG >= 1 && NRW >= 1 && TSPLIT == 1 && RW * NRW == C::LR, "all bucket rows of a head in one workgroup");
-    static_assert(NRW == kWaves || TSPLIT == 1, "a workgroup with spare wavefronts holds all the rows");
-    static_assert(C::NG % TSPLIT == 0 && kWaves % NGW == 0, "table split");
-    static_assert(NGW * C::TPG * C::R >= ROWS, "a workgroup's rows are the tables of its projection groups");
-    static_assert(C::P >= 3 && C::P <= 7, "corner bits 0..2 are register/lane bits; a partial record is P+1 <= 8 floats");
-    // production roles.  Writer hashing: one wavefront per (projection group, table of the lane, share of the
-    // high-bit indices); reader masses: one per (projection group, table of the lane) if there is room, else one
-    // per projection group; one wavefront for the in-tile term.  If they do not all fit, the reader and in-tile
-    // roles double up on the last wavefronts.
-    static constexpr int AS = (C::PHI >= 2 && NGW * C::TPL * 2 + NGW + 1 <= kWaves) ? 2 : 1;     // shares hold pairs of indices
-    static constexpr int NW = NGW * C::TPL * AS;                        // writer wavefronts
-    // (where every wavefront carries statistics, a wavefront is kept free for the in-tile term; where some do not,
-    // it doubles up on a reader: measured faster each way)
-    static constexpr int RJ = (NW + NGW * C::TPL + (NRW < kWaves ? 0 : 1) <= kWaves) ? C::TPL : 1;
-    static constexpr bool DISJ = NW + NGW * RJ + 1 <= kWaves;
-    static constexpr int RD0 = DISJ ? NW : kWaves - NGW * RJ;           // first reader wavefront
-    static constexpr int NR = NGW * RJ;                                 // reader wavefronts
-    // in-tile term: a wavefront of its own if one is left, else the last reader
-    static constexpr int TT = DISJ ? (NW + NR < kWaves ? NW + NR : kWaves - 1) : kWaves - 1 - NGW;
-    static_assert(NW <= kWaves && RD0 + NR <= kWaves, "production roles must fit the wavefronts");
-    // dX = dz . W of a tile is formed one step late, next to the production of the following tile, by the wavefronts
-    // with the lightest production roles: first those without a role, then the in-tile term's, then writers,
-    // readers last (the higher wavefront first within a class).  dx_tile(w) = column tile of wavefront w, or -1.
-    // The non-causal variant has no writer and no in-tile term: its readers start at wavefront 0 and take one table of
-    // the lane each if the wavefronts suffice.
-    static constexpr int RJ_NC = NGW * C::TPL <= kWaves ? C::TPL : 1;
-    static constexpr int NR_NC = NGW * RJ_NC;
-    static constexpr int role_weight(int w, bool causal)
+    static constexpr bool T16 = C::R == 16;
+    static_assert(T16 || C::R == 64, "one or four 16-row tiles per table");
+    // R = 64
+    static constexpr int MTG = 2;                                       // 32-row tiles of bucket rows per wavefront (128 registers of
+                                                                        // statistics per lane is what fits next to the working set)
+    static constexpr int RW = T16 ? 16 : 32 * MTG;                      // bucket rows of a table
+    static_assert(T16 || C::L == kWaves, "one table per wavefront");
+    // R = 16
+    static constexpr int TPW = C::L >= kWaves ? C::L / kWaves : 1;      // tables per wavefront
+    static constexpr int TS = C::L >= kWaves ? 1 : kWaves / C::L;       // wavefronts that share a table's tokens
+    static_assert(TS <= 2 && (T16 || TPW == 1), "tables over wavefronts");
+    static constexpr int SREGS = T16 ? TPW * C::D / 4 : MTG * C::NT * 16;        // registers of statistics
+    static constexpr int YORDER = T16 ? kPairs32 : kPairs16;
+    // First half of a tile, by role.  Production: `SLOTS` half wavefronts from wavefront 0 on; projection of the reader's rows:
+    // 2 PT 16 x 16 tiles; in-tile term: three 16 x 16 tiles; dX of the previous tile: NT column tiles.
+    static constexpr int SLOTS = C::L >= 16 ? 16 : 8;
+    static constexpr int proj_wave(int i, bool causal)
     {
-        if (!causal) return w < NR_NC ? 3 : 0;
-        return (w >= RD0 && w < RD0 + NR) ? 3 : (w < NW ? 2 : (w == TT ? 1 : 0));
+        if (!causal || C::PT == 4) return causal && !T16 ? 4 + i % 4 : i % kWaves;      // (R = 64: wavefronts 4-7, two each)
+        return i == 0 ? 0 : 3 + i;
     }
-    static constexpr int dx_tile(int w, bool causal)
-    {
-        int taken = 0;
-        for (int weight = 0; weight <= 3; ++weight) {
-            for (int v = kWaves - 1; v >= 0; --v) {
-                if (role_weight(v, causal) != weight) continue;
-                if (taken == C::NT) return -1;
-                if (v == w) return taken;
-                ++taken;
-            }
-        }
-        return -1;
-    }
+    static constexpr int tt_wave(int i) { return T16 ? (C::L >= 16 ? 5 + i : 1 + i) : i; }
+    static constexpr int dx_wave(int i, bool causal) { return T16 ? (causal && C::L >= 16 ? i : kWaves - 1 - i) : 4 + i; }
+    static_assert(C::NT <= 4, "dX on four wavefronts at most");
 };
 
-// UNIT: the unit-norm option's extras (row scales, parts of z . dz, and z next to the per-bit masses).
+// UNIT: the unit-norm option's extras (row scales, projections, parts of z . dz, a second buffer of the reader's rows, which
+// dX of a tile still reads when the next tile's rows are stored).
 // INTRA: the causal variant, whose tiles also feed the statistics: the writer's rows, assignments and the in-tile term.
 template <class C, bool UNIT, bool INTRA>
 struct GradLds {
     using G = GradCfg<C>;
+    static constexpr int XB = UNIT ? 2 : 1;                             // buffers of the reader's rows and of the scales
     static constexpr int wp = 0;                                        // [LPP][XS] bf16
-    static constexpr int DZS = G::NGW * 32 + 8;                         // bf16 row stride of the dz tile
+    static constexpr int DZS = C::LPP + 8;                              // bf16 row stride of the dz tile
     static constexpr int dz = wp + C::LPP * C::XS * 2;                  // [32][DZS] bf16
-    static constexpr int sr = dz + kTile * DZS * 2;                     // [32] fp32 extra column of reader-Y
-    static constexpr int sw = sr + kTile * 4;                           // [32] fp32 extra column of writer-Y
-    static constexpr int nrm = sw + kTile * 4;                          // [2][2][32] fp32: 1 / |x| of the reader and writer rows (unit-norm option),
-                                                                        // two buffers used by alternate tiles
-    static constexpr int rad = nrm + (UNIT ? 4 * kTile * 4 : 0);        // [kWaves][32] fp32: per-wavefront parts of z . dz per token (same option)
-    static constexpr int PMS = UNIT ? 5 * C::PP + (C::PP == 8 ? 4 : 8)  // floats per (table, token): p, q, sech^2, tanh (, z), each padded
-                                    : 4 * C::PP + 4;                    // to PP; the tail makes PMS / 4 odd, which keeps 16-byte reads of
-                                                                        // 16 tokens on distinct banks
-    static constexpr int pm = (rad + (UNIT ? kWaves * kTile * 4 : 0) + 15) & ~15;              // [TABLES][32][PMS] fp32: per-bit masses of the reader
-    static constexpr int PMT = G::TABLES < C::L ? G::TABLES : C::L;     // tables of the workgroup that exist
-    static constexpr int part = pm + PMT * kTile * PMS * 4;             // [kWaves][32][8] fp32: partial (m, G_t) of table shares
-    static constexpr int yr = part + (G::WPT > 1 ? kWaves * kTile * 8 * 4 : 0);   // [32][XS] reader-Y rows, pair-interleaved columns
-    static constexpr int ttop = yr + kTile * C::XS * 2;                 // [2][64] x 16 B: masked in-tile term as MFMA operands
-    static constexpr int xr = (ttop + (INTRA ? 2 * 64 * 16 : 0) + 255) & ~255;        // [32][XS]
-    static constexpr int mw = xr + kTile * C::XS * 2;                   // [32][MS] fp32: hashed writer rows
-    static constexpr int yw = (mw + (INTRA ? kTile * C::MS * 4 : 0) + 15) & ~15;     // [32][YS] writer-Y rows, pair-interleaved columns
-    static constexpr int phw = yw + (INTRA ? kTile * C::YS * 2 : 0);    // [32][PST] writer assignments
+    static constexpr int sr = dz + kTile * DZS * 2;                     // [2][32] fp32 extra column of reader-Y
+    static constexpr int sw = sr + 2 * kTile * 4;                       // [2][32] fp32 extra column of writer-Y
+    static constexpr int nrm = sw + 2 * kTile * 4;                      // [XB][32] fp32: 1 / |x| of the reader's rows
+    static constexpr int rad = nrm + (UNIT ? XB * kTile * 4 : 0);       // [kWaves][32] fp32: per-wavefront parts of z . dz per token
+    static constexpr int QUADS = C::L * C::PP / 4;
+    static constexpr int s2 = (rad + (UNIT ? kWaves * kTile * 4 : 0) + 15) & ~15;     // [QUADS][32] float4: 1 - tanh^2 z of four hyperplanes
+    static constexpr int zz = s2 + QUADS * kTile * 16;                  // [QUADS][32] float4: z
+    static constexpr int yr = zz + (UNIT ? QUADS * kTile * 16 : 0);     // [2][32][XS] reader-Y rows, pair-interleaved columns
+    static constexpr int yr_bytes = kTile * C::XS * 2;
+    static constexpr int xr = yr + 2 * yr_bytes;                        // [XB][32][XS] reader rows
+    static constexpr int xr_bytes = kTile * C::XS * 2;
+    static constexpr int ttop = xr + XB * xr_bytes;                     // [2][64] x 16 B: masked in-tile term as MFMA operands
+    static constexpr int yw = ttop + (INTRA ? 2 * 64 * 16 : 0);         // [2][32][YS] writer-Y rows, pair-interleaved columns
+    static constexpr int yw_bytes = kTile * C::YS * 2;
+    static constexpr int phw = yw + (INTRA ? 2 * yw_bytes : 0);         // [32][PST] writer assignments
     static constexpr int SS = 40;                                       // bf16 row stride of the output staging tiles
-    static constexpr int stg = phw + (INTRA ? kTile * C::PST * 2 : 0);  // [NT][32][SS] bf16: dX tiles on their way out
-    static constexpr int xr2 = stg + C::NT * kTile * SS * 2;            // [32][XS]: second buffer of the reader rows (unit-norm
-                                                                        // option: the dX wavefronts still read a tile's rows while the others
-                                                                        // store the next tile's)
-    static constexpr int total = xr2 + (UNIT ? kTile * C::XS * 2 : 0);
-    static_assert(total <= 160 * 1024, "LDS budget");
+    static constexpr int mass = phw + (INTRA ? kTile * C::PST * 2 : 0); // R = 16: [kWaves][TPW * 16] fp32: extra column of each wavefront's rows
+    static constexpr int stg = mass + (G::T16 ? kWaves * G::TPW * 16 * 4 : 0);  // [NT][16][SS] bf16: dX tiles on their way out, 16 tokens at a time
+    static constexpr int total = stg + C::NT * 16 * SS * 2;
+    // where the cotangent of beta is wanted:
+    static constexpr int th = total;                                    // [QUADS][32] float4: tanh z
+    static constexpr int th_bytes = QUADS * kTile * 16;
+    static_assert(yr % 16 == 0 && th % 16 == 0 && total + th_bytes <= 160 * 1024, "LDS budget");
 };
 
-// Wavefronts per SIMD the gradient kernel is compiled for.  The non-causal variant of a shape whose wavefronts carry
-// at most two accumulator tiles of statistics fits 128 registers and 80 KB of LDS, which lets two workgroups share a CU
-// (its tiles are independent of each other: nothing but latency to hide).
+// Wavefronts per SIMD the gradient kernel is compiled for: four (128 registers, two workgroups per CU, whose phases
+// interleave) where the statistics do not change, 32 registers hold a wavefront's share of them and the tiles fit 80 KB.
+// The causal variant wants 135 to 165 registers at its smallest: held to 128 it spills and takes 1.6 times as long (4.2 million
+// rows of 128 columns at L = P = 4: 1.67 ms for dQ instead of 1.06 ms).
 template <class C, bool UNIT, bool INTRA>
 constexpr int grad_waves_per_simd()
 {
-    return (!INTRA && GradCfg<C>::MTG * C::NT <= 2 && GradLds<C, UNIT, INTRA>::total <= 80 * 1024) ? 4 : 2;
+    return (!INTRA && GradCfg<C>::SREGS <= 32 && GradLds<C, UNIT, INTRA>::total <= 80 * 1024) ? 4 : 2;
 }
 
 template <class C, int SIDE, bool UNIT, bool INTRA>
 __global__ __launch_bounds__(kThreads, (grad_waves_per_simd<C, UNIT, INTRA>()))
-void grad_kernel(KArgs a, const bf16raw *Q, const bf16raw *K, const bf16raw *V, const bf16raw *O,
-                 const float *den, const bf16raw *dO, bf16raw *dX)
+void grad_kernel(KArgs a, const bf16raw *Xr, const bf16raw *V, const bf16raw *G_, bf16raw *dX)
 {
     using S = GradLds<C, UNIT, INTRA>;
     using G = GradCfg<C>;
     extern __shared__ __attribute__((aligned(256))) unsigned char lds[];
     bf16raw *wp = reinterpret_cast<bf16raw *>(lds + S::wp);
     bf16raw *dz = reinterpret_cast<bf16raw *>(lds + S::dz);
-    float *sr = reinterpret_cast<float *>(lds + S::sr);
-    float *sw = reinterpret_cast<float *>(lds + S::sw);
-    float *nrm0 = reinterpret_cast<float *>(lds + S::nrm);
     float *rad = reinterpret_cast<float *>(lds + S::rad);
-    float *pm = reinterpret_cast<float *>(lds + S::pm);
-    bf16raw *yr = reinterpret_cast<bf16raw *>(lds + S::yr);
-    bf16raw *xr0 = reinterpret_cast<bf16raw *>(lds + S::xr);
-    float *mw = reinterpret_cast<float *>(lds + S::mw);
-    bf16raw *yw = reinterpret_cast<bf16raw *>(lds + S::yw);
+    f32x4 *s2t = reinterpret_cast<f32x4 *>(lds + S::s2);
+    f32x4 *tht = reinterpret_cast<f32x4 *>(lds + S::th);
+    f32x4 *zzt = reinterpret_cast<f32x4 *>(lds + S::zz);
     bf16raw *phw = reinterpret_cast<bf16raw *>(lds + S::phw);
-    float *part = reinterpret_cast<float *>(lds + S::part);
     u32x4 *ttop = reinterpret_cast<u32x4 *>(lds + S::ttop);
     bf16raw *stg = reinterpret_cast<bf16raw *>(lds + S::stg);
+    auto buf_yr = [&](int it) { return reinterpret_cast<bf16raw *>(lds + S::yr + (it & 1) * S::yr_bytes); };
+    auto buf_yw = [&](int it) { return reinterpret_cast<bf16raw *>(lds + S::yw + (it & 1) * S::yw_bytes); };
+    auto buf_sr = [&](int it) { return reinterpret_cast<float *>(lds + S::sr) + (it & 1) * kTile; };
+    auto buf_sw = [&](int it) { return reinterpret_cast<float *>(lds + S::sw) + (it & 1) * kTile; };
+    auto buf_xr = [&](int it) { return reinterpret_cast<bf16raw *>(lds + S::xr + (UNIT ? it & 1 : 0) * S::xr_bytes); };
+    auto buf_nrm = [&](int it) { return reinterpret_cast<float *>(lds + S::nrm) + (UNIT ? it & 1 : 0) * kTile; };
 
     constexpr bool kReverse = (SIDE == 1);
     const int seg = blockIdx.x, bh = blockIdx.y, head = bh % a.H;
     const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, ln = lane & 31, h = lane >> 5;
-    constexpr int th = 0;                            // (a workgroup owns all the tables)
-    const int r_base = th * G::ROWS;                 // its first bucket row
-    const int r_own = r_base + w * G::RW;            // this wavefront's bucket rows
-    // backward pass through the soft assignment: the tables (or the share of one table) behind this wavefront's rows
-    const int tl0 = (w * G::RW) / C::R;              // first table, counted inside the workgroup
-    const int ro = (w * G::RW) % C::R;               // first corner of the share (0 unless a table spans several wavefronts)
+    const int n16 = lane & 15, q16 = lane >> 4;
+    // this wavefront's first table (R = 16, fewer tables than wavefronts: wavefronts w and w + 4 share one)
+    const int tl0 = G::TS == 2 ? (w & 3) : w * G::TPW;
+    const int r_own = tl0 * C::R;                    // ... and its bucket rows
     constexpr bool intra = INTRA;
-    // shapes with fewer than 8 x 32 bucket rows: only the first NRW wavefronts carry statistics; the others take
-    // part in the production, the loads and dX
-    const bool has_rows = G::NRW == kWaves || w < G::NRW;
 
     const size_t base = static_cast<size_t>(bh) * a.N * C::D;
-    Q += base; K += base; V += base; O += base; dO += base;
-    dX += base;
-    den += static_cast<size_t>(bh) * a.N;
-    const bf16raw *Xr = SIDE == 0 ? Q : K;
-    const float *Mw = (SIDE == 0 ? a.Mk : a.Mq) + static_cast<size_t>(bh) * a.N * C::LP;
+    Xr += base; V += base; dX += base;
+    const bf16raw *Gr = G_ + base;                   // cotangent rows and their extra column (may be dX's own memory: read two tiles ahead)
+    const float *ge = a.ge + static_cast<size_t>(bh) * a.N;
+    const size_t mbase = static_cast<size_t>(bh) * ((a.N + kTile - 1) / kTile) * (kTile * C::LP);
+    const float *Mw = (SIDE == 0 ? a.Mk : a.Mq) + mbase, *Mr = (SIDE == 0 ? a.Mq : a.Mk) + mbase;
     const float *st = a.state + (static_cast<size_t>(bh) * a.nseg + (INTRA ? seg : 0)) * C::STATE;     // (not causal: the totals)
 
     {
@@ -198,22 +153,36 @@ void grad_kernel(KArgs a, const bf16raw *Q, const bf16raw *K, const bf16raw *V, 
             *reinterpret_cast<u32x4 *>(wp + row * C::XS + ch * 8) = *reinterpret_cast<const u32x4 *>(src + row * C::D + ch * 8);
         }
     }
-    if (G::TABLES * C::R != G::ROWS || C::TPG * C::PP < 32) {
-        // projection slots of tables that do not exist are never written below: they must be zeros for dX = dz . W
+    if (C::L * C::PP < C::LPP) {
+        // projection slots that belong to no table are never written below: they must be zeros for dX = dz . W
         for (int i = tid; i < kTile * S::DZS; i += kThreads) dz[i] = 0;
     }
-    // statistics at the start of the segment, transposed tiles ST[row tile][column tile]: columns x 32 bucket rows
-    f32x16 ST[G::MTG][C::NT];
-    float macc[G::MTG];       // extra column (A or dA): per-half partial sum, lane n <-> row r_own + 32 mr + n
+    // the off-diagonal 16 x 16 tile of the in-tile term that the mask clears is never written below
+    if (intra && tid < 128) ttop[tid] = u32x4{0u, 0u, 0u, 0u};
+    // statistics at the start of the segment, transposed tiles: columns x bucket rows
+    f32x16 ST[G::MTG][C::NT];                        // R = 64: 32 x 32 tiles [row tile][column tile]
+    f32x4 SU[G::TPW][C::D / 16];                     // R = 16: 16 x 16 tiles [table][column tile]
+    float macc[G::T16 ? G::TPW : G::MTG];            // extra column (A or dA): lane partials of row r_own + 32 mr + ln (16 i + n16)
+    float *mass = reinterpret_cast<float *>(lds + S::mass) + w * G::TPW * 16;
+    if constexpr (G::T16) {
 #pragma unroll
-    for (int mr = 0; mr < G::MTG; ++mr) {
+        for (int i = 0; i < G::TPW; ++i) {
 #pragma unroll
-        for (int mtc = 0; mtc < C::NT; ++mtc) {
-#pragma unroll
-            for (int v = 0; v < 16; ++v)
-                ST[mr][mtc][v] = has_rows ? st[(r_own + 32 * mr + ln) * C::D + 32 * mtc + acc_row(v, h)] : 0.f;
+            for (int ct = 0; ct < C::D / 16; ++ct)
+                SU[i][ct] = *reinterpret_cast<const f32x4 *>(st + (r_own + 16 * i + n16) * C::D + 16 * ct + 4 * q16);
+            macc[i] = q16 == 0 ? st[C::LR * C::D + r_own + 16 * i + n16] : 0.f;
+            if (q16 == 0) mass[16 * i + n16] = macc[i];
         }
-        macc[mr] = (has_rows && h == 0) ? st[C::LR * C::D + r_own + 32 * mr + ln] : 0.f;
+    } else {
+#pragma unroll
+        for (int mr = 0; mr < G::MTG; ++mr) {
+#pragma unroll
+            for (int mtc = 0; mtc < C::NT; ++mtc) {
+#pragma unroll
+                for (int v = 0; v < 16; ++v) ST[mr][mtc][v] = st[(r_own + 32 * mr + ln) * C::D + 32 * mtc + acc_row(v, h)];
+            }
+            macc[mr] = h == 0 ? st[C::LR * C::D + r_own + 32 * mr + ln] : 0.f;
+        }
     }
 
     const int64_t t_begin = seg * a.seg_len;
@@ -222,28 +191,78 @@ void grad_kernel(KArgs a, const bf16raw *Q, const bf16raw *K, const bf16raw *V, 
     auto tile_t0 = [&](int it) { return t_begin + static_cast<int64_t>(kReverse ? ntiles - 1 - it : it) * kTile; };
     auto tile_nv = [&](int64_t t0) { return (t_end - t0 < kTile) ? static_cast<int>(t_end - t0) : kTile; };
 
-    // loads run ahead of the arithmetic: issued a step ahead, written to LDS at the next tile's start
-    RowChunks<C, kTile> pre_r, pre_v;
-    MassChunks<C, kTile> pre_w;
-    CotChunks<C, kTile> pre_c;
-    auto fetch = [&](int it) {
+    // rows: requested two tiles ahead, written to LDS one tile ahead (the reader's in the second half of a tile, behind its
+    // projection; the others in the first)
+    RowChunks<C, kTile> pre_r, pre_v, pre_g;
+    float pre_ge = 0.f;
+    auto fetch_y = [&](int it) __attribute__((always_inline)) {
         const int64_t t0 = tile_t0(it);
         const int nv = tile_nv(t0);
-        fetch_rows<C, kTile, true>(Xr, t0, nv, pre_r);
-        if (intra) fetch_masses<C, kTile>(Mw, t0, nv, pre_w);
-        if (SIDE == 1 || intra) fetch_rows<C, kTile, true>(V, t0, nv, pre_v);
-        if (SIDE == 0 || intra) fetch_cotangent<C, kTile, true>(dO, O, den, t0, nv, pre_c);
+        if (SIDE == 1 || intra) fetch_rows<C, kTile>(V, t0, nv, pre_v);
+        if (SIDE == 0 || intra) {
+            fetch_rows<C, kTile>(Gr, t0, nv, pre_g);
+            pre_ge = (ge + t0)[static_cast<uint32_t>(ln < nv ? ln : nv - 1)];
+        }
     };
-    if (ntiles > 0) fetch(0);
+    auto fetch_x = [&](int it) __attribute__((always_inline)) {
+        const int64_t t0 = tile_t0(it);
+        fetch_rows<C, kTile>(Xr, t0, tile_nv(t0), pre_r);
+    };
+    auto stage_y = [&](int it) __attribute__((always_inline)) {
+        if (SIDE == 0) {
+            store_rows<C, kTile, C::XS, G::YORDER>(pre_g, buf_yr(it));
+            if (intra) store_rows<C, kTile, C::YS, G::YORDER>(pre_v, buf_yw(it));
+        } else {
+            store_rows<C, kTile, C::XS, G::YORDER>(pre_v, buf_yr(it));
+            if (intra) store_rows<C, kTile, C::YS, G::YORDER>(pre_g, buf_yw(it));
+        }
+        if (tid < kTile) {
+            buf_sr(it)[tid] = SIDE == 0 ? pre_ge : 1.f;
+            buf_sw(it)[tid] = SIDE == 0 ? 1.f : pre_ge;
+        }
+    };
+    auto stage_x = [&](int it) __attribute__((always_inline)) {
+        store_rows<C, kTile>(pre_r, buf_xr(it));
+        if (UNIT) store_row_scales<C, kTile>(pre_r, buf_nrm(it));
+    };
+    using Sh = Share<C, G::SLOTS>;
+    const int slot = 2 * (w & (G::SLOTS / 2 - 1)) + h;
+    const bool produces = intra && w < G::SLOTS / 2;
+    typename Sh::Regs pre_w;
+    const uint32_t woff = table_offset<C>(Sh::table(slot, 0), ln);
+    // the reader's hashed rows: R = 64: token ln of the wavefront's table; R = 16: tokens n16 (and 16 + n16) of its tables
+    const int th0 = G::TS == 2 ? w >> 2 : 0;
+    const uint32_t roff = table_offset<C>(tl0, G::T16 ? 16 * th0 + n16 : ln);
+    // this wavefront's roles in the first half (compile-time tables, looked up once)
+    int my_dx = -1, my_tt = -1, my_proj[2] = {-1, -1};
+#pragma unroll
+    for (int i = 0; i < C::NT; ++i) my_dx = w == G::dx_wave(i, INTRA) ? i : my_dx;
+#pragma unroll
+    for (int i = 0; i < 3; ++i) my_tt = w == G::tt_wave(i) ? i : my_tt;
+#pragma unroll
+    for (int i = 0; i < 2 * C::PT; ++i) {
+        if (w == G::proj_wave(i, INTRA)) {
+            if (my_proj[0] < 0) my_proj[0] = i;
+            else my_proj[1] = i;
+        }
+    }
+    if (ntiles > 0) {
+        fetch_x(0);
+        fetch_y(0);
+        if (produces) Sh::load(Mw + tile_t0(0) * C::LP, woff, ln, pre_w);
+        stage_x(0);
+        stage_y(0);
+        if (ntiles > 1) { fetch_x(1); fetch_y(1); }
+        __syncthreads();
+    }
 
     // ---- dX = dz . W for one tile (the chain rule through W): a wavefront forms the transposed 32 x 32 tile of its
     //      column tile nt (lane = token, registers = columns 32 nt + acc_row(v, h)), stages it in its own corner of
-    //      LDS and stores 16-byte row pieces; nobody else touches that corner.  Called one step late (after the
-    //      next tile's first barrier, which also publishes dz), so that it runs next to the production phase
-    //      instead of keeping everybody waiting at the end of the tile; xr_t, nrm_t: the tile's reader rows and scales
-    //      (unit-norm option).
-    static_assert(C::NT <= kWaves, "one wavefront per column tile");
-    auto dx_stage = [&](int nt, int64_t t0, int nvalid, const bf16raw *xr_t, const float *nrm_t) __attribute__((always_inline)) {
+    //      LDS and stores 16-byte row pieces; nobody else touches that corner.  Called one tile late, next to the
+    //      production of the following tile.
+    auto dx_stage = [&](int nt, int it) __attribute__((always_inline)) {
+        const int64_t t0 = tile_t0(it);
+        const int nvalid = tile_nv(t0);
         const int lo = opaque(lane);                     // addresses below are rebuilt per tile, not kept in registers
         const int lno = lo & 31, ho = lo >> 5;
         f32x16 acc = {0};
@@ -251,10 +270,11 @@ void grad_kernel(KArgs a, const bf16raw *Q, const bf16raw *K, const bf16raw *V, 
         for (int s = 0; s < C::LPP / 16; ++s)
             acc = mma(lds_tr_plain(wp, C::XS, 16 * s, 32 * nt, lno, ho), lds128(dz + lno * S::DZS + 16 * s + 8 * ho), acc);
         if (UNIT) {
+            const bf16raw *xr_t = buf_xr(it);
             float cp = 0.f;                              // (z . dz) / |x|^2 of token lno, parts in wavefront order
 #pragma unroll
-            for (int i = 0; i < kWaves; ++i) cp += rad[i * kTile + lno];
-            cp *= nrm_t[lno];
+            for (int i = 0; i < kWaves / G::TS; ++i) cp += rad[((G::TS == 2 ? 4 * (lno >> 4) : 0) + i) * kTile + lno];
+            cp *= buf_nrm(it)[lno];
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
                 const u32x2 xv = *reinterpret_cast<const u32x2 *>(xr_t + lno * C::XS + 32 * nt + 8 * k + 4 * ho);
@@ -264,344 +284,335 @@ void grad_kernel(KArgs a, const bf16raw *Q, const bf16raw *K, const bf16raw *V, 
                 acc[4 * k + 3] = fmaf(-cp, bf_hi(xv.y), acc[4 * k + 3]);
             }
         }
-        bf16raw *sg = stg + nt * kTile * S::SS;
-#pragma unroll
-        for (int k = 0; k < 4; ++k)
-            *reinterpret_cast<u32x2 *>(sg + lno * S::SS + 8 * k + 4 * ho) =
-                u32x2{pack2(acc[4 * k], acc[4 * k + 1]), pack2(acc[4 * k + 2], acc[4 * k + 3])};
+        // (16 tokens at a time: the wavefront's own LDS accesses are in order)
+        bf16raw *sg = stg + nt * 16 * S::SS;
+        char *dst = reinterpret_cast<char *>(dX + t0 * C::D + 32 * nt);
 #pragma unroll
         for (int kk = 0; kk < 2; ++kk) {
+            if ((lno >> 4) == kk) {
+#pragma unroll
+                for (int k = 0; k < 4; ++k)
+                    *reinterpret_cast<u32x2 *>(sg + (lno & 15) * S::SS + 8 * k + 4 * ho) =
+                        u32x2{pack2(acc[4 * k], acc[4 * k + 1]), pack2(acc[4 * k + 2], acc[4 * k + 3])};
+            }
             const int row = (lo >> 2) + 16 * kk, ch = lo & 3;
-            const u32x4 piece = *reinterpret_cast<const u32x4 *>(sg + row * S::SS + 8 * ch);
-            if (row < nvalid) *reinterpret_cast<u32x4 *>(dX + (t0 + row) * C::D + 32 * nt + 8 * ch) = piece;
+            const u32x4 piece = *reinterpret_cast<const u32x4 *>(sg + (lo >> 2) * S::SS + 8 * ch);
+            if (row < nvalid) *reinterpret_cast<u32x4 *>(dst + static_cast<uint32_t>((row * C::D + 8 * ch) * 2)) = piece;
         }
     };
-    // this wavefront's column tile of dX (-1: none), by table look-up over the compile-time assignment
-    int my_dx = -1;
-#pragma unroll
-    for (int v = 0; v < kWaves; ++v)
-        if (w == v) my_dx = G::dx_tile(v, INTRA);
-    auto tile_xr = [&](int it) { return (UNIT && (it & 1)) ? reinterpret_cast<bf16raw *>(lds + S::xr2) : xr0; };
-    auto tile_nrm = [&](int it) { return nrm0 + ((UNIT && (it & 1)) ? 2 * kTile : 0); };
 
     float dbeta_acc = 0.f;    // this lane's share of the cotangent of beta: sum of (E_t - m (p_t - q_t)) tanh z_t
-    GRAD_PHASE_DECL
     for (int it = 0; it < ntiles; ++it) {
         const int64_t t0 = tile_t0(it);
         const int nvalid = tile_nv(t0);
-        // unit-norm option: alternate tiles use alternate buffers for the reader's rows and the scales
-        bf16raw *xr = tile_xr(it);
-        float *nrm = tile_nrm(it);
+        // ================ first half
+        // the reader's hashed rows of this wavefront's tables: used in the second half
+        constexpr int kTh = G::T16 && G::TS == 1 ? 2 : 1;      // R = 16: halves of the tile's tokens
+        float rc[G::TPW * kTh][C::P];
+#pragma unroll
+        for (int i = 0; i < G::TPW * kTh; ++i)
+            load_table_codes<C>(Mr + t0 * C::LP + (i / kTh) * C::HT + (i % kTh) * 64, roff, ln, rc[i]);      // (16 tokens are 64 floats)
+        if (it + 1 < ntiles) {
+            stage_y(it + 1);
+            if (it + 2 < ntiles) fetch_y(it + 2);
+        }
+        if (it > 0 && my_dx >= 0) dx_stage(my_dx, it - 1);
+        if (produces) {
+            produce<C, G::SLOTS, C::PST>(pre_w, slot, ln, a.soft(), ln < nvalid, phw);
+            if (it + 1 < ntiles) Sh::load(Mw + tile_t0(it + 1) * C::LP, woff, ln, pre_w);
+        }
+#pragma unroll
+        for (int pi = 0; pi < 2; ++pi) {
+            // tanh z and 1 - tanh^2 z of 16 packed hyperplanes x 16 tokens
+            if (my_proj[pi] < 0) break;
+            const int pt = my_proj[pi] >> 1, tok = 16 * (my_proj[pi] & 1) + n16, quad = 4 * pt + q16, at = quad * kTile + tok;
+            f32x4 z = {0.f, 0.f, 0.f, 0.f};
+            const bf16raw *wrow = wp + (16 * pt + n16) * C::XS + 8 * q16, *xrow = buf_xr(it) + tok * C::XS + 8 * q16;
+#pragma unroll
+            for (int s = 0; s < C::D / 32; ++s) z = mma16(lds128(wrow + 32 * s), lds128(xrow + 32 * s), z);
+            if (UNIT) z = z * buf_nrm(it)[tok];
+            f32x4 sv, uv;
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const float e2 = __expf(-2.0f * fabsf(z[v])), inv = __builtin_amdgcn_rcpf(1.0f + e2), ua = (1.0f - e2) * inv;
+                sv[v] = 4.0f * e2 * inv * inv;
+                uv[v] = z[v] >= 0.f ? ua : -ua;
+            }
+            if (C::L * C::PP % 16 == 0 || quad < S::QUADS) {
+                s2t[at] = sv;
+                if (a.want_dbeta) tht[at] = uv;
+                if (UNIT) zzt[at] = z;
+            }
+        }
+        if (intra && my_tt >= 0) {
+            // T^T[b][a] = Yw_b . Yr_a + sw_b sr_a, one of the three 16 x 16 tiles (b, a) that the mask leaves: the two on the
+            // diagonal and one off it; both row tiles keep their columns in the same order, which is all a contraction needs
+            const int bt = my_tt < 2 ? my_tt : (kReverse ? 1 : 0), at = my_tt < 2 ? my_tt : 1 - bt;
+            const bf16raw *brow = buf_yw(it) + (16 * bt + n16) * C::YS + 8 * q16, *arow = buf_yr(it) + (16 * at + n16) * C::XS + 8 * q16;
+            f32x4 tt = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int s = 0; s < C::D / 32; ++s) tt = mma16(lds128(brow + 32 * s), lds128(arow + 32 * s), tt);
+            const int ai = 16 * at + n16;
+            const float sra = buf_sr(it)[ai];
+            const f32x4 swb = *reinterpret_cast<const f32x4 *>(buf_sw(it) + 16 * bt + 4 * q16);
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int b = 16 * bt + 4 * q16 + v;
+                tt[v] = (kReverse ? b >= ai : b <= ai) ? fmaf(swb[v], sra, tt[v]) : 0.f;
+            }
+            // R = 64: rows 4 q .. of k-step bt belong to lane half q % 2, words 2 (q / 2) .. of its operand;
+            // R = 16: k-slots 4 .. 7 of a lane are its rows of the second tile
+            uint32_t *dst = G::T16 ? reinterpret_cast<uint32_t *>(ttop + 64 * at + lane) + 2 * bt
+                                   : reinterpret_cast<uint32_t *>(ttop + 64 * bt + 32 * (q16 & 1) + ai) + 2 * (q16 >> 1);
+            *reinterpret_cast<u32x2 *>(dst) = u32x2{pack2(tt[0], tt[1]), pack2(tt[2], tt[3])};
+        }
+        __syncthreads();
 
-        // ---- registers -> LDS
-        store_rows<C, kTile>(pre_r, xr, nvalid);
-        if (intra) store_masses<C, kTile>(pre_w, mw);
-        if (UNIT) store_row_scales<C, kTile>(pre_r, nrm);
-        if (SIDE == 0) {
-            store_cotangent<C, kTile, C::XS, true>(pre_c, yr, sr, a.L_real, nvalid);
-            if (intra) store_rows<C, kTile, C::YS, true>(pre_v, yw, nvalid);
-            if (tid < kTile) sw[tid] = 1.f;
+        // ================ second half
+        const bf16raw *yr = buf_yr(it), *yw = buf_yw(it);
+        if constexpr (G::T16) {
+            // ---- R = 16.  Per table and half of the tokens, lane (n16, q16): cotangents of corners 4 q16 + v of token 16 th + n16.
+            // The sums over corners and the finish are those of the other form, below: bits 0, 1 of the corner are the
+            // register, bits 2, 3 the row of lanes; lane row q16 finishes hyperplane q16.
+            const int tr_ph = 4 * (((lane & 1) << 1) | ((lane >> 1) & 1));         // a table's corners: blocks 0, 2, 1, 3
+            float radial[kTh];
+#pragma unroll
+            for (int t = 0; t < kTh; ++t) radial[t] = 0.f;
+#pragma unroll
+            for (int i = 0; i < G::TPW; ++i) {
+                u32x4 sop[C::D / 32];
+#pragma unroll
+                for (int j = 0; j < C::D / 32; ++j)
+                    sop[j] = u32x4{pack2(SU[i][2 * j][0], SU[i][2 * j][1]), pack2(SU[i][2 * j][2], SU[i][2 * j][3]),
+                                   pack2(SU[i][2 * j + 1][0], SU[i][2 * j + 1][1]), pack2(SU[i][2 * j + 1][2], SU[i][2 * j + 1][3])};
+                u32x4 pa;
+                if (intra) pa = lds_tr16(phw + r_own + 16 * i, C::PST, 4 * q16, 16 + 4 * q16, tr_ph, lane);
+                const f32x4 am = *reinterpret_cast<const f32x4 *>(mass + 16 * i + 4 * q16);
+#pragma unroll
+                for (int th = 0; th < kTh; ++th) {
+                    const int tok = 16 * (th0 + th) + n16;
+                    const float *c = rc[i * kTh + th];
+                    f32x4 dP = am * buf_sr(it)[tok];
+                    if (intra) dP = mma16(pa, ttop[64 * (th0 + th) + lane], dP);
+                    const bf16raw *yrow = yr + tok * C::XS + 8 * q16;
+#pragma unroll
+                    for (int j = 0; j < C::D / 32; ++j) dP = mma16(sop[j], lds128(yrow + 32 * j), dP);
+                    float p[4], q[4];
+                    bool mn[4];
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) {
+                        code_masses(c[t], p[t], q[t]);
+                        mn[t] = (__float_as_uint(c[t]) >> 31) != 0;
+                    }
+                    const float F = ((q16 & 1) ? p[2] : q[2]) * ((q16 & 2) ? p[3] : q[3]), F0 = F * q[1], F1 = F * p[1];
+                    const float w0 = F0 * q[0] * dP[0], w1 = F0 * p[0] * dP[1], w2 = F1 * q[0] * dP[2], w3 = F1 * p[0] * dP[3];
+                    const float s01 = w0 + w1, s23 = w2 + w3, m = s01 + s23;
+                    const float Gt = sum_rows4(mn[0] ? w1 + w3 : w0 + w2, mn[1] ? s23 : s01, mn[2] == ((q16 & 1) != 0) ? m : 0.f,
+                                               mn[3] == ((q16 & 2) != 0) ? m : 0.f);
+                    const float mt = sum_rows(m);
+                    // (values, not elements: a selection between array elements is taken for an index and sends the array to memory)
+                    const float c0 = c[0], c1 = c[1], c2 = c[2], c3 = c[3];
+                    const float ce = (q16 & 2) ? ((q16 & 1) ? +c3 : +c2) : ((q16 & 1) ? +c1 : +c0);
+                    const float small = fabsf(ce), big = 1.0f - small;
+                    const float half = small * (mt - Gt) - big * Gt;
+                    const float du = (__float_as_uint(ce) >> 31) ? -2.f * half : 2.f * half;
+                    const int at = ((tl0 + i) * kTile + tok) * 4 + q16;
+                    float dzv = a.beta * du * reinterpret_cast<const float *>(s2t)[at];
+                    if (UNIT) dzv *= buf_nrm(it)[tok];
+                    const uint32_t dzw = pack2(dzv, 0.f);
+                    dz[tok * S::DZS + 4 * (tl0 + i) + q16] = static_cast<bf16raw>(dzw);
+                    if (a.want_dbeta && tok < nvalid) dbeta_acc = fmaf(du, reinterpret_cast<const float *>(tht)[at], dbeta_acc);
+                    if (UNIT) radial[th] = fmaf(reinterpret_cast<const float *>(zzt)[at], bf_lo(dzw), radial[th]);
+                }
+                if (intra) {
+                    // ---- statistics += Yw^T . phi_writer
+                    const u32x4 pb = lds_tr16(phw + r_own + 16 * i, C::PST, 8 * q16, 8 * q16 + 4, tr_ph, lane);
+                    if (SIDE == 1)
+                        macc[i] += wsum8(pb, *reinterpret_cast<const float4 *>(buf_sw(it) + 8 * q16), *reinterpret_cast<const float4 *>(buf_sw(it) + 8 * q16 + 4));
+                    else macc[i] += sum8(pb);
+#pragma unroll
+                    for (int ct = 0; ct < C::D / 16; ++ct)
+                        SU[i][ct] = mma16(lds_tr16(yw, C::YS, 8 * q16, 8 * q16 + 4, 32 * (ct >> 1) + 8 * (lane & 3) + 4 * (ct & 1), lane), pb, SU[i][ct]);
+                    const float tot = sum_rows(macc[i]);
+                    if (q16 == 0) mass[16 * i + n16] = tot;
+                }
+            }
+            if (UNIT) {
+#pragma unroll
+                for (int th = 0; th < kTh; ++th) {
+                    const float x = sum_rows(radial[th]);
+                    if (q16 == 0) rad[w * kTile + 16 * (th0 + th) + n16] = x;
+                }
+            }
         } else {
-            store_rows<C, kTile, C::XS, true>(pre_v, yr, nvalid);
-            if (intra) store_cotangent<C, kTile, C::YS, true>(pre_c, yw, sw, a.L_real, nvalid);
-            if (tid < kTile) sr[tid] = 1.f;
-        }
-        GRAD_PHASE(0)
-        __syncthreads();
-        GRAD_PHASE(1)
-        if (it > 0 && my_dx >= 0) {
-            const int64_t tp = tile_t0(it - 1);
-            dx_stage(my_dx, tp, tile_nv(tp), tile_xr(it - 1), tile_nrm(it - 1));
-        }
-        GRAD_PHASE(12)
+            // extra columns as bf16 (hi, lo) pairs: three products hi*hi + hi*lo + lo*hi keep 16 mantissa bits
+            float sr_hi, sr_lo;
+            split_bf16(buf_sr(it)[ln], sr_hi, sr_lo);
+            const u32x4 sr_a = (h == 0) ? u32x4{pack2(sr_hi, sr_hi), pack2(sr_lo, 0.f), 0u, 0u} : u32x4{0u, 0u, 0u, 0u};
 
-        // extra columns as bf16 (hi, lo) pairs: three products hi*hi + hi*lo + lo*hi keep 16 mantissa bits
-        float sr_hi, sr_lo;
-        split_bf16(sr[ln], sr_hi, sr_lo);
-        const u32x4 sr_a = (h == 0) ? u32x4{pack2(sr_hi, sr_hi), pack2(sr_lo, 0.f), 0u, 0u} : u32x4{0u, 0u, 0u, 0u};
-
-        // ---- production, by role (see GradCfg): writer wavefronts hash the writer's tables into phw; reader
-        //      wavefronts project the reader and leave its per-bit masses (p, q, sech^2) in pm for the backward
-        //      pass through the soft assignment; one more forms the in-tile term
-        //      T^T[b][a] = Yw_b . Yr_a + sw_b * sr_a, masked, as MFMA operands for everybody
-        if (intra && w < G::NW) {
-            const int pg = w % G::NGW, pj = (w / G::NGW) % C::TPL, as = w / (G::NGW * C::TPL);
-            constexpr int kShare = (1 << C::PHI) / G::AS;
-            write_assignments<C, C::PST>(f32x16{0}, th * G::NGW + pg, ln, h, a.soft(), ln < nvalid, phw, pj, C::TPL, as * kShare,
-                                         (as + 1) * kShare, nullptr, mw + ln * C::MS);
-        }
-        constexpr int kRd0 = INTRA ? G::RD0 : 0, kNr = INTRA ? G::NR : G::NR_NC, kRj = INTRA ? G::RJ : G::RJ_NC;
-        if (w >= kRd0 && w < kRd0 + kNr) {
-            const int pg = (w - kRd0) % G::NGW, rj = (w - kRd0) / G::NGW;
-            const f32x16 zr = project<C>(wp, xr, th * G::NGW + pg, ln, h, UNIT ? nrm : nullptr);
+            // ---- per 32-row tile of this wavefront: cotangent of the reader's assignments, transposed (lane = token,
+            //      register v = bucket row r_own + 32 mr + acc_row(v, h)), then straight back through the corner
+            //      softmax (Algorithm 1, step 4) in those registers: with w_c = phi_c dphi_c over the corners c of a
+            //      table, m = sum_c w_c and, per bit t, G_t = sum of w_c over the corners on the bit's MINOR side
+            //      (the side with the smaller mass min(p_t, q_t)).  The cotangent of u_t = tanh z_t is
+            //      beta (E_t - m (p_t - q_t)) with E_t = sum_c v_{c,t} w_c; written as
+            //      +-2 beta (small_t (m - G_t) - big_t G_t) it has no cancellation when the bit is saturated
+            //      (small_t ~ 1e-7 at beta = 8), which the cotangent of beta needs.  Register v of lane half h is corner
+            //      co + 8 (v/4 mod KM) + 4h + v%4 of table tl0 + (32 mr + 8 (v/4)) / R: bits 0,1 come from v, bit 2
+            //      from h, bits 3.. from v, the bits above from the tile.  phi_c is the product over bits of p_t (bit set) or
+            //      q_t (Section 3.3: the corner softmax factorises); the minor side of bit t is -1 where the code is positive.
+            float rec[8];                  // [m, G_0 .. G_{P-1}] of the lane's token (lane partials)
 #pragma unroll
-            for (int j = 0; j < C::TPL; ++j) {
-                if ((th * G::NGW + pg) * C::TPG + h * C::TPL + j >= C::L) break;
-                if (j % kRj != rj) continue;
-                float p[C::PP], q[C::PP], s2[C::PP], u[C::PP], zz[C::PP];
+            for (int t = 0; t < 8; ++t) rec[t] = 0.f;
+            float p[C::P], q[C::P];
+            bool mn[C::P];                 // the minor side of bit t is the value 1 (else the value 0)
 #pragma unroll
-                for (int t = 0; t < C::PP; ++t) {
-                    p[t] = q[t] = s2[t] = u[t] = 0.f;
-                    zz[t] = t < C::P ? zr[zslot<C>(j, t)] : 0.f;
+            for (int t = 0; t < C::P; ++t) {
+                code_masses(rc[0][t], p[t], q[t]);
+                mn[t] = (__float_as_uint(rc[0][t]) >> 31) != 0;
+            }
+#pragma unroll
+            for (int mr = 0; mr < G::MTG; ++mr) {
+                f32x16 dP;
+                {
+                    // extra column first: sr_a * (A or dA)[r] with the masses before this tile
+                    float m_hi, m_lo;
+                    split_bf16(sum_halves(macc[mr]), m_hi, m_lo);
+                    const u32x4 mb = (h == 0) ? u32x4{pack2(m_hi, m_lo), pack2(m_hi, 0.f), 0u, 0u} : u32x4{0u, 0u, 0u, 0u};
+                    dP = mma(mb, sr_a, f32x16{0});
                 }
-                float *dst = pm + ((pg * C::TPG + h * C::TPL + j) * kTile + ln) * S::PMS;
-                // (a padding table has zero statistics and zero cotangents: any finite masses will do)
-                if (!C::PAD || (th * G::NGW + pg) * C::TPG + h * C::TPL + j < a.L_real) bit_masses<C>(zr, j, a.soft(), p, q, s2, u);
+                if (intra) {
 #pragma unroll
-                for (int t = 0; t < C::PP; t += 4) {
-                    *reinterpret_cast<float4 *>(dst + t) = float4{p[t], p[t + 1], p[t + 2], p[t + 3]};
-                    *reinterpret_cast<float4 *>(dst + C::PP + t) = float4{q[t], q[t + 1], q[t + 2], q[t + 3]};
-                    *reinterpret_cast<float4 *>(dst + 2 * C::PP + t) = float4{s2[t], s2[t + 1], s2[t + 2], s2[t + 3]};
-                    *reinterpret_cast<float4 *>(dst + 3 * C::PP + t) = float4{u[t], u[t + 1], u[t + 2], u[t + 3]};
-                    if (UNIT) *reinterpret_cast<float4 *>(dst + 4 * C::PP + t) = float4{zz[t], zz[t + 1], zz[t + 2], zz[t + 3]};
+                    for (int s = 0; s < 2; ++s)
+                        dP = mma(lds_tr_acc<true>(phw, C::PST, 16 * s, r_own + 32 * mr, ln, h), ttop[64 * s + lane], dP);
+                }
+                {
+                    const int yo = opaque(ln * C::XS + 8 * h);       // pair-interleaved columns: one 16-byte read per k-step
+#pragma unroll
+                    for (int mtc = 0; mtc < C::NT; ++mtc) {
+#pragma unroll
+                        for (int s = 0; s < 2; ++s) {
+                            const int cc = 32 * mtc + 16 * s;
+                            dP = mma(acc_operand(ST[mr][mtc], s), lds128(yr + yo + cc), dP);
+                        }
+                    }
+                }
+                {
+                    const int co = 32 * mr;            // first corner of the tile in the table
+                    float F = h ? p[2] : q[2];
+#pragma unroll
+                    for (int t = 5; t < C::P; ++t) F *= ((co >> t) & 1) ? p[t] : q[t];
+                    const float Fl[4] = {F * q[0] * q[1], F * p[0] * q[1], F * q[0] * p[1], F * p[0] * p[1]};
+                    float m = 0.f, G0 = 0.f, G1 = 0.f, Gm[2] = {0.f, 0.f};
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) {
+                        const float mid = ((k & 1) ? p[3] : q[3]) * ((k & 2) ? p[4] : q[4]);
+                        const float w0 = Fl[0] * dP[4 * k], w1 = Fl[1] * dP[4 * k + 1], w2 = Fl[2] * dP[4 * k + 2], w3 = Fl[3] * dP[4 * k + 3];
+                        const float s01 = w0 + w1, s23 = w2 + w3;
+                        const float c = mid * (s01 + s23);
+                        G0 = fmaf(mid, mn[0] ? w1 + w3 : w0 + w2, G0);
+                        G1 = fmaf(mid, mn[1] ? s23 : s01, G1);
+                        m += c;
+#pragma unroll
+                        for (int b = 0; b < 2; ++b) Gm[b] += (mn[3 + b] == (((k >> b) & 1) != 0)) ? c : 0.f;
+                    }
+                    // lane partials; bit 2 is the lane half, the bits above the tile's are uniform
+                    rec[0] += m;
+                    rec[1] += G0;
+                    rec[2] += G1;
+                    rec[3] += (mn[2] == (h != 0)) ? m : 0.f;
+#pragma unroll
+                    for (int b = 0; b < 2; ++b) rec[4 + b] += Gm[b];
+#pragma unroll
+                    for (int t = 5; t < C::P; ++t) rec[1 + t] += (mn[t] == (((co >> t) & 1) != 0)) ? m : 0.f;
                 }
             }
-        }
-        if (intra && w == G::TT) {
-            f32x16 tt = {0};
-            // both tiles keep their columns in the same (pair-interleaved) order, which is all a contraction needs
-            const int yo = opaque(ln * C::XS + 8 * h), ywo = opaque(ln * C::YS + 8 * h);
-#pragma unroll
-            for (int s = 0; s < C::D / 16; ++s) tt = mma(lds128(yw + ywo + 16 * s), lds128(yr + yo + 16 * s), tt);
-            float sw_hi, sw_lo;
-            split_bf16(sw[ln], sw_hi, sw_lo);
-            const u32x4 sw_a = (h == 0) ? u32x4{pack2(sw_hi, sw_hi), pack2(sw_lo, 0.f), 0u, 0u} : u32x4{0u, 0u, 0u, 0u};
-            const u32x4 sr_b = (h == 0) ? u32x4{pack2(sr_hi, sr_lo), pack2(sr_hi, 0.f), 0u, 0u} : u32x4{0u, 0u, 0u, 0u};
-            tt = mma(sw_a, sr_b, tt);
-#pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int b = acc_row(v, h);
-                const bool keep = kReverse ? (b >= ln) : (b <= ln);
-                tt[v] = keep ? tt[v] : 0.f;
-            }
-            ttop[lane] = acc_operand(tt, 0);
-            ttop[64 + lane] = acc_operand(tt, 1);
-        }
-        GRAD_PHASE(2)
-        __syncthreads();
-        GRAD_PHASE(3)
-        // the next tile's loads are issued a whole step ahead and fly during everything below
-        if (it + 1 < ntiles) fetch(it + 1);
-        GRAD_PHASE(4)
-
-        // ---- per 32-row tile of this wavefront: cotangent of the reader's assignments, transposed (lane = token,
-        //      register v = bucket row r_own + 32 mr + acc_row(v, h)), then straight back through the corner
-        //      softmax (Algorithm 1, step 4) in those registers: with w_c = phi_c dphi_c over the corners c of a
-        //      table, m = sum_c w_c and, per bit t, G_t = sum of w_c over the corners on the bit's MINOR side
-        //      (the side with the smaller mass min(p_t, q_t)).  The cotangent of u_t = tanh z_t is
-        //      beta (E_t - m (p_t - q_t)) with E_t = sum_c v_{c,t} w_c; written as
-        //      +-2 beta (small_t (m - G_t) - big_t G_t) it has no cancellation when the bit is saturated
-        //      (small_t ~ 1e-7 at beta = 8), which the cotangent of beta needs.  Register v of lane half h is corner
-        //      co + 8 (v/4 mod KM) + 4h + v%4 of table tl0 + (32 mr + 8 (v/4)) / R: bits 0,1 come from v, bit 2
-        //      from h, bits 3.. from v, the bits above from the tile and the wavefront's share.  phi_c is the
-        //      product over bits of p_t (bit set) or q_t (Section 3.3: the corner softmax factorises).
-        float rec[G::TWW][8];          // [m, G_0 .. G_{P-1}] of the lane's token per table of the wavefront (lane partials)
-#pragma unroll
-        for (int i = 0; i < G::TWW; ++i) {
-#pragma unroll
-            for (int t = 0; t < 8; ++t) rec[i][t] = 0.f;
-        }
-#pragma unroll
-        for (int mr = 0; mr < G::MTG; ++mr) {
-            if (!has_rows) break;
-            f32x16 dP;
+            // ---- finish per (token, table): du_t = +-2 beta (small_t (m - G_t) - big_t G_t),  dz_t = du_t (1 - tanh^2 z_t);
+            //      the two lane halves hold the two values of bit 2: add them up; lane half h' takes the quad 4h' .. 4h'+3
+            // unit-norm option: dz is the cotangent of W xhat, so the reader's row gets dx = (g - xhat (xhat . g)) / |x| with
+            // g = W^T dz and xhat . g = z . dz; dz is scaled by 1 / |x| here and this lane's share of z . dz is summed from the
+            // bf16 values the matrix product below will see (which keeps dx orthogonal to x to fp32 accuracy)
+            float radial = 0.f;
             {
-                // extra column first: sr_a * (A or dA)[r] with the masses before this tile
-                float m_hi, m_lo;
-                split_bf16(macc[mr] + __shfl_xor(macc[mr], 32, 64), m_hi, m_lo);
-                const u32x4 mb = (h == 0) ? u32x4{pack2(m_hi, m_lo), pack2(m_hi, 0.f), 0u, 0u} : u32x4{0u, 0u, 0u, 0u};
-                dP = mma(mb, sr_a, f32x16{0});
-            }
-            if (intra) {
+                const float rs = UNIT ? buf_nrm(it)[ln] : 1.f;
 #pragma unroll
-                for (int s = 0; s < 2; ++s)
-                    dP = mma(lds_tr_acc<true>(phw, C::PST, 16 * s, r_own + 32 * mr, ln, h), ttop[64 * s + lane], dP);
-            }
-            {
-                const int yo = opaque(ln * C::XS + 8 * h);       // pair-interleaved columns: one 16-byte read per k-step
+                for (int t = 0; t <= C::P; ++t) rec[t] = sum_halves(rec[t]);
+                {
+                    const int quad = (C::PP / 4) * tl0 + h, at = quad * kTile + ln;
+                    const f32x4 s2 = s2t[at];
+                    f32x4 uu = {0.f, 0.f, 0.f, 0.f};
+                    if (a.want_dbeta) uu = tht[at];
+                    float dzv[4];
 #pragma unroll
-                for (int mtc = 0; mtc < C::NT; ++mtc) {
-#pragma unroll
-                    for (int s = 0; s < 2; ++s) {
-                        const int cc = 32 * mtc + 16 * s;
-                        dP = mma(acc_operand(ST[mr][mtc], s), lds128(yr + yo + cc), dP);
+                    for (int e = 0; e < 4; ++e) {
+                        // slots beyond the table's hyperplanes: all mass on one side, no minor side, du = 0
+                        const float ce = h ? (4 + e < C::P ? rc[0][4 + e < C::P ? 4 + e : 0] : 0.f) : rc[0][e];
+                        const float Gt = h ? (4 + e < C::P ? rec[4 + e < C::P ? 5 + e : 0] : 0.f) : rec[1 + e];
+                        const float small = fabsf(ce), big = 1.0f - small;
+                        const float half = small * (rec[0] - Gt) - big * Gt;
+                        const float du = (__float_as_uint(ce) >> 31) ? -2.f * half : 2.f * half;    // cotangent of u_t up to the factor beta
+                        dzv[e] = a.beta * du * s2[e] * rs;
+                        if (a.want_dbeta && ln < nvalid) dbeta_acc = fmaf(du, uu[e], dbeta_acc);   // (not the copies past the end)
+                    }
+                    const u32x2 dzw = {pack2(dzv[0], dzv[1]), pack2(dzv[2], dzv[3])};
+                    *reinterpret_cast<u32x2 *>(dz + ln * S::DZS + 4 * quad) = dzw;
+                    if (UNIT) {
+                        const f32x4 z4 = zzt[at];
+                        radial = fmaf(z4[0], bf_lo(dzw.x), radial);
+                        radial = fmaf(z4[1], bf_hi(dzw.x), radial);
+                        radial = fmaf(z4[2], bf_lo(dzw.y), radial);
+                        radial = fmaf(z4[3], bf_hi(dzw.y), radial);
                     }
                 }
             }
-#pragma unroll
-            for (int tw = 0; tw < G::TW; ++tw) {
-                constexpr int kTilesPerTable = C::R >= 32 ? C::R / 32 : 1;
-                const int ti = C::R >= 32 ? mr / kTilesPerTable : mr * G::TW + tw;   // table of the wavefront
-                const int co = C::R >= 32 ? ro + 32 * (mr % kTilesPerTable) : 0;     // first corner of the tile in its table
-                const float *src = pm + ((tl0 + ti) * kTile + ln) * S::PMS;
-                float p[C::PP], q[C::PP];
-#pragma unroll
-                for (int t = 0; t < C::PP; t += 4) {
-                    const float4 p4 = *reinterpret_cast<const float4 *>(src + t);
-                    const float4 q4 = *reinterpret_cast<const float4 *>(src + C::PP + t);
-                    p[t] = p4.x; p[t + 1] = p4.y; p[t + 2] = p4.z; p[t + 3] = p4.w;
-                    q[t] = q4.x; q[t + 1] = q4.y; q[t + 2] = q4.z; q[t + 3] = q4.w;
-                }
-                float F = h ? p[2] : q[2];
-#pragma unroll
-                for (int t = 3 + G::MB; t < C::P; ++t) F *= ((co >> t) & 1) ? p[t] : q[t];
-                const float Fl[4] = {F * q[0] * q[1], F * p[0] * q[1], F * q[0] * p[1], F * p[0] * p[1]};
-                bool mn[C::PP];                    // the minor side of bit t is the value 1 (else the value 0)
-#pragma unroll
-                for (int t = 0; t < C::PP; ++t) mn[t] = p[t] < q[t];
-                float m = 0.f, G0 = 0.f, G1 = 0.f, Gm[2] = {0.f, 0.f};
-#pragma unroll
-                for (int k = 0; k < G::KM; ++k) {
-                    float mid = 1.f;
-#pragma unroll
-                    for (int b = 0; b < G::MB; ++b) mid *= ((k >> b) & 1) ? p[3 + b] : q[3 + b];
-                    const int v0 = 4 * (tw * G::KM + k);
-                    const float w0 = Fl[0] * dP[v0], w1 = Fl[1] * dP[v0 + 1], w2 = Fl[2] * dP[v0 + 2], w3 = Fl[3] * dP[v0 + 3];
-                    const float s01 = w0 + w1, s23 = w2 + w3;
-                    const float c = mid * (s01 + s23);
-                    G0 = fmaf(mid, mn[0] ? w1 + w3 : w0 + w2, G0);
-                    G1 = fmaf(mid, mn[1] ? s23 : s01, G1);
-                    m += c;
-#pragma unroll
-                    for (int b = 0; b < G::MB; ++b) Gm[b] += (mn[3 + b] == (((k >> b) & 1) != 0)) ? c : 0.f;
-                }
-                // lane partials; bit 2 is the lane half, the bits above the tile's are uniform
-                rec[ti][0] += m;
-                rec[ti][1] += G0;
-                rec[ti][2] += G1;
-                rec[ti][3] += (mn[2] == (h != 0)) ? m : 0.f;
-#pragma unroll
-                for (int b = 0; b < G::MB; ++b) rec[ti][4 + b] += Gm[b];
-#pragma unroll
-                for (int t = 3 + G::MB; t < C::P; ++t) rec[ti][1 + t] += (mn[t] == (((co >> t) & 1) != 0)) ? m : 0.f;
+            if (UNIT) {
+                radial = sum_halves(radial);
+                if (h == 0) rad[w * kTile + ln] = radial;
             }
-        }
-        // the two lane halves hold the two values of bit 2: add them up
+            // ---- statistics += Yw^T . phi_writer
+            if (intra) {
 #pragma unroll
-        for (int i = 0; i < G::TWW; ++i) {
+                for (int s = 0; s < 2; ++s) {
+                    float4 g0 = {1.f, 1.f, 1.f, 1.f}, g1 = g0;          // SIDE 0: the extra column of [V | 1] is one
+                    if (SIDE == 1) {
+                        g0 = *reinterpret_cast<const float4 *>(buf_sw(it) + 16 * s + 8 * h);
+                        g1 = *reinterpret_cast<const float4 *>(buf_sw(it) + 16 * s + 8 * h + 4);
+                    }
+                    u32x4 ay[C::NT];
 #pragma unroll
-            for (int t = 0; t <= C::P; ++t) rec[i][t] += __shfl_xor(rec[i][t], 32, 64);
-        }
-        if (G::WPT > 1 && has_rows && ro != 0) {
-            // a later share of a table: hand the partial sums to the wavefront that owns the table's first share
-            float *dst = part + ((w * kTile + ln) * 8 + 4 * h);
-            *reinterpret_cast<float4 *>(dst) = float4{rec[0][4 * h], rec[0][4 * h + 1], rec[0][4 * h + 2], rec[0][4 * h + 3]};
-        }
-        GRAD_PHASE(5)
-        // ---- statistics += Yw^T . phi_writer
-        if (intra && has_rows) {
+                    for (int mtc = 0; mtc < C::NT; ++mtc) ay[mtc] = lds_tr_plain<true>(yw, C::YS, 16 * s, 32 * mtc, ln, h);
 #pragma unroll
-            for (int s = 0; s < 2; ++s) {
-                float4 g0 = {1.f, 1.f, 1.f, 1.f}, g1 = g0;          // SIDE 0: the extra column of [V | 1] is one
-                if (SIDE == 1) {
-                    g0 = *reinterpret_cast<const float4 *>(sw + 16 * s + 8 * h);
-                    g1 = *reinterpret_cast<const float4 *>(sw + 16 * s + 8 * h + 4);
-                }
-                u32x4 ay[C::NT];
+                    for (int mr = 0; mr < G::MTG; ++mr) {
+                        const u32x4 bp = lds_tr_plain<true>(phw, C::PST, 16 * s, r_own + 32 * mr, ln, h);
+                        macc[mr] += SIDE == 1 ? wsum8(bp, g0, g1) : sum8(bp);
 #pragma unroll
-                for (int mtc = 0; mtc < C::NT; ++mtc) ay[mtc] = lds_tr_plain<true>(yw, C::YS, 16 * s, 32 * mtc, ln, h);
-#pragma unroll
-                for (int mr = 0; mr < G::MTG; ++mr) {
-                    const u32x4 bp = lds_tr_plain<true>(phw, C::PST, 16 * s, r_own + 32 * mr, ln, h);
-                    macc[mr] += SIDE == 1 ? wsum8(bp, g0, g1) : sum8(bp);
-#pragma unroll
-                    for (int mtc = 0; mtc < C::NT; ++mtc) ST[mr][mtc] = mma(ay[mtc], bp, ST[mr][mtc]);
+                        for (int mtc = 0; mtc < C::NT; ++mtc) ST[mr][mtc] = mma(ay[mtc], bp, ST[mr][mtc]);
+                    }
                 }
             }
         }
-        GRAD_PHASE(10)
-        GRAD_PHASE(6)
-        __syncthreads();        // partial sums are visible; the tiles of this step are dead from here on
-        GRAD_PHASE(7)
-
-        // ---- finish per (token, table): du_t = +-2 beta (small_t (m - G_t) - big_t G_t),  dz_t = du_t (1 - tanh^2 z_t);
-        //      lane half h' takes the padded projection slots 4h' .. 4h'+3
-        // unit-norm option: dz is the cotangent of W xhat, so the reader's row gets dx = (g - xhat (xhat . g)) / |x| with
-        // g = W^T dz and xhat . g = z . dz; dz is scaled by 1 / |x| here and this lane's share of z . dz is summed from the
-        // bf16 values the matrix product below will see (which keeps dx orthogonal to x to fp32 accuracy)
-        float radial = 0.f;
-        if (has_rows && ro == 0) {
-            const float rs = UNIT ? nrm[ln] : 1.f;
-#pragma unroll
-            for (int ti = 0; ti < G::TWW; ++ti) {
-                if (4 * h >= C::PP) break;
-                const int tl = tl0 + ti;
-#pragma unroll
-                for (int o = 1; o < G::WPT; ++o) {
-                    const float *src = part + ((w + o) * kTile + ln) * 8;
-                    const float4 p0 = *reinterpret_cast<const float4 *>(src);
-                    const float4 p1 = *reinterpret_cast<const float4 *>(src + 4);
-                    rec[ti][0] += p0.x; rec[ti][1] += p0.y; rec[ti][2] += p0.z; rec[ti][3] += p0.w;
-                    rec[ti][4] += p1.x; rec[ti][5] += p1.y; rec[ti][6] += p1.z; rec[ti][7] += p1.w;
-                }
-                const float *src = pm + (tl * kTile + ln) * S::PMS + 4 * h;
-                const float4 p4 = *reinterpret_cast<const float4 *>(src);
-                const float4 q4 = *reinterpret_cast<const float4 *>(src + C::PP);
-                const float4 s4 = *reinterpret_cast<const float4 *>(src + 2 * C::PP);
-                const float4 u4 = *reinterpret_cast<const float4 *>(src + 3 * C::PP);
-                const float pp[4] = {p4.x, p4.y, p4.z, p4.w}, qq[4] = {q4.x, q4.y, q4.z, q4.w};
-                const float s2[4] = {s4.x, s4.y, s4.z, s4.w};
-                const float uu[4] = {u4.x, u4.y, u4.z, u4.w};
-                float dzv[4];
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    // G of slot 4h + e is rec[1 + 4h + e]; slot 7 is padding (P <= 7) and has no entry
-                    const float Gt = h ? (e < 3 ? rec[ti][e < 3 ? 5 + e : 0] : 0.f) : rec[ti][1 + e];
-                    const bool minor1 = pp[e] < qq[e];                          // same predicate as where G was summed
-                    const float small = minor1 ? pp[e] : qq[e], big = minor1 ? qq[e] : pp[e];
-                    const float half = small * (rec[ti][0] - Gt) - big * Gt;
-                    const float du = minor1 ? -2.f * half : 2.f * half;         // cotangent of u_t up to the factor beta
-                    dzv[e] = a.beta * du * s2[e] * rs;                          // padded slots: p = q = s2 = 0
-                    dbeta_acc = fmaf(du, uu[e], dbeta_acc);                     // ... and tanh = 0
-                }
-                // slot 4c.. of the lane-half hh's j-th table is projection row 8 (slots-per-table/4 * j + c) + 4 hh of its group
-                const int gl = tl / C::TPG, tg = tl % C::TPG, hh = tg / C::TPL, j = tg % C::TPL;
-                const int col = gl * 32 + 8 * ((C::PP / 4) * j + h) + 4 * hh;
-                const u32x2 dzw = {pack2(dzv[0], dzv[1]), pack2(dzv[2], dzv[3])};
-                *reinterpret_cast<u32x2 *>(dz + ln * S::DZS + col) = dzw;
-                if (UNIT) {
-                    const float4 z4 = *reinterpret_cast<const float4 *>(src + 4 * C::PP);
-                    radial = fmaf(z4.x, bf_lo(dzw.x), radial);
-                    radial = fmaf(z4.y, bf_hi(dzw.x), radial);
-                    radial = fmaf(z4.z, bf_lo(dzw.y), radial);
-                    radial = fmaf(z4.w, bf_hi(dzw.y), radial);
-                }
-            }
+        if (it + 1 < ntiles) {
+            stage_x(it + 1);
+            if (it + 2 < ntiles) fetch_x(it + 2);
         }
-        if (UNIT) {
-            radial += __shfl_xor(radial, 32, 64);
-            if (h == 0) rad[w * kTile + ln] = radial;
-        }
-        GRAD_PHASE(9)
-        GRAD_PHASE(11)
-        // (dX of this tile is formed after the next step's first barrier, see dx_stage)
-        // no barrier here: the next step's loads-to-LDS touch none of dz, pm, part or the staging tiles, its production
-        // (which rewrites pm) comes after the next barrier, and so does this tile's dX, which reads dz (rewritten only after
-        // two more barriers) and, with the unit-norm option, this tile's reader rows and scales (the next step stores into
-        // the other buffer, the step after that only after barriers the dX wavefronts take part in).
+        __syncthreads();        // dz is visible; this tile's assignments, in-tile term and tanh are dead from here on
     }
-    if (ntiles > 0) {
-        __syncthreads();        // the last tile's dz is visible
-        if (my_dx >= 0) {
-            const int64_t tp = tile_t0(ntiles - 1);
-            dx_stage(my_dx, tp, tile_nv(tp), tile_xr(ntiles - 1), tile_nrm(ntiles - 1));
-        }
-    }
+    if (ntiles > 0 && my_dx >= 0) dx_stage(my_dx, ntiles - 1);
     // ---- cotangent of beta: lanes -> wavefront (shuffles) -> workgroup (LDS, wavefront order) -> one workspace slot
-    {
+    if (a.want_dbeta) {
 #pragma unroll
         for (int m = 32; m >= 1; m >>= 1) dbeta_acc += __shfl_xor(dbeta_acc, m, 64);
         __syncthreads();
-        if (lane == 0) sr[w] = dbeta_acc;
+        float *sums = reinterpret_cast<float *>(lds + S::sr);
+        if (lane == 0) sums[w] = dbeta_acc;
         __syncthreads();
         if (tid == 0) {
             float s = 0.f;
-            for (int i = 0; i < kWaves; ++i) s += sr[i];
+            for (int i = 0; i < kWaves; ++i) s += sums[i];
             const int wgs = gridDim.x;                  // workgroups per (side, batch*head)
             a.dbeta_part[(static_cast<size_t>(SIDE) * gridDim.y + bh) * wgs + seg] = s;
         }
     }
-    GRAD_PHASE_PRINT()
 }
 
 }  // namespace mfma

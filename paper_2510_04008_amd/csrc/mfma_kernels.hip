@@ -25,136 +25,111 @@ namespace mfma {
 
 enum Mode { kTotalsKV = 0, kTotalsQG = 1, kForward = 2, kGradV = 3 };
 
-// Developer aid: per-phase cycle counts of one workgroup, printed at kernel end (build with -DRACE_PHASE_TIMING).
-#ifdef RACE_PHASE_TIMING
-#define RACE_PHASE_DECL long long ph_t[12] = {0}; long long ph_last = clock64();
-#define RACE_PHASE(i) { long long now_ = clock64(); ph_t[i] += now_ - ph_last; ph_last = now_; }
-#define RACE_PHASE_PRINT(tag) if (blockIdx.x == 1 && blockIdx.y == 0 && (threadIdx.x & 63) == 0) \
-    printf("%s mode %d wave %d tiles %d: load %lld prod %lld contr %lld upd %lld redw %lld epi %lld | waits %lld %lld %lld %lld %lld\n", tag, MODE, (int)(threadIdx.x >> 6), ntiles, \
-           ph_t[0], ph_t[2], ph_t[4], ph_t[5], ph_t[7], ph_t[9], ph_t[1], ph_t[3], ph_t[6], ph_t[8], ph_t[10]);
-#else
-#define RACE_PHASE_DECL
-#define RACE_PHASE(i)
-#define RACE_PHASE_PRINT(tag)
-#endif
-
 // state element (bucket row r, column c) in the saved layout: B [LR][D] row-major, then A [LR]
 template <class C>
 __device__ __forceinline__ int state_b(int r, int c) { return r * C::D + c; }
 template <class C>
 __device__ __forceinline__ int state_a(int r) { return C::LR * C::D + r; }
 
+// ================================================================ hash_kernel
+// z^T (32 packed rows of W) x (32 tokens): lane (n, h) ends up with packed rows 8 (v / 4) + 4 h + v % 4 of token n in register
+// v, i.e. with natural order (row = table * PP + t) the quads t = 4 h' .. 4 h' + 3 of whole tables.
 template <class C>
-__device__ __forceinline__ void load_projection_matrix(const KArgs &a, int head, bf16raw *wp)
+struct WRows { u32x4 w[C::D / 16]; };             // this lane's row of a group, as A operands
+template <class C>
+__device__ __forceinline__ void load_w_rows(const bf16raw *Wp, int g, int ln, int h, WRows<C> &r)
 {
-    const bf16raw *src = a.Wp + static_cast<size_t>(head) * C::LPP * C::D;
-    for (int c = threadIdx.x; c < C::LPP * C::CPR; c += kThreads) {
-        const int row = c / C::CPR, ch = c % C::CPR;
-        *reinterpret_cast<u32x4 *>(wp + row * C::XS + ch * 8) = *reinterpret_cast<const u32x4 *>(src + row * C::D + ch * 8);
+#pragma unroll
+    for (int s = 0; s < C::D / 16; ++s) r.w[s] = *reinterpret_cast<const u32x4 *>(Wp + (g * 32 + ln) * C::D + 16 * s + 8 * h);
+}
+template <class C>
+__device__ __forceinline__ f32x16 project(const WRows<C> &w, const u32x4 (&x)[C::D / 16])
+{
+    // two accumulators halve the chain of dependent MFMAs
+    f32x16 z0 = {0}, z1 = {0};
+#pragma unroll
+    for (int s = 0; s < C::D / 16; s += 2) {
+        z0 = mma(w.w[s], x[s], z0);
+        z1 = mma(w.w[s + 1], x[s + 1], z1);
     }
+    return z0 + z1;
+}
+// 1 / max(|x|, 1e-12) of the row whose elements 16 s + 8 h .. + 7 the two lane halves hold (fp32 sum of squares)
+template <class C>
+__device__ __forceinline__ float row_scale(const u32x4 (&x)[C::D / 16])
+{
+    float ss = 0.f;
+#pragma unroll
+    for (int s = 0; s < C::D / 16; ++s) ss = dot2(x[s].x, x[s].x, dot2(x[s].y, x[s].y, dot2(x[s].z, x[s].z, dot2(x[s].w, x[s].w, ss))));
+    ss += __shfl_xor(ss, 32, 64);
+    return __builtin_amdgcn_rsqf(fmaxf(ss, 1e-24f));
 }
 
-// ================================================================ hash_kernel
-// Algorithm 1, steps 2-4 up to the per-bit masses, for every row of Q (blockIdx.z + first == 0) or K (== 1):
-// z = W x on the matrix cores, then one float per (table, hyperplane), see bit_code().  No state is carried, so the
-// grid is over token ranges: many small workgroups that hide each other's latencies, unlike the scans that follow.
-template <class C>
-struct HashLds {
-    static constexpr int SLOTS = 4 / C::NG;                             // 32-token tiles per step (four wavefronts)
-    static constexpr int TT = 32 * SLOTS;
-    static constexpr int wp = 0;                                        // [LPP][XS] bf16
-    static constexpr int x = wp + C::LPP * C::XS * 2;                   // [TT][XS] bf16 rows
-    static constexpr int out = x + TT * C::XS * 2;                      // [TT][MS] fp32 hashed rows
-    static constexpr int nx = out + TT * C::MS * 4;                     // [TT] fp32: 1 / |x| (unit-norm option)
-    static constexpr int total = nx + TT * 4;
-};
+// Algorithm 1, steps 2-4 up to the per-bit masses, for every row of Q (blockIdx.z + first == 0) or K (== 1): one float per
+// (table, hyperplane), see bit_code().  Bound by memory: every wavefront streams tiles of 32 rows on its own (no LDS, no
+// barrier): its rows of W stay in registers, a row of X is 16-byte pieces straight from memory (the second group's
+// wavefront finds them in L1), the results leave as contiguous pieces of a table's 32 tokens, and the next tile's rows are
+// requested before the current one's arithmetic.  (Through LDS tiles with three barriers a step, 64 rows a step:
+// 3.4 ms for 33.5 million rows of 128 columns at L = 8, P = 6.)
 constexpr int kHashThreads = 256;
 constexpr int kHashTokens = 512;        // most tokens per workgroup (amortises the load of W)
+template <class C> constexpr int hash_tiles() { return 4 / C::NG; }        // tiles a workgroup's wavefronts take at a time
 
 template <class C, bool UNIT>
 __global__ __launch_bounds__(kHashThreads) void hash_kernel(KArgs a, const bf16raw *Xq, const bf16raw *Xk, int first)
 {
-    using S = HashLds<C>;
-    constexpr int TT = S::TT;
-    extern __shared__ __attribute__((aligned(256))) unsigned char lds[];
-    bf16raw *wp = reinterpret_cast<bf16raw *>(lds + S::wp);
-    bf16raw *xs = reinterpret_cast<bf16raw *>(lds + S::x);
-    float *out = reinterpret_cast<float *>(lds + S::out);
-    float *nx = reinterpret_cast<float *>(lds + S::nx);
     const int which = static_cast<int>(blockIdx.z) + first;
     const int bh = blockIdx.y, head = bh % a.H;
-    const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, ln = lane & 31, h = lane >> 5;
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, ln = lane & 31, h = lane >> 5;
+    const int g = w % C::NG;
     const bf16raw *X = (which ? Xk : Xq) + static_cast<size_t>(bh) * a.N * C::D;
-    float *M = (which ? a.Mk : a.Mq) + static_cast<size_t>(bh) * a.N * C::LP;
-    {
-        const bf16raw *src = a.Wp + static_cast<size_t>(head) * C::LPP * C::D;
-        for (int c = tid; c < C::LPP * C::CPR; c += kHashThreads) {
-            const int row = c / C::CPR, ch = c % C::CPR;
-            *reinterpret_cast<u32x4 *>(wp + row * C::XS + ch * 8) = *reinterpret_cast<const u32x4 *>(src + row * C::D + ch * 8);
-        }
-    }
-    const int64_t t_begin = static_cast<int64_t>(blockIdx.x) * a.hash_tokens;
-    const int64_t t_end = (t_begin + a.hash_tokens < a.N) ? t_begin + a.hash_tokens : a.N;
+    const int64_t all_tiles = (a.N + kTile - 1) / kTile;
+    float *M = (which ? a.Mk : a.Mq) + static_cast<size_t>(bh) * all_tiles * kTile * C::LP;
+    WRows<C> wr;
+    load_w_rows<C>(a.Wp + static_cast<size_t>(head) * C::LPP * C::D, g, ln, h, wr);
+    const int64_t t_first = static_cast<int64_t>(blockIdx.x) * (a.hash_tokens / kTile);
+    const int64_t t_end = (t_first + a.hash_tokens / kTile < all_tiles) ? t_first + a.hash_tokens / kTile : all_tiles;
     const Soft sf = a.soft();
-    for (int64_t t0 = t_begin; t0 < t_end; t0 += TT) {
-        const int nv = (t_end - t0 < TT) ? static_cast<int>(t_end - t0) : TT;
-        // rows -> LDS (rows past the end repeat the last one: their results are not stored)
-        for (int c = tid; c < TT * C::CPR; c += kHashThreads) {
-            const int row = c / C::CPR, ch = c % C::CPR;
-            const int rr = row < nv ? row : nv - 1;
-            const u32x4 v = *reinterpret_cast<const u32x4 *>(X + (t0 + rr) * C::D + ch * 8);
-            *reinterpret_cast<u32x4 *>(xs + row * C::XS + ch * 8) = v;
-            if (UNIT) {
-                const uint32_t xw[4] = {v.x, v.y, v.z, v.w};
-                float ss = 0.f;
+    // (rows past the end repeat the last one: finite values in the padding of the last tile)
+    auto fetch = [&](int64_t tile, u32x4 (&x)[C::D / 16]) __attribute__((always_inline)) {
+        const int64_t t = tile * kTile + ln;
+        const bf16raw *src = X + (t < a.N ? t : a.N - 1) * C::D + 8 * h;
 #pragma unroll
-                for (int e = 0; e < 4; ++e) ss = dot2(xw[e], xw[e], ss);
+        for (int s = 0; s < C::D / 16; ++s) x[s] = *reinterpret_cast<const u32x4 *>(src + 16 * s);
+    };
+    int64_t tile = t_first + w / C::NG;
+    u32x4 x[C::D / 16];
+    if (tile < t_end) fetch(tile, x);
+    for (; tile < t_end; tile += hash_tiles<C>()) {
+        f32x16 z = project<C>(wr, x);
+        if (UNIT) z = z * row_scale<C>(x);
+        if (tile + hash_tiles<C>() < t_end) fetch(tile + hash_tiles<C>(), x);
+        float *Mt = M + tile * (kTile * C::LP);
 #pragma unroll
-                for (int m = C::CPR / 2; m >= 1; m >>= 1) ss += __shfl_xor(ss, m, 64);     // the chunks of a row sit in consecutive lanes
-                if (ch == 0) nx[row] = __builtin_amdgcn_rsqf(fmaxf(ss, 1e-24f));
-            }
+        for (int k = 0; k < 4; ++k) {
+            // this lane's quad of registers 4 k .. 4 k + 3: hyperplanes 4 (quad % (PP / 4)) .. of a table
+            const int quad = g * 8 + 2 * k + h, table = C::PP == 8 ? quad >> 1 : quad, t0 = C::PP == 8 ? 4 * h : 0;
+            if (table >= C::L) continue;
+            const bool real_table = !C::PAD || table < sf.L;
+            float c[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                c[e] = (real_table && (!C::PAD || t0 + e < sf.P)) ? bit_code(z[4 * k + e], sf.beta) : 0.f;
+            float *dst = Mt + table * C::HT;
+            if (C::PP == 4 || h == 0) *reinterpret_cast<float4 *>(dst + 4 * ln) = float4{c[0], c[1], c[2], c[3]};
+            else *reinterpret_cast<float2 *>(dst + 4 * kTile + 2 * ln) = float2{c[0], c[1]};
         }
-        __syncthreads();
-        {
-            const int slot = w / C::NG, g = w % C::NG;
-            const f32x16 z = project<C>(wp, xs + slot * 32 * C::XS, g, ln, h, UNIT ? nx + slot * 32 : nullptr);
-            float *orow = out + (slot * 32 + ln) * C::MS;
-#pragma unroll
-            for (int j = 0; j < C::TPL; ++j) {
-                const int table = g * C::TPG + h * C::TPL + j;
-                if (table >= C::L) break;
-                const bool real_table = !C::PAD || table < sf.L;
-#pragma unroll
-                for (int t = 0; t < C::P; t += 2) {
-                    float2 c2;
-                    c2.x = (real_table && (!C::PAD || t < sf.P)) ? bit_code(z[zslot<C>(j, t)], sf.beta) : 0.f;
-                    c2.y = (real_table && (!C::PAD || t + 1 < sf.P)) ? bit_code(z[zslot<C>(j, t + 1)], sf.beta) : 0.f;
-                    *reinterpret_cast<float2 *>(orow + table * C::P + t) = c2;
-                }
-            }
-        }
-        __syncthreads();
-        for (int c = tid; c < TT * C::MCH; c += kHashThreads) {
-            const int row = c / C::MCH, ch = c % C::MCH;
-            if (row < nv) {
-                const float2 lo = *reinterpret_cast<const float2 *>(out + row * C::MS + ch * 4);
-                const float2 hi = *reinterpret_cast<const float2 *>(out + row * C::MS + ch * 4 + 2);
-                *reinterpret_cast<float4 *>(M + (t0 + row) * C::LP + ch * 4) = float4{lo.x, lo.y, hi.x, hi.y};
-            }
-        }
-        // (the next step rewrites the row tile, which nobody reads any more, and `out` only after its first barrier)
     }
 }
 
 // ================================================================ totals_kernel
-// Statistics of one segment from a zero start, 64 tokens per step (both halves of the workgroup hash
-// 32 tokens each).  QG == 0: (phi_K, [V | 1]), Algorithm 1 step 5.  QG == 1: (phi_Q, [dO/e | -(dO.O)/e]),
+// Statistics of one segment from a zero start, 64 tokens per step (each half of the workgroup builds the assignments of
+// 32 tokens).  QG == 0: (phi_K, [V | 1]), Algorithm 1 step 5.  QG == 1: (phi_Q, [dO/e | -(dO.O)/e]),
 // the statistics the key side of the backward pass reads.
 template <class C>
 struct TotalsLds {
     static constexpr int TT = 64;
-    static constexpr int m = 0;                                         // [64][MS] fp32 hashed rows
-    static constexpr int y = m + TT * C::MS * 4;                        // [64][YS] accumulated rows
+    static constexpr int y = 0;                                         // [64][YS] accumulated rows
     static constexpr int ph = y + TT * C::YS * 2;                       // [64][PST] assignments
     static constexpr int ge = ph + TT * C::PST * 2;                     // [64] fp32
     static constexpr int total = ge + TT * 4;
@@ -165,15 +140,17 @@ struct TotalsLds {
 template <class C>
 __device__ __forceinline__ bool mass_owner(int mt, int cg) { return mt % C::CG == cg; }
 
-// M: the hashed rows of the tensor whose assignments feed the statistics (K forward, Q backward).
+// M: the hashed rows of the tensor whose assignments feed the statistics (K forward, Q backward).  QG == 1 also leaves the
+// cotangent rows it forms in memory, rows in Gout (the caller's buffer for dK, which nothing else uses before dK is
+// written, tile behind tile of its own reading) and the extra column in a.ge: the passes behind it then read 260 bytes a token instead of dO,
+// O and Den, and do not form the rows again (35 of 750 vector instructions a tile and wavefront).
 template <class C, int QG>
 __global__ __launch_bounds__(kThreads, C::STREAM_WAVES_PER_SIMD)
-void totals_kernel(KArgs a, const float *M, const bf16raw *Y, const bf16raw *Oin, const float *den_in)
+void totals_kernel(KArgs a, const float *M, const bf16raw *Y, const bf16raw *Oin, const float *den_in, bf16raw *Gout)
 {
     using S = TotalsLds<C>;
     constexpr int TT = S::TT;
     extern __shared__ __attribute__((aligned(256))) unsigned char lds[];
-    float *ms = reinterpret_cast<float *>(lds + S::m);
     bf16raw *ys = reinterpret_cast<bf16raw *>(lds + S::y);
     bf16raw *ph = reinterpret_cast<bf16raw *>(lds + S::ph);
     float *ge_lds = reinterpret_cast<float *>(lds + S::ge);
@@ -183,8 +160,9 @@ void totals_kernel(KArgs a, const float *M, const bf16raw *Y, const bf16raw *Oin
     const int rg = w % C::RG, cg = w / C::RG;
     const int r_own = rg * C::LRW, c_own = cg * C::DW;
     const size_t base = static_cast<size_t>(bh) * a.N * C::D;
-    M += static_cast<size_t>(bh) * a.N * C::LP; Y += base;
-    if (QG) { Oin += base; den_in += static_cast<size_t>(bh) * a.N; }
+    M += static_cast<size_t>(bh) * ((a.N + kTile - 1) / kTile) * (kTile * C::LP); Y += base;
+    float *ge_out = a.ge + static_cast<size_t>(bh) * a.N;
+    if (QG) { Oin += base; Gout += base; den_in += static_cast<size_t>(bh) * a.N; }
     float *st = a.state + (static_cast<size_t>(bh) * a.nseg + seg) * C::STATE;
 
     f32x16 Sacc[C::MT][C::NTW];
@@ -200,13 +178,18 @@ void totals_kernel(KArgs a, const float *M, const bf16raw *Y, const bf16raw *Oin
     const int nsteps = static_cast<int>((t_end - t_begin + TT - 1) / TT);
     auto step_nv = [&](int64_t t0) { return (t_end - t0 < TT) ? static_cast<int>(t_end - t0) : TT; };
 
-    MassChunks<C, TT> pre_m;
+    // this wavefront's tokens of a step (its half) and its lanes' share of the tables
+    const int half = w / 4, slot = 2 * (w % 4) + h, row = half * kTile + ln;
+    const uint32_t lane_off = table_offset<C>(Share<C, 8>::table(slot, 0), ln);
+    typename Share<C, 8>::Regs pre_m;
     RowChunks<C, TT> pre_y;
     CotChunks<C, TT> pre_c;
     auto fetch = [&](int it) {
         const int64_t t0 = t_begin + static_cast<int64_t>(it) * TT;
         const int nv = step_nv(t0);
-        fetch_masses<C, TT>(M, t0, nv, pre_m);
+        // (the second half of the last step may lie past the end: it reads the first half's tile, and its tokens are not valid)
+        const int64_t tile = t0 / kTile + (half && nv > kTile ? 1 : 0);
+        Share<C, 8>::load(M + tile * (kTile * C::LP), lane_off, ln, pre_m);
         if (QG) fetch_cotangent<C, TT>(Y, Oin, den_in, t0, nv, pre_c);
         else fetch_rows<C, TT>(Y, t0, nv, pre_y);
     };
@@ -215,17 +198,10 @@ void totals_kernel(KArgs a, const float *M, const bf16raw *Y, const bf16raw *Oin
     for (int it = 0; it < nsteps; ++it) {
         const int64_t t0 = t_begin + static_cast<int64_t>(it) * TT;
         const int nvalid = step_nv(t0);
-        store_masses<C, TT>(pre_m, ms);
-        if (QG) store_cotangent<C, TT, C::YS>(pre_c, ys, ge_lds, a.L_real, nvalid);
-        else store_rows<C, TT, C::YS>(pre_y, ys, nvalid);
+        if (QG) store_cotangent<C, TT, C::YS>(pre_c, ys, ge_lds, a.L_real, nvalid, Gout, ge_out, t0);
+        else store_rows<C, TT, C::YS>(pre_y, ys);
+        produce<C, 8, C::PST>(pre_m, slot, row, a.soft(), row < nvalid, ph);
         if (it + 1 < nsteps) fetch(it + 1);
-        __syncthreads();
-        {
-            // wavefront = (token half, projection group, share of the group's tables)
-            const int half = w / 4, g = w % C::NG, jq = (w % 4) / C::NG;
-            write_assignments<C, C::PST>(f32x16{0}, g, half * 32 + ln, h, a.soft(), half * 32 + ln < nvalid, ph, jq, C::JSTEP, 0,
-                                         1 << C::PHI, nullptr, ms + (half * 32 + ln) * C::MS);
-        }
         __syncthreads();
 #pragma unroll
         for (int s = 0; s < TT / 16; ++s) {
@@ -266,25 +242,21 @@ void totals_kernel(KArgs a, const float *M, const bf16raw *Y, const bf16raw *Oin
 //   kForward: Algorithm 2's loop body (Algorithm 1's read-out when not causal): O and Den.
 //   kGradV  : the mirrored pass, right to left, over the cotangent statistics: dV.
 // "reader" = tensor whose assignments read the statistics (Q forward, K for dV), "writer" = tensor
-// whose assignments feed them (K forward, Q for dV), Y = rows accumulated (V forward, dO/e for dV).
+// whose assignments feed them (K forward, Q for dV), Y = rows accumulated (V forward, the
+// cotangent rows for dV).
 template <class C>
 struct StreamLds {
     static constexpr int y = 0;                                         // [32][YS] bf16: accumulated rows
     static constexpr int mass = y + kTile * C::YS * 2;                  // [LR] fp32: bucket masses A before this tile, pair-interleaved
-    static constexpr int dnp = mass + C::LR * 4;                        // [4][2][32] fp32: mass read-outs per reader wavefront and lane half
-    static constexpr int mr = (dnp + 4 * 2 * kTile * 4 + 255) & ~255;   // [32][MS] fp32: hashed reader rows
-    static constexpr int mw = mr + kTile * C::MS * 4;                   // [32][MS] fp32: hashed writer rows
-    static constexpr int phr = (mw + kTile * C::MS * 4 + 15) & ~15;     // [32][PS] reader assignments
+    static constexpr int dnp = mass + C::LR * 4;                        // [2][4][2][32] fp32: mass read-outs per reader wavefront and lane
+                                                                        // half, two buffers used by alternate tiles
+    static constexpr int phr = (dnp + 2 * 4 * 2 * kTile * 4 + 255) & ~255;   // [32][PS] reader assignments
     static constexpr int phw = phr + kTile * C::PS * 2;                 // [32][PS] writer assignments
-    static constexpr int endA = phw + kTile * C::PS * 2;
-    // reduction over the bucket-row groups.  Where LDS allows it has bytes of its own: the epilogue of a tile then runs
-    // next to the staging of the following tile instead of between two barriers of its own; otherwise it reuses the
-    // bytes of the assignment tiles.
+    // reduction over the bucket-row groups, in bytes of its own: a tile's sums are formed next to the production of the
+    // following tile
     static constexpr int RS = C::D + 4;                                 // fp32 row stride: D numerators, 1 normaliser part
-    static constexpr int red_bytes = C::RG * kTile * RS * 4;            // [RG][32][RS] fp32
-    static constexpr bool kOwnRed = ((endA + 255) & ~255) + red_bytes <= 160 * 1024;
-    static constexpr int red = kOwnRed ? ((endA + 255) & ~255) : mr;
-    static constexpr int total = kOwnRed ? red + red_bytes : (endA > mr + red_bytes ? endA : mr + red_bytes);
+    static constexpr int red = (phw + kTile * C::PS * 2 + 255) & ~255;  // [RG][32][RS] fp32
+    static constexpr int total = red + C::RG * kTile * RS * 4;
     static_assert(total <= 160 * 1024, "LDS budget");
 };
 
@@ -294,16 +266,13 @@ struct StreamLds {
 // Mr, Mw: the hashed rows of the reader and the writer tensor.
 template <class C, int MODE, bool NC>
 __global__ __launch_bounds__(kThreads, C::STREAM_WAVES_PER_SIMD)
-void stream_kernel(KArgs a, const float *Mr, const float *Mw, const bf16raw *Y, const bf16raw *Oin,
-                   const float *den_in, bf16raw *Out, float *den_out)
+void stream_kernel(KArgs a, const float *Mr, const float *Mw, const bf16raw *Y, bf16raw *Out, float *den_out)
 {
     using S = StreamLds<C>;
     extern __shared__ __attribute__((aligned(256))) unsigned char lds[];
     bf16raw *ytile = reinterpret_cast<bf16raw *>(lds + S::y);
     float *mass = reinterpret_cast<float *>(lds + S::mass);
     float *dnp = reinterpret_cast<float *>(lds + S::dnp);
-    float *mr = reinterpret_cast<float *>(lds + S::mr);
-    float *mw = reinterpret_cast<float *>(lds + S::mw);
     bf16raw *phr = reinterpret_cast<bf16raw *>(lds + S::phr);
     bf16raw *phw = reinterpret_cast<bf16raw *>(lds + S::phw);
     float *red = reinterpret_cast<float *>(lds + S::red);
@@ -316,9 +285,9 @@ void stream_kernel(KArgs a, const float *Mr, const float *Mw, const bf16raw *Y, 
     const bool intra = NC ? false : a.causal != 0;    // causal: the tile's own keys take part
 
     const size_t base = static_cast<size_t>(bh) * a.N * C::D;
-    Mr += static_cast<size_t>(bh) * a.N * C::LP; Mw += static_cast<size_t>(bh) * a.N * C::LP;
+    const size_t mbase = static_cast<size_t>(bh) * ((a.N + kTile - 1) / kTile) * (kTile * C::LP);
+    Mr += mbase; Mw += mbase;
     Y += base; Out += base;
-    if (MODE == kGradV) { Oin += base; den_in += static_cast<size_t>(bh) * a.N; }
     if (MODE == kForward) den_out += static_cast<size_t>(bh) * a.N;
     // statistics at the start of the segment (not causal: the totals, which the scan leaves in the first segment's place)
     const float *st = a.state + (static_cast<size_t>(bh) * a.nseg + (NC ? 0 : (a.causal ? seg : 0))) * C::STATE;
@@ -344,26 +313,26 @@ void stream_kernel(KArgs a, const float *Mr, const float *Mw, const bf16raw *Y, 
     auto tile_t0 = [&](int it) { return t_begin + static_cast<int64_t>(kReverse ? ntiles - 1 - it : it) * kTile; };
     auto tile_nv = [&](int64_t t0) { return (t_end - t0 < kTile) ? static_cast<int>(t_end - t0) : kTile; };
 
+    // production: wavefronts 0-3 build the reader's assignments, 4-7 the writer's; a lane's token is ln, its tables by slot
+    const int side = w / 4, slot = 2 * (w % 4) + h;
+    const uint32_t lane_off = table_offset<C>(Share<C, 8>::table(slot, 0), ln);
     // loads run one tile ahead of the arithmetic
-    MassChunks<C, kTile> pre_r, pre_w;
+    typename Share<C, 8>::Regs pre_m;
     RowChunks<C, kTile> pre_y;
-    CotChunks<C, kTile> pre_c;
     auto fetch = [&](int it) {
         const int64_t t0 = tile_t0(it);
-        const int nv = tile_nv(t0);
-        fetch_masses<C, kTile>(Mr, t0, nv, pre_r);
-        if (intra) {
-            fetch_masses<C, kTile>(Mw, t0, nv, pre_w);
-            if (MODE == kGradV) fetch_cotangent<C, kTile>(Y, Oin, den_in, t0, nv, pre_c);
-            else fetch_rows<C, kTile>(Y, t0, nv, pre_y);
-        }
+        if (side == 0 || intra) Share<C, 8>::load((side == 0 ? Mr : Mw) + t0 * C::LP, lane_off, ln, pre_m);
+        if (intra) fetch_rows<C, kTile>(Y, t0, tile_nv(t0), pre_y);
     };
     if (ntiles > 0) fetch(0);
 
     const float inv_tables = 1.0f / static_cast<float>(a.L_real);
     // ---- epilogue of one tile: thread = (token, pieces of 4 columns: 4i.. and, for d = 128, 64 + 4i..; consecutive
     //      threads read consecutive 16-byte pieces of the partials): sum, normalise, store
-    auto epilogue = [&](int64_t t0, int nvalid) __attribute__((always_inline)) {
+    auto epilogue = [&](int it) __attribute__((always_inline)) {
+        const int64_t t0 = tile_t0(it);
+        const int nvalid = tile_nv(t0);
+        const float *dnr = dnp + (it & 1) * 256;
         {
         constexpr int NP = C::D / 64;                // pieces of 4 columns per thread
         const int tok = tid >> 4, c0 = (tid & 15) * 4;
@@ -382,7 +351,7 @@ void stream_kernel(KArgs a, const float *Mr, const float *Mw, const bf16raw *Y, 
                 }
             }
             if (MODE == kForward) {
-                const float dpart = dnp[gg * 64 + tok] + dnp[gg * 64 + 32 + tok];
+                const float dpart = dnr[gg * 64 + tok] + dnr[gg * 64 + 32 + tok];
                 e += gg < C::RG ? src[C::D] + dpart : dpart;
             }
         }
@@ -397,42 +366,19 @@ void stream_kernel(KArgs a, const float *Mr, const float *Mw, const bf16raw *Y, 
         }
     }
     };
-    RACE_PHASE_DECL
+    __syncthreads();        // the bucket masses are in place
     for (int it = 0; it < ntiles; ++it) {
-        const int64_t t0 = tile_t0(it);
-        const int nvalid = tile_nv(t0);
-        // (the reduction buffer has bytes of its own: the previous tile's epilogue runs here, next to this tile's staging)
-        if (S::kOwnRed && it > 0) {
-            const int64_t tp = tile_t0(it - 1);
-            epilogue(tp, tile_nv(tp));
+        const int nvalid = tile_nv(tile_t0(it));
+        // ---- first half: the previous tile's output, this tile's rows and assignments -> LDS
+        if (it > 0) epilogue(it - 1);
+        if (intra) store_rows<C, kTile, C::YS>(pre_y, ytile);
+        if (side == 0) {
+            const float dnl = produce<C, 8, C::PS>(pre_m, slot, ln, a.soft(), true, phr, MODE == kForward ? mass : nullptr);
+            if (MODE == kForward) dnp[(it & 1) * 256 + w * 64 + lane] = dnl;      // this lane's tables' share of the normaliser
+        } else if (intra) {
+            produce<C, 8, C::PS>(pre_m, slot, ln, a.soft(), ln < nvalid, phw);
         }
-
-        // ---- registers -> LDS, then start the next tile's loads
-        store_masses<C, kTile>(pre_r, mr);
-        if (intra) {
-            store_masses<C, kTile>(pre_w, mw);
-            if (MODE == kGradV) store_cotangent<C, kTile, C::YS>(pre_c, ytile, nullptr, a.L_real, nvalid);
-            else store_rows<C, kTile, C::YS>(pre_y, ytile, nvalid);
-        }
-        RACE_PHASE(0)
         __syncthreads();
-        RACE_PHASE(1)
-
-        // ---- production: wavefront = (side, projection group, share of the group's tables)
-        {
-            const int side = w / 4, g = w % C::NG, jq = (w % 4) / C::NG;
-            if (side == 0) {
-                const float dnl = write_assignments<C>(f32x16{0}, g, ln, h, a.soft(), true, phr, jq, C::JSTEP, 0, 1 << C::PHI,
-                                                       MODE == kForward ? mass : nullptr, mr + ln * C::MS);
-                if (MODE == kForward) dnp[w * 64 + lane] = dnl;       // this lane's tables' share of the normaliser
-            } else if (intra) {
-                write_assignments<C>(f32x16{0}, g, ln, h, a.soft(), ln < nvalid, phw, jq, C::JSTEP, 0, 1 << C::PHI, nullptr,
-                                     mw + ln * C::MS);
-            }
-        }
-        RACE_PHASE(2)
-        __syncthreads();
-        RACE_PHASE(3)
 
         // ---- contraction with the register-resident statistics (own bucket rows x own columns)
         f32x16 out[C::NTW];     // read-out, transposed: lane = reader token, register v = column acc_row(v, h) of the tile
@@ -474,7 +420,6 @@ void stream_kernel(KArgs a, const float *Mr, const float *Mw, const bf16raw *Y, 
             }
         }
         if (intra) {
-            RACE_PHASE(4)
             // ---- statistics += phi_writer^T . Y  (the read-out above used the old statistics)
 #pragma unroll
             for (int s = 0; s < 2; ++s) {
@@ -491,11 +436,8 @@ void stream_kernel(KArgs a, const float *Mr, const float *Mw, const bf16raw *Y, 
                 }
             }
         }
-        // the next tile's loads fly during the reduction and the epilogue (few registers are live there)
+        // the next tile's loads fly during the reduction and the output of this tile (few registers are live there)
         if (it + 1 < ntiles) fetch(it + 1);
-        RACE_PHASE(5)
-        if (!S::kOwnRed) __syncthreads();       // every wavefront is done with the tiles of this step (whose bytes the partials reuse)
-        RACE_PHASE(6)
 
         // ---- reduction over the bucket-row groups: partial read-outs through LDS, 16 bytes per store
         //      (a lane holds four consecutive columns of its token in registers 4k .. 4k+3)
@@ -518,19 +460,9 @@ void stream_kernel(KArgs a, const float *Mr, const float *Mw, const bf16raw *Y, 
                 if (h == 0) mass[r_own + 32 * mt + il(ln)] = tot;
             }
         }
-        RACE_PHASE(7)
         __syncthreads();
-        RACE_PHASE(8)
-        if (!S::kOwnRed) epilogue(t0, nvalid);
-        RACE_PHASE(9)
-        if (!S::kOwnRed) __syncthreads();
-        RACE_PHASE(10)
     }
-    if (S::kOwnRed && ntiles > 0) {
-        const int64_t tp = tile_t0(ntiles - 1);
-        epilogue(tp, tile_nv(tp));
-    }
-    RACE_PHASE_PRINT("stream")
+    if (ntiles > 0) epilogue(ntiles - 1);
 }
 
 // Totals over all segments of the problem's own buckets, written as A[row * a_stride] and
@@ -561,41 +493,44 @@ template <class C, bool UNIT>
 __global__ __launch_bounds__(kThreads) void hash_tap_kernel(KArgs a, const bf16raw *X, uint8_t *codes, float *phi)
 {
     extern __shared__ __attribute__((aligned(256))) unsigned char lds[];
-    bf16raw *wp = reinterpret_cast<bf16raw *>(lds);
-    bf16raw *x = wp + C::LPP * C::XS;
-    bf16raw *ph = x + kTile * C::XS;
-    float *nx = reinterpret_cast<float *>(ph + kTile * C::PS);      // [32] 1 / |x| (unit-norm option)
+    bf16raw *ph = reinterpret_cast<bf16raw *>(lds);                             // [32][PS]
+    float *zt = reinterpret_cast<float *>(lds + kTile * C::PS * 2);             // [LPP][32] projections
     const int bh = blockIdx.y, head = bh % a.H;
     const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, ln = lane & 31, h = lane >> 5;
     const int64_t t0 = static_cast<int64_t>(blockIdx.x) * kTile;
     const int nvalid = (a.N - t0 < kTile) ? static_cast<int>(a.N - t0) : kTile;
-    const bf16raw *src = a.Wp + static_cast<size_t>(head) * C::LPP * C::D;
-    for (int c = tid; c < C::LPP * C::CPR; c += kThreads) {
-        const int row = c / C::CPR, ch = c % C::CPR;
-        *reinterpret_cast<u32x4 *>(wp + row * C::XS + ch * 8) = *reinterpret_cast<const u32x4 *>(src + row * C::D + ch * 8);
-    }
-    {
-        RowChunks<C, kTile> rows;
-        fetch_rows<C, kTile>(X + static_cast<size_t>(bh) * a.N * C::D, t0, nvalid, rows);
-        store_rows<C, kTile>(rows, x, nvalid);
-        if (UNIT) store_row_scales<C, kTile>(rows, nx);
+    const Soft sf = a.soft();
+    if (w < C::NG) {
+        WRows<C> wr;
+        load_w_rows<C>(a.Wp + static_cast<size_t>(head) * C::LPP * C::D, w, ln, h, wr);
+        u32x4 x[C::D / 16];
+        const bf16raw *src = X + (static_cast<size_t>(bh) * a.N + t0 + (ln < nvalid ? ln : nvalid - 1)) * C::D + 8 * h;
+#pragma unroll
+        for (int s = 0; s < C::D / 16; ++s) x[s] = *reinterpret_cast<const u32x4 *>(src + 16 * s);
+        f32x16 z = project<C>(wr, x);
+        if (UNIT) z = z * row_scale<C>(x);
+#pragma unroll
+        for (int v = 0; v < 16; ++v) zt[(w * 32 + acc_row(v, h)) * kTile + ln] = z[v];
     }
     __syncthreads();
-    if (w < C::NG) {
-        const int g = w;
-        const f32x16 z = project<C>(wp, x, g, ln, h, UNIT ? nx : nullptr);
-        write_assignments<C>(z, g, ln, h, a.soft(), true, ph);
-        if (ln < nvalid) {
+    if (w < 4) {
+        const int slot = 2 * w + h;
+        typename Share<C, 8>::Regs r;
 #pragma unroll
-            for (int j = 0; j < C::TPL; ++j) {
-                const int table = g * C::TPG + h * C::TPL + j;
-                if (table >= C::L || table >= a.L_real) break;
-                unsigned code = 0;
+        for (int i = 0; i < Share<C, 8>::NTAB; ++i) {
+            const int table = Share<C, 8>::table(slot, i);
+            unsigned code = 0;
 #pragma unroll
-                for (int t = 0; t < C::P; ++t) code |= (t < a.P_real && z[zslot<C>(j, t)] >= 0.f ? 1u : 0u) << t;
-                codes[(static_cast<size_t>(bh) * a.N + t0 + ln) * a.L_real + table] = static_cast<uint8_t>(code);
+            for (int t = 0; t < C::P; ++t) {
+                const float z = zt[(table * C::PP + t) * kTile + ln];
+                const bool real = !C::PAD || (table < sf.L && t < sf.P);
+                r.c[i][t] = real ? bit_code(z, sf.beta) : 0.f;
+                code |= (t < a.P_real && z >= 0.f ? 1u : 0u) << t;
             }
+            if (Share<C, 8>::part(slot) == 0 && table < a.L_real && ln < nvalid)
+                codes[(static_cast<size_t>(bh) * a.N + t0 + ln) * a.L_real + table] = static_cast<uint8_t>(code);
         }
+        produce<C, 8, C::PS>(r, slot, ln, sf, true, ph);
     }
     __syncthreads();
     if (phi) {
@@ -664,6 +599,9 @@ KArgs make_kargs(const Plan &p, char *ws)
     a.Mq = reinterpret_cast<float *>(ws + p.off_massQ);
     a.Mk = reinterpret_cast<float *>(ws + p.off_massK);
     a.dbeta_part = reinterpret_cast<float *>(ws + p.off_dbeta);
+    a.ge = reinterpret_cast<float *>(ws + p.off_ge);
+    a.want_dbeta = 0;
+    a.hash_tokens = 0;
     return a;
 }
 
@@ -672,40 +610,38 @@ template <class C>
 hipError_t launch_hash(const Plan &p, KArgs a, const void *Q, const void *K, int first, int count, hipStream_t st)
 {
     auto kern = p.unit_qk ? hash_kernel<C, true> : hash_kernel<C, false>;
-    RACE_TRY(allow_lds(kern, HashLds<C>::total));
     // short sequences: fewer tokens per workgroup, down to one step, until there are four workgroups per CU
     a.hash_tokens = kHashTokens;
-    while (a.hash_tokens > HashLds<C>::TT && static_cast<int64_t>(p.BH) * count * ((p.N + a.hash_tokens - 1) / a.hash_tokens) < 1024)
+    while (a.hash_tokens > kTile * hash_tiles<C>() && static_cast<int64_t>(p.BH) * count * ((p.N + a.hash_tokens - 1) / a.hash_tokens) < 1024)
         a.hash_tokens /= 2;
     ProfileScope prof("hash_rows", st);
-    hipLaunchKernelGGL(kern, dim3(static_cast<unsigned>((p.N + a.hash_tokens - 1) / a.hash_tokens), p.BH, count), dim3(kHashThreads),
-                       HashLds<C>::total, st, a, static_cast<const bf16raw *>(Q), static_cast<const bf16raw *>(K), first);
+    hipLaunchKernelGGL(kern, dim3(static_cast<unsigned>((p.N + a.hash_tokens - 1) / a.hash_tokens), p.BH, count), dim3(kHashThreads), 0, st, a,
+                       static_cast<const bf16raw *>(Q), static_cast<const bf16raw *>(K), first);
     return hipGetLastError();
 }
 
 template <class C, int QG>
-hipError_t launch_totals(const Plan &p, KArgs a, const float *M, const void *Y, const void *O, const float *den_in,
+hipError_t launch_totals(const Plan &p, KArgs a, const float *M, const void *Y, const void *O, const float *den_in, void *Gout,
                          hipStream_t st)
 {
     auto kern = totals_kernel<C, QG>;
     RACE_TRY(allow_lds(kern, TotalsLds<C>::total));
     ProfileScope prof(QG ? "stream_totals_qg" : "stream_totals_kv", st);
     hipLaunchKernelGGL(kern, dim3(p.nseg, p.BH), dim3(kThreads), TotalsLds<C>::total, st, a, M,
-                       static_cast<const bf16raw *>(Y), static_cast<const bf16raw *>(O), den_in);
+                       static_cast<const bf16raw *>(Y), static_cast<const bf16raw *>(O), den_in, static_cast<bf16raw *>(Gout));
     return hipGetLastError();
 }
 
 template <class C, int MODE>
-hipError_t launch_stream(const Plan &p, KArgs a, const float *Mr, const float *Mw, const void *Y, const void *O,
-                         const float *den_in, void *Out, float *den_out, hipStream_t st)
+hipError_t launch_stream(const Plan &p, KArgs a, const float *Mr, const float *Mw, const void *Y, void *Out, float *den_out,
+                         hipStream_t st)
 {
     static const char *const names[] = {"stream_totals_kv", "stream_totals_qg", "stream_forward", "stream_grad_v"};
     auto kern = p.causal ? stream_kernel<C, MODE, false> : stream_kernel<C, MODE, true>;
     RACE_TRY(allow_lds(kern, StreamLds<C>::total));
     ProfileScope prof(names[MODE], st);
     hipLaunchKernelGGL(kern, dim3(p.nseg, p.BH), dim3(kThreads), StreamLds<C>::total, st, a, Mr, Mw,
-                       static_cast<const bf16raw *>(Y), static_cast<const bf16raw *>(O), den_in,
-                       static_cast<bf16raw *>(Out), den_out);
+                       static_cast<const bf16raw *>(Y), static_cast<bf16raw *>(Out), den_out);
     return hipGetLastError();
 }
 
@@ -714,27 +650,25 @@ hipError_t fwd_t(const Plan &p, const void *Q, const void *K, const void *V, voi
 {
     KArgs a = make_kargs<C>(p, ws);
     RACE_TRY((launch_hash<C>(p, a, Q, K, 0, 2, st)));
-    RACE_TRY((launch_totals<C, 0>(p, a, a.Mk, V, nullptr, nullptr, st)));
+    RACE_TRY((launch_totals<C, 0>(p, a, a.Mk, V, nullptr, nullptr, nullptr, st)));
     RACE_TRY(scan_states("segment_scan", a.state, p.nseg, p.BH, C::STATE, p.causal ? 0 : 2, st));
-    RACE_TRY((launch_stream<C, kForward>(p, a, a.Mq, a.Mk, V, nullptr, nullptr, O, den, st)));
+    RACE_TRY((launch_stream<C, kForward>(p, a, a.Mq, a.Mk, V, O, den, st)));
     return hipSuccess;
 }
 
 // dphi and the chain rule through the soft assignment and W (grad_kernel).
 template <class C, int SIDE>
-hipError_t launch_grad(const Plan &p, KArgs a, const void *Q, const void *K, const void *V, const void *O,
-                       const float *den, const void *dO, void *dX, hipStream_t st)
+hipError_t launch_grad(const Plan &p, KArgs a, const void *X, const void *V, const void *G, void *dX, hipStream_t st)
 {
     auto kern = p.causal ? (p.unit_qk ? grad_kernel<C, SIDE, true, true> : grad_kernel<C, SIDE, false, true>)
                          : (p.unit_qk ? grad_kernel<C, SIDE, true, false> : grad_kernel<C, SIDE, false, false>);
-    const int lds = p.causal ? (p.unit_qk ? GradLds<C, true, true>::total : GradLds<C, false, true>::total)
-                             : (p.unit_qk ? GradLds<C, true, false>::total : GradLds<C, false, false>::total);
+    int lds = p.causal ? (p.unit_qk ? GradLds<C, true, true>::total : GradLds<C, false, true>::total)
+                       : (p.unit_qk ? GradLds<C, true, false>::total : GradLds<C, false, false>::total);
+    if (a.want_dbeta) lds += GradLds<C, false, false>::th_bytes;
     RACE_TRY(allow_lds(kern, lds));
     ProfileScope prof(SIDE == 0 ? "grad_q" : "grad_k", st);
-    hipLaunchKernelGGL(kern, dim3(p.nseg, p.BH), dim3(kThreads), lds, st, a,
-                       static_cast<const bf16raw *>(Q), static_cast<const bf16raw *>(K),
-                       static_cast<const bf16raw *>(V), static_cast<const bf16raw *>(O), den,
-                       static_cast<const bf16raw *>(dO), static_cast<bf16raw *>(dX));
+    hipLaunchKernelGGL(kern, dim3(p.nseg, p.BH), dim3(kThreads), lds, st, a, static_cast<const bf16raw *>(X),
+                       static_cast<const bf16raw *>(V), static_cast<const bf16raw *>(G), static_cast<bf16raw *>(dX));
     return hipGetLastError();
 }
 
@@ -750,14 +684,16 @@ hipError_t bwd_t(const Plan &p, const void *Q, const void *K, const void *V, con
     // (phi_Q, read-out cotangents) at segment ends
     if (!p.fwd_state_kept) {
         RACE_TRY((launch_hash<C>(p, a, Q, K, 0, 2, st)));
-        RACE_TRY((launch_totals<C, 0>(p, a, a.Mk, V, nullptr, nullptr, st)));
+        RACE_TRY((launch_totals<C, 0>(p, a, a.Mk, V, nullptr, nullptr, nullptr, st)));
         RACE_TRY(scan_states("segment_scan", a.state, p.nseg, p.BH, C::STATE, p.causal ? 0 : 2, st));
     }
-    RACE_TRY((launch_totals<C, 1>(p, b, a.Mq, dO, O, den, st)));
+    a.want_dbeta = b.want_dbeta = dbeta != nullptr;
+    // dK's buffer holds the cotangent rows until dK itself is written
+    RACE_TRY((launch_totals<C, 1>(p, b, a.Mq, dO, O, den, dK, st)));
     RACE_TRY(scan_states("segment_scan", b.state, p.nseg, p.BH, C::STATE, p.causal ? 1 : 2, st));
-    RACE_TRY((launch_stream<C, kGradV>(p, b, a.Mk, a.Mq, dO, O, den, dV, nullptr, st)));
-    RACE_TRY((launch_grad<C, 0>(p, a, Q, K, V, O, den, dO, dQ, st)));
-    RACE_TRY((launch_grad<C, 1>(p, b, Q, K, V, O, den, dO, dK, st)));
+    RACE_TRY((launch_stream<C, kGradV>(p, b, a.Mk, a.Mq, dK, dV, nullptr, st)));
+    RACE_TRY((launch_grad<C, 0>(p, a, Q, V, dK, dQ, st)));
+    RACE_TRY((launch_grad<C, 1>(p, b, K, V, dK, dK, st)));
     if (dbeta) RACE_TRY(reduce_dbeta(p, a.dbeta_part, dbeta, st));
     return hipSuccess;
 }
@@ -768,7 +704,7 @@ hipError_t buckets_t(const Plan &p, const void *K, const void *V, float *A, floa
 {
     KArgs a = make_kargs<C>(p, ws);
     RACE_TRY((launch_hash<C>(p, a, nullptr, K, 1, 1, st)));
-    RACE_TRY((launch_totals<C, 0>(p, a, a.Mk, V, nullptr, nullptr, st)));
+    RACE_TRY((launch_totals<C, 0>(p, a, a.Mk, V, nullptr, nullptr, nullptr, st)));
     const size_t total = static_cast<size_t>(p.BH) * p.LR * (C::D + 1);
     hipLaunchKernelGGL(bucket_tap_kernel<C>, dim3(static_cast<unsigned>((total + 255) / 256)), dim3(256), 0, st, a.state,
                        p.nseg, p.BH, p.L, p.P, A, Bsum, a_stride, b_stride);
@@ -779,7 +715,7 @@ template <class C>
 hipError_t hash_t(const Plan &p, const void *X, uint8_t *codes, float *phi, char *ws, hipStream_t st)
 {
     KArgs a = make_kargs<C>(p, ws);
-    const size_t lds = (static_cast<size_t>(C::LPP) * C::XS + kTile * C::XS + kTile * C::PS) * 2 + kTile * 4;
+    const size_t lds = static_cast<size_t>(kTile) * C::PS * 2 + static_cast<size_t>(C::LPP) * kTile * 4;
     auto kern = p.unit_qk ? hash_tap_kernel<C, true> : hash_tap_kernel<C, false>;
     RACE_TRY(allow_lds(kern, lds));
     hipLaunchKernelGGL(kern, dim3(static_cast<unsigned>((p.N + kTile - 1) / kTile), p.BH), dim3(kThreads), lds, st, a,
@@ -795,26 +731,19 @@ uint16_t host_bf16(float x)
     return static_cast<uint16_t>(b >> 16);
 }
 
-// W (H, L*P, D) -> Wp (H, LPP, D) in projection-group order: row rho of group g
-// belongs to the lane half hh = (rho / 4) % 2; with a = rho / 8 and b = rho % 4 the half's slots (a, b)
-// hold, for 8-padded tables, the half's table a/2 and hyperplane 4*(a%2) + b; for 4-padded tables, the half's
-// table a and hyperplane b; the half's table j is table TPL*hh + j of the group.  Rows of padding (slots beyond
-// the half's TPL tables, tables and hyperplanes the problem does not have) are zero.
+// W (H, L*P, D) -> Wp (H, LPP, D): row l * PP + t is hyperplane t of table l; rows of padding (and of tables and hyperplanes
+// the problem does not have) are zero.
 template <class C>
 void pack_t(const Plan &p, const float *W, void *image)
 {
     uint16_t *wp = static_cast<uint16_t *>(image);
     for (int hd = 0; hd < p.H; ++hd) {
         for (int row = 0; row < C::LPP; ++row) {
-            const int g = row / 32, rho = row % 32, a = rho / 8, hh = (rho / 4) % 2, b = rho % 4;
-            const int j = (C::PP == 8) ? a / 2 : a;
-            const int t = (C::PP == 8) ? 4 * (a % 2) + b : b;
-            const int table = g * C::TPG + C::TPL * hh + j;
+            const int table = row / C::PP, t = row % C::PP;
             for (int c = 0; c < C::D; ++c) {
                 float v = 0.f;
-                if (j < C::TPL && table < p.L && t < p.P) v = W[(static_cast<size_t>(hd) * p.LP + table * p.P + t) * C::D + c];
-                const uint16_t bits = host_bf16(v);
-                wp[(static_cast<size_t>(hd) * C::LPP + row) * C::D + c] = bits;
+                if (table < p.L && t < p.P) v = W[(static_cast<size_t>(hd) * p.LP + table * p.P + t) * C::D + c];
+                wp[(static_cast<size_t>(hd) * C::LPP + row) * C::D + c] = host_bf16(v);
             }
         }
     }
@@ -860,7 +789,7 @@ bool mfma_pick(int d, int L, int P, int *Lc, int *Pc, int *pad)
 size_t mfma_hashed_bytes(const Plan &p)
 {
 #define X(DD, PP_, LL, PD) if (p.d == DD && p.Pc == PP_ && p.Lc == LL && p.pad == PD) \
-        return static_cast<size_t>(p.BH) * static_cast<size_t>(p.N) * Cfg<DD, PP_, LL, PD != 0>::LP * sizeof(float);
+        return static_cast<size_t>(p.BH) * static_cast<size_t>((p.N + kTile - 1) / kTile * kTile) * Cfg<DD, PP_, LL, PD != 0>::LP * sizeof(float);
     RACE_SHAPES(X)
 #undef X
     return 0;

@@ -282,11 +282,12 @@ race_status_t make_plan(const race_attn_desc_t *desc, Plan *pl)
         p.bytes_state = align256(static_cast<size_t>(p.BH) * p.nseg * p.LRc * (p.d + 1) * sizeof(float));
         p.bytes_part = 0;
         p.bytes_mass = align256(mfma_hashed_bytes(p));
+        p.bytes_ge = align256(static_cast<size_t>(p.BH) * n * sizeof(float));
         p.dbeta_parts = mfma_dbeta_parts(p);
     }
     p.bytes_dbeta = align256(static_cast<size_t>(2) * p.BH * p.dbeta_parts * sizeof(float));
     // [W | key/value statistics | hashed Q | hashed K | row norms | carry] is what the forward pass uses (and leaves
-    // behind); [cotangent statistics | parts of dbeta] follow
+    // behind); [cotangent statistics | extra column of the cotangents | parts of dbeta] follow
     p.off_W = 0;
     p.off_stateA = p.off_W + p.bytes_W;
     p.off_massQ = p.off_stateA + p.bytes_state;
@@ -294,7 +295,8 @@ race_status_t make_plan(const race_attn_desc_t *desc, Plan *pl)
     p.off_part = p.off_massK + p.bytes_mass;
     p.off_carry = p.off_part + p.bytes_part;
     p.off_stateB = p.off_carry + p.bytes_carry;
-    p.off_dbeta = p.off_stateB + p.bytes_state;
+    p.off_ge = p.off_stateB + p.bytes_state;
+    p.off_dbeta = p.off_ge + p.bytes_ge;
     p.total = p.off_dbeta + p.bytes_dbeta;
     p.fwd_bytes = p.off_stateB;
     *pl = p;
