@@ -101,13 +101,14 @@ race_status_t race_attn_fwd(const race_attn_desc_t *desc, const void *Q, const v
 
 /* For callers that cannot allocate (code under HIP graph capture, tight serving loops, harnesses that forbid
  * hipMalloc): race_attn_fwd without a workspace argument.  The kernels are race_attn_fwd's; their scratch (the
- * packed W and the per-segment bucket statistics) lives in an array of 32 MiB that is part of the library's code
+ * packed W, the per-segment bucket statistics, the hashed rows) lives in an array of 48 MiB that is part of the library's code
  * object, one copy per GPU, held until the process ends.  The call allocates nothing, on the host or on the device.
- *   - Size limit: if the workspace race_attn_fwd would use exceeds the array, the sequence is cut into fewer, longer
- *     scan segments (desc->chunk doubled as often as needed; O and den then differ from race_attn_fwd's by the
- *     rounding of a different summation order only); a problem that does not fit even as one segment per
- *     (batch, head) returns RACE_ERR_WORKSPACE.  At d = 128, L = 8, P = 6 (bf16) a segment's statistics take 258 KiB
- *     and the hashed rows of Q and K 384 bytes per token and head: B*H*(segments * 258 KiB + N * 384 B) < 32 MiB.
+ *   - Size limit: 32 MiB, counted as W, one segment's statistics per (batch, head) and per token and head the hashed rows of
+ *     Q and K; beyond it RACE_ERR_WORKSPACE.  At d = 128, L = 8, P = 6 (bf16) the statistics take 258 KiB and the hashed
+ *     rows 384 bytes: B*H*(258 KiB + N * 384 B) < 32 MiB.  The generic kernels are charged two sets of statistics and
+ *     12*L*d bytes per token and head.  Within the limit, the sequence is cut into fewer, longer scan segments
+ *     (desc->chunk doubled as often as needed) where race_attn_fwd's own would not fit the array; O and den then differ
+ *     from race_attn_fwd's by the rounding of a different summation order only.
  *   - The pinned host image of W for (proj_seeds, shape) must exist already, because making it allocates: any
  *     earlier call of another entry point with the same H, d, L, P, dtype and proj_seeds (race_attn_fwd,
  *     race_attn_debug_hash, ...) leaves it in the library's host cache for the life of the process.  Otherwise
@@ -205,7 +206,7 @@ size_t race_attn_step_workspace_bytes(const race_attn_desc_t *desc);
  * den (DEVICE float (B, H), with the 1/L of Algorithm 1 step 7).  desc->N, desc->causal and desc->chunk are
  * ignored.  Arithmetic is fp32 on the values as given.  Cost O(L R d) per token and head; one kernel launch.
  * The call expands proj_seeds into the workspace (a copy from pinned host memory) and leaves W there: a later step
- * with the same desc on a workspace nobody has written to since may pass proj_seeds = NULL and skips the copy. */
+ * with the same desc on a workspace nobody else has written to since may pass proj_seeds = NULL and skips the copy. */
 race_status_t race_attn_step(const race_attn_desc_t *desc, const void *q, const void *k, const void *v,
                              const uint64_t *proj_seeds, float *state, void *o, float *den,
                              void *workspace, size_t workspace_bytes, race_stream_t stream);

@@ -76,8 +76,10 @@ hipError_t allow_lds_bytes(const void *kernel, size_t bytes);
 template <class K>
 inline hipError_t allow_lds(K kernel, size_t bytes) { return allow_lds_bytes(reinterpret_cast<const void *>(kernel), bytes); }
 
-// The library's own device scratch for race_attn_fwd_static (static_scratch.hip): a fixed array in the code object.
-constexpr size_t kStaticScratchBytes = static_cast<size_t>(32) << 20;
+// The library's own device scratch for race_attn_fwd_static (static_scratch.hip): a fixed array in the code object, and the
+// limit on what its callers' problems are charged (race_api.cpp, static_limit_bytes).
+constexpr size_t kStaticScratchBytes = static_cast<size_t>(48) << 20;
+constexpr size_t kStaticLimitBytes = static_cast<size_t>(32) << 20;
 hipError_t static_scratch(void **ptr);     // device address of the current device's copy
 // Host: plain (H, L*P, d) expansion into caller memory.
 void expand_projection_host(int H, int L, int P, int d, int dtype, const uint64_t *seeds, float *out);

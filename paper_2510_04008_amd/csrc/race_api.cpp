@@ -391,6 +391,27 @@ race_status_t race_attn_fwd(const race_attn_desc_t *desc, const void *Q, const v
     return e == hipSuccess ? RACE_OK : hip_failed(e, "race_attn_fwd launch");
 }
 
+namespace {
+// What the size limit of race_attn_fwd_static counts, with the whole sequence as one segment per (batch, head): W, the
+// statistics, and per token and head the hashed rows of Q and K; the generic family is charged two sets of statistics and
+// three fp32 rows per token and table.  The limit is part of the interface and does not follow the layout of the workspace;
+// the array is half as large again, which covers what that layout adds (rows rounded up to tiles of 32 tokens; the generic
+// family's hashed rows and projections, 16 L P bytes against the 12 L d charged, at d = 8 and P > 5).
+size_t static_limit_bytes(const Plan &p)
+{
+    const size_t rows = static_cast<size_t>(p.BH) * p.N, heads = static_cast<size_t>(p.BH);
+    if (p.family == kFamilyMfma)
+        return p.bytes_W + align256(heads * p.LRc * (p.d + 1) * sizeof(float)) + 2 * align256(rows * p.Lc * p.Pc * sizeof(float));
+    return p.bytes_W + 2 * align256(heads * p.LR * (p.d + 1) * sizeof(float)) + align256(3 * rows * p.L * p.d * sizeof(float));
+}
+
+race_status_t static_too_large()
+{
+    g_last_error = "race_attn_fwd_static: the problem needs more than the 32 MiB of built-in scratch; use race_attn_fwd with a workspace";
+    return RACE_ERR_WORKSPACE;
+}
+}  // namespace
+
 // The forward pass on the library's own scratch array: same kernels, same arguments, no allocation of any kind.
 race_status_t race_attn_fwd_static(const race_attn_desc_t *desc, const void *Q, const void *K, const void *V,
                                    const uint64_t *proj_seeds, void *O, float *den, race_stream_t stream)
@@ -401,16 +422,12 @@ race_status_t race_attn_fwd_static(const race_attn_desc_t *desc, const void *Q, 
     if (p.N == 0) return RACE_OK;
     if (!Q || !K || !V || !proj_seeds || !O || !den) return RACE_ERR_INVALID_ARG;
     if (any_equal({O, den}, {Q, K, V, O, den})) return RACE_ERR_INVALID_ARG;
-    // Fewer, longer scan segments until the forward's share of the workspace (W, the segment statistics and, for the
-    // generic kernels, the per-table partial results) fits the array; a caller's own desc->chunk is kept as the
-    // smallest segment length tried.
+    if (static_limit_bytes(p) > kStaticLimitBytes) return static_too_large();
+    // Fewer, longer scan segments until the forward's share of the workspace (W, the segment statistics, the hashed rows)
+    // fits the array; a caller's own desc->chunk is kept as the smallest segment length tried.
     race_attn_desc_t fit = *desc;
-    for (;;) {
-        if (p.fwd_bytes <= kStaticScratchBytes) break;
-        if (p.nseg <= 1) {
-            g_last_error = "race_attn_fwd_static: the problem needs more than the 32 MiB of built-in scratch; use race_attn_fwd with a workspace";
-            return RACE_ERR_WORKSPACE;
-        }
+    while (p.fwd_bytes > kStaticScratchBytes) {
+        if (p.nseg <= 1) return static_too_large();
         fit.chunk = p.seg_len * 2;
         if ((s = make_plan(&fit, &p)) != RACE_OK) return s;
     }

@@ -201,7 +201,7 @@ def test_decode_entry_points_check_arguments_on_the_host():
 
 def test_forward_on_built_in_scratch_checks_everything_on_the_host():
     """race_attn_fwd_static (for callers that cannot allocate) validates like race_attn_fwd, refuses seeds whose pinned
-    image no earlier call has made (making it would allocate) and problems beyond its 32 MiB array: all before any
+    image no earlier call has made (making it would allocate) and problems beyond its 32 MiB limit: all before any
     device call, so this runs without a GPU."""
     lib = ra.lib()
     d = _desc()
@@ -221,6 +221,27 @@ def test_forward_on_built_in_scratch_checks_everything_on_the_host():
     many = (ctypes.c_uint64 * 200)(*range(200))
     assert lib.race_attn_fwd_static(ctypes.byref(big), p[0], p[1], p[2], many, p[3], p[4], None) == ra.RACE_ERR_WORKSPACE
     assert b"32 MiB" in lib.race_attn_last_error()
+
+
+@pytest.mark.parametrize("dtype, B, d, L, P, head_bytes, token_bytes", [
+    # matrix-core shapes: statistics of the compiled shape once, hashed rows of Q and K; many heads of few tokens too
+    (1, 1, 128, 8, 6, 512 * 129 * 4, 384), (1, 120, 128, 8, 6, 512 * 129 * 4, 384), (1, 900, 128, 4, 4, 64 * 129 * 4, 128),
+    (1, 400, 64, 16, 4, 256 * 65 * 4, 512),
+    # generic kernels: two sets of statistics, three fp32 rows per token and table; narrow rows with many hyperplanes
+    (0, 1, 8, 1, 8, 2 * 256 * 9 * 4, 96), (0, 3, 8, 5, 6, 2 * 320 * 9 * 4, 480), (1, 16, 8, 8, 8, 2 * 2048 * 9 * 4, 768),
+    (0, 20, 16, 3, 8, 2 * 768 * 17 * 4, 576), (0, 2, 64, 4, 4, 2 * 64 * 65 * 4, 3072)])
+@pytest.mark.parametrize("causal", [False, True])
+def test_built_in_scratch_takes_every_problem_within_its_documented_limit(dtype, B, d, L, P, head_bytes, token_bytes, causal):
+    """The limit is what the header states (plus W, a few KB here): two percent below it a problem gets as far as the
+    lookup of W, two percent above it is refused."""
+    lib = ra.lib()
+    p = [ctypes.c_void_p(256 * (i + 1)) for i in range(6)]
+    seeds = (ctypes.c_uint64 * 1)(0x5CA7C4)
+    room = (32 << 20) - (64 << 10) - B * head_bytes
+    for scale, want in ((0.98, ra.RACE_ERR_NOT_READY), (1.02, ra.RACE_ERR_WORKSPACE)):
+        n = max(1, int(room * scale / (B * token_bytes))) if scale < 1 else int(((32 << 20) * scale - B * head_bytes) / (B * token_bytes)) + 1
+        desc = ra.make_desc(B, 1, n, d, L, P, 8.0, causal, dtype)
+        assert lib.race_attn_fwd_static(ctypes.byref(desc), p[0], p[1], p[2], seeds, p[3], p[4], None) == want, n
 
 
 def test_generic_kernels_refuse_long_contexts():
