@@ -122,6 +122,12 @@ race_stream_t stream_of(PyObject *o)
     return reinterpret_cast<race_stream_t>(p);
 }
 
+// Other Python threads run while the library works (the first call with new seeds expands W; a full queue makes a launch wait).
+struct ReleaseGil {
+    PyThreadState *saved = PyEval_SaveThread();
+    ~ReleaseGil() { PyEval_RestoreThread(saved); }
+};
+
 template <int N, typename F>
 PyObject *call(PyObject *const *args, Py_ssize_t nargs, F f)
 {
@@ -151,8 +157,10 @@ PyObject *fwd(PyObject *, PyObject *const *args, Py_ssize_t n)
         void *O = tensor(a[5], "O", t, e);
         float *den = static_cast<float *>(tensor(a[6], "den", per_token(d), at::kFloat));
         const race_stream_t st = stream_of(a[8]);
-        if (a[7] == Py_None) return race_attn_fwd_static(&d.d, Q, K, V, s.ptr, O, den, st);
+        const bool built_in = a[7] == Py_None;
         const Workspace ws(a[7]);
+        const ReleaseGil released;
+        if (built_in) return race_attn_fwd_static(&d.d, Q, K, V, s.ptr, O, den, st);
         return race_attn_fwd(&d.d, Q, K, V, s.ptr, O, den, ws.ptr, ws.bytes, st);
     });
 }
@@ -171,8 +179,10 @@ PyObject *bwd(PyObject *, PyObject *const *args, Py_ssize_t n)
         void *dQ = tensor(a[8], "dQ", t, e), *dK = tensor(a[9], "dK", t, e), *dV = tensor(a[10], "dV", t, e);
         float *dbeta = a[11] == Py_None ? nullptr : static_cast<float *>(tensor(a[11], "dbeta", per_head(d), at::kFloat));
         const Workspace ws(a[12]);
-        return (a[14] == Py_True ? race_attn_bwd_saved : race_attn_bwd_beta)(&d.d, Q, K, V, O, den, dO, s.ptr, dQ, dK, dV, dbeta,
-                                                                            ws.ptr, ws.bytes, stream_of(a[13]));
+        const race_stream_t st = stream_of(a[13]);
+        const auto entry = a[14] == Py_True ? race_attn_bwd_saved : race_attn_bwd_beta;
+        const ReleaseGil released;
+        return entry(&d.d, Q, K, V, O, den, dO, s.ptr, dQ, dK, dV, dbeta, ws.ptr, ws.bytes, st);
     });
 }
 
@@ -189,7 +199,9 @@ PyObject *state_init(PyObject *, PyObject *const *args, Py_ssize_t n)
         }
         const Seeds s(a[3], d.d.H);
         const Workspace ws(a[5]);
-        return race_attn_state_init(&d.d, K, V, s.ptr, state, ws.ptr, ws.bytes, stream_of(a[6]));
+        const race_stream_t st = stream_of(a[6]);
+        const ReleaseGil released;
+        return race_attn_state_init(&d.d, K, V, s.ptr, state, ws.ptr, ws.bytes, st);
     });
 }
 
@@ -206,7 +218,9 @@ PyObject *step(PyObject *, PyObject *const *args, Py_ssize_t n)
         void *o = tensor(a[6], "o", r, e);
         float *den = static_cast<float *>(tensor(a[7], "den", per_head(d), at::kFloat));
         const Workspace ws(a[8]);
-        return race_attn_step(&d.d, q, k, v, s.ptr, state, o, den, ws.ptr, ws.bytes, stream_of(a[9]));
+        const race_stream_t st = stream_of(a[9]);
+        const ReleaseGil released;
+        return race_attn_step(&d.d, q, k, v, s.ptr, state, o, den, ws.ptr, ws.bytes, st);
     });
 }
 
