@@ -21,7 +21,7 @@
 // derivative of tanh, the in-tile term, and dX of the previous tile; second half: dphi, the corner softmax backwards, dz,
 // and the update of the statistics.  (With a third barrier between the staging of a tile's own rows and everything that reads
 // them, the projection on two wavefronts and its masses through LDS to the others: 10.4 ms for 16.8 million rows of
-// 128 columns at L = 8, P = 6.)
+// 128 columns at L = 8, P = 6; now 10.1.)
 #pragma once
 #include "mfma_common.h"
 

@@ -198,9 +198,12 @@ ProfileScope::~ProfileScope()
 
 // Segment length the MFMA family chooses, in its 32-token tiles: the k that makes
 //     rounds * k * (time of a tile in all passes) + (workgroups) * (time to move a state through passes and scans)
-// smallest.  A round is one workgroup per CU (256).  Long sequences come out at one round with as few, long segments as fill
-// the chip (two rounds with half the segment take as long and move twice the states; more rounds only where B H divides the
-// chip badly), short ones at the balance of the two terms.  The two times are fits to sweeps over segment lengths of training
+// smallest.  A round is one workgroup per CU (256).  Sequences of medium length come out at one round with as few, long
+// segments as fill the chip (two rounds with half the segment take as long and move twice the states; more rounds only
+// where B H divides the chip badly), short ones at the balance of the two terms.  Where the second round's states are
+// less than a hundredth of the whole (512 bucket rows: from 10^6 tokens at B H = 4), two rounds: segments half as long, so
+// that their boundaries stay where callers of race_attn_segment_tokens have had them and a late workgroup delays half as much.
+// The two times are fits to sweeps over segment lengths of training
 // steps, us: at 512 bucket rows of 128 columns 22 and 0.31 (B H = 16, N = 1000: 279, 197, 167, 170, 180 us at 11, 6, 4, 3, 2
 // tiles), at 64 bucket rows 11.5 and 0.04.  Shapes whose stream kernels fit a CU twice take two workgroups per CU once those
 // have a dozen tiles each (64 bucket rows, B H = 64, N = 16384: 1619 -> 1470 us); before that the gradient kernels, which fit
@@ -210,21 +213,26 @@ static int64_t mfma_segment_tokens(const Plan &p)
     const int64_t n = p.N > 0 ? p.N : 1, tiles = (n + 31) / 32;
     const double state_us = static_cast<double>(p.LRc) * (p.d + 1) * 1.2e-6 * 4, tile_us = 10.0 + 12.0 * p.LRc / 512.0;
     const int64_t slots = (mfma_workgroups_per_cu(p) == 2 && tiles * p.BH >= 512 * 12) ? 512 : 256;
-    int64_t best_k = tiles;
-    double best = 1e300;
-    auto consider = [&](int64_t k) {
-        if (k < 1 || k > tiles) return;
+    auto cost = [&](int64_t k) {
         const int64_t groups = p.BH * ((tiles + k - 1) / k);
-        const double t = static_cast<double>((groups + slots - 1) / slots * k) * tile_us + static_cast<double>(groups) * state_us;
-        if (t < best) { best = t; best_k = k; }
+        return static_cast<double>((groups + slots - 1) / slots * k) * tile_us + static_cast<double>(groups) * state_us;
     };
-    for (int64_t rounds = 1; rounds <= 4; ++rounds) {
+    int64_t best_k = tiles;
+    double best = cost(tiles);
+    auto consider = [&](int64_t k) {
+        if (k < 1 || k > tiles || cost(k) >= best) return;
+        best = cost(k);
+        best_k = k;
+    };
+    auto tiles_in_rounds = [&](int64_t rounds) {
         const int64_t nseg = slots * rounds / p.BH;
-        if (nseg > 0) consider((tiles + nseg - 1) / nseg);
-    }
+        return nseg > 0 ? (tiles + nseg - 1) / nseg : 0;
+    };
+    for (int64_t rounds = 1; rounds <= 4; ++rounds) consider(tiles_in_rounds(rounds));
     const int64_t balance = static_cast<int64_t>(std::sqrt(state_us * static_cast<double>(tiles) * p.BH / tile_us));
     for (int64_t k = balance; k <= balance + 2; ++k) consider(k);
-    consider(tiles);
+    const int64_t two = tiles_in_rounds(2);
+    if (slots == 256 && two >= 1 && two < best_k && cost(two) <= 1.01 * best) best_k = two;
     return best_k * 32;
 }
 

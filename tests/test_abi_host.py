@@ -269,3 +269,10 @@ def test_the_force_generic_switch_is_read_at_every_call():
     finally:
         del os.environ["RACE_ATTN_FORCE_GENERIC"]
     assert ra.race_attn_kernel_family(d) == 2
+
+
+def test_long_sequences_keep_two_rounds_of_segments():
+    """512 segments over the batch and heads, as long as the second round's states are a small part of the work."""
+    for n in (1 << 20, 1 << 22, 3 << 22):
+        seg = ra.race_attn_segment_tokens(ra.make_desc(1, 4, n, 128, 8, 6, 8.0, True, ra.RACE_BF16))
+        assert -(-n // seg) == 128
