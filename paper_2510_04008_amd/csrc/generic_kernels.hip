@@ -112,29 +112,39 @@ __device__ __forceinline__ float mass_of(float c, int bit)      // mass on the +
     return (minor1 == (bit != 0)) ? fabsf(c) : 1.0f - fabsf(c);
 }
 
-// C rows of X from token row0 on into xs [C][XS] as fp32; rows >= nv and columns >= d are zeros.
+__device__ __forceinline__ bool finite4(f32x4 v)
+{
+    constexpr float kMax = 3.402823466e38f;
+    return fabsf(v.x) <= kMax && fabsf(v.y) <= kMax && fabsf(v.z) <= kMax && fabsf(v.w) <= kMax;
+}
+// C rows of X from token row0 on into xs [C][XS] as fp32; rows >= nv and columns >= d are zeros.  Returns whether all that this
+// thread has loaded is finite.
 template <typename T, int RT>
-__device__ __forceinline__ void load_rows(const GArgs &a, const T *X, size_t row0, int nv, float *xs, int XS)
+__device__ __forceinline__ bool load_rows(const GArgs &a, const T *X, size_t row0, int nv, float *xs, int XS)
 {
     const int cpr = a.dp >> 2;
+    bool finite = true;
     for (int i = threadIdx.x; i < 16 * RT * cpr; i += kThreads) {
         const int row = i / cpr, c = (i - row * cpr) * 4;
         f32x4 v = {0.f, 0.f, 0.f, 0.f};
         if (row < nv && c < a.d) v = load4(X + (row0 + row) * a.d + c);
+        finite = finite && finite4(v);
         *reinterpret_cast<f32x4 *>(xs + row * XS + c) = v;
     }
+    return finite;
 }
 
 // Read-out cotangents g = dO / e (e = L Den) into gs and ge[row] = -(g . O): the cotangents of the un-averaged numerator
-// and normaliser of Algorithm 1, step 7.  16 / RT threads per row.
+// and normaliser of Algorithm 1, step 7.  16 / RT threads per row.  Returns whether this thread's share of g is finite.
 template <typename T, int RT>
-__device__ __forceinline__ void load_cotangents(const GArgs &a, const T *dO, const T *O, const float *den, size_t row0, int nv,
+__device__ __forceinline__ bool load_cotangents(const GArgs &a, const T *dO, const T *O, const float *den, size_t row0, int nv,
                                                 float *gs, int XS, float *ge)
 {
     constexpr int TPR = kThreads / (16 * RT);
     const int row = threadIdx.x / TPR, sub = threadIdx.x % TPR;
     const float inv = row < nv ? 1.0f / (den[row0 + row] * static_cast<float>(a.L)) : 0.f;
     float dot = 0.f;
+    bool finite = true;
     for (int c = 4 * sub; c < a.dp; c += 4 * TPR) {
         f32x4 g = {0.f, 0.f, 0.f, 0.f};
         if (row < nv && c < a.d) {
@@ -142,11 +152,13 @@ __device__ __forceinline__ void load_cotangents(const GArgs &a, const T *dO, con
             g = load4(dO + (row0 + row) * a.d + c) * inv;
             dot = fmaf(g.x, o.x, fmaf(g.y, o.y, fmaf(g.z, o.z, fmaf(g.w, o.w, dot))));
         }
+        finite = finite && finite4(g);
         *reinterpret_cast<f32x4 *>(gs + row * XS + c) = g;
     }
 #pragma unroll
     for (int m = 1; m < TPR; m <<= 1) dot += __shfl_xor(dot, m, 64);
     if (sub == 0) ge[row] = -dot;
+    return finite;
 }
 
 // Hashed rows of block b from the workspace into cs [C][CSS]
@@ -285,9 +297,12 @@ __device__ __forceinline__ void read_out(const float *ph, int nrt, const f32x4 (
         }
     }
 }
-// out[ti][ci] += M . ys (TR: M^T . ys) for an in-tile matrix M [C][MS]: tokens x tokens times tokens x columns
+// out[ti][ci] += M . ys (TR: M^T . ys) for an in-tile matrix M [C][MS]: tokens x tokens times tokens x columns.  M is zero above
+// its diagonal, and a row of ys must reach its own token and those behind it (TR: in front of it) only, also where it holds an
+// infinity or a NaN, which a zero does not silence: 16 x 16 tiles above the diagonal are left out, and where the rows are not
+// all finite the tiles on it are summed entry by entry instead of by a matrix product.
 template <int RT, int NCT, bool TR>
-__device__ __forceinline__ void apply_tile(const GArgs &a, const float *M, int MS, const float *ys, int XS, f32x4 (&out)[RT][NCT])
+__device__ __forceinline__ void apply_tile(const GArgs &a, const float *M, int MS, const float *ys, int XS, bool finite, f32x4 (&out)[RT][NCT])
 {
     const int lane = threadIdx.x & 63, n = lane & 15, q = lane >> 4, w = threadIdx.x >> 6;
 #pragma unroll
@@ -303,13 +318,39 @@ __device__ __forceinline__ void apply_tile(const GArgs &a, const float *M, int M
             }
 #pragma unroll
             for (int ti = 0; ti < RT; ++ti) {
+                if ((TR ? ti > jt : ti < jt) || (ti == jt && !finite)) continue;
                 const float m = TR ? M[j * MS + 16 * ti + n] : M[(16 * ti + n) * MS + j];
 #pragma unroll
                 for (int ci = 0; ci < NCT; ++ci) out[ti][ci] = mfma(m, y[ci], out[ti][ci]);
             }
         }
     }
+    if (finite) return;
+#pragma unroll 1
+    for (int j = 0; j < 16; ++j) {
+#pragma unroll
+        for (int ti = 0; ti < RT; ++ti) {
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int i = 4 * q + v;
+                if (TR ? j < i : j > i) continue;
+                const float m = TR ? M[(16 * ti + j) * MS + 16 * ti + i] : M[(16 * ti + i) * MS + 16 * ti + j];
+#pragma unroll
+                for (int ci = 0; ci < NCT; ++ci) {
+                    const int c = 16 * (w + 4 * ci);
+                    if (c < a.dp) out[ti][ci][v] = fmaf(m, ys[(16 * ti + j) * XS + c + n], out[ti][ci][v]);
+                }
+            }
+        }
+    }
 }
+// One flag of a workgroup from every thread's: posted behind one barrier, read after the next.
+__device__ __forceinline__ void post_flag(int *flags, bool mine)
+{
+    const bool all = __all(mine);
+    if ((threadIdx.x & 63) == 0) flags[threadIdx.x >> 6] = all;
+}
+__device__ __forceinline__ bool all_flags(const int *flags) { return (flags[0] & flags[1] & flags[2] & flags[3]) != 0; }
 
 // In-tile kernel values Phi_Q(i) . Phi_K(j), accumulated over the blocks: one 16 x 16 tile (i, j) per wavefront for
 // C = 32; for C = 16 every wavefront takes 16 of the block's bucket rows and the four partial tiles are added at the end.
@@ -479,6 +520,7 @@ __global__ __launch_bounds__(kThreads, 2) void generic_totals(GArgs a, const T *
 template <int RT>
 struct FwdLds {
     float *vs, *phq, *phk, *kk, *part, *csq, *csk, *am, *den;
+    int *flags;
     static size_t floats(int dp) { return static_cast<size_t>(16 * RT) * (dp + 4 + 2 * PHS + 16 * RT + 4 + 2 * CSS + 1) + KB + (RT == 1 ? 1024 : 0) + 16; }
     __device__ FwdLds(float *p, int dp)
     {
@@ -491,7 +533,8 @@ struct FwdLds {
         am = p; p += KB;
         den = p; p += C;
         csq = p; p += C * CSS;
-        csk = p;
+        csk = p; p += C * CSS;
+        flags = reinterpret_cast<int *>(p);
     }
 };
 
@@ -522,7 +565,7 @@ __global__ __launch_bounds__(kThreads, 2) void generic_forward(GArgs a, const T 
         }
         float dn = 0.f;
         __syncthreads();
-        if (a.causal) load_rows<T, RT>(a, V, row0, nv, s.vs, XS);
+        if (a.causal) post_flag(s.flags, load_rows<T, RT>(a, V, row0, nv, s.vs, XS));
         for (int b = 0; b < a.nblk; ++b) {
             const int nrt = block_rtiles(a, b);
             f32x4 sb[4][NCT];
@@ -554,7 +597,7 @@ __global__ __launch_bounds__(kThreads, 2) void generic_forward(GArgs a, const T 
             store_tile_kernel<RT>(kk, s.kk, s.part);
 #pragma unroll
             for (int k = 0; k < C / TPR; ++k) dn += s.kk[tok_r * MS + sub + k * TPR];
-            apply_tile<RT, NCT, false>(a, s.kk, MS, s.vs, XS, out);
+            apply_tile<RT, NCT, false>(a, s.kk, MS, s.vs, XS, all_flags(s.flags), out);
         }
 #pragma unroll
         for (int m = 1; m < TPR; m <<= 1) dn += __shfl_xor(dn, m, 64);
@@ -592,6 +635,7 @@ __global__ __launch_bounds__(kThreads, 2) void generic_forward(GArgs a, const T 
 template <int RT>
 struct GradLds {
     float *gs, *vs, *phq, *phk, *tt, *kk, *csq, *csk, *dz, *am, *dam, *ge, *rec, *rad, *part;
+    int *flags;
     static size_t floats(int dp)
     {
         return static_cast<size_t>(16 * RT) * (2 * (dp + 4) + 2 * PHS + 2 * (16 * RT + 4) + 2 * CSS + 2 * DZS + 1 + 18 + 2) + 2 * KB +
@@ -614,7 +658,8 @@ struct GradLds {
         rec = p; p += 2 * C * 9;        // (side, token): m and G_t of a table that spans several blocks
         rad = p; p += 2 * C;
         csq = p; p += C * CSS;
-        csk = p;
+        csk = p; p += C * CSS;
+        flags = reinterpret_cast<int *>(p);
     }
 };
 
@@ -657,7 +702,7 @@ __global__ __launch_bounds__(kThreads, RT * NCT > 2 ? 1 : 2) void generic_grads(
         }
         float radial = 0.f;                                     // threads (side, token) < 2 C: sum of z . dz (unit-norm option)
         __syncthreads();
-        load_cotangents<T, RT>(a, dO, O, den, row0, nv, s.gs, XS, s.ge);
+        post_flag(s.flags, load_cotangents<T, RT>(a, dO, O, den, row0, nv, s.gs, XS, s.ge));
         load_rows<T, RT>(a, V, row0, nv, s.vs, XS);
         __syncthreads();
         if (a.causal) {
@@ -883,7 +928,7 @@ __global__ __launch_bounds__(kThreads, RT * NCT > 2 ? 1 : 2) void generic_grads(
         }
         if (do_kv && a.causal) {
             store_tile_kernel<RT>(kk, s.kk, s.part);
-            apply_tile<RT, NCT, true>(a, s.kk, MS, s.gs, XS, av);
+            apply_tile<RT, NCT, true>(a, s.kk, MS, s.gs, XS, all_flags(s.flags), av);
         }
         if (a.unit) {
             if (tid < 2 * C) s.rad[tid] = radial;
