@@ -142,7 +142,8 @@ __device__ __forceinline__ bool load_cotangents(const GArgs &a, const T *dO, con
 {
     constexpr int TPR = kThreads / (16 * RT);
     const int row = threadIdx.x / TPR, sub = threadIdx.x % TPR;
-    const float inv = row < nv ? 1.0f / (den[row0 + row] * static_cast<float>(a.L)) : 0.f;
+    // (Den = 0: the forward pass leaves O = 0 there, a constant; so does an underflow of every bucket mass the query sees)
+    const float e = row < nv ? den[row0 + row] * static_cast<float>(a.L) : 0.f, inv = e != 0.f ? 1.0f / e : 0.f;
     float dot = 0.f;
     bool finite = true;
     for (int c = 4 * sub; c < a.dp; c += 4 * TPR) {

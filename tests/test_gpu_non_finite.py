@@ -1,6 +1,7 @@
 """GPU tests of infinities and NaNs in the generic kernels: in a causal sequence a token's value reaches itself and later
 tokens only, and a read-out cotangent itself and earlier tokens only, also where it is not finite (a caller's padding, an
-overflow elsewhere in a batch).  The reference is the same call on finite inputs."""
+overflow elsewhere in a batch), and a query whose Den has underflowed to zero costs nobody else's gradients.  The reference
+is the same call on finite inputs."""
 import pytest
 import torch
 
@@ -64,3 +65,19 @@ def test_a_non_finite_cotangent_reaches_earlier_tokens_only(w, value):
     assert not torch.isfinite(g["dV"][0, 0, :i + 1, c]).any()
     _same(g["dK"][0, 0, i + 1:], ref["dK"][0, 0, i + 1:], w)
     _same(torch.cat([g["dQ"][0, 0, :i], g["dQ"][0, 0, i + 1:]]), torch.cat([ref["dQ"][0, 0, :i], ref["dQ"][0, 0, i + 1:]]), w)
+
+
+@pytest.mark.parametrize("w", CASES + [Workload("nf-nc", 1, 2, 77, 64, 4, 4, 2.0, False, "f32", normalize_qk=True)], ids=lambda w: w.name)
+def test_a_query_with_den_zero_contributes_no_gradient(w):
+    # den = 0 comes with O = 0 (the buckets a query reads hold no mass that fp32 can express): a constant output
+    Q, K, V, dO = synth.make_inputs(w, "cuda")
+    i = 38
+    dO2 = dO.clone()
+    dO2[0, 0, i] = 0
+    ref = run_gpu(w, (Q, K, V, dO2))
+    O, den = ref["O"].clone(), ref["den"].clone()
+    O[0, 0, i] = 0
+    den[0, 0, i] = 0
+    g = run_gpu(w, (Q, K, V, dO), fwd_results=lambda O_, den_: (O, den))
+    for n in ("dQ", "dK", "dV"):
+        assert torch.isfinite(g[n]).all() and torch.equal(g[n], ref[n]), n
