@@ -22,6 +22,7 @@
 // touch every bank once.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <type_traits>
 
 #include "internal.h"
@@ -1200,18 +1201,16 @@ size_t generic_state_floats(const Plan &p) { return (static_cast<size_t>(p.LR) *
 
 // Tile and segment length.  Tiles of 16 tokens while they make less than four workgroups per CU, else 32 (half the reads
 // of the statistics per token).  Segments are single tiles unless that makes more than 2048 workgroups, where longer
-// segments save states (memory, the scan's traffic) and the chip stays full; a caller's chunk is rounded up to tiles.
+// segments save states (memory, the scan's traffic) and the chip stays full; a caller's chunk is rounded up to tiles, and no
+// segment is longer than the sequence (tiles per segment are an int in the kernels).
 void generic_geometry(int64_t chunk, Plan *p)
 {
     const int64_t n = p->N > 0 ? p->N : 1;
     p->rt = (static_cast<int64_t>(p->BH) * ((n + 15) / 16) <= 1024) ? 1 : 2;
-    const int64_t C = 16 * p->rt;
+    const int64_t C = 16 * p->rt, all = (n + C - 1) / C;
     int64_t tiles = 1;
-    if (chunk > 0) tiles = (chunk + C - 1) / C;
-    else {
-        const int64_t all = static_cast<int64_t>(p->BH) * ((n + C - 1) / C);
-        if (all > 2048) tiles = (all + 2047) / 2048;
-    }
+    if (chunk > 0) tiles = std::min((chunk - 1) / C + 1, all);
+    else if (p->BH * all > 2048) tiles = (p->BH * all + 2047) / 2048;
     p->seg_len = tiles * C;
 }
 

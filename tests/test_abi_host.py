@@ -276,3 +276,14 @@ def test_long_sequences_keep_two_rounds_of_segments():
     for n in (1 << 20, 1 << 22, 3 << 22):
         seg = ra.race_attn_segment_tokens(ra.make_desc(1, 4, n, 128, 8, 6, 8.0, True, ra.RACE_BF16))
         assert -(-n // seg) == 128
+
+
+@pytest.mark.parametrize("chunk", [301, 1 << 35, 1 << 36, 1 << 40, (1 << 63) - 1])
+@pytest.mark.parametrize("causal", [False, True])
+def test_a_chunk_beyond_the_sequence_is_one_segment_of_the_generic_family(chunk, causal):
+    """'The whole sequence as one segment' may be asked for with any chunk: same plan as with chunk = N."""
+    for n, covered in ((300, 304), (20000, 20000)):        # tiles of 16 and of 32 tokens
+        one, big = (ra.make_desc(1, 1, n, 64, 4, 4, 8.0, causal, ra.RACE_F32, c) for c in (n, max(chunk, n)))
+        assert ra.race_attn_kernel_family(big) == 1
+        assert ra.race_attn_segment_tokens(big) == ra.race_attn_segment_tokens(one) == covered
+        assert ra.race_attn_workspace_bytes(big) == ra.race_attn_workspace_bytes(one) > 0

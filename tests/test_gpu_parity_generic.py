@@ -173,3 +173,9 @@ def test_calibration_mfma_runs_and_fills_the_sink():
         ra.race_attn_calibration_mfma(16, 8, sink, vector_ops=nv)
         torch.cuda.synchronize()
         assert torch.isfinite(sink).all() and (sink > 0).all()
+
+
+@pytest.mark.parametrize("N,chunk", [(300, 1 << 36), (300, 1 << 35), (300, (1 << 63) - 1), (17000, 1 << 40)])
+@pytest.mark.parametrize("causal", [False, True])
+def test_a_chunk_beyond_the_sequence(N, chunk, causal):
+    check_case(Workload("one-segment", 1, 1, N, 32, 2, 3, 2.0, causal, "f32", normalize_qk=True, chunk=chunk), saved=True)
