@@ -23,6 +23,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cmath>
 #include <type_traits>
 
 #include "internal.h"
@@ -76,7 +77,8 @@ struct GArgs {
     const float *W;                     // (H, L P, d)
     float *Cq, *Ck, *Zq, *Zk;           // (BH, N, L P): hashed rows (see code()) and projections
     float *nrm;                         // (2, BH, N): 1 / max(|x|, floor) of the rows of Q and K (unit-norm option)
-    float *carry;                       // (BH, nseg, ST): running statistics inside a segment of several tiles
+    float *carry;                       // (BH, nseg, ST): running statistics inside a segment of several tiles (the second set of
+                                        // states: scratch of the forward pass and of dQ's; dK's and dV's carries its own on in place)
 };
 
 // first table and hyperplane of a block; tables of the block that exist
@@ -632,8 +634,8 @@ __global__ __launch_bounds__(kThreads, 2) void generic_forward(GArgs a, const T 
 // (not causal: only the first terms, with the totals), then the chain rule through the corner softmax, tanh and W.  With
 // w_r = phi_r dphi_r, m = sum_r w_r and G_t = sum of w_r over the corners on bit t's minor side, the cotangent of tanh z_t
 // is +-2 beta (small_t (m - G_t) - big_t G_t): no cancellation where a bit is saturated.
-// Segments of one tile take both sides in one launch; longer segments carry S left to right and dS right to left, one
-// launch each (sides: bit 0 = dQ, bit 1 = dK and dV).
+// Segments of one tile take both sides in one launch; longer causal segments carry dS right to left and S left to right, one
+// launch each, in this order (sides: bit 0 = dQ, bit 1 = dK and dV): dS is carried where it stands, and S where dS has been.
 template <int RT>
 struct GradLds {
     float *gs, *vs, *phq, *phk, *tt, *kk, *csq, *csk, *dz, *am, *dam, *ge, *rec, *rad, *part;
@@ -736,7 +738,7 @@ __global__ __launch_bounds__(kThreads, RT * NCT > 2 ? 1 : 2) void generic_grads(
             load_codes<RT>(a, a.Cq, row0, nv, b, s.csq);
             load_codes<RT>(a, a.Ck, row0, nv, b, s.csk);
             const bool mrow = tid < KB && b * KB + tid < a.LR;
-            const float am = mrow ? S[aoff + tid] : 0.f, dam = mrow ? D[aoff + tid] : 0.f;
+            const float am = mrow && do_q ? S[aoff + tid] : 0.f, dam = mrow && do_kv ? D[aoff + tid] : 0.f;
             // the statistics for dV (contraction over bucket rows) are on their way while the assignments are built
             f32x4 db[4][NCT];
             if (do_kv) load_state<NCT>(a, D, b, nrt, db);
@@ -1077,7 +1079,7 @@ GArgs make_args(const Plan &p, char *ws)
     a.Zq = a.Cq + rows * p.LP;
     a.Zk = a.Ck + rows * p.LP;
     a.nrm = reinterpret_cast<float *>(ws + p.off_part);
-    a.carry = reinterpret_cast<float *>(ws + p.off_carry);
+    a.carry = reinterpret_cast<float *>(ws + p.off_stateB);
     return a;
 }
 
@@ -1156,9 +1158,8 @@ hipError_t bwd_impl(const Plan &p, const T *Q, const T *K, const T *V, const T *
         }));
     }
     RACE_TRY(scan_states("simple_scan", stateD, p.nseg, p.BH, a.ST, p.causal ? 1 : 2, st));
-    // segments of one tile: both directions in one launch
-    const bool both = a.tps == 1 || !p.causal;
-    for (int sides = both ? 3 : 1; sides <= (both ? 3 : 2); ++sides) {
+    const bool both = !generic_carries(p);
+    for (int sides = both ? 3 : 2; sides >= (both ? 3 : 1); --sides) {
         ProfileScope prof("simple_grads", st);
         RACE_TRY(dispatch(p, a, [&](auto rt, auto nct) {
             constexpr int RT = decltype(rt)::value, NCT = decltype(nct)::value;
@@ -1199,18 +1200,46 @@ hipError_t scan_states(const char *name, float *state, int nseg, int BH, size_t 
 
 size_t generic_state_floats(const Plan &p) { return (static_cast<size_t>(p.LR) * (p.d + 1) + 63) & ~static_cast<size_t>(63); }
 
+bool generic_carries(const Plan &p) { return p.causal && p.seg_len > 16 * p.rt; }
+
 // Tile and segment length.  Tiles of 16 tokens while they make less than four workgroups per CU, else 32 (half the reads
 // of the statistics per token).  Segments are single tiles unless that makes more than 2048 workgroups, where longer
 // segments save states (memory, the scan's traffic) and the chip stays full; a caller's chunk is rounded up to tiles, and no
 // segment is longer than the sequence (tiles per segment are an int in the kernels).
+// A wide hash's state is large (d = 128, L = 32, P = 8: 4.2 MB per segment and head), so the two sets of states are bounded: by
+// kFreeStateBytes or, where that is more, by what keeps the workspace at the size of one fp32 row per token and table three times
+// (what the size limit counts) plus the states of 2048 tables twice.
+// Against a state per tile, fp32, d = 128, P = 8, forward + backward, causal (not causal): B H = 8, N = 8192, L = 32: workspace
+// 17.6 -> 2.4 GB, 43.2 -> 56.4 ms (33.6 -> 25.9); B H = 4, N = 4096, L = 8: 2.2 -> 1.1 GB, 3.8 -> 2.7 ms (2.6 -> 2.2); B H = 1,
+// N = 16384, L = 64: 17.5 -> 1.9 GB, 28 -> 64 ms (18 -> 28).  The shapes of up to 512 bucket rows of 128 columns stay below
+// the bound at every length (2048 states: 1.08 GB).
+constexpr double kFreeStateBytes = 1.25 * (1 << 30);
+static double most_state_bytes(const Plan &p)
+{
+    const double rows = static_cast<double>(p.BH) * static_cast<double>(p.N > 0 ? p.N : 1), column = sizeof(float) * (p.d + 1.0);
+    const double hashed = 4.0 * sizeof(float) * p.LP * rows;           // masses and projections of Q and K
+    return std::max(kFreeStateBytes, 3.0 * column * p.L * rows + 2.0 * 2048 * p.R * column - hashed);
+}
 void generic_geometry(int64_t chunk, Plan *p)
 {
     const int64_t n = p->N > 0 ? p->N : 1;
     p->rt = (static_cast<int64_t>(p->BH) * ((n + 15) / 16) <= 1024) ? 1 : 2;
-    const int64_t C = 16 * p->rt, all = (n + C - 1) / C;
+    int64_t C = 16 * p->rt, all = (n + C - 1) / C;
     int64_t tiles = 1;
     if (chunk > 0) tiles = std::min((chunk - 1) / C + 1, all);
-    else if (p->BH * all > 2048) tiles = (p->BH * all + 2047) / 2048;
+    else {
+        if (p->BH * all > 2048) tiles = (p->BH * all + 2047) / 2048;
+        const double per_segment = 2.0 * sizeof(float) * p->BH * generic_state_floats(*p);
+        const double most = std::floor(std::max(most_state_bytes(*p) / per_segment, 1.0));
+        if (static_cast<double>((all + tiles - 1) / tiles) > most) {
+            if (p->rt == 1) { p->rt = 2; C = 32; all = (n + 31) / 32; }       // first of all, larger tiles
+            const int64_t least = std::max<int64_t>(1, static_cast<int64_t>(std::ceil(static_cast<double>(all) / most)));
+            // of the lengths up to twice the least (64 more), the one whose workgroups make the fewest rounds of tiles over 256 CUs
+            const auto rounds = [&](int64_t t) { return (p->BH * ((all + t - 1) / t) + 255) / 256 * t; };
+            tiles = least;
+            for (int64_t t = least + 1; t <= std::min(least + std::min<int64_t>(least, 64), all); ++t) tiles = rounds(t) < rounds(tiles) ? t : tiles;
+        }
+    }
     p->seg_len = tiles * C;
 }
 

@@ -34,13 +34,14 @@ struct Plan {
     size_t off_W;       // projection matrix in the layout of the kernel family
     size_t bytes_W;
     size_t off_stateA;  // per-segment bucket statistics, (BH, nseg, ...) fp32
-    size_t off_stateB;  // second set (backward only: cotangent statistics)
+    size_t off_stateB;  // second set (backward: cotangent statistics; generic family: also the running statistics inside causal
+                        // segments of several tiles)
     size_t bytes_state;
     int rt;             // generic family: 16-token row tiles per tile (tiles of 16 rt tokens)
     size_t off_part;    // generic family: 1 / |x| of the rows of Q and K (unit-norm option)
     size_t bytes_part;
-    size_t off_carry;   // generic family: running statistics inside segments of several tiles
-    size_t bytes_carry;
+    size_t off_arrived; // decoding step: arrival counters
+    size_t bytes_arrived;
     size_t off_massQ;   // the hashed rows of Q and of K, (BH, N, Lc * Pc) fp32 each (one float per token, table and
     size_t off_massK;   // hyperplane: the per-bit soft-hash masses every pass rebuilds phi from); generic family: followed
                         // by the projections themselves, in the same layout
@@ -107,6 +108,7 @@ hipError_t calibration_mfma(int workgroups, int iters, int vector_ops, float *si
 // ---- generic family (generic_kernels.hip; taps and decoding in simple_kernels.hip)
 void generic_geometry(int64_t chunk, Plan *p);         // tile and segment length (rt, seg_len)
 size_t generic_state_floats(const Plan &p);            // floats per segment state
+bool generic_carries(const Plan &p);                   // the passes keep running statistics inside their segments (in the second set)
 hipError_t simple_fwd(const Plan &p, const void *Q, const void *K, const void *V, void *O, float *den,
                       char *ws, hipStream_t st);
 hipError_t simple_bwd(const Plan &p, const void *Q, const void *K, const void *V, const void *O,
@@ -118,7 +120,7 @@ hipError_t simple_hash(const Plan &p, const void *X, uint8_t *codes, float *phi,
 hipError_t simple_buckets(const Plan &p, const void *K, const void *V, float *A, float *Bsum, int a_stride,
                           int b_stride, char *ws, hipStream_t st);
 // One decoding step (simple_kernels.hip).  Workspace: W fp32 (H, L*P, d) | shares (BH, decode_shares, d+1) fp32 at off_part | arrival
-// counters (BH) at off_carry, zero between steps.
+// counters (BH) at off_arrived, zero between steps.
 int decode_shares(const Plan &p);              // workgroups per (batch, head)
 hipError_t decode_step(const Plan &p, const void *q, const void *k, const void *v, float *state, void *o, float *den, char *ws,
                        hipStream_t st);

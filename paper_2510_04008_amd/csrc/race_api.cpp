@@ -20,7 +20,8 @@ namespace {
 
 thread_local std::string g_last_error;
 
-// largest problem the generic kernels are offered, as the bytes of one fp32 gradient row per token and table, three times
+// largest problem the generic kernels are offered, as the bytes of one fp32 gradient row per token and table, three times (a
+// limit of the interface: no kernel keeps such rows)
 constexpr size_t kGenericPartialLimit = static_cast<size_t>(16) << 30;
 
 size_t align256(size_t x) { return (x + 255) & ~static_cast<size_t>(255); }
@@ -274,7 +275,6 @@ race_status_t make_plan(const race_attn_desc_t *desc, Plan *pl)
         p.bytes_state = align256(static_cast<size_t>(p.BH) * p.nseg * generic_state_floats(p) * sizeof(float));
         p.bytes_mass = align256(static_cast<size_t>(p.BH) * n * p.LP * 2 * sizeof(float));
         p.bytes_part = align256(static_cast<size_t>(p.BH) * n * 2 * sizeof(float));
-        p.bytes_carry = (p.causal && p.seg_len > 16 * p.rt) ? p.bytes_state : 0;
         // the fp32 path is not a long-context path: problems beyond this size are refused
         const size_t per_table = static_cast<size_t>(p.BH) * p.L * n * sizeof(float);
         const size_t fwd_part = per_table * (p.d + 1), bwd_part = per_table * p.d * 3;
@@ -294,19 +294,19 @@ race_status_t make_plan(const race_attn_desc_t *desc, Plan *pl)
         p.dbeta_parts = mfma_dbeta_parts(p);
     }
     p.bytes_dbeta = align256(static_cast<size_t>(2) * p.BH * p.dbeta_parts * sizeof(float));
-    // [W | key/value statistics | hashed Q | hashed K | row norms | carry] is what the forward pass uses (and leaves
-    // behind); [cotangent statistics | extra column of the cotangents | parts of dbeta] follow
+    // [W | key/value statistics | hashed Q | hashed K | row norms] is what the forward pass leaves behind; [cotangent statistics |
+    // extra column of the cotangents | parts of dbeta] follow (the generic family's forward pass may carry statistics in the first
+    // of these)
     p.off_W = 0;
     p.off_stateA = p.off_W + p.bytes_W;
     p.off_massQ = p.off_stateA + p.bytes_state;
     p.off_massK = p.off_massQ + p.bytes_mass;
     p.off_part = p.off_massK + p.bytes_mass;
-    p.off_carry = p.off_part + p.bytes_part;
-    p.off_stateB = p.off_carry + p.bytes_carry;
+    p.off_stateB = p.off_part + p.bytes_part;
     p.off_ge = p.off_stateB + p.bytes_state;
     p.off_dbeta = p.off_ge + p.bytes_ge;
     p.total = p.off_dbeta + p.bytes_dbeta;
-    p.fwd_bytes = p.off_stateB;
+    p.fwd_bytes = (p.family == kFamilySimple && generic_carries(p)) ? p.off_stateB + p.bytes_state : p.off_stateB;
     *pl = p;
     return RACE_OK;
 }
@@ -610,9 +610,9 @@ race_status_t make_step_plan(const race_attn_desc_t *desc, Plan *pl)
     pl->bytes_W = align256(static_cast<size_t>(pl->H) * pl->LP * pl->d * sizeof(float));
     pl->off_part = pl->bytes_W;
     pl->bytes_part = align256(static_cast<size_t>(pl->BH) * decode_shares(*pl) * (pl->d + 1) * sizeof(float));
-    pl->off_carry = pl->off_part + pl->bytes_part;
-    pl->bytes_carry = align256(static_cast<size_t>(pl->BH) * sizeof(unsigned));
-    pl->total = pl->off_carry + pl->bytes_carry;
+    pl->off_arrived = pl->off_part + pl->bytes_part;
+    pl->bytes_arrived = align256(static_cast<size_t>(pl->BH) * sizeof(unsigned));
+    pl->total = pl->off_arrived + pl->bytes_arrived;
     return RACE_OK;
 }
 }  // namespace
@@ -636,7 +636,7 @@ race_status_t race_attn_step(const race_attn_desc_t *desc, const void *q, const 
     char *ws = static_cast<char *>(workspace);
     hipStream_t st = reinterpret_cast<hipStream_t>(stream);
     // no seeds: the workspace still holds the W and the cleared counters that an earlier step left there
-    if (proj_seeds && (s = upload_projection(p, proj_seeds, ws, st, true, ws + p.off_carry, p.bytes_carry)) != RACE_OK) return s;
+    if (proj_seeds && (s = upload_projection(p, proj_seeds, ws, st, true, ws + p.off_arrived, p.bytes_arrived)) != RACE_OK) return s;
     hipError_t e = decode_step(p, q, k, v, state, o, den, ws, st);
     return e == hipSuccess ? RACE_OK : hip_failed(e, "race_attn_step launch");
 }

@@ -326,7 +326,7 @@ void launch_decode(const Plan &p, const T *q, const T *k, const T *v, float *sta
 {
     hipLaunchKernelGGL((decode_step_kernel<T, ROWS, NC>), dim3(p.L, p.BH, decode_shares(p) / p.L), dim3(kDecodeThreads), 0, st, p.H, p.L,
                        p.P, p.d, p.beta, p.unit_qk, reinterpret_cast<const float *>(ws + p.off_W), q, k, v, state,
-                       reinterpret_cast<float *>(ws + p.off_part), reinterpret_cast<unsigned *>(ws + p.off_carry), o, den);
+                       reinterpret_cast<float *>(ws + p.off_part), reinterpret_cast<unsigned *>(ws + p.off_arrived), o, den);
 }
 template <typename T, int ROWS>
 void decode_columns(const Plan &p, const T *q, const T *k, const T *v, float *state, T *o, float *den, char *ws, hipStream_t st)

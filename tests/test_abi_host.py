@@ -287,3 +287,25 @@ def test_a_chunk_beyond_the_sequence_is_one_segment_of_the_generic_family(chunk,
         assert ra.race_attn_kernel_family(big) == 1
         assert ra.race_attn_segment_tokens(big) == ra.race_attn_segment_tokens(one) == covered
         assert ra.race_attn_workspace_bytes(big) == ra.race_attn_workspace_bytes(one) > 0
+
+
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("dtype, BH, N, d, L, P", [
+    (0, 8, 8192, 128, 32, 8), (0, 4, 4096, 128, 8, 8), (0, 1, 2000, 64, 1024, 8), (1, 1, 2600, 128, 4096, 8), (0, 1, 16384, 128, 64, 8),
+    (0, 32, 4096, 128, 8, 8), (0, 2, 1024, 64, 512, 6), (0, 1, 200000, 64, 16, 8), (0, 30, 300, 96, 200, 7), (1, 64, 64, 32, 64, 8)])
+def test_generic_workspace_of_wide_hashes_is_bounded(dtype, BH, N, d, L, P, causal):
+    """States are kept per segment, and a wide hash's state is megabytes: the two sets of them take 1.25 GiB, or what leaves the
+    workspace at three fp32 rows per token and table and the states of 2048 tables twice, or one segment's, whichever is most."""
+    desc = ra.make_desc(1, BH, N, d, L, P, 4.0, causal, dtype)
+    assert ra.race_attn_kernel_family(desc) == 1
+    R, rows, column = 1 << P, BH * N, 4 * (d + 1)
+    W, hashed, one = 4 * BH * L * P * d, 16 * L * P * rows + 8 * rows, 2 * BH * L * R * column
+    bound = W + max(hashed + max(1.25 * 2 ** 30, one), 3 * column * L * rows + 2 * 2048 * R * column + 8 * rows)
+    assert ra.race_attn_workspace_bytes(desc) <= 1.001 * bound + (1 << 20)
+
+
+def test_generic_workspace_of_long_segments_holds_two_sets_of_states():
+    """Running statistics inside a causal segment of several tiles take no memory of their own."""
+    for N, chunk in ((4096, 512), (300, 300)):
+        sizes = [ra.race_attn_workspace_bytes(ra.make_desc(1, 8, N, 64, 4, 6, 4.0, causal, ra.RACE_F32, chunk)) for causal in (False, True)]
+        assert sizes[0] == sizes[1]

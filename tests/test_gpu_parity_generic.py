@@ -179,3 +179,25 @@ def test_calibration_mfma_runs_and_fills_the_sink():
 @pytest.mark.parametrize("causal", [False, True])
 def test_a_chunk_beyond_the_sequence(N, chunk, causal):
     check_case(Workload("one-segment", 1, 1, N, 32, 2, 3, 2.0, causal, "f32", normalize_qk=True, chunk=chunk), saved=True)
+
+
+@pytest.mark.parametrize("N", [2900, 10001])       # 32-token tiles instead of 16; segments of several tiles
+@pytest.mark.parametrize("causal", [False, True])
+def test_wide_hash_on_segments_lengthened_for_their_states(N, causal):
+    w = Workload("wide", 1, 1, N, 64, 64, 8, 2.0, causal, "f32", normalize_qk=True)
+    assert ra.race_attn_segment_tokens(desc_of(w)) == (32 if N == 2900 else 64)
+    check_case(w, saved=True)
+
+
+def test_repeated_backward_passes_on_a_saved_workspace():
+    # segments of several tiles carry their statistics in the workspace: what the forward pass has left there stays
+    w = Workload("again", 1, 2, 500, 48, 2, 5, 2.0, True, "f32", normalize_qk=True, chunk=128)
+    Q, K, V, dO = synth.make_inputs(w, "cuda")
+    d, seeds = desc_of(w), synth.projection_seeds(w)
+    ws = torch.empty(ra.race_attn_workspace_bytes(d), dtype=torch.uint8, device="cuda")
+    O, den = ra.race_attn_fwd(d, Q, K, V, seeds, workspace=ws)
+    first = ra.race_attn_bwd_saved(d, Q, K, V, O, den, dO, seeds, ws)
+    again = ra.race_attn_bwd_saved(d, Q, K, V, O, den, dO, seeds, ws)
+    fresh = ra.race_attn_bwd(d, Q, K, V, O, den, dO, seeds)
+    for a, b, c in zip(first, again, fresh):
+        assert torch.equal(a, b) and torch.equal(a, c)
