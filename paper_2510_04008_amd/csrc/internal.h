@@ -119,8 +119,8 @@ hipError_t simple_hash(const Plan &p, const void *X, uint8_t *codes, float *phi,
 // interleaved (B, H, L, R, d+1) state (A = state + d, Bsum = state, both strides d+1)
 hipError_t simple_buckets(const Plan &p, const void *K, const void *V, float *A, float *Bsum, int a_stride,
                           int b_stride, char *ws, hipStream_t st);
-// One decoding step (simple_kernels.hip).  Workspace: W fp32 (H, L*P, d) | shares (BH, decode_shares, d+1) fp32 at off_part | arrival
-// counters (BH) at off_arrived, zero between steps.
+// One decoding step (simple_kernels.hip).  Workspace: W fp32 (H, L*P, d) | arrival counters (BH) at off_arrived, zero between
+// steps | shares (BH, decode_shares, d+1) fp32 at off_part.
 int decode_shares(const Plan &p);              // workgroups per (batch, head)
 hipError_t decode_step(const Plan &p, const void *q, const void *k, const void *v, float *state, void *o, float *den, char *ws,
                        hipStream_t st);

@@ -24,6 +24,8 @@ thread_local std::string g_last_error;
 // limit of the interface: no kernel keeps such rows)
 constexpr size_t kGenericPartialLimit = static_cast<size_t>(16) << 30;
 
+constexpr int kMaxHeadTables = 65535;       // B H L
+
 size_t align256(size_t x) { return (x + 255) & ~static_cast<size_t>(255); }
 
 // ---------------------------------------------------------------- Philox-4x32-10 + Box-Muller
@@ -249,7 +251,7 @@ race_status_t make_plan(const race_attn_desc_t *desc, Plan *pl)
     if (desc->unit_qk != 0 && desc->unit_qk != 1) return RACE_ERR_INVALID_ARG;
     if (desc->P > 8 || desc->d > 256 || desc->d % 8 != 0) return RACE_ERR_UNSUPPORTED;
     if (desc->L > 4096 || static_cast<int64_t>(desc->B) * desc->H > 65535) return RACE_ERR_UNSUPPORTED;
-    if (static_cast<int64_t>(desc->B) * desc->H * desc->L > 65535) return RACE_ERR_UNSUPPORTED;
+    if (static_cast<int64_t>(desc->B) * desc->H * desc->L > kMaxHeadTables) return RACE_ERR_UNSUPPORTED;
     if (desc->N > (static_cast<int64_t>(1) << 40)) return RACE_ERR_UNSUPPORTED;
 
     Plan p{};
@@ -608,11 +610,13 @@ race_status_t make_step_plan(const race_attn_desc_t *desc, Plan *pl)
     pl->family = kFamilySimple;
     pl->off_W = 0;
     pl->bytes_W = align256(static_cast<size_t>(pl->H) * pl->LP * pl->d * sizeof(float));
-    pl->off_part = pl->bytes_W;
+    // [W | arrival counters | shares]: what an earlier step leaves for one without seeds, W and cleared counters, does not depend
+    // on B (the counters are those of the largest B H there is)
+    pl->off_arrived = pl->bytes_W;
+    pl->bytes_arrived = align256(static_cast<size_t>(kMaxHeadTables / pl->L) * sizeof(unsigned));
+    pl->off_part = pl->off_arrived + pl->bytes_arrived;
     pl->bytes_part = align256(static_cast<size_t>(pl->BH) * decode_shares(*pl) * (pl->d + 1) * sizeof(float));
-    pl->off_arrived = pl->off_part + pl->bytes_part;
-    pl->bytes_arrived = align256(static_cast<size_t>(pl->BH) * sizeof(unsigned));
-    pl->total = pl->off_arrived + pl->bytes_arrived;
+    pl->total = pl->off_part + pl->bytes_part;
     return RACE_OK;
 }
 }  // namespace

@@ -100,3 +100,20 @@ def test_later_steps_may_reuse_the_projection_in_the_workspace():
         runs.append(outs + [state])
     for a, b in zip(*runs):
         assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("d,L,P", [(128, 8, 6), (64, 4, 4), (256, 1, 7)])
+def test_the_projection_may_be_reused_with_another_batch(d, L, P):
+    # a serving loop whose batch shrinks and grows goes on without seeds: W's place does not depend on B
+    H, seeds = 2, [5, 6]
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    desc = {B: ra.make_desc(B, H, 0, d, L, P, 4.0, True, ra.RACE_F32) for B in (1, 3, 5)}
+    ws = torch.empty(ra.race_attn_step_workspace_bytes(desc[5]), dtype=torch.uint8, device="cuda")
+    for n, B in enumerate((3, 1, 5, 3, 1, 1, 5)):
+        q, k, v = (torch.randn((B, H, d), generator=gen, device="cuda") for _ in range(3))
+        ref_state, state = (ra.race_attn_state_init(desc[B], None, None, seeds) for _ in range(2))
+        ref_o, ref_den = ra.race_attn_step(desc[B], q, k, v, seeds, ref_state)
+        o, den = torch.full_like(q, float("nan")), torch.full((B, H), float("nan"), device="cuda")
+        ra.race_attn_step(desc[B], q, k, v, seeds if n == 0 else None, state, o, den, ws)
+        torch.cuda.synchronize()
+        assert torch.equal(o, ref_o) and torch.equal(den, ref_den) and torch.equal(state, ref_state), (n, B)
