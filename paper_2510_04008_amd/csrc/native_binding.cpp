@@ -35,6 +35,7 @@ struct Desc {
         }
     }
     at::ScalarType elem() const { return d.dtype == RACE_F32 ? at::kFloat : at::kBFloat16; }
+    int32_t heads() const { return d.N == 0 ? 0 : d.H; }       // seeds that a pass over the sequence reads
 };
 
 struct Shape { int n; int64_t s[5]; };
@@ -78,18 +79,20 @@ struct Workspace {
     }
 };
 
+// int(s) modulo 2^64 of every element (any number, not integers only).  needed: how many the call reads (an empty sequence
+// needs none); None is for the decoding step alone.
 struct Seeds {
     std::vector<uint64_t> v;
     const uint64_t *ptr = nullptr;
-    Seeds(PyObject *o, int32_t heads)
+    Seeds(PyObject *o, int32_t needed, bool optional = false)
     {
-        if (o == Py_None) return;
+        if (optional && o == Py_None) return;
         PyObject *fast = PySequence_Fast(o, "proj_seeds must be a sequence of integers");
         if (!fast) throw BadArgument{};
         const Py_ssize_t n = PySequence_Fast_GET_SIZE(fast);
         v.resize(n);
         for (Py_ssize_t i = 0; i < n; ++i) {
-            PyObject *num = PyNumber_Index(PySequence_Fast_GET_ITEM(fast, i));
+            PyObject *num = PyNumber_Long(PySequence_Fast_GET_ITEM(fast, i));
             if (num) {
                 v[i] = PyLong_AsUnsignedLongLongMask(num);
                 Py_DECREF(num);
@@ -100,8 +103,8 @@ struct Seeds {
             }
         }
         Py_DECREF(fast);
-        if (n < heads) {
-            PyErr_Format(PyExc_ValueError, "proj_seeds must have one seed per head (%d)", static_cast<int>(heads));
+        if (n < needed) {
+            PyErr_Format(PyExc_ValueError, "proj_seeds must have one seed per head (%d)", static_cast<int>(needed));
             throw BadArgument{};
         }
         ptr = v.data();
@@ -113,7 +116,7 @@ race_stream_t stream_of(PyObject *o)
     if (o == Py_None) return reinterpret_cast<race_stream_t>(c10::hip::getCurrentHIPStream().stream());
     PyObject *raw = PyObject_HasAttrString(o, "cuda_stream") ? PyObject_GetAttrString(o, "cuda_stream") : (Py_INCREF(o), o);
     if (!raw) throw BadArgument{};
-    PyObject *num = PyNumber_Index(raw);
+    PyObject *num = PyNumber_Long(raw);
     Py_DECREF(raw);
     if (!num) throw BadArgument{};
     void *p = PyLong_AsVoidPtr(num);
@@ -153,7 +156,7 @@ PyObject *fwd(PyObject *, PyObject *const *args, Py_ssize_t n)
         const Shape t = full(d);
         const at::ScalarType e = d.elem();
         void *Q = tensor(a[1], "Q", t, e), *K = tensor(a[2], "K", t, e), *V = tensor(a[3], "V", t, e);
-        const Seeds s(a[4], d.d.H);
+        const Seeds s(a[4], d.heads());
         void *O = tensor(a[5], "O", t, e);
         float *den = static_cast<float *>(tensor(a[6], "den", per_token(d), at::kFloat));
         const race_stream_t st = stream_of(a[8]);
@@ -175,7 +178,7 @@ PyObject *bwd(PyObject *, PyObject *const *args, Py_ssize_t n)
         void *Q = tensor(a[1], "Q", t, e), *K = tensor(a[2], "K", t, e), *V = tensor(a[3], "V", t, e), *O = tensor(a[4], "O", t, e);
         const float *den = static_cast<float *>(tensor(a[5], "den", per_token(d), at::kFloat));
         void *dO = tensor(a[6], "dO", t, e);
-        const Seeds s(a[7], d.d.H);
+        const Seeds s(a[7], d.heads());
         void *dQ = tensor(a[8], "dQ", t, e), *dK = tensor(a[9], "dK", t, e), *dV = tensor(a[10], "dV", t, e);
         float *dbeta = a[11] == Py_None ? nullptr : static_cast<float *>(tensor(a[11], "dbeta", per_head(d), at::kFloat));
         const Workspace ws(a[12]);
@@ -197,7 +200,7 @@ PyObject *state_init(PyObject *, PyObject *const *args, Py_ssize_t n)
             K = tensor(a[1], "K", full(d), d.elem());
             V = tensor(a[2], "V", full(d), d.elem());
         }
-        const Seeds s(a[3], d.d.H);
+        const Seeds s(a[3], d.heads());
         const Workspace ws(a[5]);
         const race_stream_t st = stream_of(a[6]);
         const ReleaseGil released;
@@ -213,7 +216,7 @@ PyObject *step(PyObject *, PyObject *const *args, Py_ssize_t n)
         const Shape r = rows(d);
         const at::ScalarType e = d.elem();
         void *q = tensor(a[1], "q", r, e), *k = tensor(a[2], "k", r, e), *v = tensor(a[3], "v", r, e);
-        const Seeds s(a[4], d.d.H);
+        const Seeds s(a[4], d.d.H, true);
         float *state = static_cast<float *>(tensor(a[5], "state", state_shape(d), at::kFloat));
         void *o = tensor(a[6], "o", r, e);
         float *den = static_cast<float *>(tensor(a[7], "den", per_head(d), at::kFloat));
