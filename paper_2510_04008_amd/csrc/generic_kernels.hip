@@ -398,6 +398,56 @@ __device__ __forceinline__ void store_tile_kernel(const f32x4 &kk, float *KK, fl
     __syncthreads();
 }
 
+// inv[row] = 1 / max(|x_row|, floor) of the tile's rows in xs (unit-norm option).  16 / RT threads per row.
+template <int RT>
+__device__ __forceinline__ void row_scales(const GArgs &a, const float *xs, int XS, float *inv)
+{
+    constexpr int TPR = kThreads / (16 * RT);
+    const int row = threadIdx.x / TPR, sub = threadIdx.x % TPR;
+    float ss = 0.f;
+    for (int c = sub; c < a.d; c += TPR) { const float x = xs[row * XS + c]; ss = fmaf(x, x, ss); }
+#pragma unroll
+    for (int m = 1; m < TPR; m <<= 1) ss += __shfl_xor(ss, m, 64);
+    if (sub == 0) inv[row] = 1.0f / fmaxf(sqrtf(ss), kUnitFloor);
+}
+// Hashed rows of a tile on np <= 32 hyperplanes (W: the first one's row) into cs [C][CSS]; put(token, hyperplane, hashed form,
+// projection) sees each of them.  z = X W^T: 16 tokens x 16 hyperplanes per wavefront and step, contraction over d, accumulated in
+// fp64 (products of fp32 are exact there): a bit's mass multiplies an error of z by 2 beta, and the projection is a small share
+// of the work.
+template <int RT, typename F>
+__device__ __forceinline__ void hash_block(const GArgs &a, const float *W, int np, const float *xs, int XS, const float *inv, float *cs, F put)
+{
+    const int lane = threadIdx.x & 63, n = lane & 15, q = lane >> 4, w = threadIdx.x >> 6;
+    const int npj = (np + 15) >> 4;
+    for (int tl = w; tl < RT * npj; tl += kWaves) {
+        const int ti = tl % RT, pl = 16 * (tl / RT) + n;
+        const bool real = pl < np;
+        const float *wr = W + static_cast<size_t>(real ? pl : 0) * a.d;
+        f64x4 z0 = {0., 0., 0., 0.}, z1 = z0;
+        for (int c = 4 * q; c < a.dp; c += 16) {
+            const f32x4 x = lds4(xs + (16 * ti + n) * XS + c);
+            f32x4 y = {0.f, 0.f, 0.f, 0.f};
+            if (c < a.d) y = *reinterpret_cast<const f32x4 *>(wr + c);
+            z0 = mfma64(x[0], y[0], z0);
+            z1 = mfma64(x[1], y[1], z1);
+            z0 = mfma64(x[2], y[2], z0);
+            z1 = mfma64(x[3], y[3], z1);
+        }
+        const f64x4 z = z0 + z1;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const int tok = 16 * ti + q + 4 * v;
+            float zz = static_cast<float>(z[v]);
+            if (a.unit) zz *= inv[tok];
+            const float c = code(zz, a.beta);
+            if (real) {
+                cs[tok * CSS + pl] = c;
+                put(tok, pl, c, zz);
+            }
+        }
+    }
+}
+
 // ================================================================ totals
 // blockIdx = (segment, block, batch*head).  SIDE 0: block < nblk: hashes the keys of the segment on the block's
 // hyperplanes (Algorithm 1, steps 2-4; hashed rows and projections go to the workspace) and accumulates the block's
@@ -427,7 +477,7 @@ __global__ __launch_bounds__(kThreads, 2) void generic_totals(GArgs a, const T *
     constexpr int C = 16 * RT;
     TotalsLds<RT> s(lds, a.dp, SIDE);
     const int XS = a.dp + 4;
-    const int seg = blockIdx.x, bh = blockIdx.z, tid = threadIdx.x, w = tid >> 6, lane = tid & 63, n = lane & 15, q = lane >> 4;
+    const int seg = blockIdx.x, bh = blockIdx.z, tid = threadIdx.x;
     const bool query = SIDE == 0 && static_cast<int>(blockIdx.y) >= a.nblk;
     const int b = query ? blockIdx.y - a.nblk : blockIdx.y;
     const bool writes = a.bpt == 1 || b % a.bpt == 0;       // hashed rows: the first block of a table
@@ -454,52 +504,17 @@ __global__ __launch_bounds__(kThreads, 2) void generic_totals(GArgs a, const T *
             if (!query) load_rows<T, RT>(a, Y, row0, nv, s.ys, XS);
             __syncthreads();
             if (a.unit) {
-                constexpr int TPR = kThreads / C;
-                const int row = tid / TPR, sub = tid % TPR;
-                float ss = 0.f;
-                for (int c = sub; c < a.d; c += TPR) { const float x = s.xs[row * XS + c]; ss = fmaf(x, x, ss); }
-#pragma unroll
-                for (int m = 1; m < TPR; m <<= 1) ss += __shfl_xor(ss, m, 64);
-                if (sub == 0) {
-                    const float inv = 1.0f / fmaxf(sqrtf(ss), kUnitFloor);
-                    s.inv[row] = inv;
-                    if (b == 0 && row < nv) a.nrm[(query ? 0 : static_cast<size_t>(a.BH) * a.N) + row0 + row] = inv;
-                }
+                row_scales<RT>(a, s.xs, XS, s.inv);
                 __syncthreads();
+                if (b == 0 && tid < nv) a.nrm[(query ? 0 : static_cast<size_t>(a.BH) * a.N) + row0 + tid] = s.inv[tid];
             }
-            // z = X W^T: 16 tokens x 16 hyperplanes per wavefront and step, contraction over d, accumulated in fp64 (products
-            // of fp32 are exact there): a bit's mass multiplies an error of z by 2 beta, and the projection is a small share
-            // of the work
-            const int npj = (np + 15) >> 4;
-            for (int tl = w; tl < RT * npj; tl += kWaves) {
-                const int ti = tl % RT, pl = 16 * (tl / RT) + n;
-                const bool real = pl < np;
-                const float *wr = W + static_cast<size_t>(real ? pl : 0) * a.d;
-                f64x4 z0 = {0., 0., 0., 0.}, z1 = z0;
-                for (int c = 4 * q; c < a.dp; c += 16) {
-                    const f32x4 x = lds4(s.xs + (16 * ti + n) * XS + c);
-                    f32x4 y = {0.f, 0.f, 0.f, 0.f};
-                    if (c < a.d) y = *reinterpret_cast<const f32x4 *>(wr + c);
-                    z0 = mfma64(x[0], y[0], z0);
-                    z1 = mfma64(x[1], y[1], z1);
-                    z0 = mfma64(x[2], y[2], z0);
-                    z1 = mfma64(x[3], y[3], z1);
+            hash_block<RT>(a, W, np, s.xs, XS, s.inv, s.cs, [&](int tok, int pl, float c, float z) __attribute__((always_inline)) {
+                if (writes && tok < nv) {
+                    const size_t at = (row0 + tok) * a.LP + pl0 + pl;
+                    (query ? a.Cq : a.Ck)[at] = c;
+                    (query ? a.Zq : a.Zk)[at] = z;
                 }
-                const f64x4 z = z0 + z1;
-                float *Cx = query ? a.Cq : a.Ck, *Zx = query ? a.Zq : a.Zk;
-#pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    const int tok = 16 * ti + q + 4 * v;
-                    float zz = static_cast<float>(z[v]);
-                    if (a.unit) zz *= s.inv[tok];
-                    const float c = code(zz, a.beta);
-                    if (real) s.cs[tok * CSS + pl] = c;
-                    if (real && writes && tok < nv) {
-                        Cx[(row0 + tok) * a.LP + pl0 + pl] = c;
-                        Zx[(row0 + tok) * a.LP + pl0 + pl] = zz;
-                    }
-                }
-            }
+            });
             if (query) continue;
         } else {
             load_codes<RT>(a, a.Cq, row0, nv, b, s.cs);
@@ -979,6 +994,44 @@ __global__ __launch_bounds__(kThreads, RT * NCT > 2 ? 1 : 2) void generic_grads(
     }
 }
 
+// Debug tap: hard codes and assignments of 16 rows of X on the hyperplanes of one block, as the passes form them.
+// blockIdx = (tile, block, batch*head); the first block of a table writes its codes.
+template <typename T>
+__global__ __launch_bounds__(kThreads) void generic_hash_tap(GArgs a, const T *X, uint8_t *codes, float *phi)
+{
+    extern __shared__ __attribute__((aligned(16))) float lds[];
+    TotalsLds<1> s(lds, a.dp, 1);           // (the rows of X take the place of the cotangents)
+    const int XS = a.dp + 4, bh = blockIdx.z, b = blockIdx.y, tid = threadIdx.x;
+    const int64_t t0 = static_cast<int64_t>(blockIdx.x) * 16;
+    const int nv = a.N - t0 < 16 ? static_cast<int>(a.N - t0) : 16;
+    const size_t row0 = static_cast<size_t>(bh) * a.N + t0;
+    const int tb0 = block_table(a, b), pl0 = tb0 * a.P, np = a.LP - pl0 < a.PB ? a.LP - pl0 : a.PB;
+    load_rows<T, 1>(a, X, row0, nv, s.ys, XS);
+    __syncthreads();
+    if (a.unit) {
+        row_scales<1>(a, s.ys, XS, s.inv);
+        __syncthreads();
+    }
+    hash_block<1>(a, a.W + (static_cast<size_t>(bh % a.H) * a.LP + pl0) * a.d, np, s.ys, XS, s.inv, s.cs, [](int, int, float, float) {});
+    __syncthreads();
+    if (a.bpt == 1 || b % a.bpt == 0) {
+        for (int i = tid; i < 16 * a.TB; i += kThreads) {
+            const int tok = i / a.TB, table = tb0 + i % a.TB;
+            if (tok >= nv || table >= a.L) continue;
+            unsigned c = 0;
+            for (int t = 0; t < a.P; ++t) c |= (1u - (__float_as_uint(s.cs[tok * CSS + (table - tb0) * a.P + t]) >> 31)) << t;
+            codes[(row0 + tok) * a.L + table] = static_cast<uint8_t>(c);
+        }
+    }
+    if (!phi) return;
+    build_phi<1>(a, b, s.cs, nv, s.ph);
+    __syncthreads();
+    for (int i = tid; i < 16 * KB; i += kThreads) {
+        const int tok = i / KB, r = b * KB + i % KB;
+        if (tok < nv && r < a.LR) phi[(row0 + tok) * a.LR + r] = s.ph[tok * PHS + i % KB];
+    }
+}
+
 // Sum of the per-segment totals, written as A[row * a_stride] and Bsum[row * b_stride + column], row = (bh, l, r).
 __global__ void generic_bucket_tap(GArgs a, const float *state, float *A, float *Bsum, int a_stride, int b_stride)
 {
@@ -1186,6 +1239,16 @@ hipError_t buckets_impl(const Plan &p, const T *K, const T *V, float *A, float *
     return hipGetLastError();
 }
 
+template <typename T>
+hipError_t hash_impl(const Plan &p, const T *X, uint8_t *codes, float *phi, char *ws, hipStream_t st)
+{
+    const GArgs a = make_args(p, ws);
+    const size_t lds = TotalsLds<1>::floats(a.dp, 1) * sizeof(float);
+    RACE_TRY(allow_lds(generic_hash_tap<T>, lds));
+    hipLaunchKernelGGL((generic_hash_tap<T>), dim3(static_cast<unsigned>((p.N + 15) / 16), a.nblk, p.BH), dim3(kThreads), lds, st, a, X, codes, phi);
+    return hipGetLastError();
+}
+
 }  // namespace
 
 hipError_t scan_states(const char *name, float *state, int nseg, int BH, size_t stride, int mode, hipStream_t st)
@@ -1258,6 +1321,12 @@ hipError_t simple_bwd(const Plan &p, const void *Q, const void *K, const void *V
                                (const float *)dO, (float *)dQ, (float *)dK, (float *)dV, dbeta, ws, st);
     return bwd_impl<bf16_t>(p, (const bf16_t *)Q, (const bf16_t *)K, (const bf16_t *)V, (const bf16_t *)O, den,
                             (const bf16_t *)dO, (bf16_t *)dQ, (bf16_t *)dK, (bf16_t *)dV, dbeta, ws, st);
+}
+
+hipError_t simple_hash(const Plan &p, const void *X, uint8_t *codes, float *phi, char *ws, hipStream_t st)
+{
+    if (p.dtype == RACE_F32) return hash_impl<float>(p, (const float *)X, codes, phi, ws, st);
+    return hash_impl<bf16_t>(p, (const bf16_t *)X, codes, phi, ws, st);
 }
 
 hipError_t simple_buckets(const Plan &p, const void *K, const void *V, float *A, float *Bsum, int a_stride, int b_stride,

@@ -105,7 +105,7 @@ hipError_t calibration_copy(void *dst, const void *src, size_t bytes, hipStream_
 // Dense bf16 MFMA loop on register operands (mfma_kernels.hip).
 hipError_t calibration_mfma(int workgroups, int iters, int vector_ops, float *sink, hipStream_t st);
 
-// ---- generic family (generic_kernels.hip; taps and decoding in simple_kernels.hip)
+// ---- generic family (generic_kernels.hip; decoding in simple_kernels.hip)
 void generic_geometry(int64_t chunk, Plan *p);         // tile and segment length (rt, seg_len)
 size_t generic_state_floats(const Plan &p);            // floats per segment state
 bool generic_carries(const Plan &p);                   // the passes keep running statistics inside their segments (in the second set)

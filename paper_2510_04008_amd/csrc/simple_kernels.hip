@@ -1,6 +1,6 @@
-// Small kernels outside the passes: the hash tap of the generic family, incremental decoding, the reduction of the
-// temperature's partial cotangents, zero fill and the plain copy benchmarks calibrate with.  All arithmetic in fp32 on the
-// vector ALUs, any (L, P <= 8, d <= 256), fp32 or bf16 tensors.
+// Small kernels outside the passes: incremental decoding, the reduction of the temperature's partial cotangents, zero fill and
+// the plain copy benchmarks calibrate with.  All arithmetic in fp32 on the vector ALUs, any (L, P <= 8, d <= 256), fp32 or bf16
+// tensors.
 #include <hip/hip_runtime.h>
 
 #include "internal.h"
@@ -25,14 +25,6 @@ __device__ __forceinline__ void store_elem(bf16_t *p, size_t i, float v)
     p[i].bits = static_cast<uint16_t>(b >> 16);
 }
 
-struct Args {
-    int H, L, P, R, d, LP;
-    int unit;            // 1: rows of Q and K are divided by their Euclidean norms before the projection
-    int64_t N;
-    float beta;
-    const float *W;      // (H, L*P, d)
-};
-
 // e = exp(-2 beta |u|), the ratio of the two masses of a bit.  beta = +infinity is the hard hash of Section 3.3:
 // e = 0 for u != 0, and for u = 0 (where -inf * 0 is NaN; fmaxf returns its other argument) the bit counts as set, like z >= 0.
 __device__ __forceinline__ float mass_ratio(float beta, float u)
@@ -44,46 +36,6 @@ __device__ __forceinline__ float mass_ratio(float beta, float u)
 // length ss into a unit vector; rows shorter than the floor are divided by the floor (a zero row stays zero).
 constexpr float kUnitFloor = 1e-12f;
 __device__ __forceinline__ float unit_scale(float ss) { return 1.0f / fmaxf(sqrtf(ss), kUnitFloor); }
-
-// Debug tap: hard codes and phi of every (row, table).
-template <typename T>
-__global__ void simple_hash_tap(Args a, int BH, const T *X, uint8_t *codes, float *phi)
-{
-    const size_t i = blockIdx.x * static_cast<size_t>(blockDim.x) + threadIdx.x;
-    const size_t total = static_cast<size_t>(BH) * a.N * a.L;
-    if (i >= total) return;
-    const size_t row = i / a.L;
-    const int l = static_cast<int>(i - row * a.L);
-    const int h = static_cast<int>((row / a.N) % a.H);
-    const float *Wl = a.W + (static_cast<size_t>(h) * a.LP + l * a.P) * a.d;
-    float p[8], q[8];
-    unsigned code = 0;
-    float inv = 1.f;
-    if (a.unit) {
-        float ss = 0.f;
-        for (int c = 0; c < a.d; ++c) { const float x = load_elem(X, row * a.d + c); ss = fmaf(x, x, ss); }
-        inv = unit_scale(ss);
-    }
-    for (int t = 0; t < a.P; ++t) {
-        float z = 0.f;
-        for (int c = 0; c < a.d; ++c) z = fmaf(Wl[t * a.d + c], load_elem(X, row * a.d + c), z);
-        z *= inv;
-        code |= (z >= 0.f ? 1u : 0u) << t;
-        const float u = tanhf(z);
-        const float e = mass_ratio(a.beta, u);
-        const float big = 1.0f / (1.0f + e), small = e / (1.0f + e);
-        p[t] = (u >= 0.f) ? big : small;
-        q[t] = (u >= 0.f) ? small : big;
-    }
-    codes[i] = static_cast<uint8_t>(code);
-    if (phi) {
-        for (int r = 0; r < a.R; ++r) {
-            float f = 1.f;
-            for (int t = 0; t < a.P; ++t) f *= ((r >> t) & 1) ? p[t] : q[t];
-            phi[i * a.R + r] = f;
-        }
-    }
-}
 
 // ------------------------------------------------------------------ incremental decoding
 // One decoding step.  A workgroup of 256 threads owns up to 32 G bucket rows of one table of one (batch*head): its threads
@@ -250,18 +202,6 @@ __global__ void zero_kernel(float *dst, size_t n)
     for (size_t i = static_cast<size_t>(blockIdx.x) * blockDim.x + threadIdx.x; i < n; i += stride) dst[i] = 0.f;
 }
 
-// ------------------------------------------------------------------ host side
-Args make_args(const Plan &p, const char *ws)
-{
-    Args a;
-    a.H = p.H; a.L = p.L; a.P = p.P; a.R = p.R; a.d = p.d; a.LP = p.LP;
-    a.N = p.N; a.beta = p.beta; a.unit = p.unit_qk;
-    a.W = reinterpret_cast<const float *>(ws + p.off_W);
-    return a;
-}
-
-unsigned blocks_for(size_t n, unsigned per) { return static_cast<unsigned>((n + per - 1) / per); }
-
 // One wavefront per (batch, head): every lane takes a fixed share of both sides' partial sums, the lanes are added by a
 // butterfly (the order of the sum does not depend on the run).
 __global__ __launch_bounds__(64) void dbeta_reduce_kernel(const float *part, int BH, int parts, float *dbeta)
@@ -290,19 +230,6 @@ bool simple_supported(int R, int d, int P)
 {
     const size_t floats = static_cast<size_t>(R) * (d + 1) + 2 * d + 2 * (d + 1) + 2 * (5 * P + R + 1) + R + P;
     return floats * sizeof(float) <= 160 * 1024;
-}
-
-hipError_t simple_hash(const Plan &p, const void *X, uint8_t *codes, float *phi, char *ws, hipStream_t st)
-{
-    const Args a = make_args(p, ws);
-    const size_t total = static_cast<size_t>(p.BH) * p.N * p.L;
-    if (p.dtype == RACE_F32)
-        hipLaunchKernelGGL((simple_hash_tap<float>), dim3(blocks_for(total, 128)), dim3(128), 0, st, a, p.BH,
-                           (const float *)X, codes, phi);
-    else
-        hipLaunchKernelGGL((simple_hash_tap<bf16_t>), dim3(blocks_for(total, 128)), dim3(128), 0, st, a, p.BH,
-                           (const bf16_t *)X, codes, phi);
-    return hipGetLastError();
 }
 
 hipError_t zero_floats(float *dst, size_t n, hipStream_t st)

@@ -201,3 +201,40 @@ def test_repeated_backward_passes_on_a_saved_workspace():
     fresh = ra.race_attn_bwd(d, Q, K, V, O, den, dO, seeds)
     for a, b, c in zip(first, again, fresh):
         assert torch.equal(a, b) and torch.equal(a, c)
+
+
+TAP_SHAPES = [(5, 1, 8, "f32"), (3, 2, 24, "f32"), (4, 4, 64, "f32"), (40, 3, 16, "bf16"), (2, 7, 40, "f32"), (1, 8, 136, "bf16")]
+
+
+@pytest.mark.parametrize("L,P,d,dtype", TAP_SHAPES)
+@pytest.mark.parametrize("unit", [False, True])
+def test_hash_tap_shows_the_assignments_the_passes_use(L, P, d, dtype, unit):
+    # sequences of one key: the bucket masses are that key's assignments, so the two must agree in every bit
+    w = Workload("tap", 40, 4, 1, d, L, P, 6.0, False, dtype, unit_qk=unit)
+    _, K, V, _ = synth.make_inputs(w, "cuda")
+    seeds = synth.projection_seeds(w)
+    assert ra.race_attn_kernel_family(desc_of(w)) == 1
+    codes, phi = ra.race_attn_debug_hash(desc_of(w), K, seeds, want_phi=True)
+    A, _ = ra.race_attn_debug_buckets(desc_of(w), K, V, seeds)
+    torch.cuda.synchronize()
+    assert torch.equal(phi[:, :, 0], A)
+    best = phi.gather(-1, codes.long().unsqueeze(-1)).squeeze(-1)
+    assert torch.equal(best, phi.amax(dim=-1))           # the code is the arg-max corner
+
+
+@pytest.mark.parametrize("L,P,d,dtype", TAP_SHAPES)
+def test_hash_tap_counts_what_the_hard_hash_accumulates(L, P, d, dtype):
+    # rows all but orthogonal to a hyperplane, where the sign hangs on the last place of the projection
+    w = Workload("tap-hard", 1, 2, 1000, d, L, P, float("inf"), False, dtype)
+    _, K, V, _ = synth.make_inputs(w, "cuda")
+    seeds = synth.projection_seeds(w)
+    W = torch.from_numpy(ra.race_attn_expand_projection(desc_of(w), seeds)).cuda()
+    wt = W[:, torch.arange(w.N, device="cuda") % (L * P)].unsqueeze(0).double()       # one hyperplane per token, in turn
+    x = K.double()
+    K = (x - (x * wt).sum(-1, keepdim=True) / (wt * wt).sum(-1, keepdim=True) * wt).to(K.dtype).contiguous()
+    codes, _ = ra.race_attn_debug_hash(desc_of(w), K, seeds)
+    A, _ = ra.race_attn_debug_buckets(desc_of(w), K, V, seeds)
+    torch.cuda.synchronize()
+    count = torch.zeros((1, 2, L, 1 << P), device="cuda")
+    count.scatter_add_(3, codes.long().transpose(2, 3), torch.ones((1, 2, L, w.N), device="cuda"))
+    assert torch.equal(count, A)
