@@ -2,6 +2,7 @@
 // seed -> W generator with its host cache, and dispatch to the kernel families.
 #include <hip/hip_runtime_api.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdlib>
 #include <cstring>
@@ -25,6 +26,7 @@ thread_local std::string g_last_error;
 constexpr size_t kGenericPartialLimit = static_cast<size_t>(16) << 30;
 
 constexpr int kMaxHeadTables = 65535;       // B H L
+constexpr int64_t kMaxSegments = 65535;     // per (batch, head)
 
 size_t align256(size_t x) { return (x + 255) & ~static_cast<size_t>(255); }
 
@@ -223,7 +225,7 @@ static int64_t mfma_segment_tokens(const Plan &p)
     int64_t best_k = tiles;
     double best = cost(tiles);
     auto consider = [&](int64_t k) {
-        if (k < 1 || k > tiles || cost(k) >= best) return;
+        if (k < 1 || k > tiles || (tiles + k - 1) / k > kMaxSegments || cost(k) >= best) return;
         best = cost(k);
         best_k = k;
     };
@@ -270,9 +272,10 @@ race_status_t make_plan(const race_attn_desc_t *desc, Plan *pl)
 
     const int64_t n = p.N > 0 ? p.N : 1;
     if (p.family == kFamilySimple) {
+        // (segments as the caller's chunk has them, in eights of tokens: the limit does not follow the kernels' tiles)
+        if (desc->chunk > 0 && (n - 1) / ((std::min(desc->chunk, n) + 7) / 8 * 8) + 1 > kMaxSegments) return RACE_ERR_UNSUPPORTED;
         generic_geometry(desc->chunk, &p);
         p.nseg = static_cast<int>((n + p.seg_len - 1) / p.seg_len);
-        if ((n + p.seg_len - 1) / p.seg_len > 65535) return RACE_ERR_UNSUPPORTED;
         p.bytes_W = align256(static_cast<size_t>(p.H) * p.LP * p.d * sizeof(float));
         p.bytes_state = align256(static_cast<size_t>(p.BH) * p.nseg * generic_state_floats(p) * sizeof(float));
         p.bytes_mass = align256(static_cast<size_t>(p.BH) * n * p.LP * 2 * sizeof(float));
@@ -286,7 +289,7 @@ race_status_t make_plan(const race_attn_desc_t *desc, Plan *pl)
         int64_t len = desc->chunk > 0 ? desc->chunk : mfma_segment_tokens(p);
         len = (len + 31) / 32 * 32;
         p.seg_len = len;
-        if ((n + len - 1) / len > 65535) return RACE_ERR_UNSUPPORTED;
+        if ((n + len - 1) / len > kMaxSegments) return RACE_ERR_UNSUPPORTED;
         p.nseg = static_cast<int>((n + len - 1) / len);
         p.bytes_W = align256(mfma_projection_bytes(p));
         p.bytes_state = align256(static_cast<size_t>(p.BH) * p.nseg * p.LRc * (p.d + 1) * sizeof(float));

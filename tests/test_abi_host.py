@@ -309,3 +309,16 @@ def test_generic_workspace_of_long_segments_holds_two_sets_of_states():
     for N, chunk in ((4096, 512), (300, 300)):
         sizes = [ra.race_attn_workspace_bytes(ra.make_desc(1, 8, N, 64, 4, 6, 4.0, causal, ra.RACE_F32, chunk)) for causal in (False, True)]
         assert sizes[0] == sizes[1]
+
+
+def test_the_library_never_cuts_a_sequence_into_more_segments_than_it_takes():
+    """65535 segments per (batch, head) is the limit; the library's own choice stays within it at any length."""
+    for BH, N, d, L, P in ((60, 48228835812, 64, 1, 1), (22, 108809068001, 64, 1, 1), (144, 773350119915, 128, 14, 2), (60, 1 << 40, 128, 8, 6), (1, 1 << 40, 64, 16, 4)):
+        desc = ra.make_desc(1, BH, N, d, L, P, 4.0, True, ra.RACE_BF16)
+        assert ra.race_attn_kernel_family(desc) == 2 and -(-N // ra.race_attn_segment_tokens(desc)) <= 65535
+
+
+@pytest.mark.parametrize("chunk, longest", [(1, 65535 * 8), (8, 65535 * 8), (9, 65535 * 16), (16, 65535 * 16), (100, 65535 * 104)])
+def test_segments_a_caller_may_ask_of_the_generic_family(chunk, longest):
+    for n, family in ((longest, 1), (longest + 1, 0)):
+        assert ra.race_attn_kernel_family(ra.make_desc(1, 1, n, 8, 2, 3, 4.0, True, ra.RACE_F32, chunk)) == family
