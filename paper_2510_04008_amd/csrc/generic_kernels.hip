@@ -44,11 +44,14 @@ struct bf16_t { uint16_t bits; };
 
 __device__ __forceinline__ float load1(const float *p) { return *p; }
 __device__ __forceinline__ float load1(const bf16_t *p) { return __uint_as_float(static_cast<uint32_t>(p->bits) << 16); }
-// four consecutive elements (16- or 8-byte aligned: d is a multiple of 8)
-__device__ __forceinline__ f32x4 load4(const float *p) { return *reinterpret_cast<const f32x4 *>(p); }
+// four consecutive elements of a caller's tensor, which need be aligned to its elements only (a view into a larger buffer);
+// the wide loads stay one instruction: global memory takes them at any address
+typedef f32x4 __attribute__((aligned(4))) f32x4_of_elements;
+typedef __attribute__((ext_vector_type(2), aligned(2))) uint32_t u32x2_of_elements;
+__device__ __forceinline__ f32x4 load4(const float *p) { return *reinterpret_cast<const f32x4_of_elements *>(p); }
 __device__ __forceinline__ f32x4 load4(const bf16_t *p)
 {
-    const uint2 w = *reinterpret_cast<const uint2 *>(p);
+    const u32x2_of_elements w = *reinterpret_cast<const u32x2_of_elements *>(p);
     return f32x4{__uint_as_float(w.x << 16), __uint_as_float(w.x & 0xffff0000u), __uint_as_float(w.y << 16),
                  __uint_as_float(w.y & 0xffff0000u)};
 }

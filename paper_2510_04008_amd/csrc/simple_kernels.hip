@@ -55,10 +55,17 @@ __device__ __forceinline__ float unit_scale(float ss) { return 1.0f / fmaxf(sqrt
 constexpr int kDecodeThreads = 256;
 constexpr int kDecodeMaxRows = 32;      // bucket rows of a thread
 
-__device__ __forceinline__ float4 load_quad(const float *p) { return *reinterpret_cast<const float4 *>(p); }
+// (a caller's rows need be aligned to their elements only; global memory takes wide loads at any address)
+typedef __attribute__((ext_vector_type(4), aligned(4))) float f32x4_of_elements;
+typedef __attribute__((ext_vector_type(2), aligned(2))) uint32_t u32x2_of_elements;
+__device__ __forceinline__ float4 load_quad(const float *p)
+{
+    const f32x4_of_elements w = *reinterpret_cast<const f32x4_of_elements *>(p);
+    return float4{w.x, w.y, w.z, w.w};
+}
 __device__ __forceinline__ float4 load_quad(const bf16_t *p)
 {
-    const uint2 w = *reinterpret_cast<const uint2 *>(p);
+    const u32x2_of_elements w = *reinterpret_cast<const u32x2_of_elements *>(p);
     return float4{__uint_as_float(w.x << 16), __uint_as_float(w.x & 0xffff0000u), __uint_as_float(w.y << 16),
                   __uint_as_float(w.y & 0xffff0000u)};
 }

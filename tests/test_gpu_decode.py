@@ -117,3 +117,19 @@ def test_the_projection_may_be_reused_with_another_batch(d, L, P):
         ra.race_attn_step(desc[B], q, k, v, seeds if n == 0 else None, state, o, den, ws)
         torch.cuda.synchronize()
         assert torch.equal(o, ref_o) and torch.equal(den, ref_den) and torch.equal(state, ref_state), (n, B)
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+def test_rows_need_be_aligned_to_their_elements_only(dtype):
+    B, H, d, L, P, seeds = 2, 2, 72, 3, 5, [3, 4]
+    desc = ra.make_desc(B, H, 0, d, L, P, 4.0, True, ra.RACE_F32 if dtype == torch.float32 else ra.RACE_BF16)
+    gen = torch.Generator(device="cuda").manual_seed(1)
+    buf = torch.randn((3, B * H * d + 1), generator=gen, device="cuda").to(dtype)
+    shifted = [torch.cat([b, b])[1:B * H * d + 1].view(B, H, d) for b in buf]
+    runs = []
+    for rows in (shifted, [r.clone() for r in shifted]):
+        state = ra.race_attn_state_init(desc, None, None, seeds)
+        o, den = ra.race_attn_step(desc, *rows, seeds, state)
+        torch.cuda.synchronize()
+        runs.append((o, den, state))
+    assert shifted[0].data_ptr() % 8 == dtype.itemsize and all(torch.equal(a, b) for a, b in zip(*runs))

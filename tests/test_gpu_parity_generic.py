@@ -238,3 +238,23 @@ def test_hash_tap_counts_what_the_hard_hash_accumulates(L, P, d, dtype):
     count = torch.zeros((1, 2, L, 1 << P), device="cuda")
     count.scatter_add_(3, codes.long().transpose(2, 3), torch.ones((1, 2, L, w.N), device="cuda"))
     assert torch.equal(count, A)
+
+
+def _shifted(t):
+    """The same values one element further on in a larger buffer: aligned to the element, not to a wide load."""
+    buf = torch.empty(t.numel() + 1, dtype=t.dtype, device=t.device)
+    out = buf[1:].view(t.shape)
+    out.copy_(t)
+    assert out.is_contiguous() and out.data_ptr() % 16 == t.element_size()
+    return out
+
+
+@pytest.mark.parametrize("N,d,dtype", [(77, 40, "f32"), (77, 40, "bf16"), (17000, 32, "f32")])
+def test_tensors_need_be_aligned_to_their_elements_only(N, d, dtype):
+    w = Workload("shifted", 1, 2, N, d, 3, 4, 2.0, True, dtype, normalize_qk=True)
+    assert ra.race_attn_kernel_family(desc_of(w)) == 1
+    T = synth.make_inputs(w, "cuda")
+    a = run_gpu(w, T)
+    b = run_gpu(w, tuple(_shifted(t) for t in T), fwd_results=lambda O, den: (_shifted(O), _shifted(den)))
+    for n in ("O", "den", "dQ", "dK", "dV"):
+        assert torch.equal(a[n], b[n]), n
