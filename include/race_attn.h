@@ -42,6 +42,11 @@
  *     than RACE_ERR_HIP the outputs are untouched.  N == 0 is a valid no-op.
  *   - Arithmetic: products of bf16 operands are accumulated in fp32; the fp32 element
  *     type computes in fp32 throughout.
+ *   - Infinities and NaNs: a non-finite element of V reaches the outputs of the tokens that read it, a non-finite element of dO
+ *     the gradients of the tokens its row depends on; in the causal case the generic kernels (race_attn_kernel_family() == 1)
+ *     keep it to those, the bf16 MFMA kernels may spread it over the other tokens of its tile (32 tokens from a multiple of 32
+ *     within a segment).  With a non-finite element in Q or K a token's assignments are arbitrary but finite; its own row's
+ *     gradient (and dbeta) is not.
  */
 #ifndef RACE_ATTN_H
 #define RACE_ATTN_H
@@ -221,7 +226,7 @@ const char *race_attn_last_error(void);
 
 /* Which kernel family a descriptor is served by: 0 = invalid/unsupported, 1 = generic fp32-math
  * kernels, 2 = bf16 MFMA kernels.  Informational (benchmarks and tests report it).
- * The generic kernels serve fp32 tensors and every bf16 shape without an MFMA instantiation; they are not a long-context
+ * The generic kernels serve fp32 tensors and every bf16 shape without an MFMA instantiation (P = 8: d <= 152); they are not a long-context
  * path, and a descriptor with 3 * B*H*L*N*d floats beyond 16 GiB is RACE_ERR_UNSUPPORTED (e.g. fp32, d = 64, L = 4: B*H*N
  * beyond 5.6 million).
  * Test switch: with RACE_ATTN_FORCE_GENERIC=1 in the environment every descriptor is planned on the generic kernels

@@ -9,7 +9,7 @@
 namespace race {
 
 constexpr int kFamilyNone = 0;
-constexpr int kFamilySimple = 1;   // generic kernels, fp32 arithmetic on the vector ALUs
+constexpr int kFamilySimple = 1;   // generic kernels, fp32 arithmetic (contractions on the fp32 matrix instructions)
 constexpr int kFamilyMfma = 2;     // bf16 MFMA kernels, register-resident bucket state
 
 // Everything the launchers need, derived once from a validated descriptor.

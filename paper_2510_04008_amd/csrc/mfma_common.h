@@ -70,8 +70,6 @@ struct Cfg {
     // on the CU, whose phases interleave with the first one's (measured: with two column tiles the kernels spill
     // at 128 registers and lose more than the second workgroup gains)
     static constexpr int STREAM_WAVES_PER_SIMD = (MT * NTW <= 2 && NTW == 1) ? 4 : 2;
-    static constexpr int LRG = LR / kWaves;             // bucket rows per wavefront (grad kernel)
-    static constexpr int MTG = LRG / 32;                // 32-row tiles per wavefront (grad kernel)
     static constexpr int PLO = P < 3 ? P : 3, PHI = P - PLO;
     static constexpr int CPR = D / 8;                   // 16-byte chunks per row
     // LDS row strides, in bf16 elements (rows stay 16-byte aligned; the pad staggers banks)
@@ -147,11 +145,6 @@ __device__ __forceinline__ f32x16 mma(u32x4 a, u32x4 b, f32x16 c)
                                                    0, 0, 0);
 }
 __device__ __forceinline__ u32x4 lds128(const bf16raw *p) { return *reinterpret_cast<const u32x4 *>(p); }
-__device__ __forceinline__ u32x4 lds64x2(const bf16raw *p0, const bf16raw *p1)
-{
-    const u32x2 a = *reinterpret_cast<const u32x2 *>(p0), b = *reinterpret_cast<const u32x2 *>(p1);
-    return u32x4{a.x, a.y, b.x, b.y};
-}
 // accumulator registers 8s..8s+7 as a bf16 B (or A) operand
 __device__ __forceinline__ u32x4 acc_operand(const f32x16 &t, int s)
 {

@@ -15,7 +15,7 @@
 
 namespace race {
 
-bool simple_supported(int R, int d, int P);
+bool simple_supported(int R, int d);
 
 namespace {
 
@@ -267,7 +267,7 @@ race_status_t make_plan(const race_attn_desc_t *desc, Plan *pl)
     if (p.dtype == RACE_BF16 && !forced && mfma_pick(p.d, p.L, p.P, &p.Lc, &p.Pc, &p.pad)) {
         p.family = kFamilyMfma;
         p.LRc = p.Lc * (1 << p.Pc);
-    } else if (simple_supported(p.R, p.d, p.P)) p.family = kFamilySimple;
+    } else if (simple_supported(p.R, p.d)) p.family = kFamilySimple;
     else return RACE_ERR_UNSUPPORTED;
 
     const int64_t n = p.N > 0 ? p.N : 1;

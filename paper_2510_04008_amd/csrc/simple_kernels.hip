@@ -1,6 +1,6 @@
 // Small kernels outside the passes: incremental decoding, the reduction of the temperature's partial cotangents, zero fill and
-// the plain copy benchmarks calibrate with.  All arithmetic in fp32 on the vector ALUs, any (L, P <= 8, d <= 256), fp32 or bf16
-// tensors.
+// the plain copy benchmarks calibrate with.  All arithmetic in fp32 on the vector ALUs, every shape the generic family takes,
+// fp32 or bf16 tensors.
 #include <hip/hip_runtime.h>
 
 #include "internal.h"
@@ -232,12 +232,9 @@ hipError_t reduce_dbeta(const Plan &p, const float *part, float *dbeta, hipStrea
     return hipGetLastError();
 }
 
-// The shapes the generic family takes: one table's statistics and one token's rows within 160 KB.
-bool simple_supported(int R, int d, int P)
-{
-    const size_t floats = static_cast<size_t>(R) * (d + 1) + 2 * d + 2 * (d + 1) + 2 * (5 * P + R + 1) + R + P;
-    return floats * sizeof(float) <= 160 * 1024;
-}
+// The shapes the generic family takes: all up to d = 256, tables of 256 bucket rows up to d = 152 (a limit of the interface, from
+// the time when a table's statistics had to fit the 160 KB of LDS; these kernels have no such bound).
+bool simple_supported(int R, int d) { return R < 256 || d <= 152; }
 
 hipError_t zero_floats(float *dst, size_t n, hipStream_t st)
 {

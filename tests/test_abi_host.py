@@ -245,9 +245,9 @@ def test_built_in_scratch_takes_every_problem_within_its_documented_limit(dtype,
 
 
 def test_generic_kernels_refuse_long_contexts():
-    """The generic kernels keep per-table partial results of every token (L * N * d floats per pass): beyond 16 GiB of
-    them the descriptor is unsupported instead of asking for a workspace the design was never meant for."""
-    ok = _desc(N=1 << 20)                                  # fp32, H = 2, d = 64, L = 4: 6 GiB of partial results
+    """The generic kernels are not a long-context path: a problem of more than 16 GiB, counted as three fp32 rows per token and
+    table, is unsupported (a limit of the interface, whatever the workspace holds)."""
+    ok = _desc(N=1 << 20)                                  # fp32, H = 2, d = 64, L = 4: 6 GiB
     assert ra.race_attn_kernel_family(ok) == 1 and ra.race_attn_workspace_bytes(ok) > 0
     big = _desc(N=1 << 22)                                 # 24 GiB
     assert ra.race_attn_kernel_family(big) == 0 and ra.race_attn_workspace_bytes(big) == 0
