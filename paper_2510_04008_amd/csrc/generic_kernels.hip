@@ -118,32 +118,23 @@ __device__ __forceinline__ float mass_of(float c, int bit)      // mass on the +
     return (minor1 == (bit != 0)) ? fabsf(c) : 1.0f - fabsf(c);
 }
 
-__device__ __forceinline__ bool finite4(f32x4 v)
-{
-    constexpr float kMax = 3.402823466e38f;
-    return fabsf(v.x) <= kMax && fabsf(v.y) <= kMax && fabsf(v.z) <= kMax && fabsf(v.w) <= kMax;
-}
-// C rows of X from token row0 on into xs [C][XS] as fp32; rows >= nv and columns >= d are zeros.  Returns whether all that this
-// thread has loaded is finite.
+// C rows of X from token row0 on into xs [C][XS] as fp32; rows >= nv and columns >= d are zeros.
 template <typename T, int RT>
-__device__ __forceinline__ bool load_rows(const GArgs &a, const T *X, size_t row0, int nv, float *xs, int XS)
+__device__ __forceinline__ void load_rows(const GArgs &a, const T *X, size_t row0, int nv, float *xs, int XS)
 {
     const int cpr = a.dp >> 2;
-    bool finite = true;
     for (int i = threadIdx.x; i < 16 * RT * cpr; i += kThreads) {
         const int row = i / cpr, c = (i - row * cpr) * 4;
         f32x4 v = {0.f, 0.f, 0.f, 0.f};
         if (row < nv && c < a.d) v = load4(X + (row0 + row) * a.d + c);
-        finite = finite && finite4(v);
         *reinterpret_cast<f32x4 *>(xs + row * XS + c) = v;
     }
-    return finite;
 }
 
 // Read-out cotangents g = dO / e (e = L Den) into gs and ge[row] = -(g . O): the cotangents of the un-averaged numerator
-// and normaliser of Algorithm 1, step 7.  16 / RT threads per row.  Returns whether this thread's share of g is finite.
+// and normaliser of Algorithm 1, step 7.  16 / RT threads per row.
 template <typename T, int RT>
-__device__ __forceinline__ bool load_cotangents(const GArgs &a, const T *dO, const T *O, const float *den, size_t row0, int nv,
+__device__ __forceinline__ void load_cotangents(const GArgs &a, const T *dO, const T *O, const float *den, size_t row0, int nv,
                                                 float *gs, int XS, float *ge)
 {
     constexpr int TPR = kThreads / (16 * RT);
@@ -151,7 +142,6 @@ __device__ __forceinline__ bool load_cotangents(const GArgs &a, const T *dO, con
     // (Den = 0: the forward pass leaves O = 0 there, a constant; so does an underflow of every bucket mass the query sees)
     const float e = row < nv ? den[row0 + row] * static_cast<float>(a.L) : 0.f, inv = e != 0.f ? 1.0f / e : 0.f;
     float dot = 0.f;
-    bool finite = true;
     for (int c = 4 * sub; c < a.dp; c += 4 * TPR) {
         f32x4 g = {0.f, 0.f, 0.f, 0.f};
         if (row < nv && c < a.d) {
@@ -159,13 +149,11 @@ __device__ __forceinline__ bool load_cotangents(const GArgs &a, const T *dO, con
             g = load4(dO + (row0 + row) * a.d + c) * inv;
             dot = fmaf(g.x, o.x, fmaf(g.y, o.y, fmaf(g.z, o.z, fmaf(g.w, o.w, dot))));
         }
-        finite = finite && finite4(g);
         *reinterpret_cast<f32x4 *>(gs + row * XS + c) = g;
     }
 #pragma unroll
     for (int m = 1; m < TPR; m <<= 1) dot += __shfl_xor(dot, m, 64);
     if (sub == 0) ge[row] = -dot;
-    return finite;
 }
 
 // Hashed rows of block b from the workspace into cs [C][CSS]
@@ -306,58 +294,56 @@ __device__ __forceinline__ void read_out(const float *ph, int nrt, const f32x4 (
 }
 // out[ti][ci] += M . ys (TR: M^T . ys) for an in-tile matrix M [C][MS]: tokens x tokens times tokens x columns.  M is zero above
 // its diagonal, and a row of ys must reach its own token and those behind it (TR: in front of it) only, also where it holds an
-// infinity or a NaN, which a zero does not silence: 16 x 16 tiles above the diagonal are left out, and where the rows are not
-// all finite the tiles on it are summed entry by entry instead of by a matrix product.
+// infinity or a NaN, which a zero does not silence: 16 x 16 tiles above the diagonal are left out, and on the diagonal such
+// entries stay out of the matrix product and are added one by one.
 template <int RT, int NCT, bool TR>
-__device__ __forceinline__ void apply_tile(const GArgs &a, const float *M, int MS, const float *ys, int XS, bool finite, f32x4 (&out)[RT][NCT])
+__device__ __forceinline__ void apply_tile(const GArgs &a, const float *M, int MS, const float *ys, int XS, f32x4 (&out)[RT][NCT])
 {
     const int lane = threadIdx.x & 63, n = lane & 15, q = lane >> 4, w = threadIdx.x >> 6;
+    bool finite = true;
 #pragma unroll
     for (int jt = 0; jt < RT; ++jt) {
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
             const int j = 16 * jt + 4 * q + v;
-            float y[NCT];
+            float y[NCT], yf[NCT];
 #pragma unroll
             for (int ci = 0; ci < NCT; ++ci) {
                 const int c = 16 * (w + 4 * ci);
                 y[ci] = c < a.dp ? ys[j * XS + c + n] : 0.f;
+                const bool f = __builtin_isfinite(y[ci]);
+                yf[ci] = f ? y[ci] : 0.f;
+                finite &= f;
             }
 #pragma unroll
             for (int ti = 0; ti < RT; ++ti) {
-                if ((TR ? ti > jt : ti < jt) || (ti == jt && !finite)) continue;
+                if (TR ? ti > jt : ti < jt) continue;
                 const float m = TR ? M[j * MS + 16 * ti + n] : M[(16 * ti + n) * MS + j];
 #pragma unroll
-                for (int ci = 0; ci < NCT; ++ci) out[ti][ci] = mfma(m, y[ci], out[ti][ci]);
+                for (int ci = 0; ci < NCT; ++ci) out[ti][ci] = mfma(m, ti == jt ? yf[ci] : y[ci], out[ti][ci]);
             }
         }
     }
-    if (finite) return;
+    if (__all(finite)) return;
 #pragma unroll 1
     for (int j = 0; j < 16; ++j) {
 #pragma unroll
         for (int ti = 0; ti < RT; ++ti) {
 #pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const int i = 4 * q + v;
-                if (TR ? j < i : j > i) continue;
-                const float m = TR ? M[(16 * ti + j) * MS + 16 * ti + i] : M[(16 * ti + i) * MS + 16 * ti + j];
+            for (int ci = 0; ci < NCT; ++ci) {
+                const int c = 16 * (w + 4 * ci);
+                const float y = c < a.dp ? ys[(16 * ti + j) * XS + c + n] : 0.f;
+                if (__builtin_isfinite(y)) continue;
 #pragma unroll
-                for (int ci = 0; ci < NCT; ++ci) {
-                    const int c = 16 * (w + 4 * ci);
-                    if (c < a.dp) out[ti][ci][v] = fmaf(m, ys[(16 * ti + j) * XS + c + n], out[ti][ci][v]);
+                for (int v = 0; v < 4; ++v) {
+                    const int i = 4 * q + v;
+                    const float m = TR ? M[(16 * ti + j) * MS + 16 * ti + i] : M[(16 * ti + i) * MS + 16 * ti + j];
+                    if (TR ? j >= i : j <= i) out[ti][ci][v] = fmaf(m, y, out[ti][ci][v]);
                 }
             }
         }
     }
 }
-// One flag of a workgroup from every thread's: posted behind one barrier, read after the next.
-__device__ __forceinline__ void post_flag(int *flags, bool mine)
-{
-    const bool all = __all(mine);
-    if ((threadIdx.x & 63) == 0) flags[threadIdx.x >> 6] = all;
-}
-__device__ __forceinline__ bool all_flags(const int *flags) { return (flags[0] & flags[1] & flags[2] & flags[3]) != 0; }
 
 // In-tile kernel values Phi_Q(i) . Phi_K(j), accumulated over the blocks: one 16 x 16 tile (i, j) per wavefront for
 // C = 32; for C = 16 every wavefront takes 16 of the block's bucket rows and the four partial tiles are added at the end.
@@ -401,9 +387,10 @@ __device__ __forceinline__ void store_tile_kernel(const f32x4 &kk, float *KK, fl
     __syncthreads();
 }
 
-// inv[row] = 1 / max(|x_row|, floor) of the tile's rows in xs (unit-norm option).  16 / RT threads per row.
+// 1 / max(|x|, floor) of the row of the tile in xs that this thread shares with its neighbours, 16 / RT threads per row
+// (unit-norm option)
 template <int RT>
-__device__ __forceinline__ void row_scales(const GArgs &a, const float *xs, int XS, float *inv)
+__device__ __forceinline__ float row_scale(const GArgs &a, const float *xs, int XS)
 {
     constexpr int TPR = kThreads / (16 * RT);
     const int row = threadIdx.x / TPR, sub = threadIdx.x % TPR;
@@ -411,14 +398,15 @@ __device__ __forceinline__ void row_scales(const GArgs &a, const float *xs, int 
     for (int c = sub; c < a.d; c += TPR) { const float x = xs[row * XS + c]; ss = fmaf(x, x, ss); }
 #pragma unroll
     for (int m = 1; m < TPR; m <<= 1) ss += __shfl_xor(ss, m, 64);
-    if (sub == 0) inv[row] = 1.0f / fmaxf(sqrtf(ss), kUnitFloor);
+    return 1.0f / fmaxf(sqrtf(ss), kUnitFloor);
 }
-// Hashed rows of a tile on np <= 32 hyperplanes (W: the first one's row) into cs [C][CSS]; put(token, hyperplane, hashed form,
-// projection) sees each of them.  z = X W^T: 16 tokens x 16 hyperplanes per wavefront and step, contraction over d, accumulated in
-// fp64 (products of fp32 are exact there): a bit's mass multiplies an error of z by 2 beta, and the projection is a small share
-// of the work.
-template <int RT, typename F>
-__device__ __forceinline__ void hash_block(const GArgs &a, const float *W, int np, const float *xs, int XS, const float *inv, float *cs, F put)
+// Hashed rows of a tile on np <= 32 hyperplanes (W: the first one's row) into cs [C][CSS]; those of its first nst rows and the
+// projections also to Cx and Zx (token row0 and hyperplane pl0 on).  z = X W^T: 16 tokens x 16 hyperplanes per wavefront and
+// step, contraction over d, accumulated in fp64 (products of fp32 are exact there): a bit's mass multiplies an error of z by
+// 2 beta, and the projection is a small share of the work.
+template <int RT>
+__device__ __forceinline__ void hash_block(const GArgs &a, const float *W, int np, const float *xs, int XS, const float *inv, float *cs,
+                                           float *Cx, float *Zx, size_t row0, int pl0, int nst)
 {
     const int lane = threadIdx.x & 63, n = lane & 15, q = lane >> 4, w = threadIdx.x >> 6;
     const int npj = (np + 15) >> 4;
@@ -443,9 +431,10 @@ __device__ __forceinline__ void hash_block(const GArgs &a, const float *W, int n
             float zz = static_cast<float>(z[v]);
             if (a.unit) zz *= inv[tok];
             const float c = code(zz, a.beta);
-            if (real) {
-                cs[tok * CSS + pl] = c;
-                put(tok, pl, c, zz);
+            if (real) cs[tok * CSS + pl] = c;
+            if (real && tok < nst) {
+                Cx[(row0 + tok) * a.LP + pl0 + pl] = c;
+                Zx[(row0 + tok) * a.LP + pl0 + pl] = zz;
             }
         }
     }
@@ -477,7 +466,7 @@ __global__ __launch_bounds__(kThreads, 2) void generic_totals(GArgs a, const T *
                                                               const float *den, float *state)
 {
     extern __shared__ __attribute__((aligned(16))) float lds[];
-    constexpr int C = 16 * RT;
+    constexpr int C = 16 * RT, TPR = kThreads / C;
     TotalsLds<RT> s(lds, a.dp, SIDE);
     const int XS = a.dp + 4;
     const int seg = blockIdx.x, bh = blockIdx.z, tid = threadIdx.x;
@@ -507,17 +496,15 @@ __global__ __launch_bounds__(kThreads, 2) void generic_totals(GArgs a, const T *
             if (!query) load_rows<T, RT>(a, Y, row0, nv, s.ys, XS);
             __syncthreads();
             if (a.unit) {
-                row_scales<RT>(a, s.xs, XS, s.inv);
-                __syncthreads();
-                if (b == 0 && tid < nv) a.nrm[(query ? 0 : static_cast<size_t>(a.BH) * a.N) + row0 + tid] = s.inv[tid];
-            }
-            hash_block<RT>(a, W, np, s.xs, XS, s.inv, s.cs, [&](int tok, int pl, float c, float z) __attribute__((always_inline)) {
-                if (writes && tok < nv) {
-                    const size_t at = (row0 + tok) * a.LP + pl0 + pl;
-                    (query ? a.Cq : a.Ck)[at] = c;
-                    (query ? a.Zq : a.Zk)[at] = z;
+                const float inv = row_scale<RT>(a, s.xs, XS);
+                if (tid % TPR == 0) {
+                    const int row = tid / TPR;
+                    s.inv[row] = inv;
+                    if (b == 0 && row < nv) a.nrm[(query ? 0 : static_cast<size_t>(a.BH) * a.N) + row0 + row] = inv;
                 }
-            });
+                __syncthreads();
+            }
+            hash_block<RT>(a, W, np, s.xs, XS, s.inv, s.cs, query ? a.Cq : a.Ck, query ? a.Zq : a.Zk, row0, pl0, writes ? nv : 0);
             if (query) continue;
         } else {
             load_codes<RT>(a, a.Cq, row0, nv, b, s.cs);
@@ -542,7 +529,6 @@ __global__ __launch_bounds__(kThreads, 2) void generic_totals(GArgs a, const T *
 template <int RT>
 struct FwdLds {
     float *vs, *phq, *phk, *kk, *part, *csq, *csk, *am, *den;
-    int *flags;
     static size_t floats(int dp) { return static_cast<size_t>(16 * RT) * (dp + 4 + 2 * PHS + 16 * RT + 4 + 2 * CSS + 1) + KB + (RT == 1 ? 1024 : 0) + 16; }
     __device__ FwdLds(float *p, int dp)
     {
@@ -555,8 +541,7 @@ struct FwdLds {
         am = p; p += KB;
         den = p; p += C;
         csq = p; p += C * CSS;
-        csk = p; p += C * CSS;
-        flags = reinterpret_cast<int *>(p);
+        csk = p;
     }
 };
 
@@ -587,7 +572,7 @@ __global__ __launch_bounds__(kThreads, 2) void generic_forward(GArgs a, const T 
         }
         float dn = 0.f;
         __syncthreads();
-        if (a.causal) post_flag(s.flags, load_rows<T, RT>(a, V, row0, nv, s.vs, XS));
+        if (a.causal) load_rows<T, RT>(a, V, row0, nv, s.vs, XS);
         for (int b = 0; b < a.nblk; ++b) {
             const int nrt = block_rtiles(a, b);
             f32x4 sb[4][NCT];
@@ -619,7 +604,7 @@ __global__ __launch_bounds__(kThreads, 2) void generic_forward(GArgs a, const T 
             store_tile_kernel<RT>(kk, s.kk, s.part);
 #pragma unroll
             for (int k = 0; k < C / TPR; ++k) dn += s.kk[tok_r * MS + sub + k * TPR];
-            apply_tile<RT, NCT, false>(a, s.kk, MS, s.vs, XS, all_flags(s.flags), out);
+            apply_tile<RT, NCT, false>(a, s.kk, MS, s.vs, XS, out);
         }
 #pragma unroll
         for (int m = 1; m < TPR; m <<= 1) dn += __shfl_xor(dn, m, 64);
@@ -657,7 +642,6 @@ __global__ __launch_bounds__(kThreads, 2) void generic_forward(GArgs a, const T 
 template <int RT>
 struct GradLds {
     float *gs, *vs, *phq, *phk, *tt, *kk, *csq, *csk, *dz, *am, *dam, *ge, *rec, *rad, *part;
-    int *flags;
     static size_t floats(int dp)
     {
         return static_cast<size_t>(16 * RT) * (2 * (dp + 4) + 2 * PHS + 2 * (16 * RT + 4) + 2 * CSS + 2 * DZS + 1 + 18 + 2) + 2 * KB +
@@ -680,8 +664,7 @@ struct GradLds {
         rec = p; p += 2 * C * 9;        // (side, token): m and G_t of a table that spans several blocks
         rad = p; p += 2 * C;
         csq = p; p += C * CSS;
-        csk = p; p += C * CSS;
-        flags = reinterpret_cast<int *>(p);
+        csk = p;
     }
 };
 
@@ -724,7 +707,7 @@ __global__ __launch_bounds__(kThreads, RT * NCT > 2 ? 1 : 2) void generic_grads(
         }
         float radial = 0.f;                                     // threads (side, token) < 2 C: sum of z . dz (unit-norm option)
         __syncthreads();
-        post_flag(s.flags, load_cotangents<T, RT>(a, dO, O, den, row0, nv, s.gs, XS, s.ge));
+        load_cotangents<T, RT>(a, dO, O, den, row0, nv, s.gs, XS, s.ge);
         load_rows<T, RT>(a, V, row0, nv, s.vs, XS);
         __syncthreads();
         if (a.causal) {
@@ -950,7 +933,7 @@ __global__ __launch_bounds__(kThreads, RT * NCT > 2 ? 1 : 2) void generic_grads(
         }
         if (do_kv && a.causal) {
             store_tile_kernel<RT>(kk, s.kk, s.part);
-            apply_tile<RT, NCT, true>(a, s.kk, MS, s.gs, XS, all_flags(s.flags), av);
+            apply_tile<RT, NCT, true>(a, s.kk, MS, s.gs, XS, av);
         }
         if (a.unit) {
             if (tid < 2 * C) s.rad[tid] = radial;
@@ -1012,10 +995,11 @@ __global__ __launch_bounds__(kThreads) void generic_hash_tap(GArgs a, const T *X
     load_rows<T, 1>(a, X, row0, nv, s.ys, XS);
     __syncthreads();
     if (a.unit) {
-        row_scales<1>(a, s.ys, XS, s.inv);
+        const float inv = row_scale<1>(a, s.ys, XS);
+        if (tid % 16 == 0) s.inv[tid / 16] = inv;
         __syncthreads();
     }
-    hash_block<1>(a, a.W + (static_cast<size_t>(bh % a.H) * a.LP + pl0) * a.d, np, s.ys, XS, s.inv, s.cs, [](int, int, float, float) {});
+    hash_block<1>(a, a.W + (static_cast<size_t>(bh % a.H) * a.LP + pl0) * a.d, np, s.ys, XS, s.inv, s.cs, nullptr, nullptr, 0, 0, 0);
     __syncthreads();
     if (a.bpt == 1 || b % a.bpt == 0) {
         for (int i = tid; i < 16 * a.TB; i += kThreads) {

@@ -13,7 +13,7 @@ from parity_util import desc_of, run_gpu
 
 pytestmark = pytest.mark.gpu
 
-# the same sums in another order where a tile is summed entry by entry: some 32 terms of fp32 (bf16: one rounding of the result)
+# room for the same sums in another order: some 32 terms of fp32 (bf16: one rounding of the result)
 CLOSE = {"f32": 1e-5, "bf16": 2.0 ** -7}
 
 # tiles of 16 tokens; of 32; narrow bf16; segments of several tiles; a table over several blocks; more than 128 columns
