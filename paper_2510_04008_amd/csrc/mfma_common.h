@@ -35,6 +35,7 @@ namespace mfma {
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
 typedef __attribute__((ext_vector_type(2))) float f32x2;
+typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 typedef __attribute__((ext_vector_type(2))) uint32_t u32x2;
@@ -65,6 +66,7 @@ struct Cfg {
     static constexpr int NT = D / 32;                   // 32-column tiles of the head dimension
     static constexpr int NTW = NT / CG;                 // column tiles per wavefront
     static constexpr int DW = D / CG;                   // columns per wavefront
+    static constexpr int MA = (MT + CG - 1) / CG;       // row tiles whose extra column a wavefront carries
     // wavefronts per SIMD the stream and totals kernels are compiled for: shapes with at most two accumulator
     // tiles of statistics and one column tile per wavefront fit 128 registers and leave room for a second workgroup
     // on the CU, whose phases interleave with the first one's (measured: with two column tiles the kernels spill
@@ -95,6 +97,22 @@ struct Cfg {
 // Scheduling fence: keeps the instruction scheduler from hoisting the loads and conversions of later
 // loop iterations (and with them dozens of live registers) above this point.
 #define RACE_SCHED_FENCE() __builtin_amdgcn_sched_barrier(0)
+
+// Lets this wavefront issue before the other one of its SIMD (wavefronts w and w + 4), which wins by its age otherwise.  In the
+// second half of a tile the two run the same code: with the younger one ahead in the first part and the older one from
+// there on, one's matrix products meet the other's vector work and both reach the barrier together.  (By age alone the older
+// wavefront was done 1300 of 4800-5500 cycles early and the younger one ran out the rest alone, at half the issue rate.  Training
+// steps of 4.2 million rows of 128 columns, L = 8, P = 6: 44.26 -> 43.02 ms; 160 000 rows of 64 columns: 366 -> 359 us.)
+__device__ __forceinline__ void lead(bool on)
+{
+    if (on) __builtin_amdgcn_s_setprio(1);
+    else __builtin_amdgcn_s_setprio(0);
+}
+
+// Waits for this wavefront's loads.  Loads and stores share a counter and count in order: where loaded rows are used behind
+// stores that may or may not be issued (output rows past the end), the compiler has to wait for the stores as well, a
+// trip to memory.  With this in front of the stores nothing is left to wait for behind them.
+__device__ __forceinline__ void wait_loads() { __builtin_amdgcn_s_waitcnt(0x0F70); }        // vmcnt(0), the other counters as they are
 
 // Hides the value of an index from the optimiser inside a loop body, so that the dozens of addresses
 // derived from it (index + constant) are folded into instruction offsets instead of being hoisted out of
@@ -163,18 +181,6 @@ __device__ __forceinline__ float dot2(uint32_t a, uint32_t b, float c)
     return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, a), __builtin_bit_cast(bf16x2, b), c, false);
 }
 constexpr uint32_t kOnePair = 0x3F803F80u;     // (1.0, 1.0)
-// sum of the eight bf16 of v
-__device__ __forceinline__ float sum8(u32x4 v)
-{
-    return dot2(v.y, kOnePair, dot2(v.x, kOnePair, 0.f)) + dot2(v.w, kOnePair, dot2(v.z, kOnePair, 0.f));
-}
-// sum of v_i g_i over the eight bf16 of v with fp32 weights.  (Plain multiply-adds: with the weights as bf16 (hi, lo)
-// pairs and eight packed dot instructions the totals and gradient kernels measured 1-4 % slower.)
-__device__ __forceinline__ float wsum8(u32x4 v, float4 g0, float4 g1)
-{
-    return bf_lo(v.x) * g0.x + bf_hi(v.x) * g0.y + bf_lo(v.y) * g0.z + bf_hi(v.y) * g0.w +
-           bf_lo(v.z) * g1.x + bf_hi(v.z) * g1.y + bf_lo(v.w) * g1.z + bf_hi(v.w) * g1.w;
-}
 // row of accumulator register v for lane half h
 __device__ __forceinline__ int acc_row(int v, int h) { return 8 * (v >> 2) + 4 * h + (v & 3); }
 // pair-interleaved position of feature c: bits 2 and 3 of the index swapped
@@ -236,6 +242,12 @@ __device__ __forceinline__ float sum_rows(float x)
     return sum_halves(__uint_as_float(r[0]) + __uint_as_float(r[1]));
 }
 
+// Two sums over the halves at once: the lower half of the lanes gets the sum of x0, the upper one that of x1.
+__device__ __forceinline__ float sum_halves2(float x0, float x1)
+{
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x0), __float_as_uint(x1), false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
 // Four sums over the rows of 16 lanes at once: row i of lanes gets the sum of x_i.
 __device__ __forceinline__ float sum_rows4(float x0, float x1, float x2, float x3)
 {
@@ -246,12 +258,54 @@ __device__ __forceinline__ float sum_rows4(float x0, float x1, float x2, float x
     return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
+// ---------------------------------------------------------------- the extra column of the statistics (bucket masses)
+// Sums of assignments over the tokens of a k-step, with weights, on the matrix cores: the same registers that are the
+// assignments' operand of the 32 x 32 x 16 update (lane = 32 h + n: bucket row n, tokens 8 h ..) are, read as the B operand of a
+// 16 x 16 x 32 product, column n % 16 with k-slots 8 (n / 16 + 2 h) .., i.e. both halves of the bucket rows in one column.  An A
+// operand whose rows 0 .. 2 hold the weights in the slots of bucket rows 0 .. 15 and whose rows 4 .. 6 hold them in the slots
+// of rows 16 .. 31 keeps the halves apart: D register v of lane n < 32 is the sum of bucket row n with weight part v.  fp32
+// weights enter as three bf16 parts (truncated, 8 bits each: exact), weights of one as a single part.  (One 16-cycle matrix
+// instruction in place of 16 vector ones; both totals kernels spent 128 of their 320-450 vector instructions a step on these sums.)
+constexpr int kParts = 4;                       // rows of a [kParts][tokens] bf16 array of weight parts; the last one is zeros
+__device__ __forceinline__ bf16raw weight_part(float x, int i)
+{
+    const float a = bf_hi(__float_as_uint(x)), r = __builtin_isfinite(x) ? x - a : 0.f, b = bf_hi(__float_as_uint(r)), c = r - b;
+    const float part = i == 0 ? a : (i == 1 ? b : c);
+    return static_cast<bf16raw>(i < kParts - 1 ? __float_as_uint(part) >> 16 : 0u);
+}
+// This lane's element of a [kParts][tokens] array for a k-step at its first token, and the operand of weights of one.
+// Form 32: against operands of 32 bucket rows; form 16: against B operands of 16 x 16 x 32 products (16 bucket rows, 32 tokens).
+__device__ __forceinline__ int parts_offset32(int tokens, int lane)
+{
+    const int i = lane & 15, q = lane >> 4;
+    return (i < 8 && (i >> 2) == (q & 1) ? i & 3 : kParts - 1) * tokens + 8 * (q >> 1);
+}
+__device__ __forceinline__ int parts_offset16(int tokens, int lane)
+{
+    const int i = lane & 15, q = lane >> 4;
+    return (i < kParts - 1 ? i : kParts - 1) * tokens + 8 * q;
+}
+__device__ __forceinline__ u32x4 ones32(int lane)
+{
+    const uint32_t one = (lane & 15) == 4 * ((lane >> 4) & 1) ? kOnePair : 0u;
+    return u32x4{one, one, one, one};
+}
+__device__ __forceinline__ u32x4 ones16(int lane)
+{
+    const uint32_t one = (lane & 15) == 0 ? kOnePair : 0u;
+    return u32x4{one, one, one, one};
+}
+__device__ __forceinline__ float sum_parts(f32x4 x) { return (x[2] + x[1]) + x[0]; }
+// the sums so far as the accumulator of the next products (the parts are added up per tile: one register between tiles, not four)
+__device__ __forceinline__ f32x4 as_parts(float x) { return f32x4{x, 0.f, 0.f, 0.f}; }
+
 // ---------------------------------------------------------------- global -> registers -> LDS tiles
 // A tile of ROWS rows is ROWS*CPR chunks of 16 bytes; thread t owns chunks t, t + 512, ...  Loads are
 // issued ahead of use (fetch) and written to LDS later (store), so that HBM latency overlaps arithmetic.
 template <class C, int ROWS>
 struct RowChunks {
     static constexpr int N = (ROWS * C::CPR + kThreads - 1) / kThreads;
+    static constexpr bool EVEN = ROWS * C::CPR % kThreads == 0;        // every thread's chunks are inside the tile
     u32x4 v[N];
 };
 
@@ -294,11 +348,11 @@ __device__ __forceinline__ void store_chunk(bf16raw *dst, int row, int ch, u32x4
 template <class C, int ROWS, int STRIDE = C::XS, int IL = kPlain>
 __device__ __forceinline__ void store_rows(const RowChunks<C, ROWS> &r, bf16raw *dst)
 {
-    const int tid = opaque(static_cast<int>(threadIdx.x));       // keeps the tile addresses out of long-lived registers
+    const uint32_t tid = opaque(static_cast<int>(threadIdx.x)) & (kThreads - 1);      // keeps the tile addresses out of long-lived registers
 #pragma unroll
     for (int k = 0; k < RowChunks<C, ROWS>::N; ++k) {
-        const int c = tid + k * kThreads, row = c / C::CPR, ch = c % C::CPR;
-        if (row < ROWS) store_chunk<STRIDE, IL>(dst, row, ch, r.v[k]);
+        const uint32_t c = tid + k * kThreads, row = c / C::CPR, ch = c % C::CPR;
+        if (RowChunks<C, ROWS>::EVEN || row < ROWS) store_chunk<STRIDE, IL>(dst, row, ch, r.v[k]);
     }
 }
 
@@ -345,10 +399,10 @@ __device__ __forceinline__ void fetch_cotangent(const bf16raw *dO, const bf16raw
     }
 }
 
-// Forms the cotangent rows of a tile, into LDS (dst, ge) and into memory (Gout, ge_out: rows from t0 on), where the later
-// passes read them back as plain rows.
+// Forms the cotangent rows of a tile, into LDS (dst, ge_parts) and into memory (Gout, ge_out: rows from t0 on), where the later
+// passes read them back as plain rows.  ge_parts: [kParts][ROWS], see weight_part().
 template <class C, int ROWS, int STRIDE>
-__device__ __forceinline__ void store_cotangent(const CotChunks<C, ROWS> &r, bf16raw *dst, float *ge, int L_real, int nvalid,
+__device__ __forceinline__ void store_cotangent(const CotChunks<C, ROWS> &r, bf16raw *dst, bf16raw *ge_parts, int L_real, int nvalid,
                                                 bf16raw *Gout, float *ge_out, int64_t t0)
 {
     const int tid = opaque(static_cast<int>(threadIdx.x));
@@ -374,14 +428,12 @@ __device__ __forceinline__ void store_cotangent(const CotChunks<C, ROWS> &r, bf1
         // the CPR threads of one row are consecutive lanes
 #pragma unroll
         for (int m = C::CPR / 2; m >= 1; m >>= 1) dot += __shfl_xor(dot, m, 64);
-        if (ch == 0 && row < ROWS) ge[row] = -dot;
+        if (ch < kParts && row < ROWS) ge_parts[ch * ROWS + row] = weight_part(-dot, ch);
         if (ch == 0 && row < nvalid) ge_out[t0 + row] = -dot;
     }
 }
 
 // ---------------------------------------------------------------- projection + soft assignment
-typedef __attribute__((ext_vector_type(4))) float f32x4;
-
 // 16 x 16 x 32 product: A row / B column lane % 16, k-slots 8 (lane / 16) ..; D column lane % 16, rows 4 (lane / 16) + v.
 __device__ __forceinline__ f32x4 mma16(u32x4 a, u32x4 b, f32x4 c)
 {
@@ -409,6 +461,14 @@ __device__ __forceinline__ void code_masses(float c, float &p, float &q)
     p = pos ? big : small;
     q = pos ? small : big;
 }
+
+// the mass on one side (bit != 0: +1), and the product of the two
+__device__ __forceinline__ float side_mass(float c, int bit)
+{
+    const float small = fabsf(c);
+    return ((__float_as_uint(c) >> 31) != 0) == (bit != 0) ? small : 1.0f - small;
+}
+__device__ __forceinline__ float minor_major(float c) { return fabsf(c) * (1.0f - fabsf(c)); }
 
 // Hashed rows of NTAB tables for one token per lane.
 template <class C, int NTAB>
@@ -493,18 +553,31 @@ __device__ __forceinline__ float produce(const typename Share<C, SLOTS>::Regs &c
         }
         constexpr int kA = kSplitA ? NA / 2 : NA;
         const int abase = kSplitA ? part * (NA / 2) * 8 : 0;
+        // (the masses of a pair are requested one pair ahead: read where they are used, their latency was a third of the
+        // production's time)
+        float4 next[4];
+        auto load_masses = [&](int a) __attribute__((always_inline)) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) next[i] = *reinterpret_cast<const float4 *>(mass + tbase + abase + a * 8 + 4 * i);
+        };
+        if (mass) load_masses(0);
 #pragma unroll
         for (int a = 0; a < kA; a += 2) {
+            float4 mq[4];
+            if (mass) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) mq[i] = next[i];
+                if (a + 2 < kA) load_masses(a + 2);
+            }
 #pragma unroll
             for (int half = 0; half < 2; ++half) {
                 if (Sh::PARTS == 2 && !kSplitA && half != part) continue;
                 const int pos = tbase + abase + a * 8 + 8 * half;
+                const float4 m0 = mq[2 * half], m1 = mq[2 * half + 1];
                 float f[8];
 #pragma unroll
                 for (int b = 0; b < 4; ++b) { f[b] = hi[a] * lo[4 * half + b]; f[4 + b] = hi[a + 1] * lo[4 * half + b]; }
                 if (mass) {
-                    const float4 m0 = *reinterpret_cast<const float4 *>(mass + pos);
-                    const float4 m1 = *reinterpret_cast<const float4 *>(mass + pos + 4);
                     dn = fmaf(f[0], m0.x, dn); dn = fmaf(f[1], m0.y, dn); dn = fmaf(f[2], m0.z, dn); dn = fmaf(f[3], m0.w, dn);
                     dn = fmaf(f[4], m1.x, dn); dn = fmaf(f[5], m1.y, dn); dn = fmaf(f[6], m1.z, dn); dn = fmaf(f[7], m1.w, dn);
                 }

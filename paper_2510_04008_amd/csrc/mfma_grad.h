@@ -49,16 +49,16 @@ struct GradCfg {
     static constexpr int SREGS = T16 ? TPW * C::D / 4 : MTG * C::NT * 16;        // registers of statistics
     static constexpr int YORDER = T16 ? kPairs32 : kPairs16;
     // First half of a tile, by role.  Production: `SLOTS` half wavefronts from wavefront 0 on; projection of the reader's rows:
-    // 2 PT 16 x 16 tiles; in-tile term: three 16 x 16 tiles; dX of the previous tile: NT column tiles.
+    // 2 PT 16 x 16 tiles; in-tile term: three 16 x 16 tiles; dX of the previous tile: 2 NT pieces.
     static constexpr int SLOTS = C::L >= 16 ? 16 : 8;
     static constexpr int proj_wave(int i, bool causal)
     {
-        if (!causal || C::PT == 4) return causal && !T16 ? 4 + i % 4 : i % kWaves;      // (R = 64: wavefronts 4-7, two each)
+        if (!causal || C::PT == 4) return i % kWaves;
         return i == 0 ? 0 : 3 + i;
     }
-    static constexpr int tt_wave(int i) { return T16 ? (C::L >= 16 ? 5 + i : 1 + i) : i; }
-    static constexpr int dx_wave(int i, bool causal) { return T16 ? (causal && C::L >= 16 ? i : kWaves - 1 - i) : 4 + i; }
-    static_assert(C::NT <= 4, "dX on four wavefronts at most");
+    static constexpr int tt_wave(int i) { return T16 ? (C::L >= 16 ? 5 + i : 1 + i) : 4 + i; }
+    static constexpr int dx_wave(int i, bool causal) { return T16 && causal && C::L >= 16 ? i : kWaves - 1 - i; }
+    static_assert(2 * C::NT <= kWaves, "one piece of dX per wavefront at most");
 };
 
 // UNIT: the unit-norm option's extras (row scales, projections, parts of z . dz, a second buffer of the reader's rows, which
@@ -73,7 +73,8 @@ struct GradLds {
     static constexpr int dz = wp + C::LPP * C::XS * 2;                  // [32][DZS] bf16
     static constexpr int sr = dz + kTile * DZS * 2;                     // [2][32] fp32 extra column of reader-Y
     static constexpr int sw = sr + 2 * kTile * 4;                       // [2][32] fp32 extra column of writer-Y
-    static constexpr int nrm = sw + 2 * kTile * 4;                      // [XB][32] fp32: 1 / |x| of the reader's rows
+    static constexpr int swp = sw + 2 * kTile * 4;                      // [2][kParts][32] bf16: parts of sw (key side)
+    static constexpr int nrm = swp + 2 * kParts * kTile * 2;                      // [XB][32] fp32: 1 / |x| of the reader's rows
     static constexpr int rad = nrm + (UNIT ? XB * kTile * 4 : 0);       // [kWaves][32] fp32: per-wavefront parts of z . dz per token
     static constexpr int QUADS = C::L * C::PP / 4;
     static constexpr int s2 = (rad + (UNIT ? kWaves * kTile * 4 : 0) + 15) & ~15;     // [QUADS][32] float4: 1 - tanh^2 z of four hyperplanes
@@ -86,10 +87,8 @@ struct GradLds {
     static constexpr int yw = ttop + (INTRA ? 2 * 64 * 16 : 0);         // [2][32][YS] writer-Y rows, pair-interleaved columns
     static constexpr int yw_bytes = kTile * C::YS * 2;
     static constexpr int phw = yw + (INTRA ? 2 * yw_bytes : 0);         // [32][PST] writer assignments
-    static constexpr int SS = 40;                                       // bf16 row stride of the output staging tiles
     static constexpr int mass = phw + (INTRA ? kTile * C::PST * 2 : 0); // R = 16: [kWaves][TPW * 16] fp32: extra column of each wavefront's rows
-    static constexpr int stg = mass + (G::T16 ? kWaves * G::TPW * 16 * 4 : 0);  // [NT][16][SS] bf16: dX tiles on their way out, 16 tokens at a time
-    static constexpr int total = stg + C::NT * 16 * SS * 2;
+    static constexpr int total = mass + (G::T16 ? kWaves * G::TPW * 16 * 4 : 0);
     // where the cotangent of beta is wanted:
     static constexpr int th = total;                                    // [QUADS][32] float4: tanh z
     static constexpr int th_bytes = QUADS * kTile * 16;
@@ -121,11 +120,11 @@ void grad_kernel(KArgs a, const bf16raw *Xr, const bf16raw *V, const bf16raw *G_
     f32x4 *zzt = reinterpret_cast<f32x4 *>(lds + S::zz);
     bf16raw *phw = reinterpret_cast<bf16raw *>(lds + S::phw);
     u32x4 *ttop = reinterpret_cast<u32x4 *>(lds + S::ttop);
-    bf16raw *stg = reinterpret_cast<bf16raw *>(lds + S::stg);
     auto buf_yr = [&](int it) { return reinterpret_cast<bf16raw *>(lds + S::yr + (it & 1) * S::yr_bytes); };
     auto buf_yw = [&](int it) { return reinterpret_cast<bf16raw *>(lds + S::yw + (it & 1) * S::yw_bytes); };
     auto buf_sr = [&](int it) { return reinterpret_cast<float *>(lds + S::sr) + (it & 1) * kTile; };
     auto buf_sw = [&](int it) { return reinterpret_cast<float *>(lds + S::sw) + (it & 1) * kTile; };
+    auto buf_swp = [&](int it) { return reinterpret_cast<bf16raw *>(lds + S::swp) + (it & 1) * kParts * kTile; };
     auto buf_xr = [&](int it) { return reinterpret_cast<bf16raw *>(lds + S::xr + (UNIT ? it & 1 : 0) * S::xr_bytes); };
     auto buf_nrm = [&](int it) { return reinterpret_cast<float *>(lds + S::nrm) + (UNIT ? it & 1 : 0) * kTile; };
 
@@ -162,7 +161,7 @@ void grad_kernel(KArgs a, const bf16raw *Xr, const bf16raw *V, const bf16raw *G_
     // statistics at the start of the segment, transposed tiles: columns x bucket rows
     f32x16 ST[G::MTG][C::NT];                        // R = 64: 32 x 32 tiles [row tile][column tile]
     f32x4 SU[G::TPW][C::D / 16];                     // R = 16: 16 x 16 tiles [table][column tile]
-    float macc[G::T16 ? G::TPW : G::MTG];            // extra column (A or dA): lane partials of row r_own + 32 mr + ln (16 i + n16)
+    float macc[G::T16 ? G::TPW : G::MTG];            // extra column (A or dA): lane n < 32 <-> row r_own + 32 mr + n (n < 16 <-> r_own + 16 i + n)
     float *mass = reinterpret_cast<float *>(lds + S::mass) + w * G::TPW * 16;
     if constexpr (G::T16) {
 #pragma unroll
@@ -220,6 +219,7 @@ void grad_kernel(KArgs a, const bf16raw *Xr, const bf16raw *V, const bf16raw *G_
             buf_sr(it)[tid] = SIDE == 0 ? pre_ge : 1.f;
             buf_sw(it)[tid] = SIDE == 0 ? 1.f : pre_ge;
         }
+        if (SIDE == 1 && intra && tid < kParts * kTile) buf_swp(it)[tid] = weight_part(pre_ge, tid / kTile);
     };
     auto stage_x = [&](int it) __attribute__((always_inline)) {
         store_rows<C, kTile>(pre_r, buf_xr(it));
@@ -236,7 +236,7 @@ void grad_kernel(KArgs a, const bf16raw *Xr, const bf16raw *V, const bf16raw *G_
     // this wavefront's roles in the first half (compile-time tables, looked up once)
     int my_dx = -1, my_tt = -1, my_proj[2] = {-1, -1};
 #pragma unroll
-    for (int i = 0; i < C::NT; ++i) my_dx = w == G::dx_wave(i, INTRA) ? i : my_dx;
+    for (int i = 0; i < 2 * C::NT; ++i) my_dx = w == G::dx_wave(i, INTRA) ? i : my_dx;
 #pragma unroll
     for (int i = 0; i < 3; ++i) my_tt = w == G::tt_wave(i) ? i : my_tt;
 #pragma unroll
@@ -256,51 +256,68 @@ void grad_kernel(KArgs a, const bf16raw *Xr, const bf16raw *V, const bf16raw *G_
         __syncthreads();
     }
 
-    // ---- dX = dz . W for one tile (the chain rule through W): a wavefront forms the transposed 32 x 32 tile of its
-    //      column tile nt (lane = token, registers = columns 32 nt + acc_row(v, h)), stages it in its own corner of
-    //      LDS and stores 16-byte row pieces; nobody else touches that corner.  Called one tile late, next to the
-    //      production of the following tile.
-    auto dx_stage = [&](int nt, int it) __attribute__((always_inline)) {
+    // ---- dX = dz . W for one tile (the chain rule through W), one step late, next to the production of the following tile.  Piece
+    //      i is 16 tokens x 32 columns, as two transposed 16 x 16 tiles whose rows are columns 8 q + 0 .. 3 and 8 q + 4 .. 7: lane
+    //      (n, q) holds eight consecutive columns of token n and stores them as one 16-byte piece, without a stop in LDS.
+    //      (As 32 x 32 tiles on four wavefronts, staged in LDS on their way out, this chain of dependent steps took 1700 of the
+    //      3750 cycles of the first half; here every wavefront has a quarter of that.)
+    auto dx_stage = [&](int i, int it) __attribute__((always_inline)) {
         const int64_t t0 = tile_t0(it);
-        const int nvalid = tile_nv(t0);
-        const int lo = opaque(lane);                     // addresses below are rebuilt per tile, not kept in registers
-        const int lno = lo & 31, ho = lo >> 5;
-        f32x16 acc = {0};
+        const int lo = opaque(lane), n = lo & 15, q = lo >> 4;       // addresses below are rebuilt per tile, not kept in registers
+        const int c0 = 32 * (i >> 1), tok = 16 * (i & 1) + n;
+        f32x4 x0 = {0.f, 0.f, 0.f, 0.f}, x1 = x0;
 #pragma unroll
-        for (int s = 0; s < C::LPP / 16; ++s)
-            acc = mma(lds_tr_plain(wp, C::XS, 16 * s, 32 * nt, lno, ho), lds128(dz + lno * S::DZS + 16 * s + 8 * ho), acc);
-        if (UNIT) {
-            const bf16raw *xr_t = buf_xr(it);
-            float cp = 0.f;                              // (z . dz) / |x|^2 of token lno, parts in wavefront order
-#pragma unroll
-            for (int i = 0; i < kWaves / G::TS; ++i) cp += rad[((G::TS == 2 ? 4 * (lno >> 4) : 0) + i) * kTile + lno];
-            cp *= buf_nrm(it)[lno];
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                const u32x2 xv = *reinterpret_cast<const u32x2 *>(xr_t + lno * C::XS + 32 * nt + 8 * k + 4 * ho);
-                acc[4 * k] = fmaf(-cp, bf_lo(xv.x), acc[4 * k]);
-                acc[4 * k + 1] = fmaf(-cp, bf_hi(xv.x), acc[4 * k + 1]);
-                acc[4 * k + 2] = fmaf(-cp, bf_lo(xv.y), acc[4 * k + 2]);
-                acc[4 * k + 3] = fmaf(-cp, bf_hi(xv.y), acc[4 * k + 3]);
-            }
+        for (int s = 0; s < C::LPP / 32; ++s) {
+            const u32x4 d = lds128(dz + tok * S::DZS + 32 * s + 8 * q);
+            const int k = 32 * s + 8 * q, chunk = c0 + 8 * (lo & 3);
+            x0 = mma16(lds_tr16(wp, C::XS, k, k + 4, chunk, lo), d, x0);
+            x1 = mma16(lds_tr16(wp, C::XS, k, k + 4, chunk + 4, lo), d, x1);
         }
-        // (16 tokens at a time: the wavefront's own LDS accesses are in order)
-        bf16raw *sg = stg + nt * 16 * S::SS;
-        char *dst = reinterpret_cast<char *>(dX + t0 * C::D + 32 * nt);
+        if (UNIT) {
+            float cp = 0.f;                              // (z . dz) / |x|^2 of the token, parts in wavefront order
 #pragma unroll
-        for (int kk = 0; kk < 2; ++kk) {
-            if ((lno >> 4) == kk) {
+            for (int w8 = 0; w8 < kWaves / G::TS; ++w8) cp += rad[((G::TS == 2 ? 4 * (tok >> 4) : 0) + w8) * kTile + tok];
+            cp *= buf_nrm(it)[tok];
+            const u32x4 xv = lds128(buf_xr(it) + tok * C::XS + c0 + 8 * q);
+            x0[0] = fmaf(-cp, bf_lo(xv.x), x0[0]); x0[1] = fmaf(-cp, bf_hi(xv.x), x0[1]);
+            x0[2] = fmaf(-cp, bf_lo(xv.y), x0[2]); x0[3] = fmaf(-cp, bf_hi(xv.y), x0[3]);
+            x1[0] = fmaf(-cp, bf_lo(xv.z), x1[0]); x1[1] = fmaf(-cp, bf_hi(xv.z), x1[1]);
+            x1[2] = fmaf(-cp, bf_lo(xv.w), x1[2]); x1[3] = fmaf(-cp, bf_hi(xv.w), x1[3]);
+        }
+        char *dst = reinterpret_cast<char *>(dX + t0 * C::D);
+        if (tok < tile_nv(t0))
+            *reinterpret_cast<u32x4 *>(dst + static_cast<uint32_t>((tok * C::D + c0 + 8 * q) * 2)) =
+                u32x4{pack2(x0[0], x0[1]), pack2(x0[2], x0[3]), pack2(x1[0], x1[1]), pack2(x1[2], x1[3])};
+    };
+    // ---- projections of the reader's rows, 16 packed hyperplanes x 16 tokens (tile i of 2 PT), and what the chain rule through
+    //      tanh needs of them: tanh z and 1 - tanh^2 z
+    constexpr bool kAllProject = 2 * C::PT == kWaves;       // one tile per wavefront, no roles
+    auto project = [&](int i, int it) __attribute__((always_inline)) {
+        const int lo = opaque(lane), n = lo & 15, q = lo >> 4;      // (addresses rebuilt per tile, not kept in registers)
+        const bf16raw *wrow = wp + (16 * (i >> 1) + n) * C::XS + 8 * q, *xrow = buf_xr(it) + (16 * (i & 1) + n) * C::XS + 8 * q;
+        f32x4 z = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                for (int k = 0; k < 4; ++k)
-                    *reinterpret_cast<u32x2 *>(sg + (lno & 15) * S::SS + 8 * k + 4 * ho) =
-                        u32x2{pack2(acc[4 * k], acc[4 * k + 1]), pack2(acc[4 * k + 2], acc[4 * k + 3])};
-            }
-            const int row = (lo >> 2) + 16 * kk, ch = lo & 3;
-            const u32x4 piece = *reinterpret_cast<const u32x4 *>(sg + (lo >> 2) * S::SS + 8 * ch);
-            if (row < nvalid) *reinterpret_cast<u32x4 *>(dst + static_cast<uint32_t>((row * C::D + 8 * ch) * 2)) = piece;
+        for (int s = 0; s < C::D / 32; ++s) z = mma16(lds128(wrow + 32 * s), lds128(xrow + 32 * s), z);
+        return z;
+    };
+    auto finish_projection = [&](int i, int it, f32x4 z) __attribute__((always_inline)) {
+        const int lo = opaque(lane), tok = 16 * (i & 1) + (lo & 15), quad = 4 * (i >> 1) + (lo >> 4), at = quad * kTile + tok;
+        if (UNIT) z = z * buf_nrm(it)[tok];
+        f32x4 sv, uv;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const float e2 = __expf(-2.0f * fabsf(z[v])), inv = __builtin_amdgcn_rcpf(1.0f + e2), ua = (1.0f - e2) * inv;
+            sv[v] = 4.0f * e2 * inv * inv;
+            uv[v] = z[v] >= 0.f ? ua : -ua;
+        }
+        if (C::L * C::PP % 16 == 0 || quad < S::QUADS) {
+            s2t[at] = sv;
+            if (a.want_dbeta) tht[at] = uv;
+            if (UNIT) zzt[at] = z;
         }
     };
 
+    if (G::T16 && w >= 4) lead(true);       // (R = 16: all along; handing the lead back half way through the tables is slower)
     float dbeta_acc = 0.f;    // this lane's share of the cotangent of beta: sum of (E_t - m (p_t - q_t)) tanh z_t
     for (int it = 0; it < ntiles; ++it) {
         const int64_t t0 = tile_t0(it);
@@ -312,6 +329,8 @@ void grad_kernel(KArgs a, const bf16raw *Xr, const bf16raw *V, const bf16raw *G_
 #pragma unroll
         for (int i = 0; i < G::TPW * kTh; ++i)
             load_table_codes<C>(Mr + t0 * C::LP + (i / kTh) * C::HT + (i % kTh) * 64, roff, ln, rc[i]);      // (16 tokens are 64 floats)
+        f32x4 z_own = {0.f, 0.f, 0.f, 0.f};
+        if (kAllProject) z_own = project(w, it);             // (under the staging and the production)
         if (it + 1 < ntiles) {
             stage_y(it + 1);
             if (it + 2 < ntiles) fetch_y(it + 2);
@@ -321,54 +340,42 @@ void grad_kernel(KArgs a, const bf16raw *Xr, const bf16raw *V, const bf16raw *G_
             produce<C, G::SLOTS, C::PST>(pre_w, slot, ln, a.soft(), ln < nvalid, phw);
             if (it + 1 < ntiles) Sh::load(Mw + tile_t0(it + 1) * C::LP, woff, ln, pre_w);
         }
+        if (kAllProject) {
+            finish_projection(w, it, z_own);
+        } else {
 #pragma unroll
-        for (int pi = 0; pi < 2; ++pi) {
-            // tanh z and 1 - tanh^2 z of 16 packed hyperplanes x 16 tokens
-            if (my_proj[pi] < 0) break;
-            const int pt = my_proj[pi] >> 1, tok = 16 * (my_proj[pi] & 1) + n16, quad = 4 * pt + q16, at = quad * kTile + tok;
-            f32x4 z = {0.f, 0.f, 0.f, 0.f};
-            const bf16raw *wrow = wp + (16 * pt + n16) * C::XS + 8 * q16, *xrow = buf_xr(it) + tok * C::XS + 8 * q16;
-#pragma unroll
-            for (int s = 0; s < C::D / 32; ++s) z = mma16(lds128(wrow + 32 * s), lds128(xrow + 32 * s), z);
-            if (UNIT) z = z * buf_nrm(it)[tok];
-            f32x4 sv, uv;
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const float e2 = __expf(-2.0f * fabsf(z[v])), inv = __builtin_amdgcn_rcpf(1.0f + e2), ua = (1.0f - e2) * inv;
-                sv[v] = 4.0f * e2 * inv * inv;
-                uv[v] = z[v] >= 0.f ? ua : -ua;
-            }
-            if (C::L * C::PP % 16 == 0 || quad < S::QUADS) {
-                s2t[at] = sv;
-                if (a.want_dbeta) tht[at] = uv;
-                if (UNIT) zzt[at] = z;
+            for (int pi = 0; pi < 2; ++pi) {
+                if (my_proj[pi] < 0) break;
+                finish_projection(my_proj[pi], it, project(my_proj[pi], it));
             }
         }
         if (intra && my_tt >= 0) {
             // T^T[b][a] = Yw_b . Yr_a + sw_b sr_a, one of the three 16 x 16 tiles (b, a) that the mask leaves: the two on the
             // diagonal and one off it; both row tiles keep their columns in the same order, which is all a contraction needs
+            const int lo = opaque(lane), n = lo & 15, q = lo >> 4;
             const int bt = my_tt < 2 ? my_tt : (kReverse ? 1 : 0), at = my_tt < 2 ? my_tt : 1 - bt;
-            const bf16raw *brow = buf_yw(it) + (16 * bt + n16) * C::YS + 8 * q16, *arow = buf_yr(it) + (16 * at + n16) * C::XS + 8 * q16;
+            const bf16raw *brow = buf_yw(it) + (16 * bt + n) * C::YS + 8 * q, *arow = buf_yr(it) + (16 * at + n) * C::XS + 8 * q;
             f32x4 tt = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int s = 0; s < C::D / 32; ++s) tt = mma16(lds128(brow + 32 * s), lds128(arow + 32 * s), tt);
-            const int ai = 16 * at + n16;
+            const int ai = 16 * at + n;
             const float sra = buf_sr(it)[ai];
-            const f32x4 swb = *reinterpret_cast<const f32x4 *>(buf_sw(it) + 16 * bt + 4 * q16);
+            const f32x4 swb = *reinterpret_cast<const f32x4 *>(buf_sw(it) + 16 * bt + 4 * q);
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
-                const int b = 16 * bt + 4 * q16 + v;
+                const int b = 16 * bt + 4 * q + v;
                 tt[v] = (kReverse ? b >= ai : b <= ai) ? fmaf(swb[v], sra, tt[v]) : 0.f;
             }
             // R = 64: rows 4 q .. of k-step bt belong to lane half q % 2, words 2 (q / 2) .. of its operand;
             // R = 16: k-slots 4 .. 7 of a lane are its rows of the second tile
-            uint32_t *dst = G::T16 ? reinterpret_cast<uint32_t *>(ttop + 64 * at + lane) + 2 * bt
-                                   : reinterpret_cast<uint32_t *>(ttop + 64 * bt + 32 * (q16 & 1) + ai) + 2 * (q16 >> 1);
+            uint32_t *dst = G::T16 ? reinterpret_cast<uint32_t *>(ttop + 64 * at + lo) + 2 * bt
+                                   : reinterpret_cast<uint32_t *>(ttop + 64 * bt + 32 * (q & 1) + ai) + 2 * (q >> 1);
             *reinterpret_cast<u32x2 *>(dst) = u32x2{pack2(tt[0], tt[1]), pack2(tt[2], tt[3])};
         }
         __syncthreads();
 
         // ================ second half
+        if (!G::T16 && w >= 4) lead(true);
         const bf16raw *yr = buf_yr(it), *yw = buf_yw(it);
         if constexpr (G::T16) {
             // ---- R = 16.  Per table and half of the tokens, lane (n16, q16): cotangents of corners 4 q16 + v of token 16 th + n16.
@@ -397,25 +404,18 @@ void grad_kernel(KArgs a, const bf16raw *Xr, const bf16raw *V, const bf16raw *G_
                     const bf16raw *yrow = yr + tok * C::XS + 8 * q16;
 #pragma unroll
                     for (int j = 0; j < C::D / 32; ++j) dP = mma16(sop[j], lds128(yrow + 32 * j), dP);
-                    float p[4], q[4];
-                    bool mn[4];
-#pragma unroll
-                    for (int t = 0; t < 4; ++t) {
-                        code_masses(c[t], p[t], q[t]);
-                        mn[t] = (__float_as_uint(c[t]) >> 31) != 0;
-                    }
-                    const float F = ((q16 & 1) ? p[2] : q[2]) * ((q16 & 2) ? p[3] : q[3]), F0 = F * q[1], F1 = F * p[1];
-                    const float w0 = F0 * q[0] * dP[0], w1 = F0 * p[0] * dP[1], w2 = F1 * q[0] * dP[2], w3 = F1 * p[0] * dP[3];
-                    const float s01 = w0 + w1, s23 = w2 + w3, m = s01 + s23;
-                    const float Gt = sum_rows4(mn[0] ? w1 + w3 : w0 + w2, mn[1] ? s23 : s01, mn[2] == ((q16 & 1) != 0) ? m : 0.f,
-                                               mn[3] == ((q16 & 2) != 0) ? m : 0.f);
-                    const float mt = sum_rows(m);
+                    float p0, q0, p1, q1;
+                    code_masses(c[0], p0, q0);
+                    code_masses(c[1], p1, q1);
+                    const float m2 = side_mass(c[2], q16 & 1), m3 = side_mass(c[3], q16 >> 1);
+                    // expectations over bit 0, then differences and expectation over bits 0 and 1
+                    const float f0 = fmaf(p0, dP[1], q0 * dP[0]), f1 = fmaf(p0, dP[3], q0 * dP[2]);
+                    const float e0 = fmaf(p1, dP[3] - dP[2], q1 * (dP[1] - dP[0])), e1 = f1 - f0, m = fmaf(p1, f1, q1 * f0);
+                    const float F = m2 * m3, E = sum_rows4(F * e0, F * e1, m3 * ((q16 & 1) ? m : -m), m2 * ((q16 & 2) ? m : -m));
                     // (values, not elements: a selection between array elements is taken for an index and sends the array to memory)
                     const float c0 = c[0], c1 = c[1], c2 = c[2], c3 = c[3];
                     const float ce = (q16 & 2) ? ((q16 & 1) ? +c3 : +c2) : ((q16 & 1) ? +c1 : +c0);
-                    const float small = fabsf(ce), big = 1.0f - small;
-                    const float half = small * (mt - Gt) - big * Gt;
-                    const float du = (__float_as_uint(ce) >> 31) ? -2.f * half : 2.f * half;
+                    const float du = 2.f * minor_major(ce) * E;
                     const int at = ((tl0 + i) * kTile + tok) * 4 + q16;
                     float dzv = a.beta * du * reinterpret_cast<const float *>(s2t)[at];
                     if (UNIT) dzv *= buf_nrm(it)[tok];
@@ -427,14 +427,12 @@ void grad_kernel(KArgs a, const bf16raw *Xr, const bf16raw *V, const bf16raw *G_
                 if (intra) {
                     // ---- statistics += Yw^T . phi_writer
                     const u32x4 pb = lds_tr16(phw + r_own + 16 * i, C::PST, 8 * q16, 8 * q16 + 4, tr_ph, lane);
-                    if (SIDE == 1)
-                        macc[i] += wsum8(pb, *reinterpret_cast<const float4 *>(buf_sw(it) + 8 * q16), *reinterpret_cast<const float4 *>(buf_sw(it) + 8 * q16 + 4));
-                    else macc[i] += sum8(pb);
+                    const f32x4 mp = mma16(SIDE == 1 ? lds128(buf_swp(it) + parts_offset16(kTile, opaque(lane))) : ones16(opaque(lane)), pb, as_parts(macc[i]));
+                    macc[i] = SIDE == 1 ? sum_parts(mp) : mp[0];
 #pragma unroll
                     for (int ct = 0; ct < C::D / 16; ++ct)
                         SU[i][ct] = mma16(lds_tr16(yw, C::YS, 8 * q16, 8 * q16 + 4, 32 * (ct >> 1) + 8 * (lane & 3) + 4 * (ct & 1), lane), pb, SU[i][ct]);
-                    const float tot = sum_rows(macc[i]);
-                    if (q16 == 0) mass[16 * i + n16] = tot;
+                    if (q16 == 0) mass[16 * i + n16] = macc[i];
                 }
             }
             if (UNIT) {
@@ -446,38 +444,34 @@ void grad_kernel(KArgs a, const bf16raw *Xr, const bf16raw *V, const bf16raw *G_
             }
         } else {
             // extra columns as bf16 (hi, lo) pairs: three products hi*hi + hi*lo + lo*hi keep 16 mantissa bits
-            float sr_hi, sr_lo;
-            split_bf16(buf_sr(it)[ln], sr_hi, sr_lo);
+            float sr_hi = 1.f, sr_lo = 0.f;                  // (key side: [V | 1])
+            if (SIDE == 0) split_bf16(buf_sr(it)[ln], sr_hi, sr_lo);
             const u32x4 sr_a = (h == 0) ? u32x4{pack2(sr_hi, sr_hi), pack2(sr_lo, 0.f), 0u, 0u} : u32x4{0u, 0u, 0u, 0u};
 
             // ---- per 32-row tile of this wavefront: cotangent of the reader's assignments, transposed (lane = token,
             //      register v = bucket row r_own + 32 mr + acc_row(v, h)), then straight back through the corner
-            //      softmax (Algorithm 1, step 4) in those registers: with w_c = phi_c dphi_c over the corners c of a
-            //      table, m = sum_c w_c and, per bit t, G_t = sum of w_c over the corners on the bit's MINOR side
-            //      (the side with the smaller mass min(p_t, q_t)).  The cotangent of u_t = tanh z_t is
-            //      beta (E_t - m (p_t - q_t)) with E_t = sum_c v_{c,t} w_c; written as
-            //      +-2 beta (small_t (m - G_t) - big_t G_t) it has no cancellation when the bit is saturated
-            //      (small_t ~ 1e-7 at beta = 8), which the cotangent of beta needs.  Register v of lane half h is corner
-            //      co + 8 (v/4 mod KM) + 4h + v%4 of table tl0 + (32 mr + 8 (v/4)) / R: bits 0,1 come from v, bit 2
-            //      from h, bits 3.. from v, the bits above from the tile.  phi_c is the product over bits of p_t (bit set) or
-            //      q_t (Section 3.3: the corner softmax factorises); the minor side of bit t is -1 where the code is positive.
-            float rec[8];                  // [m, G_0 .. G_{P-1}] of the lane's token (lane partials)
-#pragma unroll
-            for (int t = 0; t < 8; ++t) rec[t] = 0.f;
+            //      softmax (Algorithm 1, step 4) in those registers.  phi_c is the product over the bits of p_t (bit set) or
+            //      q_t (Section 3.3: the corner softmax factorises), so sum_c phi_c dphi_c is linear in every p_t, and with
+            //      E_t the difference of its two sides, the expectation of dphi over the other bits with bit t set minus
+            //      that with bit t clear, the cotangent of u_t = tanh z_t is 2 beta p_t q_t E_t: p_t q_t = small (1 - small)
+            //      is exact to rounding also where a bit is saturated (small ~ 1e-7 at beta = 8), which the cotangent of
+            //      beta needs.  Register v of lane half h is corner 32 mr + 8 (v / 4) + 4 h + v % 4: bits 0, 1 are v % 4, bit 2
+            //      is h, bits 3, 4 are v / 4, bit 5 is mr.  The 32 corners of a lane are contracted once over bits 3 - 5
+            //      (into lows[4]) and once over bits 0, 1 and then bit 5 (into highs[4]), and the E_t are differences of those.  (Sums over the minor side of each bit: 170 vector instructions a tile instead of 120.)
             float p[C::P], q[C::P];
-            bool mn[C::P];                 // the minor side of bit t is the value 1 (else the value 0)
 #pragma unroll
-            for (int t = 0; t < C::P; ++t) {
-                code_masses(rc[0][t], p[t], q[t]);
-                mn[t] = (__float_as_uint(rc[0][t]) >> 31) != 0;
-            }
+            for (int t = 0; t < C::P; ++t) code_masses(rc[0][t], p[t], q[t]);
+            const float wl[4] = {q[0] * q[1], p[0] * q[1], q[0] * p[1], p[0] * p[1]};
+            const float wm[4] = {q[3] * q[4], p[3] * q[4], q[3] * p[4], p[3] * p[4]};
+            float lows[4], highs[4], e5 = 0.f;      // (bit 5 is contracted, and its difference taken, as the tiles come)
 #pragma unroll
             for (int mr = 0; mr < G::MTG; ++mr) {
                 f32x16 dP;
+                if (mr == 1 && w >= 4) lead(false);
                 {
                     // extra column first: sr_a * (A or dA)[r] with the masses before this tile
                     float m_hi, m_lo;
-                    split_bf16(sum_halves(macc[mr]), m_hi, m_lo);
+                    split_bf16(macc[mr], m_hi, m_lo);
                     const u32x4 mb = (h == 0) ? u32x4{pack2(m_hi, m_lo), pack2(m_hi, 0.f), 0u, 0u} : u32x4{0u, 0u, 0u, 0u};
                     dP = mma(mb, sr_a, f32x16{0});
                 }
@@ -497,46 +491,39 @@ void grad_kernel(KArgs a, const bf16raw *Xr, const bf16raw *V, const bf16raw *G_
                         }
                     }
                 }
-                {
-                    const int co = 32 * mr;            // first corner of the tile in the table
-                    float F = h ? p[2] : q[2];
 #pragma unroll
-                    for (int t = 5; t < C::P; ++t) F *= ((co >> t) & 1) ? p[t] : q[t];
-                    const float Fl[4] = {F * q[0] * q[1], F * p[0] * q[1], F * q[0] * p[1], F * p[0] * p[1]};
-                    float m = 0.f, G0 = 0.f, G1 = 0.f, Gm[2] = {0.f, 0.f};
+                for (int k = 0; k < 4; ++k) {
+                    const float wh = wm[k] * (mr ? p[C::P - 1] : q[C::P - 1]);
+                    float x = wl[0] * dP[4 * k];
 #pragma unroll
-                    for (int k = 0; k < 4; ++k) {
-                        const float mid = ((k & 1) ? p[3] : q[3]) * ((k & 2) ? p[4] : q[4]);
-                        const float w0 = Fl[0] * dP[4 * k], w1 = Fl[1] * dP[4 * k + 1], w2 = Fl[2] * dP[4 * k + 2], w3 = Fl[3] * dP[4 * k + 3];
-                        const float s01 = w0 + w1, s23 = w2 + w3;
-                        const float c = mid * (s01 + s23);
-                        G0 = fmaf(mid, mn[0] ? w1 + w3 : w0 + w2, G0);
-                        G1 = fmaf(mid, mn[1] ? s23 : s01, G1);
-                        m += c;
+                    for (int v = 1; v < 4; ++v) x = fmaf(wl[v], dP[4 * k + v], x);
+                    highs[k] = mr ? fmaf(p[C::P - 1], x, highs[k]) : q[C::P - 1] * x;
+                    e5 = fmaf(mr ? wm[k] : -wm[k], x, e5);
 #pragma unroll
-                        for (int b = 0; b < 2; ++b) Gm[b] += (mn[3 + b] == (((k >> b) & 1) != 0)) ? c : 0.f;
-                    }
-                    // lane partials; bit 2 is the lane half, the bits above the tile's are uniform
-                    rec[0] += m;
-                    rec[1] += G0;
-                    rec[2] += G1;
-                    rec[3] += (mn[2] == (h != 0)) ? m : 0.f;
-#pragma unroll
-                    for (int b = 0; b < 2; ++b) rec[4 + b] += Gm[b];
-#pragma unroll
-                    for (int t = 5; t < C::P; ++t) rec[1 + t] += (mn[t] == (((co >> t) & 1) != 0)) ? m : 0.f;
+                    for (int v = 0; v < 4; ++v) lows[v] = (mr || k) ? fmaf(wh, dP[4 * k + v], lows[v]) : wh * dP[v];
                 }
             }
-            // ---- finish per (token, table): du_t = +-2 beta (small_t (m - G_t) - big_t G_t),  dz_t = du_t (1 - tanh^2 z_t);
-            //      the two lane halves hold the two values of bit 2: add them up; lane half h' takes the quad 4h' .. 4h'+3
+            // E_t of this lane half, the mass of its value of bit 2 included (for bit 2 itself: the signed half)
+            float E[8];
+            {
+                const float F = h ? p[2] : q[2];
+                E[0] = F * fmaf(p[1], lows[3] - lows[2], q[1] * (lows[1] - lows[0]));
+                E[1] = F * fmaf(p[0], lows[3] - lows[1], q[0] * (lows[2] - lows[0]));
+                const float g0 = fmaf(p[3], highs[1], q[3] * highs[0]), g1 = fmaf(p[3], highs[3], q[3] * highs[2]), m = fmaf(p[4], g1, q[4] * g0);
+                E[2] = h ? m : -m;
+                E[3] = F * fmaf(p[4], highs[3] - highs[2], q[4] * (highs[1] - highs[0]));
+                E[4] = F * (g1 - g0);
+                E[5] = F * e5;
+                E[6] = E[7] = 0.f;
+            }
+            // ---- finish per (token, table): du_t = 2 beta p_t q_t E_t,  dz_t = du_t (1 - tanh^2 z_t);
+            //      the two lane halves hold the two values of bit 2: add them up; lane half h' gets the quad 4h' .. 4h'+3
             // unit-norm option: dz is the cotangent of W xhat, so the reader's row gets dx = (g - xhat (xhat . g)) / |x| with
             // g = W^T dz and xhat . g = z . dz; dz is scaled by 1 / |x| here and this lane's share of z . dz is summed from the
             // bf16 values the matrix product below will see (which keeps dx orthogonal to x to fp32 accuracy)
             float radial = 0.f;
             {
                 const float rs = UNIT ? buf_nrm(it)[ln] : 1.f;
-#pragma unroll
-                for (int t = 0; t <= C::P; ++t) rec[t] = sum_halves(rec[t]);
                 {
                     const int quad = (C::PP / 4) * tl0 + h, at = quad * kTile + ln;
                     const f32x4 s2 = s2t[at];
@@ -545,12 +532,9 @@ void grad_kernel(KArgs a, const bf16raw *Xr, const bf16raw *V, const bf16raw *G_
                     float dzv[4];
 #pragma unroll
                     for (int e = 0; e < 4; ++e) {
-                        // slots beyond the table's hyperplanes: all mass on one side, no minor side, du = 0
-                        const float ce = h ? (4 + e < C::P ? rc[0][4 + e < C::P ? 4 + e : 0] : 0.f) : rc[0][e];
-                        const float Gt = h ? (4 + e < C::P ? rec[4 + e < C::P ? 5 + e : 0] : 0.f) : rec[1 + e];
-                        const float small = fabsf(ce), big = 1.0f - small;
-                        const float half = small * (rec[0] - Gt) - big * Gt;
-                        const float du = (__float_as_uint(ce) >> 31) ? -2.f * half : 2.f * half;    // cotangent of u_t up to the factor beta
+                        // slots beyond the table's hyperplanes: all mass on one side, du = 0
+                        const float pq = h ? (4 + e < C::P ? p[4 + e < C::P ? 4 + e : 0] * q[4 + e < C::P ? 4 + e : 0] : 0.f) : p[e] * q[e];
+                        const float du = 2.f * pq * sum_halves2(E[e], E[4 + e]);       // cotangent of u_t up to the factor beta
                         dzv[e] = a.beta * du * s2[e] * rs;
                         if (a.want_dbeta && ln < nvalid) dbeta_acc = fmaf(du, uu[e], dbeta_acc);   // (not the copies past the end)
                     }
@@ -571,20 +555,18 @@ void grad_kernel(KArgs a, const bf16raw *Xr, const bf16raw *V, const bf16raw *G_
             }
             // ---- statistics += Yw^T . phi_writer
             if (intra) {
+                const int lo = opaque(lane), swp_off = parts_offset32(kTile, lo);
 #pragma unroll
                 for (int s = 0; s < 2; ++s) {
-                    float4 g0 = {1.f, 1.f, 1.f, 1.f}, g1 = g0;          // SIDE 0: the extra column of [V | 1] is one
-                    if (SIDE == 1) {
-                        g0 = *reinterpret_cast<const float4 *>(buf_sw(it) + 16 * s + 8 * h);
-                        g1 = *reinterpret_cast<const float4 *>(buf_sw(it) + 16 * s + 8 * h + 4);
-                    }
+                    const u32x4 gw = SIDE == 1 ? lds128(buf_swp(it) + swp_off + 16 * s) : ones32(lo);   // (SIDE 0: [V | 1])
                     u32x4 ay[C::NT];
 #pragma unroll
                     for (int mtc = 0; mtc < C::NT; ++mtc) ay[mtc] = lds_tr_plain<true>(yw, C::YS, 16 * s, 32 * mtc, ln, h);
 #pragma unroll
                     for (int mr = 0; mr < G::MTG; ++mr) {
                         const u32x4 bp = lds_tr_plain<true>(phw, C::PST, 16 * s, r_own + 32 * mr, ln, h);
-                        macc[mr] += SIDE == 1 ? wsum8(bp, g0, g1) : sum8(bp);
+                        const f32x4 mp = mma16(gw, bp, as_parts(macc[mr]));
+                        macc[mr] = SIDE == 1 ? sum_parts(mp) : mp[0];
 #pragma unroll
                         for (int mtc = 0; mtc < C::NT; ++mtc) ST[mr][mtc] = mma(ay[mtc], bp, ST[mr][mtc]);
                     }

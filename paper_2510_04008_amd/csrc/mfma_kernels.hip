@@ -131,8 +131,8 @@ struct TotalsLds {
     static constexpr int TT = 64;
     static constexpr int y = 0;                                         // [64][YS] accumulated rows
     static constexpr int ph = y + TT * C::YS * 2;                       // [64][PST] assignments
-    static constexpr int ge = ph + TT * C::PST * 2;                     // [64] fp32
-    static constexpr int total = ge + TT * 4;
+    static constexpr int ge = ph + TT * C::PST * 2;                     // [kParts][64] bf16
+    static constexpr int total = ge + kParts * TT * 2;
     static_assert(total <= 160 * 1024, "LDS budget");
 };
 
@@ -153,7 +153,7 @@ void totals_kernel(KArgs a, const float *M, const bf16raw *Y, const bf16raw *Oin
     extern __shared__ __attribute__((aligned(256))) unsigned char lds[];
     bf16raw *ys = reinterpret_cast<bf16raw *>(lds + S::y);
     bf16raw *ph = reinterpret_cast<bf16raw *>(lds + S::ph);
-    float *ge_lds = reinterpret_cast<float *>(lds + S::ge);
+    bf16raw *ge_lds = reinterpret_cast<bf16raw *>(lds + S::ge);
 
     const int seg = blockIdx.x, bh = blockIdx.y;
     const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, ln = lane & 31, h = lane >> 5;
@@ -166,10 +166,11 @@ void totals_kernel(KArgs a, const float *M, const bf16raw *Y, const bf16raw *Oin
     float *st = a.state + (static_cast<size_t>(bh) * a.nseg + seg) * C::STATE;
 
     f32x16 Sacc[C::MT][C::NTW];
-    float macc[C::MT];
+    f32x4 macc[C::MA];                 // extra column of row tiles cg, cg + CG, ...: lane n < 32 <-> row, weight parts
+#pragma unroll
+    for (int i = 0; i < C::MA; ++i) macc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int mt = 0; mt < C::MT; ++mt) {
-        macc[mt] = 0.f;
 #pragma unroll
         for (int nt = 0; nt < C::NTW; ++nt) Sacc[mt][nt] = f32x16{0};
     }
@@ -181,6 +182,7 @@ void totals_kernel(KArgs a, const float *M, const bf16raw *Y, const bf16raw *Oin
     // this wavefront's tokens of a step (its half) and its lanes' share of the tables
     const int half = w / 4, slot = 2 * (w % 4) + h, row = half * kTile + ln;
     const uint32_t lane_off = table_offset<C>(Share<C, 8>::table(slot, 0), ln);
+    const bf16raw *ge_lane = ge_lds + parts_offset32(TT, lane);
     typename Share<C, 8>::Regs pre_m;
     RowChunks<C, TT> pre_y;
     CotChunks<C, TT> pre_c;
@@ -198,9 +200,13 @@ void totals_kernel(KArgs a, const float *M, const bf16raw *Y, const bf16raw *Oin
     for (int it = 0; it < nsteps; ++it) {
         const int64_t t0 = t_begin + static_cast<int64_t>(it) * TT;
         const int nvalid = step_nv(t0);
-        if (QG) store_cotangent<C, TT, C::YS>(pre_c, ys, ge_lds, a.L_real, nvalid, Gout, ge_out, t0);
-        else store_rows<C, TT, C::YS>(pre_y, ys);
         produce<C, 8, C::PST>(pre_m, slot, row, a.soft(), row < nvalid, ph);
+        if (QG) {
+            wait_loads();
+            store_cotangent<C, TT, C::YS>(pre_c, ys, ge_lds, a.L_real, nvalid, Gout, ge_out, t0);
+        } else {
+            store_rows<C, TT, C::YS>(pre_y, ys);
+        }
         if (it + 1 < nsteps) fetch(it + 1);
         __syncthreads();
 #pragma unroll
@@ -208,16 +214,12 @@ void totals_kernel(KArgs a, const float *M, const bf16raw *Y, const bf16raw *Oin
             u32x4 by[C::NTW];
 #pragma unroll
             for (int nt = 0; nt < C::NTW; ++nt) by[nt] = lds_tr_plain(ys, C::YS, 16 * s, c_own + 32 * nt, ln, h);
-            float4 g0 = {1.f, 1.f, 1.f, 1.f}, g1 = g0;
-            if (QG) {
-                g0 = *reinterpret_cast<const float4 *>(ge_lds + 16 * s + 8 * h);
-                g1 = *reinterpret_cast<const float4 *>(ge_lds + 16 * s + 8 * h + 4);
-            }
+            const u32x4 gw = QG ? lds128(ge_lane + 16 * s) : ones32(lane);
 #pragma unroll
             for (int mt = 0; mt < C::MT; ++mt) {
                 const u32x4 ap = lds_tr_plain<true>(ph, C::PST, 16 * s, r_own + 32 * mt, ln, h);
                 if (mass_owner<C>(mt, cg))      // the extra column (bucket mass, or its cotangent): shared out over the column groups
-                    macc[mt] += wsum8(ap, g0, g1);
+                    macc[mt / C::CG] = mma16(gw, ap, macc[mt / C::CG]);
 #pragma unroll
                 for (int nt = 0; nt < C::NTW; ++nt) Sacc[mt][nt] = mma(ap, by[nt], Sacc[mt][nt]);
             }
@@ -232,8 +234,7 @@ void totals_kernel(KArgs a, const float *M, const bf16raw *Y, const bf16raw *Oin
             for (int v = 0; v < 16; ++v)
                 st[state_b<C>(r_own + 32 * mt + acc_row(v, h), c_own + 32 * nt + ln)] = Sacc[mt][nt][v];
         }
-        const float tot = macc[mt] + __shfl_xor(macc[mt], 32, 64);
-        if (mass_owner<C>(mt, cg) && h == 0) st[state_a<C>(r_own + 32 * mt + ln)] = tot;
+        if (mass_owner<C>(mt, cg) && h == 0) st[state_a<C>(r_own + 32 * mt + ln)] = sum_parts(macc[mt / C::CG]);
     }
 }
 
@@ -282,7 +283,7 @@ void stream_kernel(KArgs a, const float *Mr, const float *Mw, const bf16raw *Y, 
     const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, ln = lane & 31, h = lane >> 5;
     const int rg = w % C::RG, cg = w / C::RG;
     const int r_own = rg * C::LRW, c_own = cg * C::DW;
-    const bool intra = NC ? false : a.causal != 0;    // causal: the tile's own keys take part
+    const bool intra = NC ? false : (C::STREAM_WAVES_PER_SIMD == 4 ? a.causal != 0 : true);
 
     const size_t base = static_cast<size_t>(bh) * a.N * C::D;
     const size_t mbase = static_cast<size_t>(bh) * ((a.N + kTile - 1) / kTile) * (kTile * C::LP);
@@ -293,7 +294,9 @@ void stream_kernel(KArgs a, const float *Mr, const float *Mw, const bf16raw *Y, 
     const float *st = a.state + (static_cast<size_t>(bh) * a.nseg + (NC ? 0 : (a.causal ? seg : 0))) * C::STATE;
 
     f32x16 Sacc[C::MT][C::NTW];
-    float macc[C::MT];                 // bucket masses (tiles mt % 2 == cg): per-half partial sums, lane n <-> row
+    float macc[C::MA];                 // bucket masses of row tiles cg, cg + CG, ... (balances the work): lane n < 32 <-> row
+#pragma unroll
+    for (int i = 0; i < C::MA; ++i) macc[i] = 0.f;
 #pragma unroll
     for (int mt = 0; mt < C::MT; ++mt) {
 #pragma unroll
@@ -302,9 +305,20 @@ void stream_kernel(KArgs a, const float *Mr, const float *Mw, const bf16raw *Y, 
             for (int v = 0; v < 16; ++v)
                 Sacc[mt][nt][v] = st[state_b<C>(r_own + 32 * mt + acc_row(v, h), c_own + 32 * nt + ln)];
         }
-        // the bucket masses of tile mt are carried by column group mt % 2 (balances the vector work)
-        macc[mt] = (MODE == kForward && mass_owner<C>(mt, cg) && h == 0) ? st[state_a<C>(r_own + 32 * mt + ln)] : 0.f;
-        if (MODE == kForward && mass_owner<C>(mt, cg) && h == 0) mass[r_own + 32 * mt + il(ln)] = macc[mt];
+    }
+    if (MODE == kForward) {
+        // (behind the loads of the statistics, all of which are in flight together)
+#pragma unroll
+        for (int i = 0; i < C::MA; ++i) {
+            const int mt = i * C::CG + cg;
+            if (mt < C::MT) macc[i] = st[state_a<C>(r_own + 32 * mt + ln)];
+        }
+#pragma unroll
+        for (int i = 0; i < C::MA; ++i) {
+            const int mt = i * C::CG + cg;
+            macc[i] = h == 0 ? macc[i] : 0.f;
+            if (mt < C::MT && h == 0) mass[r_own + 32 * mt + il(ln)] = macc[i];
+        }
     }
 
     const int64_t t_begin = seg * a.seg_len;
@@ -369,8 +383,8 @@ void stream_kernel(KArgs a, const float *Mr, const float *Mw, const bf16raw *Y, 
     __syncthreads();        // the bucket masses are in place
     for (int it = 0; it < ntiles; ++it) {
         const int nvalid = tile_nv(tile_t0(it));
-        // ---- first half: the previous tile's output, this tile's rows and assignments -> LDS
-        if (it > 0) epilogue(it - 1);
+        // ---- first half: this tile's rows and assignments -> LDS, then the previous tile's output (its stores are issued when
+        //      nothing loaded is waited for any more; in front of the production every tile waited for them to complete)
         if (intra) store_rows<C, kTile, C::YS>(pre_y, ytile);
         if (side == 0) {
             const float dnl = produce<C, 8, C::PS>(pre_m, slot, ln, a.soft(), true, phr, MODE == kForward ? mass : nullptr);
@@ -378,8 +392,10 @@ void stream_kernel(KArgs a, const float *Mr, const float *Mw, const bf16raw *Y, 
         } else if (intra) {
             produce<C, 8, C::PS>(pre_m, slot, ln, a.soft(), ln < nvalid, phw);
         }
+        if (it > 0) epilogue(it - 1);
         __syncthreads();
 
+        if (side == 1) lead(true);
         // ---- contraction with the register-resident statistics (own bucket rows x own columns)
         f32x16 out[C::NTW];     // read-out, transposed: lane = reader token, register v = column acc_row(v, h) of the tile
         f32x16 sct = {0};       // in-tile kernel values, transposed: row = writer token, lane = reader token
@@ -401,6 +417,7 @@ void stream_kernel(KArgs a, const float *Mr, const float *Mw, const bf16raw *Y, 
                 RACE_SCHED_FENCE();
             }
         }
+        if (side == 1) lead(false);
         if (intra) {
             // mask (writer token j = row, reader token i = lane), row sums, and (mask o kernel) . Y
 #pragma unroll
@@ -429,7 +446,7 @@ void stream_kernel(KArgs a, const float *Mr, const float *Mw, const bf16raw *Y, 
 #pragma unroll
                 for (int mt = 0; mt < C::MT; ++mt) {
                     const u32x4 ap = lds_tr_plain<true>(phw, C::PS, 16 * s, r_own + 32 * mt, ln, h);
-                    if (MODE == kForward && mass_owner<C>(mt, cg)) macc[mt] += sum8(ap);
+                    if (MODE == kForward && mass_owner<C>(mt, cg)) macc[mt / C::CG] = mma16(ones32(opaque(lane)), ap, as_parts(macc[mt / C::CG]))[0];
 #pragma unroll
                     for (int nt = 0; nt < C::NTW; ++nt) Sacc[mt][nt] = mma(ap, by[nt], Sacc[mt][nt]);
                     RACE_SCHED_FENCE();
@@ -455,9 +472,7 @@ void stream_kernel(KArgs a, const float *Mr, const float *Mw, const bf16raw *Y, 
             // masses after this tile, for the next tile's read-out
 #pragma unroll
             for (int mt = 0; mt < C::MT; ++mt) {
-                if (!mass_owner<C>(mt, cg)) continue;
-                const float tot = macc[mt] + __shfl_xor(macc[mt], 32, 64);
-                if (h == 0) mass[r_own + 32 * mt + il(ln)] = tot;
+                if (mass_owner<C>(mt, cg) && h == 0) mass[r_own + 32 * mt + il(ln)] = macc[mt / C::CG];
             }
         }
         __syncthreads();
