@@ -12,8 +12,10 @@
 //
 // What bounds it: at the sizes it serves (small layers) the number of dependent launches and the latency of one
 // workgroup, hence three launches forward (totals with the hashing, scan, output), three backward (totals, scan, all
-// three gradients), and tiles of 16 tokens until they fill the chip.  Measured forward + backward against a
-// token-at-a-time kernel per table (B = H = 1, N = 1024, d = 64, L = P = 4, fp32, not causal): 337 -> 42 us.
+// three gradients), tiles of 16 tokens until they fill the chip, and all loads of a tile requested together.  Measured
+// forward + backward (B = H = 1, N = 1024, d = 64, L = P = 4, fp32, not causal): 337 us with a token-at-a-time kernel per
+// table, 41 with the loads of a tile under conditions, one trip to memory after the other, 35 now (B = 2, H = 4, N = 2003, causal:
+// 98 -> 82; bf16, B = 2, H = 8, N = 1024, d = 32: 75 -> 61; B = 2, H = 4, N = 3501, d = 128, L = 6, P = 5: 485 -> 381).
 //
 // Matrix operand layouts (lane = 16 q + n): A: row n, k = q; B: column n, k = q; C/D: column n, rows 4 q + v in register v.
 // Four consecutive k-steps take k = 4 q + v, v = 0..3, so that an operand whose k axis runs along a row of LDS is one
@@ -34,13 +36,30 @@ namespace {
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(4))) double f64x4;
 
-constexpr int kThreads = 256, kWaves = 4;
+constexpr int kThreads = 256;
 constexpr int KB = 64;          // bucket rows per block
 constexpr int PHS = KB + 4;     // row stride of an assignment tile
 constexpr int CSS = 33;         // row stride of the hashed rows of a block (at most 32 hyperplanes: R <= 2 gives 32 tables)
 constexpr int DZS = 36;         // row stride of the dz tiles
 
 struct bf16_t { uint16_t bits; };
+
+// The thread's number, hidden from the optimiser: addresses and conditions that derive from it are worked out where they are
+// used.  (Hoisted out of the loops over tiles and blocks they took 200 scalar and 100 vector registers of the gradient kernel.)
+__device__ __forceinline__ int thread_id()
+{
+    int t = threadIdx.x;
+    asm volatile("" : "+v"(t));
+    return t & (kThreads - 1);
+}
+// the same for a value that is the same in all lanes
+__device__ __forceinline__ int uniform(int x)
+{
+    asm volatile("" : "+s"(x));
+    return x;
+}
+// this wavefront's number, as the uniform value that it is
+__device__ __forceinline__ int wave_id() { return __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); }
 
 __device__ __forceinline__ float load1(const float *p) { return *p; }
 __device__ __forceinline__ float load1(const bf16_t *p) { return __uint_as_float(static_cast<uint32_t>(p->bits) << 16); }
@@ -84,6 +103,16 @@ struct GArgs {
                                         // states: scratch of the forward pass and of dQ's; dK's and dV's carries its own on in place)
 };
 
+// The same arguments with their sizes hidden from the optimiser (see thread_id()): a loop body that starts with this works out
+// its conditions itself.
+__device__ __forceinline__ GArgs fresh(GArgs a)
+{
+    a.d = uniform(a.d); a.dp = uniform(a.dp); a.L = uniform(a.L); a.P = uniform(a.P); a.R = uniform(a.R); a.LP = uniform(a.LP);
+    a.LR = uniform(a.LR); a.TB = uniform(a.TB); a.bpt = uniform(a.bpt); a.PB = uniform(a.PB); a.causal = uniform(a.causal);
+    a.unit = uniform(a.unit);
+    return a;
+}
+
 // first table and hyperplane of a block; tables of the block that exist
 __device__ __forceinline__ int block_table(const GArgs &a, int b) { return a.bpt > 1 ? b / a.bpt : b * a.TB; }
 __device__ __forceinline__ int block_rtiles(const GArgs &a, int b)
@@ -118,55 +147,108 @@ __device__ __forceinline__ float mass_of(float c, int bit)      // mass on the +
     return (minor1 == (bit != 0)) ? fabsf(c) : 1.0f - fabsf(c);
 }
 
-// C rows of X from token row0 on into xs [C][XS] as fp32; rows >= nv and columns >= d are zeros.
-template <typename T, int RT>
-__device__ __forceinline__ void load_rows(const GArgs &a, const T *X, size_t row0, int nv, float *xs, int XS)
+// Loads of a tile.  All of them are unconditional, at addresses clamped into the tensors, and go to registers first (fetch_*)
+// and to LDS later (put_*): what a tile needs is requested together and costs one trip to memory.  (A load under a condition
+// is a branch, and the compiler waits for the loads before it: the passes spent three to five such trips of about a
+// microsecond one after the other, 3.5 us before the first product of the gradients.)
+// 16 / RT threads share a row of the tile; thread `sub` of them takes columns 4 (sub + k 16 / RT) ..
+template <int RT>
+struct RowThread {
+    static constexpr int TPR = kThreads / (16 * RT);
+    int row, sub;
+    __device__ RowThread()
+    {
+        const int t = thread_id();
+        row = t / TPR;
+        sub = t % TPR;
+    }
+    __device__ int column(int k) const { return 4 * (sub + k * TPR); }
+};
+template <int RT, int NCT>
+struct RowRegs { f32x4 v[RT * NCT]; };
+template <typename T, int RT, int NCT>
+__device__ __forceinline__ void fetch_rows(const GArgs &a, const T *X, size_t row0, int nv, RowRegs<RT, NCT> &r)
 {
-    const int cpr = a.dp >> 2;
-    for (int i = threadIdx.x; i < 16 * RT * cpr; i += kThreads) {
-        const int row = i / cpr, c = (i - row * cpr) * 4;
-        f32x4 v = {0.f, 0.f, 0.f, 0.f};
-        if (row < nv && c < a.d) v = load4(X + (row0 + row) * a.d + c);
-        *reinterpret_cast<f32x4 *>(xs + row * XS + c) = v;
+    const RowThread<RT> t;
+    const T *src = X + (row0 + (t.row < nv ? t.row : nv - 1)) * a.d;
+#pragma unroll
+    for (int k = 0; k < RT * NCT; ++k) r.v[k] = load4(src + (t.column(k) < a.d ? t.column(k) : 0));
+}
+// ... into xs [C][XS]; rows >= nv and columns >= d are zeros
+template <int RT, int NCT>
+__device__ __forceinline__ void put_rows(const GArgs &a, const RowRegs<RT, NCT> &r, int nv, float *xs, int XS)
+{
+    const RowThread<RT> t;
+#pragma unroll
+    for (int k = 0; k < RT * NCT; ++k) {
+        const int c = t.column(k);
+        if (c < a.dp) *reinterpret_cast<f32x4 *>(xs + t.row * XS + c) = (t.row < nv && c < a.d) ? r.v[k] : f32x4{0.f, 0.f, 0.f, 0.f};
     }
 }
 
 // Read-out cotangents g = dO / e (e = L Den) into gs and ge[row] = -(g . O): the cotangents of the un-averaged numerator
-// and normaliser of Algorithm 1, step 7.  16 / RT threads per row.
-template <typename T, int RT>
-__device__ __forceinline__ void load_cotangents(const GArgs &a, const T *dO, const T *O, const float *den, size_t row0, int nv,
-                                                float *gs, int XS, float *ge)
+// and normaliser of Algorithm 1, step 7.
+template <int RT, int NCT>
+struct CotRegs {
+    RowRegs<RT, NCT> g, o;
+    float den;
+};
+template <typename T, int RT, int NCT>
+__device__ __forceinline__ void fetch_cotangents(const GArgs &a, const T *dO, const T *O, const float *den, size_t row0, int nv, CotRegs<RT, NCT> &r)
 {
-    constexpr int TPR = kThreads / (16 * RT);
-    const int row = threadIdx.x / TPR, sub = threadIdx.x % TPR;
+    const RowThread<RT> t;
+    r.den = den[row0 + (t.row < nv ? t.row : nv - 1)];
+    fetch_rows<T, RT, NCT>(a, O, row0, nv, r.o);
+    fetch_rows<T, RT, NCT>(a, dO, row0, nv, r.g);
+}
+template <int RT, int NCT>
+__device__ __forceinline__ void put_cotangents(const GArgs &a, const CotRegs<RT, NCT> &r, int nv, float *gs, int XS, float *ge)
+{
+    const RowThread<RT> t;
     // (Den = 0: the forward pass leaves O = 0 there, a constant; so does an underflow of every bucket mass the query sees)
-    const float e = row < nv ? den[row0 + row] * static_cast<float>(a.L) : 0.f, inv = e != 0.f ? 1.0f / e : 0.f;
+    const float e = t.row < nv ? r.den * static_cast<float>(a.L) : 0.f, inv = e != 0.f ? 1.0f / e : 0.f;
     float dot = 0.f;
-    for (int c = 4 * sub; c < a.dp; c += 4 * TPR) {
+#pragma unroll
+    for (int k = 0; k < RT * NCT; ++k) {
+        const int c = t.column(k);
         f32x4 g = {0.f, 0.f, 0.f, 0.f};
-        if (row < nv && c < a.d) {
-            const f32x4 o = load4(O + (row0 + row) * a.d + c);
-            g = load4(dO + (row0 + row) * a.d + c) * inv;
+        if (t.row < nv && c < a.d) {
+            const f32x4 o = r.o.v[k];
+            g = r.g.v[k] * inv;
             dot = fmaf(g.x, o.x, fmaf(g.y, o.y, fmaf(g.z, o.z, fmaf(g.w, o.w, dot))));
         }
-        *reinterpret_cast<f32x4 *>(gs + row * XS + c) = g;
+        if (c < a.dp) *reinterpret_cast<f32x4 *>(gs + t.row * XS + c) = g;
     }
 #pragma unroll
-    for (int m = 1; m < TPR; m <<= 1) dot += __shfl_xor(dot, m, 64);
-    if (sub == 0) ge[row] = -dot;
+    for (int m = 1; m < RowThread<RT>::TPR; m <<= 1) dot += __shfl_xor(dot, m, 64);
+    if (t.sub == 0) ge[t.row] = -dot;
 }
 
-// Hashed rows of block b from the workspace into cs [C][CSS]
+// Hashed rows (or projections) of block b from the workspace, into cs [C][CSS].  One row per 32 (or 8) consecutive threads: the
+// hyperplanes of a block are contiguous.
 template <int RT>
-__device__ __forceinline__ void load_codes(const GArgs &a, const float *Cx, size_t row0, int nv, int b, float *cs)
+struct CodeRegs { float v[2 * RT]; };
+struct CodeThread {
+    int t, pl0, np, sh;
+    __device__ CodeThread(const GArgs &a, int b) : t(thread_id()), pl0(block_table(a, b) * a.P), np(a.LP - pl0 < a.PB ? a.LP - pl0 : a.PB), sh(a.PB > 8 ? 5 : 3) {}
+    __device__ int row(int k) const { return (t + k * kThreads) >> sh; }
+    __device__ int plane() const { return t & ((1 << sh) - 1); }
+};
+template <int RT>
+__device__ __forceinline__ void fetch_codes(const GArgs &a, const float *Cx, size_t row0, int nv, int b, CodeRegs<RT> &r)
 {
-    const int pl0 = block_table(a, b) * a.P, left = a.LP - pl0, np = left < a.PB ? left : a.PB;
-    // one row per 32 (or 8) consecutive threads: the hyperplanes of a block are contiguous
-    const int w = a.PB > 8 ? 32 : 8, sh = a.PB > 8 ? 5 : 3;
-    for (int i = threadIdx.x; i < 16 * RT * w; i += kThreads) {
-        const int row = i >> sh, p = i & (w - 1);
-        if (p < np && row < nv) cs[row * CSS + p] = Cx[(row0 + row) * a.LP + pl0 + p];
-    }
+    const CodeThread t(a, b);
+    const float *src = Cx + row0 * a.LP + t.pl0 + (t.plane() < t.np ? t.plane() : 0);
+#pragma unroll
+    for (int k = 0; k < 2 * RT; ++k) r.v[k] = src[static_cast<size_t>(t.row(k) < nv ? t.row(k) : nv - 1) * a.LP];
+}
+template <int RT>
+__device__ __forceinline__ void put_codes(const GArgs &a, const CodeRegs<RT> &r, int nv, int b, float *cs)
+{
+    const CodeThread t(a, b);
+#pragma unroll
+    for (int k = 0; k < 2 * RT; ++k)
+        if (t.plane() < t.np && t.row(k) < nv) cs[t.row(k) * CSS + t.plane()] = r.v[k];
 }
 
 // Assignments of block b as fp32 rows ph [C][PHS] from the hashed rows: phi_r = prod_t mass_t(bit t of r); eight corners
@@ -175,7 +257,7 @@ template <int RT>
 __device__ __forceinline__ void build_phi(const GArgs &a, int b, const float *cs, int nv, float *ph)
 {
     const int tb0 = block_table(a, b);
-    for (int g = threadIdx.x; g < 16 * RT * (KB / 8); g += kThreads) {
+    for (int g = thread_id(); g < 16 * RT * (KB / 8); g += kThreads) {
         const int tok = g >> 3, k0 = (g & 7) * 8, lr = b * KB + k0;
         float f[8];
         if (a.P >= 3) {
@@ -215,7 +297,7 @@ __device__ __forceinline__ void build_phi(const GArgs &a, int b, const float *cs
 template <int RT, int NCT>
 __device__ __forceinline__ void accumulate(const GArgs &a, const float *ph, const float *ys, int XS, int nrt, f32x4 (&acc)[4][NCT])
 {
-    const int lane = threadIdx.x & 63, n = lane & 15, q = lane >> 4, w = threadIdx.x >> 6;
+    const int lane = thread_id() & 63, n = lane & 15, q = lane >> 4, w = wave_id();
 #pragma unroll
     for (int jt = 0; jt < RT; ++jt) {
 #pragma unroll
@@ -240,7 +322,7 @@ __device__ __forceinline__ void accumulate(const GArgs &a, const float *ph, cons
 template <int NCT>
 __device__ __forceinline__ void store_state(const GArgs &a, float *S, int b, int nrt, const f32x4 (&acc)[4][NCT])
 {
-    const int lane = threadIdx.x & 63, n = lane & 15, q = lane >> 4, w = threadIdx.x >> 6;
+    const int lane = thread_id() & 63, n = lane & 15, q = lane >> 4, w = wave_id();
 #pragma unroll
     for (int rt = 0; rt < 4; ++rt) {
         if (rt >= nrt) break;
@@ -255,21 +337,37 @@ __device__ __forceinline__ void store_state(const GArgs &a, float *S, int b, int
         }
     }
 }
-// The block's statistics as tiles in the C/D layout (= B operands of a product over bucket rows)
+// The block's statistics as tiles in the C/D layout (= B operands of a product over bucket rows).  Rows and columns that do not
+// exist repeat the last ones: their assignments are zeros and their results go nowhere, but a zero does not silence an infinity,
+// so clear_rows() has to come before a product over bucket rows (row tiles beyond nrt take no part in any).
 template <int NCT>
-__device__ __forceinline__ void load_state(const GArgs &a, const float *S, int b, int nrt, f32x4 (&acc)[4][NCT])
+__device__ __forceinline__ void load_state(const GArgs &a, const float *S, int b, f32x4 (&acc)[4][NCT])
 {
-    const int lane = threadIdx.x & 63, n = lane & 15, q = lane >> 4, w = threadIdx.x >> 6;
+    const int lane = thread_id() & 63, n = lane & 15, q = lane >> 4, w = wave_id(), last = a.LR - 1 - b * KB;
+    const float *Sb = S + static_cast<size_t>(b) * KB * a.d;
 #pragma unroll
     for (int rt = 0; rt < 4; ++rt) {
 #pragma unroll
         for (int ci = 0; ci < NCT; ++ci) {
             const int c = 16 * (w + 4 * ci) + n;
 #pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const int r = b * KB + 16 * rt + 4 * q + v;
-                acc[rt][ci][v] = (rt < nrt && c < a.d && r < a.LR) ? S[static_cast<size_t>(r) * a.d + c] : 0.f;
-            }
+            for (int v = 0; v < 4; ++v)
+                acc[rt][ci][v] = Sb[static_cast<uint32_t>(min(16 * rt + 4 * q + v, last) * a.d + min(c, a.d - 1))];
+        }
+    }
+}
+template <int NCT>
+__device__ __forceinline__ void clear_rows(const GArgs &a, int b, f32x4 (&acc)[4][NCT])
+{
+    if ((a.LR & 15) == 0) return;                       // (only tables of fewer than 16 corners leave part of a row tile)
+    const int q = (thread_id() & 63) >> 4;
+#pragma unroll
+    for (int rt = 0; rt < 4; ++rt) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const bool in = b * KB + 16 * rt + 4 * q + v < a.LR;
+#pragma unroll
+            for (int ci = 0; ci < NCT; ++ci) acc[rt][ci][v] = in ? acc[rt][ci][v] : 0.f;
         }
     }
 }
@@ -277,7 +375,7 @@ __device__ __forceinline__ void load_state(const GArgs &a, const float *S, int b
 template <int RT, int NCT>
 __device__ __forceinline__ void read_out(const float *ph, int nrt, const f32x4 (&S)[4][NCT], f32x4 (&out)[RT][NCT])
 {
-    const int lane = threadIdx.x & 63, n = lane & 15, q = lane >> 4;
+    const int lane = thread_id() & 63, n = lane & 15, q = lane >> 4;
 #pragma unroll
     for (int rt = 0; rt < 4; ++rt) {
         if (rt >= nrt) break;
@@ -299,7 +397,7 @@ __device__ __forceinline__ void read_out(const float *ph, int nrt, const f32x4 (
 template <int RT, int NCT, bool TR>
 __device__ __forceinline__ void apply_tile(const GArgs &a, const float *M, int MS, const float *ys, int XS, f32x4 (&out)[RT][NCT])
 {
-    const int lane = threadIdx.x & 63, n = lane & 15, q = lane >> 4, w = threadIdx.x >> 6;
+    const int lane = thread_id() & 63, n = lane & 15, q = lane >> 4, w = wave_id();
     bool finite = true;
 #pragma unroll
     for (int jt = 0; jt < RT; ++jt) {
@@ -350,7 +448,7 @@ __device__ __forceinline__ void apply_tile(const GArgs &a, const float *M, int M
 template <int RT>
 __device__ __forceinline__ void tile_kernel(const float *phq, const float *phk, int nrt, f32x4 &kk)
 {
-    const int lane = threadIdx.x & 63, n = lane & 15, q = lane >> 4, w = threadIdx.x >> 6;
+    const int lane = thread_id() & 63, n = lane & 15, q = lane >> 4, w = wave_id();
     const int ti = RT == 2 ? w >> 1 : 0, tj = RT == 2 ? w & 1 : 0;
     if (ti < tj) return;                              // wholly above the diagonal
 #pragma unroll
@@ -368,7 +466,7 @@ template <int RT>
 __device__ __forceinline__ void store_tile_kernel(const f32x4 &kk, float *KK, float *part)
 {
     constexpr int MS = 16 * RT + 4;
-    const int lane = threadIdx.x & 63, n = lane & 15, q = lane >> 4, w = threadIdx.x >> 6;
+    const int lane = thread_id() & 63, n = lane & 15, q = lane >> 4, w = wave_id();
     if (RT == 1) {
 #pragma unroll
         for (int v = 0; v < 4; ++v) part[w * 256 + (4 * q + v) * 16 + n] = kk[v];
@@ -401,38 +499,82 @@ __device__ __forceinline__ float row_scale(const GArgs &a, const float *xs, int 
     return 1.0f / fmaxf(sqrtf(ss), kUnitFloor);
 }
 // Hashed rows of a tile on np <= 32 hyperplanes (W: the first one's row) into cs [C][CSS]; those of its first nst rows and the
-// projections also to Cx and Zx (token row0 and hyperplane pl0 on).  z = X W^T: 16 tokens x 16 hyperplanes per wavefront and
-// step, contraction over d, accumulated in fp64 (products of fp32 are exact there): a bit's mass multiplies an error of z by
-// 2 beta, and the projection is a small share of the work.
-template <int RT>
-__device__ __forceinline__ void hash_block(const GArgs &a, const float *W, int np, const float *xs, int XS, const float *inv, float *cs,
-                                           float *Cx, float *Zx, size_t row0, int pl0, int nst)
+// projections also to Cx and Zx (token row0 and hyperplane pl0 on).  z = X W^T: 16 tokens x 16 hyperplanes are a tile, and the
+// waves share tiles and the contraction over d: its k-steps go round four partial sums, a wavefront forms one, two or all of
+// them, and they are added in pairs, the same for every split.  Accumulated in fp64 (products of fp32 are exact there): a bit's mass
+// multiplies an error of z by 2 beta, and the projection is a small share of the work.  Then one (token, hyperplane) per
+// thread.  (A tile per wavefront left three of four idle at L = P = 4 and gave the busy one four evaluations a lane.)
+// zp: LDS, 4 x 256 doubles.  Two barriers: before the partial sums are read, and none behind (cs is not visible yet).
+template <int NCT>
+struct PlaneRegs { f32x4 v[4 * NCT]; };         // this lane's share of its hyperplane's row, k-steps of its wavefront's parts
+struct HashSplit {
+    int tiles, parts, tile, part0;              // tiles of a pass over the hyperplanes; partial sums of this wavefront: part0 ..
+    template <int RT>
+    __device__ static HashSplit of(int np)
+    {
+        HashSplit h;
+        const int w = wave_id();
+        h.tiles = RT * ((np + 15) >> 4);        // 1, 2 or 4
+        h.parts = h.tiles;
+        h.tile = w & (h.tiles - 1);
+        h.part0 = (w / h.tiles) * h.parts;
+        return h;
+    }
+};
+template <int RT, int NCT>
+__device__ __forceinline__ void fetch_planes(const GArgs &a, const float *W, int np, PlaneRegs<NCT> &r)
 {
-    const int lane = threadIdx.x & 63, n = lane & 15, q = lane >> 4, w = threadIdx.x >> 6;
-    const int npj = (np + 15) >> 4;
-    for (int tl = w; tl < RT * npj; tl += kWaves) {
-        const int ti = tl % RT, pl = 16 * (tl / RT) + n;
-        const bool real = pl < np;
-        const float *wr = W + static_cast<size_t>(real ? pl : 0) * a.d;
+    const HashSplit h = HashSplit::of<RT>(np);
+    const int lane = thread_id() & 63, n = lane & 15, q = lane >> 4, pl = 16 * (h.tile / RT) + n;
+    const float *wr = W + static_cast<size_t>(pl < np ? pl : 0) * a.d;
+#pragma unroll
+    for (int p = 0; p < 4; ++p) {
+#pragma unroll
+        for (int j = 0; j < NCT; ++j) {
+            const int c = 16 * (4 * j + h.part0 + p) + 4 * q;
+            if (p < h.parts) r.v[p * NCT + j] = *reinterpret_cast<const f32x4 *>(wr + (c < a.d ? c : 0));
+        }
+    }
+}
+template <int RT, int NCT>
+__device__ __forceinline__ void hash_block(const GArgs &a, const PlaneRegs<NCT> &wr, int np, const float *xs, int XS, const float *inv, double *zp,
+                                           float *cs, float *Cx, float *Zx, size_t row0, int pl0, int nst)
+{
+    const HashSplit h = HashSplit::of<RT>(np);
+    const int lane = thread_id() & 63, n = lane & 15, q = lane >> 4;
+    const float *xrow = xs + (16 * (h.tile % RT) + n) * XS + 4 * q;
+    f64x4 sum = {0., 0., 0., 0.}, pair = sum;
+#pragma unroll
+    for (int p = 0; p < 4; ++p) {
+        if (p >= h.parts) break;
         f64x4 z0 = {0., 0., 0., 0.}, z1 = z0;
-        for (int c = 4 * q; c < a.dp; c += 16) {
-            const f32x4 x = lds4(xs + (16 * ti + n) * XS + c);
-            f32x4 y = {0.f, 0.f, 0.f, 0.f};
-            if (c < a.d) y = *reinterpret_cast<const f32x4 *>(wr + c);
+#pragma unroll
+        for (int j = 0; j < NCT; ++j) {
+            const int c0 = 16 * (4 * j + h.part0 + p);
+            if (c0 >= a.dp) break;
+            const f32x4 x = lds4(xrow + c0), y = wr.v[p * NCT + j];          // (columns beyond d are zeros in xs)
             z0 = mfma64(x[0], y[0], z0);
             z1 = mfma64(x[1], y[1], z1);
             z0 = mfma64(x[2], y[2], z0);
             z1 = mfma64(x[3], y[3], z1);
         }
-        const f64x4 z = z0 + z1;
+        if (p & 1) sum = sum + (pair + (z0 + z1));
+        else pair = z0 + z1;
+    }
+    if (h.parts == 1) sum = pair;
 #pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            const int tok = 16 * ti + q + 4 * v;
-            float zz = static_cast<float>(z[v]);
-            if (a.unit) zz *= inv[tok];
-            const float c = code(zz, a.beta);
-            if (real) cs[tok * CSS + pl] = c;
-            if (real && tok < nst) {
+    for (int v = 0; v < 4; ++v) zp[wave_id() * 256 + (q + 4 * v) * 16 + n] = sum[v];
+    __syncthreads();
+    for (int t = 0; t < h.tiles; ++t) {
+        const int tok = 16 * (t % RT) + (threadIdx.x >> 4), pl = 16 * (t / RT) + (threadIdx.x & 15);
+        const double *z4 = zp + t * 256 + threadIdx.x;
+        const double zd = h.tiles == 1 ? (z4[0] + z4[256]) + (z4[512] + z4[768]) : (h.tiles == 2 ? z4[0] + z4[512] : z4[0]);
+        float zz = static_cast<float>(zd);
+        if (a.unit) zz *= inv[tok];
+        const float c = code(zz, a.beta);
+        if (pl < np) {
+            cs[tok * CSS + pl] = c;
+            if (tok < nst) {
                 Cx[(row0 + tok) * a.LP + pl0 + pl] = c;
                 Zx[(row0 + tok) * a.LP + pl0 + pl] = zz;
             }
@@ -447,14 +589,16 @@ __device__ __forceinline__ void hash_block(const GArgs &a, const float *W, int n
 // SIDE 1: the statistics of (phi_Q, [g | g_e]) of the backward pass from the hashed queries.
 template <int RT>
 struct TotalsLds {
+    // (the assignments' place also takes the partial projections, 4 x 256 doubles)
+    static constexpr int PH = 16 * RT * PHS > 2048 ? 16 * RT * PHS : 2048;
     float *ys, *xs, *ph, *cs, *ge, *inv;
-    static size_t floats(int dp, int side) { return static_cast<size_t>(16 * RT) * ((side == 0 ? 2 : 1) * (dp + 4) + PHS + CSS + 2) + 16; }
+    static size_t floats(int dp, int side) { return static_cast<size_t>(16 * RT) * ((side == 0 ? 2 : 1) * (dp + 4) + CSS + 2) + PH + 16; }
     __device__ TotalsLds(float *p, int dp, int side)
     {
         constexpr int C = 16 * RT;
         ys = p; p += C * (dp + 4);
         xs = p; if (side == 0) p += C * (dp + 4);
-        ph = p; p += C * PHS;
+        ph = p; p += PH;
         ge = p; p += C;
         inv = p; p += C;
         cs = p;
@@ -484,16 +628,21 @@ __global__ __launch_bounds__(kThreads, 2) void generic_totals(GArgs a, const T *
         for (int ci = 0; ci < NCT; ++ci) acc[rt][ci] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
     float mass = 0.f;                                       // threads 0..63: extra column of bucket row tid
+    PlaneRegs<NCT> wr;
+    if (SIDE == 0) fetch_planes<RT, NCT>(a, W, np, wr);
     const int64_t seg0 = static_cast<int64_t>(seg) * a.tps * C;
     for (int it = 0; it < a.tps; ++it) {
         const int64_t t0 = seg0 + it * C;
         if (t0 >= a.N) break;
         const int nv = a.N - t0 < C ? static_cast<int>(a.N - t0) : C;
         const size_t row0 = static_cast<size_t>(bh) * a.N + t0;
-        if (it > 0) __syncthreads();                        // the previous tile's readers are done
         if (SIDE == 0) {
-            load_rows<T, RT>(a, query ? Xq : Xk, row0, nv, s.xs, XS);
-            if (!query) load_rows<T, RT>(a, Y, row0, nv, s.ys, XS);
+            RowRegs<RT, NCT> x, y;
+            fetch_rows<T, RT, NCT>(a, query ? Xq : Xk, row0, nv, x);
+            if (!query) fetch_rows<T, RT, NCT>(a, Y, row0, nv, y);
+            if (it > 0) __syncthreads();                    // the previous tile's readers are done
+            put_rows<RT, NCT>(a, x, nv, s.xs, XS);
+            if (!query) put_rows<RT, NCT>(a, y, nv, s.ys, XS);
             __syncthreads();
             if (a.unit) {
                 const float inv = row_scale<RT>(a, s.xs, XS);
@@ -502,13 +651,18 @@ __global__ __launch_bounds__(kThreads, 2) void generic_totals(GArgs a, const T *
                     s.inv[row] = inv;
                     if (b == 0 && row < nv) a.nrm[(query ? 0 : static_cast<size_t>(a.BH) * a.N) + row0 + row] = inv;
                 }
-                __syncthreads();
             }
-            hash_block<RT>(a, W, np, s.xs, XS, s.inv, s.cs, query ? a.Cq : a.Ck, query ? a.Zq : a.Zk, row0, pl0, writes ? nv : 0);
+            hash_block<RT, NCT>(a, wr, np, s.xs, XS, s.inv, reinterpret_cast<double *>(s.ph), s.cs, query ? a.Cq : a.Ck, query ? a.Zq : a.Zk, row0,
+                                pl0, writes ? nv : 0);
             if (query) continue;
         } else {
-            load_codes<RT>(a, a.Cq, row0, nv, b, s.cs);
-            load_cotangents<T, RT>(a, Y, O, den, row0, nv, s.ys, XS, s.ge);
+            CodeRegs<RT> c;
+            CotRegs<RT, NCT> g;
+            fetch_codes<RT>(a, a.Cq, row0, nv, b, c);
+            fetch_cotangents<T, RT, NCT>(a, Y, O, den, row0, nv, g);
+            if (it > 0) __syncthreads();
+            put_codes<RT>(a, c, nv, b, s.cs);
+            put_cotangents<RT, NCT>(a, g, nv, s.ys, XS, s.ge);
         }
         __syncthreads();
         build_phi<RT>(a, b, s.cs, nv, s.ph);
@@ -546,18 +700,20 @@ struct FwdLds {
 };
 
 template <typename T, int RT, int NCT>
-__global__ __launch_bounds__(kThreads, 2) void generic_forward(GArgs a, const T *V, const float *state, T *Out, float *den_out)
+__global__ __launch_bounds__(kThreads, 2) void generic_forward(GArgs args, const T *V, const float *state, T *Out, float *den_out)
 {
+    const GArgs &a = args;
     extern __shared__ __attribute__((aligned(16))) float lds[];
     constexpr int C = 16 * RT, MS = C + 4, TPR = kThreads / C;
     FwdLds<RT> s(lds, a.dp);
     const int XS = a.dp + 4;
-    const int seg = blockIdx.x, bh = blockIdx.y, tid = threadIdx.x, w = tid >> 6, lane = tid & 63, n = lane & 15, q = lane >> 4;
+    const int seg = blockIdx.x, bh = blockIdx.y, tid = threadIdx.x, w = wave_id(), lane = tid & 63, n = lane & 15, q = lane >> 4;
     const float *S0 = state + (static_cast<size_t>(bh) * a.nseg + (a.causal ? seg : 0)) * a.ST;
     float *Sc = a.carry + (static_cast<size_t>(bh) * a.nseg + seg) * a.ST;
     const int64_t seg0 = static_cast<int64_t>(seg) * a.tps * C;
     const int tok_r = tid / TPR, sub = tid % TPR;                // row and share of the normaliser sums
-    for (int it = 0; it < a.tps; ++it) {
+    for (int it = 0; it < args.tps; ++it) {
+        const GArgs a = fresh(args);
         const int64_t t0 = seg0 + it * C;
         if (t0 >= a.N) break;
         const int nv = a.N - t0 < C ? static_cast<int>(a.N - t0) : C;
@@ -571,20 +727,37 @@ __global__ __launch_bounds__(kThreads, 2) void generic_forward(GArgs a, const T 
             for (int ci = 0; ci < NCT; ++ci) out[ti][ci] = f32x4{0.f, 0.f, 0.f, 0.f};
         }
         float dn = 0.f;
-        __syncthreads();
-        if (a.causal) load_rows<T, RT>(a, V, row0, nv, s.vs, XS);
-        for (int b = 0; b < a.nblk; ++b) {
+        // the first block's operands and the rows of V are requested together, a following block's next to the products of the one
+        // in front of it
+        f32x4 sb[4][NCT];
+        CodeRegs<RT> cq, ck;
+        float am;
+        auto fetch_block = [&](int b) __attribute__((always_inline)) {
+            fetch_codes<RT>(a, a.Cq, row0, nv, b, cq);
+            if (a.causal) fetch_codes<RT>(a, a.Ck, row0, nv, b, ck);
+            const bool mrow = tid < KB && b * KB + tid < a.LR;
+            const float x = S[static_cast<size_t>(a.LR) * a.d + (mrow ? b * KB + tid : 0)];
+            am = mrow ? x : 0.f;
+        };
+        RowRegs<RT, NCT> vr;
+        fetch_block(0);
+        if (a.causal) fetch_rows<T, RT, NCT>(a, V, row0, nv, vr);
+        load_state<NCT>(a, S, 0, sb);
+        if (it > 0) __syncthreads();
+        if (a.causal) put_rows<RT, NCT>(a, vr, nv, s.vs, XS);
+        for (int b = 0; b < args.nblk; ++b) {
+            const GArgs a = fresh(args);
             const int nrt = block_rtiles(a, b);
-            f32x4 sb[4][NCT];
-            load_state<NCT>(a, S, b, nrt, sb);                   // in flight while the assignments are built
-            const float am = (tid < KB && b * KB + tid < a.LR) ? S[static_cast<size_t>(a.LR) * a.d + b * KB + tid] : 0.f;
-            load_codes<RT>(a, a.Cq, row0, nv, b, s.csq);
-            if (a.causal) load_codes<RT>(a, a.Ck, row0, nv, b, s.csk);
+            const float am_b = am;
+            put_codes<RT>(a, cq, nv, b, s.csq);
+            if (a.causal) put_codes<RT>(a, ck, nv, b, s.csk);
+            if (tid < KB) s.am[tid] = am;
+            if (b + 1 < a.nblk) fetch_block(b + 1);
             __syncthreads();
             build_phi<RT>(a, b, s.csq, nv, s.phq);
             if (a.causal) build_phi<RT>(a, b, s.csk, nv, s.phk);
-            if (tid < KB) s.am[tid] = am;
             __syncthreads();
+            clear_rows<NCT>(a, b, sb);
             read_out<RT, NCT>(s.phq, nrt, sb, out);
 #pragma unroll
             for (int k = 0; k < KB / TPR; ++k) dn = fmaf(s.phq[tok_r * PHS + sub + k * TPR], s.am[sub + k * TPR], dn);
@@ -593,11 +766,12 @@ __global__ __launch_bounds__(kThreads, 2) void generic_forward(GArgs a, const T 
                 accumulate<RT, NCT>(a, s.phk, s.vs, XS, nrt, sb);
                 store_state<NCT>(a, Sc, b, nrt, sb);
                 if (tid < KB && b * KB + tid < a.LR) {
-                    float m = am;
+                    float m = am_b;
                     for (int j = 0; j < C; ++j) m += s.phk[j * PHS + tid];
                     Sc[static_cast<size_t>(a.LR) * a.d + b * KB + tid] = m;
                 }
             }
+            if (b + 1 < a.nblk) load_state<NCT>(a, S, b + 1, sb);
             __syncthreads();
         }
         if (a.causal) {
@@ -641,10 +815,10 @@ __global__ __launch_bounds__(kThreads, 2) void generic_forward(GArgs a, const T 
 // launch each, in this order (sides: bit 0 = dQ, bit 1 = dK and dV): dS is carried where it stands, and S where dS has been.
 template <int RT>
 struct GradLds {
-    float *gs, *vs, *phq, *phk, *tt, *kk, *csq, *csk, *dz, *am, *dam, *ge, *rec, *rad, *part;
+    float *gs, *vs, *phq, *phk, *tt, *kk, *csq, *csk, *zsq, *zsk, *dz, *am, *dam, *ge, *rec, *rad, *part;
     static size_t floats(int dp)
     {
-        return static_cast<size_t>(16 * RT) * (2 * (dp + 4) + 2 * PHS + 2 * (16 * RT + 4) + 2 * CSS + 2 * DZS + 1 + 18 + 2) + 2 * KB +
+        return static_cast<size_t>(16 * RT) * (2 * (dp + 4) + 2 * PHS + 2 * (16 * RT + 4) + 4 * CSS + 2 * DZS + 1 + 18 + 2) + 2 * KB +
                (RT == 1 ? 1024 : 0) + 16;
     }
     __device__ GradLds(float *p, int dp)
@@ -664,22 +838,28 @@ struct GradLds {
         rec = p; p += 2 * C * 9;        // (side, token): m and G_t of a table that spans several blocks
         rad = p; p += 2 * C;
         csq = p; p += C * CSS;
-        csk = p;
+        csk = p; p += C * CSS;
+        zsq = p; p += C * CSS;
+        zsk = p;
     }
 };
 
-// (One workgroup per CU where the accumulators need more than 256 registers; LDS allows no more there either.)
-template <typename T, int RT, int NCT>
-__global__ __launch_bounds__(kThreads, RT * NCT > 2 ? 1 : 2) void generic_grads(GArgs a, int sides, const T *Q, const T *K, const T *V, const T *O,
+// CARRY: causal segments of several tiles.
+// (One workgroup per CU where the accumulators need more than 256 registers; LDS allows no more there either.  Three where 168
+// registers do: four, with 21 spilled, measured the same.)
+template <typename T, int RT, int NCT, bool CARRY>
+__global__ __launch_bounds__(kThreads, RT * NCT > 2 ? 1 : (RT * NCT == 2 ? 2 : 3)) void generic_grads(GArgs args, int sides, const T *Q, const T *K, const T *V, const T *O,
                                                              const float *den, const T *dO, const float *stateS, const float *stateD,
                                                              T *dQ, T *dK, T *dV, float *dbeta_part)
 {
+    const GArgs &a = args;
     extern __shared__ __attribute__((aligned(16))) float lds[];
     constexpr int C = 16 * RT, MS = C + 4, NCH = 2 * RT;
+    constexpr bool PRE = RT * NCT <= 2;                      // registers for the rows of the statistics a block ahead
     GradLds<RT> s(lds, a.dp);
     const int XS = a.dp + 4;
-    const int seg = blockIdx.x, bh = blockIdx.y, tid = threadIdx.x, w = tid >> 6, lane = tid & 63, n = lane & 15, q = lane >> 4;
-    const bool do_q = sides & 1, do_kv = sides & 2;
+    const int seg = blockIdx.x, bh = blockIdx.y, w = wave_id();
+    const bool do_q = CARRY ? (sides & 1) != 0 : true, do_kv = CARRY ? (sides & 2) != 0 : true;
     const size_t slot = (static_cast<size_t>(bh) * a.nseg + (a.causal ? seg : 0)) * a.ST;
     float *Sc = a.carry + (static_cast<size_t>(bh) * a.nseg + seg) * a.ST;
     const float *W = a.W + static_cast<size_t>(bh % a.H) * a.LP * a.d;
@@ -690,15 +870,17 @@ __global__ __launch_bounds__(kThreads, RT * NCT > 2 ? 1 : 2) void generic_grads(
     const int cside = w >> 1, ct = RT == 2 ? w & 1 : 0, cr0 = RT == 2 ? 0 : 2 * (w & 1);
     const bool cdo = cside == 0 ? do_q : do_kv;
     float dbeta_acc = 0.f;
-    for (int i = tid; i < 2 * C * DZS; i += kThreads) s.dz[i] = 0.f;          // padding hyperplanes stay zero
+    for (int i = threadIdx.x; i < 2 * C * DZS; i += kThreads) s.dz[i] = 0.f;          // padding hyperplanes stay zero
     for (int it = 0; it < ntiles; ++it) {
-        const int tile = (do_q || ntiles == 1) ? it : ntiles - 1 - it;
+        const GArgs a = fresh(args);
+        const int tid = thread_id(), n = tid & 15, q = (tid & 63) >> 4;
+        const int tile = (!CARRY || do_q) ? it : ntiles - 1 - it;
         const int64_t t0 = seg0 + static_cast<int64_t>(tile) * C;
         const int nv = a.N - t0 < C ? static_cast<int>(a.N - t0) : C;
         const size_t row0 = static_cast<size_t>(bh) * a.N + t0;
-        const bool more = a.causal && it + 1 < ntiles;
-        const float *S = (a.causal && it > 0 && do_q) ? Sc : stateS + slot;
-        const float *D = (a.causal && it > 0 && do_kv) ? Sc : stateD + slot;
+        const bool more = CARRY && it + 1 < ntiles;
+        const float *S = (CARRY && it > 0 && do_q) ? Sc : stateS + slot;
+        const float *D = (CARRY && it > 0 && do_kv) ? Sc : stateD + slot;
         f32x4 aq[RT][NCT], ak[RT][NCT], av[RT][NCT], kk = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int ti = 0; ti < RT; ++ti) {
@@ -706,9 +888,49 @@ __global__ __launch_bounds__(kThreads, RT * NCT > 2 ? 1 : 2) void generic_grads(
             for (int ci = 0; ci < NCT; ++ci) aq[ti][ci] = ak[ti][ci] = av[ti][ci] = f32x4{0.f, 0.f, 0.f, 0.f};
         }
         float radial = 0.f;                                     // threads (side, token) < 2 C: sum of z . dz (unit-norm option)
-        __syncthreads();
-        load_cotangents<T, RT>(a, dO, O, den, row0, nv, s.gs, XS, s.ge);
-        load_rows<T, RT>(a, V, row0, nv, s.vs, XS);
+        // the first block's operands and the tile's rows are requested together, a following block's as soon as the registers are free
+        CodeRegs<RT> cq, ck, zq, zk;
+        f32x4 db[4][NCT], st[PRE ? 4 * NCT : 1][NCH];
+        float am, dam;
+        auto fetch_block = [&](int b) __attribute__((always_inline)) {
+            fetch_codes<RT>(a, a.Cq, row0, nv, b, cq);
+            fetch_codes<RT>(a, a.Ck, row0, nv, b, ck);
+            const bool mrow = tid < KB && b * KB + tid < a.LR;
+            const size_t at = static_cast<size_t>(a.LR) * a.d + (mrow ? b * KB + tid : 0);
+            const float x = S[at], y = D[at];
+            am = mrow ? x : 0.f;
+            dam = mrow ? y : 0.f;
+            fetch_codes<RT>(a, a.Zq, row0, nv, b, zq);
+            fetch_codes<RT>(a, a.Zk, row0, nv, b, zk);
+        };
+        // rows of the statistics for dphi (contraction over columns) of this wavefront's side: k-step j, row tile cr0 + i
+        // (rows that do not exist repeat the last one: their share of dphi is not used; columns beyond d are cleared where they are used)
+        const float *St = cside == 0 ? S : D;
+        auto state_row = [&](int b, int j, int i) __attribute__((always_inline)) {
+            const int r = min(16 * (cr0 + i) + n, a.LR - 1 - b * KB), c = min(16 * j + 4 * q, a.d - 4);
+            return *reinterpret_cast<const f32x4 *>(St + static_cast<size_t>(b) * KB * a.d + static_cast<uint32_t>(r * a.d + c));
+        };
+        auto fetch_state_rows = [&](int b) __attribute__((always_inline)) {
+            if constexpr (PRE) {
+#pragma unroll
+                for (int j = 0; j < 4 * NCT; ++j) {
+#pragma unroll
+                    for (int i = 0; i < NCH; ++i) st[j][i] = state_row(b, j, i);
+                }
+            }
+        };
+        {
+            CotRegs<RT, NCT> g;
+            RowRegs<RT, NCT> v;
+            fetch_cotangents<T, RT, NCT>(a, dO, O, den, row0, nv, g);
+            fetch_rows<T, RT, NCT>(a, V, row0, nv, v);
+            fetch_block(0);
+            fetch_state_rows(0);
+            if (do_kv) load_state<NCT>(a, D, 0, db);
+            __syncthreads();
+            put_cotangents<RT, NCT>(a, g, nv, s.gs, XS, s.ge);
+            put_rows<RT, NCT>(a, v, nv, s.vs, XS);
+        }
         __syncthreads();
         if (a.causal) {
             // T: C = 32: one 16 x 16 tile per wavefront; C = 16: wavefront 0
@@ -733,20 +955,22 @@ __global__ __launch_bounds__(kThreads, RT * NCT > 2 ? 1 : 2) void generic_grads(
             }
         }
         for (int b = 0; b < a.nblk; ++b) {
+            const GArgs a = fresh(args);
+            const int tid = thread_id(), n = tid & 15, q = (tid & 63) >> 4;
             const int nrt = block_rtiles(a, b), tb0 = block_table(a, b), pl0 = tb0 * a.P;
             const bool first = a.bpt == 1 || b % a.bpt == 0, last = a.bpt == 1 || b % a.bpt == a.bpt - 1;
             const size_t aoff = static_cast<size_t>(a.LR) * a.d + b * KB;
-            load_codes<RT>(a, a.Cq, row0, nv, b, s.csq);
-            load_codes<RT>(a, a.Ck, row0, nv, b, s.csk);
             const bool mrow = tid < KB && b * KB + tid < a.LR;
-            const float am = mrow && do_q ? S[aoff + tid] : 0.f, dam = mrow && do_kv ? D[aoff + tid] : 0.f;
-            // the statistics for dV (contraction over bucket rows) are on their way while the assignments are built
-            f32x4 db[4][NCT];
-            if (do_kv) load_state<NCT>(a, D, b, nrt, db);
+            const float am_b = am, dam_b = dam;
+            put_codes<RT>(a, cq, nv, b, s.csq);
+            put_codes<RT>(a, ck, nv, b, s.csk);
+            put_codes<RT>(a, zq, nv, b, s.zsq);
+            put_codes<RT>(a, zk, nv, b, s.zsk);
+            if (tid < KB) { s.am[tid] = am; s.dam[tid] = dam; }
+            if (b + 1 < a.nblk) fetch_block(b + 1);
             __syncthreads();
             build_phi<RT>(a, b, s.csq, nv, s.phq);
             build_phi<RT>(a, b, s.csk, nv, s.phk);
-            if (tid < KB) { s.am[tid] = am; s.dam[tid] = dam; }
             __syncthreads();
             // ---- dphi, transposed (rows = bucket rows, columns = tokens), then w = phi dphi
             f32x4 dp[NCH];
@@ -754,19 +978,21 @@ __global__ __launch_bounds__(kThreads, RT * NCT > 2 ? 1 : 2) void generic_grads(
             for (int i = 0; i < NCH; ++i) dp[i] = f32x4{0.f, 0.f, 0.f, 0.f};
             if (cdo) {
                 const float *ys = cside == 0 ? s.gs : s.vs;
-                const float *St = (cside == 0 ? S : D) + static_cast<size_t>(b * KB) * a.d;
-                const int rleft = a.LR - b * KB;
-                for (int c = 4 * q; c < a.dp; c += 16) {
-                    const f32x4 y = lds4(ys + (16 * ct + n) * XS + c);
+#pragma unroll
+                for (int j = 0; j < 4 * NCT; ++j) {
+                    if (16 * j >= a.dp) break;
+                    const f32x4 y = lds4(ys + (16 * ct + n) * XS + 16 * j + 4 * q);
 #pragma unroll
                     for (int i = 0; i < NCH; ++i) {
-                        const int r = 16 * (cr0 + i) + n;
-                        f32x4 x = {0.f, 0.f, 0.f, 0.f};
-                        if (r < rleft && c < a.d) x = *reinterpret_cast<const f32x4 *>(St + static_cast<size_t>(r) * a.d + c);
+                        f32x4 x;
+                        if constexpr (PRE) x = st[j][i];
+                        else x = state_row(b, j, i);
+                        if (16 * j + 16 > a.d) x = 16 * j + 4 * q < a.d ? x : f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
                         for (int v = 0; v < 4; ++v) dp[i] = mfma(x[v], y[v], dp[i]);
                     }
                 }
+                if (b + 1 < a.nblk) fetch_state_rows(b + 1);
                 if (a.causal) {
                     const float *po = cside == 0 ? s.phk : s.phq;
 #pragma unroll
@@ -792,12 +1018,13 @@ __global__ __launch_bounds__(kThreads, RT * NCT > 2 ? 1 : 2) void generic_grads(
                 }
             }
             if (do_kv) {
+                clear_rows<NCT>(a, b, db);
                 read_out<RT, NCT>(s.phk, nrt, db, av);
                 if (a.causal) tile_kernel<RT>(s.phq, s.phk, nrt, kk);
             }
             if (more) {                                         // the statistics behind this tile, for the next one
                 f32x4 sb[4][NCT];
-                if (do_q) load_state<NCT>(a, S, b, nrt, sb);
+                if (do_q) load_state<NCT>(a, S, b, sb);
                 else {
 #pragma unroll
                     for (int rt = 0; rt < 4; ++rt) {
@@ -809,11 +1036,12 @@ __global__ __launch_bounds__(kThreads, RT * NCT > 2 ? 1 : 2) void generic_grads(
                 __syncthreads();                                // S and the carry may be the same memory: all of it has been read
                 store_state<NCT>(a, Sc, b, nrt, sb);
                 if (mrow) {
-                    float m = do_q ? am : dam;
+                    float m = do_q ? am_b : dam_b;
                     for (int j = 0; j < C; ++j) m += do_q ? s.phk[j * PHS + tid] : s.phq[j * PHS + tid] * s.ge[j];
                     Sc[aoff + tid] = m;
                 }
             }
+            if (do_kv && b + 1 < a.nblk) load_state<NCT>(a, D, b + 1, db);
             __syncthreads();
             if (cdo) {
                 float *ps = (cside == 0 ? s.phq : s.phk) + (16 * ct + n) * PHS;
@@ -826,16 +1054,16 @@ __global__ __launch_bounds__(kThreads, RT * NCT > 2 ? 1 : 2) void generic_grads(
             // ---- back through the corner softmax: an item is (side, table, token, share of CP corners); the shares of a
             //      token's table are neighbouring lanes
             {
-                const int Rb = a.R < KB ? a.R : KB, CP = Rb < 8 * RT ? Rb : 8 * RT, NS = Rb / CP;
-                const int lns = __builtin_ctz(NS), lcp = __builtin_ctz(CP);
-                const int items = 2 * a.TB * C * NS;
-                for (int ix = tid; ix < items; ix += kThreads) {
+                const int items = 2 * a.TB * C * (((a.R < KB ? a.R : KB) + 8 * RT - 1) / (8 * RT));
+                for (int ix = thread_id(); ix < items; ix += kThreads) {
+                    const int P = uniform(a.P), R = 1 << P, Rb = R < KB ? R : KB, CP = Rb < 8 * RT ? Rb : 8 * RT;
+                    const int lcp = __builtin_ctz(CP), lns = __builtin_ctz(Rb) - lcp, NS = 1 << lns;
                     const int sub = ix & (NS - 1), tok = (ix >> lns) & (C - 1), st = (ix >> lns) / C;
                     const int side = st & 1, tl = st >> 1, table = tb0 + tl;
                     if (side == 0 ? !do_q : !do_kv) continue;
                     const float *wv = (side == 0 ? s.phq : s.phk) + tok * PHS + tl * Rb + sub * CP;
-                    const float *cs = (side == 0 ? s.csq : s.csk) + tok * CSS + tl * a.P;
-                    float *dzr = s.dz + (side * C + tok) * DZS + tl * a.P;
+                    const float *cs = (side == 0 ? s.csq : s.csk) + tok * CSS + tl * P;
+                    float *dzr = s.dz + (side * C + tok) * DZS + tl * P;
                     const bool real = table < a.L && tok < nv;
                     float v[8 * RT], g[8], m = 0.f;
 #pragma unroll
@@ -844,7 +1072,7 @@ __global__ __launch_bounds__(kThreads, RT * NCT > 2 ? 1 : 2) void generic_grads(
                     int len = 8 * RT;
 #pragma unroll
                     for (int t = 0; t < 3 + (RT == 2); ++t) {
-                        const bool minor1 = t < a.P && real && (__float_as_uint(cs[t]) >> 31) != 0;
+                        const bool minor1 = t < P && real && (__float_as_uint(cs[t]) >> 31) != 0;
                         float sum = 0.f;
 #pragma unroll
                         for (int i = 0; i < 4 * RT; ++i) {
@@ -860,7 +1088,7 @@ __global__ __launch_bounds__(kThreads, RT * NCT > 2 ? 1 : 2) void generic_grads(
                     const int r0 = (sub * CP) | (a.bpt > 1 ? (b % a.bpt) * KB : 0);
 #pragma unroll
                     for (int t = 0; t < 8; ++t) {
-                        if (t < lcp || t >= a.P) { if (t >= lcp) g[t] = 0.f; continue; }
+                        if (t < lcp || t >= P) { if (t >= lcp) g[t] = 0.f; continue; }
                         const bool minor1 = real && (__float_as_uint(cs[t]) >> 31) != 0;
                         g[t] = (minor1 == (((r0 >> t) & 1) != 0)) ? m : 0.f;
                     }
@@ -869,27 +1097,30 @@ __global__ __launch_bounds__(kThreads, RT * NCT > 2 ? 1 : 2) void generic_grads(
 #pragma unroll
                         for (int t = 0; t < 8; ++t) g[t] += __shfl_xor(g[t], o, 64);
                     }
-                    if (sub != 0) continue;
+                    // finish: the shares take hyperplanes in turn (a table over several blocks: the first share, in its last block)
+                    int t0 = sub, step = NS;
                     if (a.bpt > 1) {
+                        if (sub != 0) continue;
                         float *rec = s.rec + (side * C + tok) * 9;
                         rec[8] += m;
                         m = rec[8];
 #pragma unroll
                         for (int t = 0; t < 8; ++t) { rec[t] += g[t]; g[t] = rec[t]; }
                         if (!last) continue;
+                        step = 1;
                     }
-                    const float *zr = (side == 0 ? a.Zq : a.Zk) + (row0 + tok) * a.LP + pl0 + tl * a.P;
+                    const float *zr = (side == 0 ? s.zsq : s.zsk) + tok * CSS + tl * P;
+                    for (int t = t0; t < P; t += step) {
+                        float dz = 0.f, gt = g[0];
 #pragma unroll
-                    for (int t = 0; t < 8; ++t) {
-                        if (t >= a.P) break;
-                        float dz = 0.f;
+                        for (int k = 1; k < 8; ++k) gt = t == k ? g[k] : gt;
                         if (real) {
                             const float c = cs[t], z = zr[t], small = fabsf(c), big = 1.0f - small;
                             const float e2 = expf(-2.0f * fabsf(z)), s2 = 4.0f * e2 / ((1.0f + e2) * (1.0f + e2));   // 1 - tanh^2 z
-                            const float half = small * (m - g[t]) - big * g[t];
+                            const float half = small * (m - gt) - big * gt;
                             const float du = (__float_as_uint(c) >> 31) ? -2.0f * half : 2.0f * half;
                             dz = a.beta * du * s2;
-                            dbeta_acc = fmaf(du, tanhf(z), dbeta_acc);
+                            if (dbeta_part) dbeta_acc = fmaf(du, tanhf(z), dbeta_acc);
                         }
                         dzr[t] = dz;
                     }
@@ -924,12 +1155,13 @@ __global__ __launch_bounds__(kThreads, RT * NCT > 2 ? 1 : 2) void generic_grads(
                     }
                 }
                 if (a.unit && tid < 2 * C && (tid % C) < nv) {
-                    const float *zr = (tid < C ? a.Zq : a.Zk) + (row0 + tid % C) * a.LP + pl0;
+                        const float *zr = (tid < C ? s.zsq : s.zsk) + (tid % C) * CSS;
                     for (int p = 0; p < np; ++p) radial = fmaf(zr[p], s.dz[tid * DZS + p], radial);
                 }
             }
-            // (the next block rewrites cs behind this barrier-free stretch only after everybody has left the finish
-            // step, phi and w after its own barriers, and dz after three more)
+            // (the next block rewrites the hashed rows behind this barrier-free stretch only after everybody has left the finish
+            // step, phi and w after its own barriers, and dz after three more; the projections are still read above)
+            if (a.unit && b + 1 < a.nblk) __syncthreads();
         }
         if (do_kv && a.causal) {
             store_tile_kernel<RT>(kk, s.kk, s.part);
@@ -968,12 +1200,13 @@ __global__ __launch_bounds__(kThreads, RT * NCT > 2 ? 1 : 2) void generic_grads(
         }
     }
     // ---- partial cotangent of beta, (2, BH, nseg): slot 0 holds dQ's side (or both), slot 1 dK's
+    if (!dbeta_part) return;
 #pragma unroll
     for (int m = 32; m >= 1; m >>= 1) dbeta_acc += __shfl_xor(dbeta_acc, m, 64);
     __syncthreads();
-    if (lane == 0) s.dz[w] = dbeta_acc;
+    if ((threadIdx.x & 63) == 0) s.dz[w] = dbeta_acc;
     __syncthreads();
-    if (tid == 0) {
+    if (threadIdx.x == 0) {
         const float t = (s.dz[0] + s.dz[1]) + (s.dz[2] + s.dz[3]);
         if (do_q) dbeta_part[static_cast<size_t>(bh) * a.nseg + seg] = t;
         if (do_kv) dbeta_part[(static_cast<size_t>(a.BH) + bh) * a.nseg + seg] = do_q ? 0.f : t;
@@ -992,14 +1225,17 @@ __global__ __launch_bounds__(kThreads) void generic_hash_tap(GArgs a, const T *X
     const int nv = a.N - t0 < 16 ? static_cast<int>(a.N - t0) : 16;
     const size_t row0 = static_cast<size_t>(bh) * a.N + t0;
     const int tb0 = block_table(a, b), pl0 = tb0 * a.P, np = a.LP - pl0 < a.PB ? a.LP - pl0 : a.PB;
-    load_rows<T, 1>(a, X, row0, nv, s.ys, XS);
+    RowRegs<1, 4> x;
+    PlaneRegs<4> wr;
+    fetch_rows<T, 1, 4>(a, X, row0, nv, x);
+    fetch_planes<1, 4>(a, a.W + (static_cast<size_t>(bh % a.H) * a.LP + pl0) * a.d, np, wr);
+    put_rows<1, 4>(a, x, nv, s.ys, XS);
     __syncthreads();
     if (a.unit) {
         const float inv = row_scale<1>(a, s.ys, XS);
         if (tid % 16 == 0) s.inv[tid / 16] = inv;
-        __syncthreads();
     }
-    hash_block<1>(a, a.W + (static_cast<size_t>(bh % a.H) * a.LP + pl0) * a.d, np, s.ys, XS, s.inv, s.cs, nullptr, nullptr, 0, 0, 0);
+    hash_block<1, 4>(a, wr, np, s.ys, XS, s.inv, reinterpret_cast<double *>(s.ph), s.cs, nullptr, nullptr, 0, 0, 0);
     __syncthreads();
     if (a.bpt == 1 || b % a.bpt == 0) {
         for (int i = tid; i < 16 * a.TB; i += kThreads) {
@@ -1198,17 +1434,23 @@ hipError_t bwd_impl(const Plan &p, const T *Q, const T *K, const T *V, const T *
         }));
     }
     RACE_TRY(scan_states("simple_scan", stateD, p.nseg, p.BH, a.ST, p.causal ? 1 : 2, st));
-    const bool both = !generic_carries(p);
-    for (int sides = both ? 3 : 2; sides >= (both ? 3 : 1); --sides) {
+    const auto launch = [&](auto carry, int sides) {
         ProfileScope prof("simple_grads", st);
-        RACE_TRY(dispatch(p, a, [&](auto rt, auto nct) {
+        return dispatch(p, a, [&](auto rt, auto nct) {
             constexpr int RT = decltype(rt)::value, NCT = decltype(nct)::value;
+            constexpr bool CARRY = decltype(carry)::value;
             const size_t lds = GradLds<RT>::floats(a.dp) * sizeof(float);
-            RACE_TRY(allow_lds(generic_grads<T, RT, NCT>, lds));
-            hipLaunchKernelGGL((generic_grads<T, RT, NCT>), dim3(p.nseg, p.BH), dim3(kThreads), lds, st, a, sides, Q, K, V, O, den,
-                               dO, static_cast<const float *>(stateS), static_cast<const float *>(stateD), dQ, dK, dV, dbeta_part);
+            RACE_TRY(allow_lds(generic_grads<T, RT, NCT, CARRY>, lds));
+            hipLaunchKernelGGL((generic_grads<T, RT, NCT, CARRY>), dim3(p.nseg, p.BH), dim3(kThreads), lds, st, a, sides, Q, K, V, O, den, dO,
+                               static_cast<const float *>(stateS), static_cast<const float *>(stateD), dQ, dK, dV, dbeta ? dbeta_part : nullptr);
             return hipGetLastError();
-        }));
+        });
+    };
+    if (generic_carries(p)) {
+        RACE_TRY(launch(std::true_type{}, 2));
+        RACE_TRY(launch(std::true_type{}, 1));
+    } else {
+        RACE_TRY(launch(std::false_type{}, 3));
     }
     if (dbeta) RACE_TRY(reduce_dbeta(p, dbeta_part, dbeta, st));
     return hipSuccess;
