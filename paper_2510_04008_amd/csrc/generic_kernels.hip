@@ -1273,15 +1273,16 @@ __global__ void generic_bucket_tap(GArgs a, const float *state, float *A, float 
 }
 
 // In-place scan over the segments of one batch*head, four floats per thread; the blockDim.y groups of a workgroup take
-// consecutive runs of segments.  mode 0: exclusive prefix; 1: exclusive suffix; 2: the total, into segment 0 only.
+// consecutive runs of segments.  mode: see ScanMode; `open`: the open forms.
 // (Bound by memory: every state is read once and written once when a group's run fits registers.  One thread per element
 // walking all segments alone is bound by its chain of loads instead: 30 us against 6 at 64 segments of 4160 floats.)
 constexpr int kScanRun = 8;
-__global__ __launch_bounds__(1024) void scan_states_kernel(float *state, int nseg, int n4, size_t stride, int mode)
+__global__ __launch_bounds__(1024) void scan_states_kernel(float *state, int nseg, int n4, size_t stride, int mode, int open)
 {
     __shared__ f32x4 tot[16][64];
     const int G = blockDim.y, g = threadIdx.y, x = threadIdx.x, e = blockIdx.x * 64 + x;
-    const int per = (nseg + G - 1) / G, i0 = g * per, i1 = i0 + per < nseg ? i0 + per : nseg;
+    const int per = (nseg + G - 1) / G, i0 = g * per, i1 = i0 + per < nseg ? i0 + per : nseg, i1r = i1 - (open && i1 == nseg ? 1 : 0);
+    const int first = open ? 1 : 0;                        // the first state that is written
     const bool on = e < n4;
     f32x4 *base = reinterpret_cast<f32x4 *>(state + static_cast<size_t>(blockIdx.y) * nseg * stride) + e;
     const size_t st4 = stride / 4;
@@ -1290,13 +1291,13 @@ __global__ __launch_bounds__(1024) void scan_states_kernel(float *state, int nse
     f32x4 v[kScanRun], sum = zero;
     if (per <= kScanRun) {
 #pragma unroll
-        for (int k = 0; k < kScanRun; ++k) v[k] = (on && k < per && i0 + k < i1) ? *at(i0 + k) : zero;
+        for (int k = 0; k < kScanRun; ++k) v[k] = (on && k < per && i0 + k < i1r) ? *at(i0 + k) : zero;
 #pragma unroll
         for (int k = 0; k < kScanRun; ++k) sum += v[k];
     } else if (on) {
         for (int i = i0; i < i1; i += kScanRun) {
 #pragma unroll
-            for (int k = 0; k < kScanRun; ++k) v[k] = i + k < i1 ? *at(i + k) : zero;
+            for (int k = 0; k < kScanRun; ++k) v[k] = i + k < i1r ? *at(i + k) : zero;
 #pragma unroll
             for (int k = 0; k < kScanRun; ++k) sum += v[k];
         }
@@ -1313,16 +1314,16 @@ __global__ __launch_bounds__(1024) void scan_states_kernel(float *state, int nse
     if (per <= kScanRun) {
 #pragma unroll
         for (int k = 0; k < kScanRun; ++k) {
-            if (k < per && i0 + k < i1) *at(i0 + k) = run;
+            if (k < per && i0 + k < i1 && i0 + k >= first) *at(i0 + k) = run;
             run += v[k];
         }
     } else {
         for (int i = i0; i < i1; i += kScanRun) {
 #pragma unroll
-            for (int k = 0; k < kScanRun; ++k) v[k] = i + k < i1 ? *at(i + k) : zero;
+            for (int k = 0; k < kScanRun; ++k) v[k] = i + k < i1r ? *at(i + k) : zero;
 #pragma unroll
             for (int k = 0; k < kScanRun; ++k) {
-                if (i + k < i1) *at(i + k) = run;
+                if (i + k < i1 && i + k >= first) *at(i + k) = run;
                 run += v[k];
             }
         }
@@ -1399,7 +1400,7 @@ hipError_t fwd_impl(const Plan &p, const T *Q, const T *K, const T *V, T *O, flo
     const GArgs a = make_args(p, ws);
     float *state = reinterpret_cast<float *>(ws + p.off_stateA);
     RACE_TRY(totals_kv<T>(p, a, Q, K, V, state, st));
-    RACE_TRY(scan_states("simple_scan", state, p.nseg, p.BH, a.ST, p.causal ? 0 : 2, st));
+    RACE_TRY(scan_states("simple_scan", state, p.nseg, p.BH, a.ST, p.causal ? kScanPrefix : kScanTotal, st));
     ProfileScope prof("simple_fwd_replay", st);
     return dispatch(p, a, [&](auto rt, auto nct) {
         constexpr int RT = decltype(rt)::value, NCT = decltype(nct)::value;
@@ -1420,7 +1421,7 @@ hipError_t bwd_impl(const Plan &p, const T *Q, const T *K, const T *V, const T *
     float *dbeta_part = reinterpret_cast<float *>(ws + p.off_dbeta);
     if (!p.fwd_state_kept) {
         RACE_TRY(totals_kv<T>(p, a, Q, K, V, stateS, st));
-        RACE_TRY(scan_states("simple_scan", stateS, p.nseg, p.BH, a.ST, p.causal ? 0 : 2, st));
+        RACE_TRY(scan_states("simple_scan", stateS, p.nseg, p.BH, a.ST, p.causal ? kScanPrefix : kScanTotal, st));
     }
     {
         ProfileScope prof("simple_totals_qg", st);
@@ -1433,7 +1434,7 @@ hipError_t bwd_impl(const Plan &p, const T *Q, const T *K, const T *V, const T *
             return hipGetLastError();
         }));
     }
-    RACE_TRY(scan_states("simple_scan", stateD, p.nseg, p.BH, a.ST, p.causal ? 1 : 2, st));
+    RACE_TRY(scan_states("simple_scan", stateD, p.nseg, p.BH, a.ST, p.causal ? kScanSuffix : kScanTotal, st));
     const auto launch = [&](auto carry, int sides) {
         ProfileScope prof("simple_grads", st);
         return dispatch(p, a, [&](auto rt, auto nct) {
@@ -1486,7 +1487,7 @@ hipError_t scan_states(const char *name, float *state, int nseg, int BH, size_t 
     int groups = 1;
     while (groups < 16 && groups * kScanRun < nseg) groups *= 2;
     const int n4 = static_cast<int>(stride / 4);
-    hipLaunchKernelGGL(scan_states_kernel, dim3((n4 + 63) / 64, BH), dim3(64, groups), 0, st, state, nseg, n4, stride, mode);
+    hipLaunchKernelGGL(scan_states_kernel, dim3((n4 + 63) / 64, BH), dim3(64, groups), 0, st, state, nseg, n4, stride, mode & 3, mode >> 2);
     return hipGetLastError();
 }
 

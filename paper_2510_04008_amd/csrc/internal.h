@@ -93,8 +93,10 @@ struct ProfileScope {
     hipStream_t st_;
 };
 
-// In-place scan of per-segment states (BH, nseg, stride) fp32, stride a multiple of 4 (generic_kernels.hip).  mode 0: exclusive
-// prefix over the segments, 1: exclusive suffix, 2: the total over all segments, into segment 0 only.
+// In-place scan of per-segment states (BH, nseg, stride) fp32, stride a multiple of 4 (generic_kernels.hip): exclusive prefix or
+// suffix over the segments, or the total over all segments, into segment 0 only.  Open: the totals of the segment that comes last
+// are not read, and no state is written for the one that comes first (it is zero).
+enum ScanMode { kScanPrefix = 0, kScanSuffix = 1, kScanTotal = 2, kScanPrefixOpen = 4, kScanSuffixOpen = 5 };
 hipError_t scan_states(const char *name, float *state, int nseg, int BH, size_t stride, int mode, hipStream_t st);
 
 // dbeta[bh] = sum over the two sides and the dbeta_parts partial sums of part, in index order (simple_kernels.hip).

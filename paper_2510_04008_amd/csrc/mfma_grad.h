@@ -163,7 +163,26 @@ void grad_kernel(KArgs a, const bf16raw *Xr, const bf16raw *V, const bf16raw *G_
     f32x4 SU[G::TPW][C::D / 16];                     // R = 16: 16 x 16 tiles [table][column tile]
     float macc[G::T16 ? G::TPW : G::MTG];            // extra column (A or dA): lane n < 32 <-> row r_own + 32 mr + n (n < 16 <-> r_own + 16 i + n)
     float *mass = reinterpret_cast<float *>(lds + S::mass) + w * G::TPW * 16;
-    if constexpr (G::T16) {
+    // (causal: nothing precedes the first segment, right to left the last one, and the scan writes no state for it)
+    const bool from_zero = INTRA && seg == (kReverse ? a.nseg - 1 : 0);
+    if (from_zero) {
+#pragma unroll
+        for (int i = 0; i < (G::T16 ? G::TPW : G::MTG); ++i) macc[i] = 0.f;
+        if constexpr (G::T16) {
+#pragma unroll
+            for (int i = 0; i < G::TPW; ++i) {
+#pragma unroll
+                for (int ct = 0; ct < C::D / 16; ++ct) SU[i][ct] = f32x4{0.f, 0.f, 0.f, 0.f};
+                if (q16 == 0) mass[16 * i + n16] = 0.f;
+            }
+        } else {
+#pragma unroll
+            for (int mr = 0; mr < G::MTG; ++mr) {
+#pragma unroll
+                for (int mtc = 0; mtc < C::NT; ++mtc) ST[mr][mtc] = f32x16{0};
+            }
+        }
+    } else if constexpr (G::T16) {
 #pragma unroll
         for (int i = 0; i < G::TPW; ++i) {
 #pragma unroll

@@ -164,6 +164,9 @@ void totals_kernel(KArgs a, const float *M, const bf16raw *Y, const bf16raw *Oin
     float *ge_out = a.ge + static_cast<size_t>(bh) * a.N;
     if (QG) { Oin += base; Gout += base; den_in += static_cast<size_t>(bh) * a.N; }
     float *st = a.state + (static_cast<size_t>(bh) * a.nseg + seg) * C::STATE;
+    // causal: the totals of the last segment (backward: of the first) are in no other segment's start state
+    const bool unread = a.scanned && seg == (QG ? 0 : a.nseg - 1);
+    if (!QG && unread) return;
 
     f32x16 Sacc[C::MT][C::NTW];
     f32x4 macc[C::MA];                 // extra column of row tiles cg, cg + CG, ...: lane n < 32 <-> row, weight parts
@@ -226,6 +229,7 @@ void totals_kernel(KArgs a, const float *M, const bf16raw *Y, const bf16raw *Oin
         }
         __syncthreads();
     }
+    if (unread) return;
 #pragma unroll
     for (int mt = 0; mt < C::MT; ++mt) {
 #pragma unroll
@@ -297,13 +301,23 @@ void stream_kernel(KArgs a, const float *Mr, const float *Mw, const bf16raw *Y, 
     float macc[C::MA];                 // bucket masses of row tiles cg, cg + CG, ... (balances the work): lane n < 32 <-> row
 #pragma unroll
     for (int i = 0; i < C::MA; ++i) macc[i] = 0.f;
+    // (causal: nothing precedes the first segment, right to left the last one, and the scan writes no state for it)
+    const bool from_zero = !NC && seg == (kReverse ? a.nseg - 1 : 0);
+    if (from_zero) {
 #pragma unroll
-    for (int mt = 0; mt < C::MT; ++mt) {
+        for (int mt = 0; mt < C::MT; ++mt) {
 #pragma unroll
-        for (int nt = 0; nt < C::NTW; ++nt) {
+            for (int nt = 0; nt < C::NTW; ++nt) Sacc[mt][nt] = f32x16{0};
+        }
+    } else {
 #pragma unroll
-            for (int v = 0; v < 16; ++v)
-                Sacc[mt][nt][v] = st[state_b<C>(r_own + 32 * mt + acc_row(v, h), c_own + 32 * nt + ln)];
+        for (int mt = 0; mt < C::MT; ++mt) {
+#pragma unroll
+            for (int nt = 0; nt < C::NTW; ++nt) {
+#pragma unroll
+                for (int v = 0; v < 16; ++v)
+                    Sacc[mt][nt][v] = st[state_b<C>(r_own + 32 * mt + acc_row(v, h), c_own + 32 * nt + ln)];
+            }
         }
     }
     if (MODE == kForward) {
@@ -311,7 +325,7 @@ void stream_kernel(KArgs a, const float *Mr, const float *Mw, const bf16raw *Y, 
 #pragma unroll
         for (int i = 0; i < C::MA; ++i) {
             const int mt = i * C::CG + cg;
-            if (mt < C::MT) macc[i] = st[state_a<C>(r_own + 32 * mt + ln)];
+            if (mt < C::MT && !from_zero) macc[i] = st[state_a<C>(r_own + 32 * mt + ln)];
         }
 #pragma unroll
         for (int i = 0; i < C::MA; ++i) {
@@ -482,22 +496,37 @@ void stream_kernel(KArgs a, const float *Mr, const float *Mw, const bf16raw *Y, 
 
 // Totals over all segments of the problem's own buckets, written as A[row * a_stride] and
 // Bsum[row * b_stride + c] with row = (bh * L_real + l) * R_real + r.  Real corner r of a real table sits at
-// the compiled corner with all padding bits set.
+// the compiled corner with all padding bits set.  The threads of an element share its segments.  (Bound by memory; one thread
+// per element adding up 63 segments alone is bound by its chain of loads: 22.7 us at B H = 4, 264 KB a state.)
+constexpr int kTapElements = 64, kTapGroups = 8;
 template <class C>
-__global__ void bucket_tap_kernel(const float *state, int nseg, int BH, int L_real, int P_real, float *A, float *Bsum,
+__global__ __launch_bounds__(kTapElements * kTapGroups) void bucket_tap_kernel(const float *state, int nseg, int L_real, int P_real, float *A, float *Bsum,
                                   int a_stride, int b_stride)
 {
     const int R_real = 1 << P_real, pad = (C::R - 1) & ~(R_real - 1);
     const size_t per = static_cast<size_t>(L_real) * R_real * (C::D + 1);
-    const size_t i = blockIdx.x * static_cast<size_t>(blockDim.x) + threadIdx.x;
-    if (i >= static_cast<size_t>(BH) * per) return;
-    const size_t bh = i / per;
-    const int e = static_cast<int>(i - bh * per);
+    __shared__ float part[kTapGroups][kTapElements];
+    const int x = threadIdx.x, g = threadIdx.y, run_len = (nseg + kTapGroups - 1) / kTapGroups;
+    const size_t bh = blockIdx.y, at = blockIdx.x * static_cast<size_t>(kTapElements) + x;
+    const int e = static_cast<int>(at < per ? at : per - 1);
     const int row = e / (C::D + 1), c = e % (C::D + 1), l = row / R_real, r = row % R_real;
     const int src = l * C::R + (r | pad);
     const int off = c < C::D ? src * C::D + c : C::LR * C::D + src;
     float run = 0.f;
-    for (int s = 0; s < nseg; ++s) run += state[(bh * nseg + s) * C::STATE + off];
+    const float *base = state + bh * nseg * C::STATE + off;
+    const int s1 = (g + 1) * run_len < nseg ? (g + 1) * run_len : nseg;
+    for (int s = g * run_len; s < s1; s += 8) {
+        float v[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) v[k] = base[static_cast<size_t>(s + k < s1 ? s + k : s) * C::STATE];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) run += s + k < s1 ? v[k] : 0.f;
+    }
+    part[g][x] = run;
+    __syncthreads();
+    if (g != 0 || at >= per) return;
+#pragma unroll
+    for (int k = 1; k < kTapGroups; ++k) run += part[k][x];
     const size_t dst = (bh * L_real + l) * R_real + r;
     if (c < C::D) Bsum[dst * b_stride + c] = run;
     else A[dst * a_stride] = run;
@@ -617,6 +646,7 @@ KArgs make_kargs(const Plan &p, char *ws)
     a.ge = reinterpret_cast<float *>(ws + p.off_ge);
     a.want_dbeta = 0;
     a.hash_tokens = 0;
+    a.scanned = 0;
     return a;
 }
 
@@ -664,9 +694,10 @@ template <class C>
 hipError_t fwd_t(const Plan &p, const void *Q, const void *K, const void *V, void *O, float *den, char *ws, hipStream_t st)
 {
     KArgs a = make_kargs<C>(p, ws);
+    a.scanned = p.causal;
     RACE_TRY((launch_hash<C>(p, a, Q, K, 0, 2, st)));
     RACE_TRY((launch_totals<C, 0>(p, a, a.Mk, V, nullptr, nullptr, nullptr, st)));
-    RACE_TRY(scan_states("segment_scan", a.state, p.nseg, p.BH, C::STATE, p.causal ? 0 : 2, st));
+    RACE_TRY(scan_states("segment_scan", a.state, p.nseg, p.BH, C::STATE, p.causal ? kScanPrefixOpen : kScanTotal, st));
     RACE_TRY((launch_stream<C, kForward>(p, a, a.Mq, a.Mk, V, O, den, st)));
     return hipSuccess;
 }
@@ -692,6 +723,7 @@ hipError_t bwd_t(const Plan &p, const void *Q, const void *K, const void *V, con
                  const void *dO, void *dQ, void *dK, void *dV, float *dbeta, char *ws, hipStream_t st)
 {
     KArgs a = make_kargs<C>(p, ws);
+    a.scanned = p.causal;
     KArgs b = a;
     b.state = reinterpret_cast<float *>(ws + p.off_stateB);
     // the hashed rows of Q and K and the statistics of (phi_K, [V | 1]) at segment starts (the forward leaves exactly
@@ -700,12 +732,12 @@ hipError_t bwd_t(const Plan &p, const void *Q, const void *K, const void *V, con
     if (!p.fwd_state_kept) {
         RACE_TRY((launch_hash<C>(p, a, Q, K, 0, 2, st)));
         RACE_TRY((launch_totals<C, 0>(p, a, a.Mk, V, nullptr, nullptr, nullptr, st)));
-        RACE_TRY(scan_states("segment_scan", a.state, p.nseg, p.BH, C::STATE, p.causal ? 0 : 2, st));
+        RACE_TRY(scan_states("segment_scan", a.state, p.nseg, p.BH, C::STATE, p.causal ? kScanPrefixOpen : kScanTotal, st));
     }
     a.want_dbeta = b.want_dbeta = dbeta != nullptr;
     // dK's buffer holds the cotangent rows until dK itself is written
     RACE_TRY((launch_totals<C, 1>(p, b, a.Mq, dO, O, den, dK, st)));
-    RACE_TRY(scan_states("segment_scan", b.state, p.nseg, p.BH, C::STATE, p.causal ? 1 : 2, st));
+    RACE_TRY(scan_states("segment_scan", b.state, p.nseg, p.BH, C::STATE, p.causal ? kScanSuffixOpen : kScanTotal, st));
     RACE_TRY((launch_stream<C, kGradV>(p, b, a.Mk, a.Mq, dK, dV, nullptr, st)));
     RACE_TRY((launch_grad<C, 0>(p, a, Q, V, dK, dQ, st)));
     RACE_TRY((launch_grad<C, 1>(p, b, K, V, dK, dK, st)));
@@ -720,9 +752,9 @@ hipError_t buckets_t(const Plan &p, const void *K, const void *V, float *A, floa
     KArgs a = make_kargs<C>(p, ws);
     RACE_TRY((launch_hash<C>(p, a, nullptr, K, 1, 1, st)));
     RACE_TRY((launch_totals<C, 0>(p, a, a.Mk, V, nullptr, nullptr, nullptr, st)));
-    const size_t total = static_cast<size_t>(p.BH) * p.LR * (C::D + 1);
-    hipLaunchKernelGGL(bucket_tap_kernel<C>, dim3(static_cast<unsigned>((total + 255) / 256)), dim3(256), 0, st, a.state,
-                       p.nseg, p.BH, p.L, p.P, A, Bsum, a_stride, b_stride);
+    const int per = p.LR * (C::D + 1);
+    hipLaunchKernelGGL(bucket_tap_kernel<C>, dim3((per + kTapElements - 1) / kTapElements, p.BH), dim3(kTapElements, kTapGroups), 0, st, a.state,
+                       p.nseg, p.L, p.P, A, Bsum, a_stride, b_stride);
     return hipGetLastError();
 }
 

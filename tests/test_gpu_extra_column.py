@@ -14,8 +14,8 @@ pytestmark = pytest.mark.gpu
 
 # every split of the bucket rows over the wavefronts: eight tables of 64, 16 of 16, four of 16 (two wavefronts a table), padded
 SHAPES = [(128, 8, 6), (64, 16, 4), (128, 4, 4), (64, 5, 5), (128, 7, 3)]
-# one token, around a tile of 32 and a step of 64, several segments
-LENGTHS = [1, 31, 33, 64, 95, 300]
+# one token, around a tile of 32 and a step of 64, several segments, more segments than groups that add them up
+LENGTHS = [1, 31, 33, 64, 95, 300, 2300]
 
 
 @pytest.mark.parametrize("shape", SHAPES, ids=str)
