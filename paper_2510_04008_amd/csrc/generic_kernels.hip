@@ -1155,7 +1155,7 @@ __global__ __launch_bounds__(kThreads, RT * NCT > 2 ? 1 : (RT * NCT == 2 ? 2 : 3
                     }
                 }
                 if (a.unit && tid < 2 * C && (tid % C) < nv) {
-                        const float *zr = (tid < C ? s.zsq : s.zsk) + (tid % C) * CSS;
+                    const float *zr = (tid < C ? s.zsq : s.zsk) + (tid % C) * CSS;
                     for (int p = 0; p < np; ++p) radial = fmaf(zr[p], s.dz[tid * DZS + p], radial);
                 }
             }

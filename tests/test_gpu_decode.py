@@ -133,3 +133,18 @@ def test_rows_need_be_aligned_to_their_elements_only(dtype):
         torch.cuda.synchronize()
         runs.append((o, den, state))
     assert shifted[0].data_ptr() % 8 == dtype.itemsize and all(torch.equal(a, b) for a, b in zip(*runs))
+
+
+@pytest.mark.parametrize("segments", [1, 2, 8, 9, 17, 64, 67])
+def test_state_of_a_prompt_is_the_sum_over_its_segments(segments):
+    """One to eight threads an element add up the segments' totals, eight at a time: runs of one, full and ragged ones."""
+    w = Workload("dec-segments-%d" % segments, 1, 2, 32 * segments - 5, 128, 3, 5, 4.0, True, "bf16", chunk=32)
+    _, K, V, _ = synth.make_inputs(w, "cuda")
+    seeds = synth.projection_seeds(w)
+    W = oracle_w(w, seeds)
+    state = to_f64(ra.race_attn_state_init(desc_of(w), K, V, seeds))
+    Kd, Vd = to_f64(K), to_f64(V)
+    for h in range(w.H):
+        A, Bs = ro.bucket_statistics(Kd[0, h], Vd[0, h], W[h], w.sharpening, w.L, w.P)
+        ref = np.concatenate([Bs, A[:, :, None]], axis=2)
+        assert np.abs(state[0, h] - ref).max() <= TOL["bf16"] * np.abs(ref).max()
