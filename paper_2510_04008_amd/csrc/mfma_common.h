@@ -163,6 +163,11 @@ __device__ __forceinline__ f32x16 mma(u32x4 a, u32x4 b, f32x16 c)
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c,
                                                    0, 0, 0);
 }
+// 16 x 16 x 32 product: A row / B column lane % 16, k-slots 8 (lane / 16) ..; D column lane % 16, rows 4 (lane / 16) + v.
+__device__ __forceinline__ f32x4 mma16(u32x4 a, u32x4 b, f32x4 c)
+{
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+}
 __device__ __forceinline__ u32x4 lds128(const bf16raw *p) { return *reinterpret_cast<const u32x4 *>(p); }
 // accumulator registers 8s..8s+7 as a bf16 B (or A) operand
 __device__ __forceinline__ u32x4 acc_operand(const f32x16 &t, int s)
@@ -263,8 +268,9 @@ __device__ __forceinline__ float sum_rows4(float x0, float x1, float x2, float x
 // Sums of assignments over the tokens of a k-step, with weights, on the matrix cores: the same registers that are the
 // assignments' operand of the 32 x 32 x 16 update (lane = 32 h + n: bucket row n, tokens 8 h ..) are, read as the B operand of a
 // 16 x 16 x 32 product, column n % 16 with k-slots 8 (n / 16 + 2 h) .., i.e. both halves of the bucket rows in one column.  An A
-// operand whose rows 0 .. 2 hold the weights in the slots of bucket rows 0 .. 15 and whose rows 4 .. 6 hold them in the slots
-// of rows 16 .. 31 keeps the halves apart: D register v of lane n < 32 is the sum of bucket row n with weight part v.  fp32
+// operand whose rows 4 q + 0 .. 2 hold the weights in slots 8 q .. and zeros in the others keeps them apart: D register v of lane
+// 32 h + n is the sum over tokens 8 h .. of bucket row n with weight part v.  With rows 0 .. 2 holding them in slots 0 .. 7 and
+// 16 .. 23 and rows 4 .. 6 in the others the halves of the tokens are added up too, lane n < 32 gets the sum (`whole`).  fp32
 // weights enter as three bf16 parts (truncated, 8 bits each: exact), weights of one as a single part.  (One 16-cycle matrix
 // instruction in place of 16 vector ones; both totals kernels spent 128 of their 320-450 vector instructions a step on these sums.)
 constexpr int kParts = 4;                       // rows of a [kParts][tokens] bf16 array of weight parts; the last one is zeros
@@ -276,19 +282,22 @@ __device__ __forceinline__ bf16raw weight_part(float x, int i)
 }
 // This lane's element of a [kParts][tokens] array for a k-step at its first token, and the operand of weights of one.
 // Form 32: against operands of 32 bucket rows; form 16: against B operands of 16 x 16 x 32 products (16 bucket rows, 32 tokens).
+template <bool WHOLE>
 __device__ __forceinline__ int parts_offset32(int tokens, int lane)
 {
     const int i = lane & 15, q = lane >> 4;
-    return (i < 8 && (i >> 2) == (q & 1) ? i & 3 : kParts - 1) * tokens + 8 * (q >> 1);
+    return ((i >> 2) == (WHOLE ? q & 1 : q) ? i & 3 : kParts - 1) * tokens + 8 * (q >> 1);
 }
 __device__ __forceinline__ int parts_offset16(int tokens, int lane)
 {
     const int i = lane & 15, q = lane >> 4;
     return (i < kParts - 1 ? i : kParts - 1) * tokens + 8 * q;
 }
+template <bool WHOLE>
 __device__ __forceinline__ u32x4 ones32(int lane)
 {
-    const uint32_t one = (lane & 15) == 4 * ((lane >> 4) & 1) ? kOnePair : 0u;
+    const int q = lane >> 4;
+    const uint32_t one = (lane & 15) == 4 * (WHOLE ? q & 1 : q) ? kOnePair : 0u;
     return u32x4{one, one, one, one};
 }
 __device__ __forceinline__ u32x4 ones16(int lane)
@@ -296,9 +305,16 @@ __device__ __forceinline__ u32x4 ones16(int lane)
     const uint32_t one = (lane & 15) == 0 ? kOnePair : 0u;
     return u32x4{one, one, one, one};
 }
-__device__ __forceinline__ float sum_parts(f32x4 x) { return (x[2] + x[1]) + x[0]; }
-// the sums so far as the accumulator of the next products (the parts are added up per tile: one register between tiles, not four)
-__device__ __forceinline__ f32x4 as_parts(float x) { return f32x4{x, 0.f, 0.f, 0.f}; }
+// A product starts from zero and the vector ALU adds what it returns to the running sum.  (The matrix cores do not round to
+// nearest when they add to a large accumulator: with the running sum there the masses of 524288 tokens in one segment were
+// 3.1e-6 to 4.7e-6 too small and 4.8e-6 to 6.0e-6 off by root mean square; so 1.6e-6 to 2.1e-6, as with sums in the vector ALU alone, which
+// the halves of the tokens keep apart as well.  One register between products instead of four.)
+template <bool PARTS>
+__device__ __forceinline__ float column_sum(u32x4 weights, u32x4 phi)
+{
+    const f32x4 x = mma16(weights, phi, f32x4{0.f, 0.f, 0.f, 0.f});
+    return PARTS ? (x[2] + x[1]) + x[0] : x[0];
+}
 
 // ---------------------------------------------------------------- global -> registers -> LDS tiles
 // A tile of ROWS rows is ROWS*CPR chunks of 16 bytes; thread t owns chunks t, t + 512, ...  Loads are
@@ -435,12 +451,6 @@ __device__ __forceinline__ void store_cotangent(const CotChunks<C, ROWS> &r, bf1
 }
 
 // ---------------------------------------------------------------- projection + soft assignment
-// 16 x 16 x 32 product: A row / B column lane % 16, k-slots 8 (lane / 16) ..; D column lane % 16, rows 4 (lane / 16) + v.
-__device__ __forceinline__ f32x4 mma16(u32x4 a, u32x4 b, f32x4 c)
-{
-    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
-}
-
 // The hashed form of one projection: c = +small or -small, where small = sigmoid(-2 beta |tanh z|) is the mass of the
 // bit's minor side and the sign bit tells which side that is (clear: z >= 0, the major side is +1).  One float per
 // (token, table, hyperplane) is all that the soft assignment of Algorithm 1, step 4 depends on: every pass after the

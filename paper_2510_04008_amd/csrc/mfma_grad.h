@@ -446,8 +446,7 @@ void grad_kernel(KArgs a, const bf16raw *Xr, const bf16raw *V, const bf16raw *G_
                 if (intra) {
                     // ---- statistics += Yw^T . phi_writer
                     const u32x4 pb = lds_tr16(phw + r_own + 16 * i, C::PST, 8 * q16, 8 * q16 + 4, tr_ph, lane);
-                    const f32x4 mp = mma16(SIDE == 1 ? lds128(buf_swp(it) + parts_offset16(kTile, opaque(lane))) : ones16(opaque(lane)), pb, as_parts(macc[i]));
-                    macc[i] = SIDE == 1 ? sum_parts(mp) : mp[0];
+                    macc[i] += column_sum<SIDE == 1>(SIDE == 1 ? lds128(buf_swp(it) + parts_offset16(kTile, opaque(lane))) : ones16(opaque(lane)), pb);
 #pragma unroll
                     for (int ct = 0; ct < C::D / 16; ++ct)
                         SU[i][ct] = mma16(lds_tr16(yw, C::YS, 8 * q16, 8 * q16 + 4, 32 * (ct >> 1) + 8 * (lane & 3) + 4 * (ct & 1), lane), pb, SU[i][ct]);
@@ -574,18 +573,17 @@ void grad_kernel(KArgs a, const bf16raw *Xr, const bf16raw *V, const bf16raw *G_
             }
             // ---- statistics += Yw^T . phi_writer
             if (intra) {
-                const int lo = opaque(lane), swp_off = parts_offset32(kTile, lo);
+                const int lo = opaque(lane), swp_off = parts_offset32<true>(kTile, lo);
 #pragma unroll
                 for (int s = 0; s < 2; ++s) {
-                    const u32x4 gw = SIDE == 1 ? lds128(buf_swp(it) + swp_off + 16 * s) : ones32(lo);   // (SIDE 0: [V | 1])
+                    const u32x4 gw = SIDE == 1 ? lds128(buf_swp(it) + swp_off + 16 * s) : ones32<true>(lo);   // (SIDE 0: [V | 1])
                     u32x4 ay[C::NT];
 #pragma unroll
                     for (int mtc = 0; mtc < C::NT; ++mtc) ay[mtc] = lds_tr_plain<true>(yw, C::YS, 16 * s, 32 * mtc, ln, h);
 #pragma unroll
                     for (int mr = 0; mr < G::MTG; ++mr) {
                         const u32x4 bp = lds_tr_plain<true>(phw, C::PST, 16 * s, r_own + 32 * mr, ln, h);
-                        const f32x4 mp = mma16(gw, bp, as_parts(macc[mr]));
-                        macc[mr] = SIDE == 1 ? sum_parts(mp) : mp[0];
+                        macc[mr] += column_sum<SIDE == 1>(gw, bp);
 #pragma unroll
                         for (int mtc = 0; mtc < C::NT; ++mtc) ST[mr][mtc] = mma(ay[mtc], bp, ST[mr][mtc]);
                     }

@@ -169,9 +169,9 @@ void totals_kernel(KArgs a, const float *M, const bf16raw *Y, const bf16raw *Oin
     if (!QG && unread) return;
 
     f32x16 Sacc[C::MT][C::NTW];
-    f32x4 macc[C::MA];                 // extra column of row tiles cg, cg + CG, ...: lane n < 32 <-> row, weight parts
+    float macc[C::MA];                 // extra column of row tiles cg, cg + CG, ...: lane n <-> row, per-half partial sums
 #pragma unroll
-    for (int i = 0; i < C::MA; ++i) macc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int i = 0; i < C::MA; ++i) macc[i] = 0.f;
 #pragma unroll
     for (int mt = 0; mt < C::MT; ++mt) {
 #pragma unroll
@@ -185,7 +185,7 @@ void totals_kernel(KArgs a, const float *M, const bf16raw *Y, const bf16raw *Oin
     // this wavefront's tokens of a step (its half) and its lanes' share of the tables
     const int half = w / 4, slot = 2 * (w % 4) + h, row = half * kTile + ln;
     const uint32_t lane_off = table_offset<C>(Share<C, 8>::table(slot, 0), ln);
-    const bf16raw *ge_lane = ge_lds + parts_offset32(TT, lane);
+    const bf16raw *ge_lane = ge_lds + parts_offset32<false>(TT, lane);
     typename Share<C, 8>::Regs pre_m;
     RowChunks<C, TT> pre_y;
     CotChunks<C, TT> pre_c;
@@ -217,12 +217,12 @@ void totals_kernel(KArgs a, const float *M, const bf16raw *Y, const bf16raw *Oin
             u32x4 by[C::NTW];
 #pragma unroll
             for (int nt = 0; nt < C::NTW; ++nt) by[nt] = lds_tr_plain(ys, C::YS, 16 * s, c_own + 32 * nt, ln, h);
-            const u32x4 gw = QG ? lds128(ge_lane + 16 * s) : ones32(lane);
+            const u32x4 gw = QG ? lds128(ge_lane + 16 * s) : ones32<false>(lane);
 #pragma unroll
             for (int mt = 0; mt < C::MT; ++mt) {
                 const u32x4 ap = lds_tr_plain<true>(ph, C::PST, 16 * s, r_own + 32 * mt, ln, h);
                 if (mass_owner<C>(mt, cg))      // the extra column (bucket mass, or its cotangent): shared out over the column groups
-                    macc[mt / C::CG] = mma16(gw, ap, macc[mt / C::CG]);
+                    macc[mt / C::CG] += column_sum<QG != 0>(gw, ap);
 #pragma unroll
                 for (int nt = 0; nt < C::NTW; ++nt) Sacc[mt][nt] = mma(ap, by[nt], Sacc[mt][nt]);
             }
@@ -238,7 +238,10 @@ void totals_kernel(KArgs a, const float *M, const bf16raw *Y, const bf16raw *Oin
             for (int v = 0; v < 16; ++v)
                 st[state_b<C>(r_own + 32 * mt + acc_row(v, h), c_own + 32 * nt + ln)] = Sacc[mt][nt][v];
         }
-        if (mass_owner<C>(mt, cg) && h == 0) st[state_a<C>(r_own + 32 * mt + ln)] = sum_parts(macc[mt / C::CG]);
+        if (mass_owner<C>(mt, cg)) {
+            const float tot = sum_halves(macc[mt / C::CG]);
+            if (h == 0) st[state_a<C>(r_own + 32 * mt + ln)] = tot;
+        }
     }
 }
 
@@ -298,7 +301,7 @@ void stream_kernel(KArgs a, const float *Mr, const float *Mw, const bf16raw *Y, 
     const float *st = a.state + (static_cast<size_t>(bh) * a.nseg + (NC ? 0 : (a.causal ? seg : 0))) * C::STATE;
 
     f32x16 Sacc[C::MT][C::NTW];
-    float macc[C::MA];                 // bucket masses of row tiles cg, cg + CG, ... (balances the work): lane n < 32 <-> row
+    float macc[C::MA];                 // bucket masses of row tiles cg, cg + CG, ... (balances the work): lane n <-> row, per-half partial sums
 #pragma unroll
     for (int i = 0; i < C::MA; ++i) macc[i] = 0.f;
     // (causal: nothing precedes the first segment, right to left the last one, and the scan writes no state for it)
@@ -460,7 +463,7 @@ void stream_kernel(KArgs a, const float *Mr, const float *Mw, const bf16raw *Y, 
 #pragma unroll
                 for (int mt = 0; mt < C::MT; ++mt) {
                     const u32x4 ap = lds_tr_plain<true>(phw, C::PS, 16 * s, r_own + 32 * mt, ln, h);
-                    if (MODE == kForward && mass_owner<C>(mt, cg)) macc[mt / C::CG] = mma16(ones32(opaque(lane)), ap, as_parts(macc[mt / C::CG]))[0];
+                    if (MODE == kForward && mass_owner<C>(mt, cg)) macc[mt / C::CG] += column_sum<false>(ones32<false>(opaque(lane)), ap);
 #pragma unroll
                     for (int nt = 0; nt < C::NTW; ++nt) Sacc[mt][nt] = mma(ap, by[nt], Sacc[mt][nt]);
                     RACE_SCHED_FENCE();
@@ -486,7 +489,9 @@ void stream_kernel(KArgs a, const float *Mr, const float *Mw, const bf16raw *Y, 
             // masses after this tile, for the next tile's read-out
 #pragma unroll
             for (int mt = 0; mt < C::MT; ++mt) {
-                if (mass_owner<C>(mt, cg) && h == 0) mass[r_own + 32 * mt + il(ln)] = macc[mt / C::CG];
+                if (!mass_owner<C>(mt, cg)) continue;
+                const float tot = sum_halves(macc[mt / C::CG]);
+                if (h == 0) mass[r_own + 32 * mt + il(ln)] = tot;
             }
         }
         __syncthreads();

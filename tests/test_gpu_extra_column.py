@@ -34,6 +34,37 @@ def test_masses_are_the_sums_of_the_assignments(shape, N):
 
 
 @pytest.mark.parametrize("shape", SHAPES, ids=str)
+def test_masses_of_a_long_segment_are_rounded_to_nearest(shape):
+    """One segment of 524288 tokens: the masses that the accumulation alone forms, and those that the forward pass carries along,
+    read by queries of zeros (whose assignments are 2^-P, exactly)."""
+    d, L, P = shape
+    w = Workload("long", 1, 1, 1 << 19, d, L, P, 2.0, True, "bf16", normalize_qk=True, chunk=1 << 19)
+    Q, K, V, _ = synth.make_inputs(w, "cuda")
+    Q = torch.zeros_like(Q)
+    seeds, desc, last = synth.projection_seeds(w), desc_of(w), 256
+    ref = torch.zeros((L << P,), dtype=torch.float64, device="cuda")
+    for t0 in range(0, w.N, 1 << 15):
+        part = K[:, :, t0:t0 + (1 << 15)].contiguous()
+        _, phi = ra.race_attn_debug_hash(ra.make_desc(1, 1, 1 << 15, d, L, P, 2.0, True, ra.RACE_BF16), part, seeds, want_phi=True)
+        phi = phi[0, 0].double().reshape(1 << 15, -1)
+        ref += phi.sum(dim=0)
+    A, _ = ra.race_attn_debug_buckets(desc, K, V, seeds)
+    err = (A[0, 0].double().reshape(-1) - ref) / ref
+    # two sums, of eight tokens in sixteen each, that grow evenly in n = N / 16 steps: a step is rounded to nearest, its error up to
+    # 2^-24 of the sum so far, uniform (1 / sqrt 3) and independent, and the sum so far is 1 / sqrt 3 of the whole by root mean square
+    rms = 2.0 ** -24 * (w.N / 32) ** 0.5 / 3
+    off, mean = err.square().mean().sqrt().item(), err.mean().item()
+    assert off <= rms, (off, mean)
+    _, den = ra.race_attn_fwd(desc, Q, K, V, seeds)
+    behind = phi[-last:].flip(0).cumsum(0).flip(0).sum(dim=1)       # mass of token i and those behind it
+    want = (ref.sum() - torch.cat([behind[1:], behind.new_zeros(1)])) / (L << P)
+    err = (den[0, 0, -last:].double() - want) / want
+    # the same errors averaged over the bucket rows (four standard deviations), and the read-out's own sums
+    most = err.abs().max().item()
+    assert most <= 4 * rms / (L << P) ** 0.5 + 2.0 ** -22, most
+
+
+@pytest.mark.parametrize("shape", SHAPES, ids=str)
 @pytest.mark.parametrize("causal", [True, False])
 def test_gradient_through_the_cotangents_of_the_masses_alone(shape, causal):
     """With V = 0 the key side sees nothing but dA; O is an argument of the backward pass and is left as it is, and its rows are
