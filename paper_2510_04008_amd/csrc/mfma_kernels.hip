@@ -286,6 +286,13 @@ void stream_kernel(KArgs a, const float *Mr, const float *Mw, const bf16raw *Y, 
     float *red = reinterpret_cast<float *>(lds + S::red);
 
     constexpr bool kReverse = (MODE == kGradV);
+    // Without the in-tile term half of the wavefronts have nothing to produce.  They finish the output under the others' production
+    // either way; where the producing ones come to it last, the tile waits for them.  With the output first and no lead in the
+    // second half dV takes 100.2 instead of 118.7 us at B H = 16, N = 65536, (d, L, P) = (128, 4, 4), 97.4 instead of 106.4 at B H = 8,
+    // (128, 16, 4), 91.7 instead of 97.3 at (64, 8, 6), 102.1 and 102.8 at B H = 64, N = 16384, (64, 16, 4); the forward pass of 128
+    // columns 107.9 instead of 111.7, 117.4 instead of 124.6 (86.1 and 85.5 at B H = 16, N = 16384, (128, 8, 6)).  The forward pass of 64
+    // columns, whose output is half as long, has it last: 125.3 instead of 133.5 us at (64, 16, 4).
+    constexpr bool kOutputFirst = NC && (MODE == kGradV || C::D == 128);
     const int seg = blockIdx.x, bh = blockIdx.y;
     const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, ln = lane & 31, h = lane >> 5;
     const int rg = w % C::RG, cg = w / C::RG;
@@ -402,6 +409,7 @@ void stream_kernel(KArgs a, const float *Mr, const float *Mw, const bf16raw *Y, 
         const int nvalid = tile_nv(tile_t0(it));
         // ---- first half: this tile's rows and assignments -> LDS, then the previous tile's output (its stores are issued when
         //      nothing loaded is waited for any more; in front of the production every tile waited for them to complete)
+        if (kOutputFirst && it > 0) epilogue(it - 1);
         if (intra) store_rows<C, kTile, C::YS>(pre_y, ytile);
         if (side == 0) {
             const float dnl = produce<C, 8, C::PS>(pre_m, slot, ln, a.soft(), true, phr, MODE == kForward ? mass : nullptr);
@@ -409,10 +417,10 @@ void stream_kernel(KArgs a, const float *Mr, const float *Mw, const bf16raw *Y, 
         } else if (intra) {
             produce<C, 8, C::PS>(pre_m, slot, ln, a.soft(), ln < nvalid, phw);
         }
-        if (it > 0) epilogue(it - 1);
+        if (!kOutputFirst && it > 0) epilogue(it - 1);
         __syncthreads();
 
-        if (side == 1) lead(true);
+        if (!kOutputFirst && side == 1) lead(true);
         // ---- contraction with the register-resident statistics (own bucket rows x own columns)
         f32x16 out[C::NTW];     // read-out, transposed: lane = reader token, register v = column acc_row(v, h) of the tile
         f32x16 sct = {0};       // in-tile kernel values, transposed: row = writer token, lane = reader token
@@ -434,7 +442,7 @@ void stream_kernel(KArgs a, const float *Mr, const float *Mw, const bf16raw *Y, 
                 RACE_SCHED_FENCE();
             }
         }
-        if (side == 1) lead(false);
+        if (!kOutputFirst && side == 1) lead(false);
         if (intra) {
             // mask (writer token j = row, reader token i = lane), row sums, and (mask o kernel) . Y
 #pragma unroll
