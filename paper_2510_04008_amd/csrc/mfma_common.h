@@ -134,7 +134,7 @@ struct Soft {
 
 // kernel arguments common to the family
 struct KArgs {
-    int H, nseg, causal;
+    int H, nseg;
     int scanned;           // totals: their segments are scanned (not added up), which leaves the last one's unread
     int hash_tokens;       // tokens per workgroup of the hashing kernel
     int64_t N, seg_len;

@@ -268,9 +268,7 @@ struct StreamLds {
     static_assert(total <= 160 * 1024, "LDS budget");
 };
 
-// NC: the non-causal variant only (the in-tile term and the update are compiled out, which frees registers); the
-// other variant reads the flag at run time (with the flag known to be set the compiler's schedule of the causal
-// kernels needed more registers: the 128-register shapes spilled).
+// NC: not causal (the in-tile term and the update are compiled out).
 // Mr, Mw: the hashed rows of the reader and the writer tensor.
 template <class C, int MODE, bool NC>
 __global__ __launch_bounds__(kThreads, C::STREAM_WAVES_PER_SIMD)
@@ -297,7 +295,7 @@ void stream_kernel(KArgs a, const float *Mr, const float *Mw, const bf16raw *Y, 
     const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, ln = lane & 31, h = lane >> 5;
     const int rg = w % C::RG, cg = w / C::RG;
     const int r_own = rg * C::LRW, c_own = cg * C::DW;
-    const bool intra = NC ? false : (C::STREAM_WAVES_PER_SIMD == 4 ? a.causal != 0 : true);
+    constexpr bool intra = !NC;
 
     const size_t base = static_cast<size_t>(bh) * a.N * C::D;
     const size_t mbase = static_cast<size_t>(bh) * ((a.N + kTile - 1) / kTile) * (kTile * C::LP);
@@ -305,7 +303,7 @@ void stream_kernel(KArgs a, const float *Mr, const float *Mw, const bf16raw *Y, 
     Y += base; Out += base;
     if (MODE == kForward) den_out += static_cast<size_t>(bh) * a.N;
     // statistics at the start of the segment (not causal: the totals, which the scan leaves in the first segment's place)
-    const float *st = a.state + (static_cast<size_t>(bh) * a.nseg + (NC ? 0 : (a.causal ? seg : 0))) * C::STATE;
+    const float *st = a.state + (static_cast<size_t>(bh) * a.nseg + (NC ? 0 : seg)) * C::STATE;
 
     f32x16 Sacc[C::MT][C::NTW];
     float macc[C::MA];                 // bucket masses of row tiles cg, cg + CG, ... (balances the work): lane n <-> row, per-half partial sums
@@ -663,7 +661,7 @@ template <class C>
 KArgs make_kargs(const Plan &p, char *ws)
 {
     KArgs a;
-    a.H = p.H; a.nseg = p.nseg; a.causal = p.causal; a.N = p.N; a.seg_len = p.seg_len; a.beta = p.beta;
+    a.H = p.H; a.nseg = p.nseg; a.N = p.N; a.seg_len = p.seg_len; a.beta = p.beta;
     a.L_real = p.L; a.P_real = p.P;
     a.Wp = reinterpret_cast<const bf16raw *>(ws + p.off_W);
     a.state = reinterpret_cast<float *>(ws + p.off_stateA);
