@@ -506,7 +506,13 @@ __device__ __forceinline__ float row_scale(const GArgs &a, const float *xs, int 
 // thread.  (A tile per wavefront left three of four idle at L = P = 4 and gave the busy one four evaluations a lane.)
 // zp: LDS, 4 x 256 doubles.  Two barriers: before the partial sums are read, and none behind (cs is not visible yet).
 template <int NCT>
-struct PlaneRegs { f32x4 v[4 * NCT]; };         // this lane's share of its hyperplane's row, k-steps of its wavefront's parts
+struct PlaneRegs {                              // this lane's share of its hyperplane's row, k-steps of its wavefront's parts
+    // (With more than 64 columns the first part only; the others are requested one part ahead, under the 8 matrix instructions and more of
+    // the part in front.  All of them at once, next to the rows and the statistics, cost a workgroup per CU and spilled 22 to
+    // 32 registers at 256 columns: fp32, L = P = 4, B H = 32, N = 4096, 114 us for the totals at d = 128 and 220 at 256; 97 and 176 now.)
+    static constexpr int HELD = NCT > 1 ? 1 : 4;
+    f32x4 v[HELD * NCT];
+};
 struct HashSplit {
     int tiles, parts, tile, part0;              // tiles of a pass over the hyperplanes; partial sums of this wavefront: part0 ..
     template <int RT>
@@ -521,38 +527,55 @@ struct HashSplit {
         return h;
     }
 };
+// k-steps of part p of them
+template <int RT, int NCT>
+__device__ __forceinline__ void fetch_part(const GArgs &a, const float *W, int np, const HashSplit &h, int p, f32x4 (&v)[NCT])
+{
+    const int lane = thread_id() & 63, n = lane & 15, q = lane >> 4, pl = 16 * (h.tile / RT) + n;
+    const float *wr = W + static_cast<size_t>(pl < np ? pl : 0) * a.d;
+#pragma unroll
+    for (int j = 0; j < NCT; ++j) {
+        const int c = 16 * (4 * j + h.part0 + p) + 4 * q;
+        v[j] = *reinterpret_cast<const f32x4 *>(wr + (c < a.d ? c : 0));
+    }
+}
 template <int RT, int NCT>
 __device__ __forceinline__ void fetch_planes(const GArgs &a, const float *W, int np, PlaneRegs<NCT> &r)
 {
     const HashSplit h = HashSplit::of<RT>(np);
-    const int lane = thread_id() & 63, n = lane & 15, q = lane >> 4, pl = 16 * (h.tile / RT) + n;
-    const float *wr = W + static_cast<size_t>(pl < np ? pl : 0) * a.d;
 #pragma unroll
-    for (int p = 0; p < 4; ++p) {
-#pragma unroll
-        for (int j = 0; j < NCT; ++j) {
-            const int c = 16 * (4 * j + h.part0 + p) + 4 * q;
-            if (p < h.parts) r.v[p * NCT + j] = *reinterpret_cast<const f32x4 *>(wr + (c < a.d ? c : 0));
-        }
-    }
+    for (int p = 0; p < PlaneRegs<NCT>::HELD; ++p)
+        if (p < h.parts) fetch_part<RT, NCT>(a, W, np, h, p, *reinterpret_cast<f32x4 (*)[NCT]>(r.v + p * NCT));
 }
 template <int RT, int NCT>
-__device__ __forceinline__ void hash_block(const GArgs &a, const PlaneRegs<NCT> &wr, int np, const float *xs, int XS, const float *inv, double *zp,
+__device__ __forceinline__ void hash_block(const GArgs &a, const PlaneRegs<NCT> &wr, const float *W, int np, const float *xs, int XS, const float *inv, double *zp,
                                            float *cs, float *Cx, float *Zx, size_t row0, int pl0, int nst)
 {
     const HashSplit h = HashSplit::of<RT>(np);
     const int lane = thread_id() & 63, n = lane & 15, q = lane >> 4;
     const float *xrow = xs + (16 * (h.tile % RT) + n) * XS + 4 * q;
     f64x4 sum = {0., 0., 0., 0.}, pair = sum;
+    f32x4 next[NCT];
+#pragma unroll
+    for (int j = 0; j < NCT; ++j) next[j] = wr.v[j];
 #pragma unroll
     for (int p = 0; p < 4; ++p) {
         if (p >= h.parts) break;
         f64x4 z0 = {0., 0., 0., 0.}, z1 = z0;
+        f32x4 part[NCT];
+        if constexpr (PlaneRegs<NCT>::HELD == 1) {
+#pragma unroll
+            for (int j = 0; j < NCT; ++j) part[j] = next[j];
+            if (p + 1 < h.parts) fetch_part<RT, NCT>(a, W, np, h, p + 1, next);
+        } else {
+#pragma unroll
+            for (int j = 0; j < NCT; ++j) part[j] = wr.v[p * NCT + j];
+        }
 #pragma unroll
         for (int j = 0; j < NCT; ++j) {
             const int c0 = 16 * (4 * j + h.part0 + p);
             if (c0 >= a.dp) break;
-            const f32x4 x = lds4(xrow + c0), y = wr.v[p * NCT + j];          // (columns beyond d are zeros in xs)
+            const f32x4 x = lds4(xrow + c0), y = part[j];                   // (columns beyond d are zeros in xs)
             z0 = mfma64(x[0], y[0], z0);
             z1 = mfma64(x[1], y[1], z1);
             z0 = mfma64(x[2], y[2], z0);
@@ -605,8 +628,10 @@ struct TotalsLds {
     }
 };
 
+// (Three workgroups per CU where 168 registers do: 192 columns, B H = 8, N = 2048, L = 6, P = 5: 75 us for the totals with two, at 180
+// registers, 66 with three.  256 columns would spill 74: 89 us with two, 112 with three.)
 template <typename T, int RT, int NCT, int SIDE>
-__global__ __launch_bounds__(kThreads, 2) void generic_totals(GArgs a, const T *Xq, const T *Xk, const T *Y, const T *O,
+__global__ __launch_bounds__(kThreads, RT * NCT <= 4 && NCT < 4 ? 3 : 2) void generic_totals(GArgs a, const T *Xq, const T *Xk, const T *Y, const T *O,
                                                               const float *den, float *state)
 {
     extern __shared__ __attribute__((aligned(16))) float lds[];
@@ -652,7 +677,7 @@ __global__ __launch_bounds__(kThreads, 2) void generic_totals(GArgs a, const T *
                     if (b == 0 && row < nv) a.nrm[(query ? 0 : static_cast<size_t>(a.BH) * a.N) + row0 + row] = inv;
                 }
             }
-            hash_block<RT, NCT>(a, wr, np, s.xs, XS, s.inv, reinterpret_cast<double *>(s.ph), s.cs, query ? a.Cq : a.Ck, query ? a.Zq : a.Zk, row0,
+            hash_block<RT, NCT>(a, wr, W, np, s.xs, XS, s.inv, reinterpret_cast<double *>(s.ph), s.cs, query ? a.Cq : a.Ck, query ? a.Zq : a.Zk, row0,
                                 pl0, writes ? nv : 0);
             if (query) continue;
         } else {
@@ -1228,14 +1253,15 @@ __global__ __launch_bounds__(kThreads) void generic_hash_tap(GArgs a, const T *X
     RowRegs<1, 4> x;
     PlaneRegs<4> wr;
     fetch_rows<T, 1, 4>(a, X, row0, nv, x);
-    fetch_planes<1, 4>(a, a.W + (static_cast<size_t>(bh % a.H) * a.LP + pl0) * a.d, np, wr);
+    const float *W = a.W + (static_cast<size_t>(bh % a.H) * a.LP + pl0) * a.d;
+    fetch_planes<1, 4>(a, W, np, wr);
     put_rows<1, 4>(a, x, nv, s.ys, XS);
     __syncthreads();
     if (a.unit) {
         const float inv = row_scale<1>(a, s.ys, XS);
         if (tid % 16 == 0) s.inv[tid / 16] = inv;
     }
-    hash_block<1, 4>(a, wr, np, s.ys, XS, s.inv, reinterpret_cast<double *>(s.ph), s.cs, nullptr, nullptr, 0, 0, 0);
+    hash_block<1, 4>(a, wr, W, np, s.ys, XS, s.inv, reinterpret_cast<double *>(s.ph), s.cs, nullptr, nullptr, 0, 0, 0);
     __syncthreads();
     if (a.bpt == 1 || b % a.bpt == 0) {
         for (int i = tid; i < 16 * a.TB; i += kThreads) {
