@@ -81,3 +81,52 @@ def test_gradient_through_the_cotangents_of_the_masses_alone(shape, causal):
     acc = ErrAcc().update(g["dK"], dK)
     print("%s causal=%s: %s" % (shape, causal, acc), flush=True)
     assert acc.linf < TOL["bf16"] and acc.l2 < TOL["bf16"]
+
+
+@pytest.mark.parametrize("shape", SHAPES, ids=str)
+@pytest.mark.parametrize("causal", [True, False])
+@pytest.mark.parametrize("bit", [10, 16])
+def test_every_part_of_a_weight_counts(shape, causal, bit):
+    """dA where all but the second (bit 10) or third (bit 16) eight bits of the weights cancel: queries come in pairs with the same
+    row, hence the same assignments, and weights -s (1 + 2^-bit) and s.  Without those bits dA, and with V = 0 all of dK, is zero.
+    Only the last 32 queries have cotangents, so that the keys in front of them meet fp32 statistics alone: those of earlier segments
+    the scanned ones, those of earlier tiles of the same segment what the gradient kernel adds to them."""
+    d, L, P = shape
+    w = Workload("parts", 1, 2, 288, d, L, P, 2.0, causal, "bf16", normalize_qk=True, chunk=96)
+    Q, K, V, _ = synth.make_inputs(w, "cuda")
+    first = w.N - 32
+    Q[:, :, first + 1::2] = Q[:, :, first::2]
+    V, dO, O_in = torch.zeros_like(V), torch.zeros_like(V), torch.zeros_like(V)
+    s = torch.tensor([1.0, -2.0, 0.5, -1.0, 4.0, 2.0, -0.25, -4.0, 1.0, 0.5, -2.0, 1.0, -0.5, 4.0, -1.0, 2.0], device="cuda").to(V.dtype)
+    O_in[..., 0], O_in[..., 8] = 1.0, 2.0 ** -(bit // 2)
+    dO[:, :, first::2, 0], dO[:, :, first::2, 8], dO[:, :, first + 1::2, 0] = s, s * 2.0 ** -(bit // 2), -s
+    seeds = synth.projection_seeds(w)
+    _, _, ctx = oracle_forward(w, Q, K, V, seeds)
+    den_in = torch.full((1, 2, w.N), 1.0 / L, dtype=torch.float32, device="cuda")          # dO / (L Den) is dO itself
+    g = run_gpu(w, (Q, K, V, dO), fwd_results=lambda O, den: (O_in, den_in))
+    _, dK, _ = oracle_backward(w, ctx, to_f64(O_in), to_f64(den_in), dO)
+    for part in (slice(0, 192), slice(192, first)):
+        acc = ErrAcc().update(g["dK"][:, :, part], dK[:, :, part])
+        print("%s causal=%s bit %d, keys %s: %s" % (shape, causal, bit, part, acc), flush=True)
+        assert acc.linf < TOL["bf16"] and acc.l2 < TOL["bf16"]
+
+
+@pytest.mark.parametrize("shape", SHAPES, ids=str)
+@pytest.mark.parametrize("unit", [False, True])
+@pytest.mark.parametrize("value", [float("inf"), float("nan")])
+def test_a_non_finite_key_has_finite_assignments(shape, unit, value):
+    """... so that two tables that share a column of a matrix product cannot disturb one another."""
+    d, L, P = shape
+    w = Workload("key", 1, 1, 100, d, L, P, 2.0, True, "bf16", normalize_qk=True, chunk=96)
+    _, K, V, _ = synth.make_inputs(w, "cuda")
+    K2 = K.clone()
+    K2[0, 0, 37, 5] = value
+    desc = ra.make_desc(1, 1, w.N, d, L, P, 2.0, True, ra.RACE_BF16, 96, unit)
+    seeds = synth.projection_seeds(w)
+    _, phi = ra.race_attn_debug_hash(desc, K, seeds, want_phi=True)
+    _, phi2 = ra.race_attn_debug_hash(desc, K2, seeds, want_phi=True)
+    others = [i for i in range(w.N) if i != 37]
+    assert torch.isfinite(phi2).all() and torch.equal(phi2[:, :, others], phi[:, :, others])
+    A, B = ra.race_attn_debug_buckets(desc, K2, V, seeds)
+    ref = phi2.double().sum(dim=2)
+    assert torch.isfinite(B).all() and ((A.double() - ref).abs() <= w.N * 2.0 ** -24 * ref).all()

@@ -37,3 +37,22 @@ def test_an_infinity_stays_in_its_column(case):
     assert torch.equal(g["O"][..., cols], ref["O"][..., cols]) and torch.equal(g["den"], ref["den"])
     assert (g["O"][0, 0, :, 3] == float("inf")).all()
     assert torch.equal(g["dV"], ref["dV"])
+
+
+@pytest.mark.parametrize("case", CASES[:4], ids=str)
+@pytest.mark.parametrize("causal", [True, False])
+def test_an_infinite_cotangent_stays_in_its_column(case, causal):
+    """The same for the read-out of the cotangent statistics: dV's column is an infinity, not the NaN of a zero times one."""
+    B, H, N, d, L, P = case
+    w = Workload("inf", B, H, N, d, L, P, 2.0, causal, "f32", normalize_qk=True)
+    Q, K, V, dO = synth.make_inputs(w, "cuda")
+    ref = run_gpu(w, (Q, K, V, dO))
+    i = N // 2
+    dO2 = dO.clone()
+    dO2[0, 0, i, 3] = float("inf")
+    g = run_gpu(w, (Q, K, V, dO2))
+    last = i + 1 if causal else N                                   # tokens whose value the query reads
+    cols = [c for c in range(d) if c != 3]
+    assert torch.equal(g["dV"][..., cols], ref["dV"][..., cols]) and torch.equal(g["dV"][0, 0, last:], ref["dV"][0, 0, last:])
+    assert torch.equal(g["dV"][0, 1:], ref["dV"][0, 1:])
+    assert (g["dV"][0, 0, :last, 3] == float("inf")).all()
