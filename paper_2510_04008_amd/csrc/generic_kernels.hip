@@ -14,8 +14,8 @@
 // workgroup, hence three launches forward (totals with the hashing, scan, output), three backward (totals, scan, all
 // three gradients), tiles of 16 tokens until they fill the chip, and all loads of a tile requested together.  Measured
 // forward + backward (B = H = 1, N = 1024, d = 64, L = P = 4, fp32, not causal): 337 us with a token-at-a-time kernel per
-// table, 41 with the loads of a tile under conditions, one trip to memory after the other, 35 now (B = 2, H = 4, N = 2003, causal:
-// 98 -> 82; bf16, B = 2, H = 8, N = 1024, d = 32: 75 -> 61; B = 2, H = 4, N = 3501, d = 128, L = 6, P = 5: 485 -> 381).
+// table, 41 with the loads of a tile under conditions, one trip to memory after the other, 34 now (B = 2, H = 4, N = 2003, causal:
+// 96 -> 79; bf16, B = 2, H = 8, N = 1024, d = 32: 76 -> 62; fp32, B = 2, H = 4, N = 3501, d = 128, L = 6, P = 5: 477 -> 360).
 //
 // Matrix operand layouts (lane = 16 q + n): A: row n, k = q; B: column n, k = q; C/D: column n, rows 4 q + v in register v.
 // Four consecutive k-steps take k = 4 q + v, v = 0..3, so that an operand whose k axis runs along a row of LDS is one

@@ -271,7 +271,8 @@ __device__ __forceinline__ float sum_rows4(float x0, float x1, float x2, float x
 // operand whose rows 4 q + 0 .. 2 hold the weights in slots 8 q .. and zeros in the others keeps them apart: D register v of lane
 // 32 h + n is the sum over tokens 8 h .. of bucket row n with weight part v.  With rows 0 .. 2 holding them in slots 0 .. 7 and
 // 16 .. 23 and rows 4 .. 6 in the others the halves of the tokens are added up too, lane n < 32 gets the sum (`whole`).  fp32
-// weights enter as three bf16 parts (truncated, 8 bits each: exact), weights of one as a single part.  (One 16-cycle matrix
+// weights enter as three bf16 parts (truncated, 8 bits each: exact from about 2^-110 up, below which the last bits of the third part
+// are lost), weights of one as a single part.  (One 16-cycle matrix
 // instruction in place of 16 vector ones; both totals kernels spent 128 of their 320-450 vector instructions a step on these sums.)
 constexpr int kParts = 4;                       // rows of a [kParts][tokens] bf16 array of weight parts; the last one is zeros
 __device__ __forceinline__ bf16raw weight_part(float x, int i)

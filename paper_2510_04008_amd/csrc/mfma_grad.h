@@ -97,8 +97,8 @@ struct GradLds {
 
 // Wavefronts per SIMD the gradient kernel is compiled for: four (128 registers, two workgroups per CU, whose phases
 // interleave) where the statistics do not change, 32 registers hold a wavefront's share of them and the tiles fit 80 KB.
-// The causal variant wants 135 to 165 registers at its smallest: held to 128 it spills and takes 1.6 times as long (4.2 million
-// rows of 128 columns at L = P = 4: 1.67 ms for dQ instead of 1.06 ms).
+// The causal variants are compiled for two.  Those of (128, 4, 4) fit a CU twice all the same, at 120 to 127 registers; (128, 4, 8)
+// takes 133 to 136 and (64, 4, 16) 139 to 144.  (Kernels that wanted 139 spilled when they were held to 128 and took 1.6 times as long.)
 template <class C, bool UNIT, bool INTRA>
 constexpr int grad_waves_per_simd()
 {
@@ -337,7 +337,7 @@ void grad_kernel(KArgs a, const bf16raw *Xr, const bf16raw *V, const bf16raw *G_
     };
 
     if (G::T16 && w >= 4) lead(true);       // (R = 16: all along; handing the lead back half way through the tables is slower)
-    float dbeta_acc = 0.f;    // this lane's share of the cotangent of beta: sum of (E_t - m (p_t - q_t)) tanh z_t
+    float dbeta_acc = 0.f;    // this lane's share of the cotangent of beta: sum of 2 p_t q_t E_t tanh z_t
     for (int it = 0; it < ntiles; ++it) {
         const int64_t t0 = tile_t0(it);
         const int nvalid = tile_nv(t0);

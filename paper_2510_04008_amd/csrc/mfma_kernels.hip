@@ -3,12 +3,11 @@
 // Kernels
 //   hash_kernel      projection and per-bit soft-hash masses of every row of Q and K, once per call: the "hashed rows"
 //                    (one float per token, table and hyperplane) that every later pass rebuilds phi from.
-//   totals_kernel    statistics of every segment from a zero start; an exclusive prefix (forward) or suffix (backward)
+//   totals_kernel    statistics of every segment from a zero start, of (phi_K, [V | 1]) (Algorithm 1, step 5) or, for the
+//                    backward pass, of (phi_Q, read-out cotangents); an exclusive prefix (forward) or suffix (backward)
 //                    scan over segments (scan_states) turns them into segment-start states.
 //   stream_kernel    one pass over a segment carrying statistics [L*R][d] in accumulator registers
 //                    as tiles (bucket rows x head columns).  Modes:
-//                      kTotalsKV  statistics of (phi_K, [V | 1])          (Algorithm 1, step 5)
-//                      kTotalsQG  statistics of (phi_Q, read-out cotangents) for the backward pass
 //                      kForward   Algorithm 2's loop / Algorithm 1's read-out: O and Den
 //                      kGradV     the mirrored pass, right to left: dV
 //   grad_kernel      (mfma_grad.h) the passes that contract over the head dimension: dQ and dK.
@@ -23,7 +22,7 @@
 namespace race {
 namespace mfma {
 
-enum Mode { kTotalsKV = 0, kTotalsQG = 1, kForward = 2, kGradV = 3 };
+enum Mode { kForward, kGradV };
 
 // state element (bucket row r, column c) in the saved layout: B [LR][D] row-major, then A [LR]
 template <class C>
@@ -507,8 +506,8 @@ void stream_kernel(KArgs a, const float *Mr, const float *Mw, const bf16raw *Y, 
 
 // Totals over all segments of the problem's own buckets, written as A[row * a_stride] and
 // Bsum[row * b_stride + c] with row = (bh * L_real + l) * R_real + r.  Real corner r of a real table sits at
-// the compiled corner with all padding bits set.  `groups` (a power of two) threads share an element's segments, up to eight each,
-// whose loads are requested together.  (Bound by memory; one thread per element adding up 63 segments alone is bound by its chain of
+// the compiled corner with all padding bits set.  `groups` (a power of two, at most eight) threads share an element's segments and
+// add them up in runs of eight, whose loads are requested together; more than 64 segments take several runs a thread.  (Bound by memory; one thread per element adding up 63 segments alone is bound by its chain of
 // loads: 22.7 us at B H = 4, 264 KB a state.  Where there is one segment, as with many heads, a second thread has nothing to add.
 // State of a prompt, one thread an element -> this: 4 x 30011 tokens 74.9 -> 67.6 us, 256 x 4096 320 -> 309 us.)
 constexpr int kTapThreads = 512, kTapRun = 8, kTapMaxGroups = kTapThreads / 64;
@@ -706,7 +705,7 @@ template <class C, int MODE>
 hipError_t launch_stream(const Plan &p, KArgs a, const float *Mr, const float *Mw, const void *Y, void *Out, float *den_out,
                          hipStream_t st)
 {
-    static const char *const names[] = {"stream_totals_kv", "stream_totals_qg", "stream_forward", "stream_grad_v"};
+    static const char *const names[] = {"stream_forward", "stream_grad_v"};
     auto kern = p.causal ? stream_kernel<C, MODE, false> : stream_kernel<C, MODE, true>;
     RACE_TRY(allow_lds(kern, StreamLds<C>::total));
     ProfileScope prof(names[MODE], st);

@@ -208,10 +208,11 @@ ProfileScope::~ProfileScope()
 // where B H divides the chip badly), short ones at the balance of the two terms.  Where the second round's states are
 // less than a hundredth of the whole (512 bucket rows: from 10^6 tokens at B H = 4), two rounds: segments half as long, so
 // that their boundaries stay where callers of race_attn_segment_tokens have had them and a late workgroup delays half as much.
-// The two times are fits to sweeps over segment lengths of training
-// steps, us: at 512 bucket rows of 128 columns 22 and 0.31 (B H = 16, N = 1000: 279, 197, 167, 170, 180 us at 11, 6, 4, 3, 2
-// tiles), at 64 bucket rows 11.5 and 0.04.  Shapes whose stream kernels fit a CU twice take two workgroups per CU once those
-// have a dozen tiles each (64 bucket rows, B H = 64, N = 16384: 1619 -> 1470 us); before that the gradient kernels, which fit
+// The two times are fits to sweeps over segment lengths of training steps, us: at 512 bucket rows of 128 columns 22 and 0.31, at 64
+// bucket rows 11.5 and 0.04.  They were made with kernels whose tiles took about 7 % longer; the present ones have their
+// minimum in the same place (512 bucket rows, B H = 16, N = 1000: 237, 171, 151, 152, 165 us at 11, 6, 4, 3, 2 tiles, the rule's choice
+// 151; N = 4096: 294, 406, 430 at 8, 6, 4, the rule's 297; 64 bucket rows, N = 1000: 67, 63, 60, 70 at 4, 3, 2, 1, the rule's 60).  Shapes whose stream kernels fit a CU twice take two workgroups per CU once those
+// have a dozen tiles each (64 bucket rows, B H = 64, N = 16384, when the rule was made: 1619 -> 1470 us); before that the gradient kernels, which fit
 // once, would run a second, nearly empty round.
 static int64_t mfma_segment_tokens(const Plan &p)
 {
