@@ -56,3 +56,11 @@ def test_an_infinite_cotangent_stays_in_its_column(case, causal):
     assert torch.equal(g["dV"][..., cols], ref["dV"][..., cols]) and torch.equal(g["dV"][0, 0, last:], ref["dV"][0, 0, last:])
     assert torch.equal(g["dV"][0, 1:], ref["dV"][0, 1:])
     assert (g["dV"][0, 0, :last, 3] == float("inf")).all()
+
+
+@pytest.mark.parametrize("d", [72, 136, 200, 256])
+@pytest.mark.parametrize("shape", [(1, 2, 45), (8, 8, 300)], ids=["tiles16", "tiles32"])
+@pytest.mark.parametrize("L,P", [(3, 2), (9, 3)])
+def test_wide_rows_take_their_hyperplanes_part_by_part(d, shape, L, P):
+    """More than 64 columns: 6, 24 and 3 hyperplanes a block, i.e. one, two and four parts of a hyperplane's row per wavefront."""
+    check_case(Workload("wide", *shape, d, L, P, 2.0, True, "f32", normalize_qk=True), saved=True)
