@@ -527,25 +527,25 @@ struct HashSplit {
         return h;
     }
 };
-// k-steps of part p of them
-template <int RT, int NCT>
-__device__ __forceinline__ void fetch_part(const GArgs &a, const float *W, int np, const HashSplit &h, int p, f32x4 (&v)[NCT])
+// COUNT parts of them from p0 on, as far as there are such
+template <int RT, int NCT, int COUNT>
+__device__ __forceinline__ void fetch_parts(const GArgs &a, const float *W, int np, const HashSplit &h, int p0, f32x4 (&v)[COUNT * NCT])
 {
     const int lane = thread_id() & 63, n = lane & 15, q = lane >> 4, pl = 16 * (h.tile / RT) + n;
     const float *wr = W + static_cast<size_t>(pl < np ? pl : 0) * a.d;
 #pragma unroll
-    for (int j = 0; j < NCT; ++j) {
-        const int c = 16 * (4 * j + h.part0 + p) + 4 * q;
-        v[j] = *reinterpret_cast<const f32x4 *>(wr + (c < a.d ? c : 0));
+    for (int p = 0; p < COUNT; ++p) {
+#pragma unroll
+        for (int j = 0; j < NCT; ++j) {
+            const int c = 16 * (4 * j + h.part0 + p0 + p) + 4 * q;
+            if (p0 + p < h.parts) v[p * NCT + j] = *reinterpret_cast<const f32x4 *>(wr + (c < a.d ? c : 0));
+        }
     }
 }
 template <int RT, int NCT>
 __device__ __forceinline__ void fetch_planes(const GArgs &a, const float *W, int np, PlaneRegs<NCT> &r)
 {
-    const HashSplit h = HashSplit::of<RT>(np);
-#pragma unroll
-    for (int p = 0; p < PlaneRegs<NCT>::HELD; ++p)
-        if (p < h.parts) fetch_part<RT, NCT>(a, W, np, h, p, *reinterpret_cast<f32x4 (*)[NCT]>(r.v + p * NCT));
+    fetch_parts<RT, NCT, PlaneRegs<NCT>::HELD>(a, W, np, HashSplit::of<RT>(np), 0, r.v);
 }
 template <int RT, int NCT>
 __device__ __forceinline__ void hash_block(const GArgs &a, const PlaneRegs<NCT> &wr, const float *W, int np, const float *xs, int XS, const float *inv, double *zp,
@@ -555,27 +555,27 @@ __device__ __forceinline__ void hash_block(const GArgs &a, const PlaneRegs<NCT> 
     const int lane = thread_id() & 63, n = lane & 15, q = lane >> 4;
     const float *xrow = xs + (16 * (h.tile % RT) + n) * XS + 4 * q;
     f64x4 sum = {0., 0., 0., 0.}, pair = sum;
+    constexpr bool kAhead = PlaneRegs<NCT>::HELD == 1;
     f32x4 next[NCT];
+    if (kAhead) {
 #pragma unroll
-    for (int j = 0; j < NCT; ++j) next[j] = wr.v[j];
+        for (int j = 0; j < NCT; ++j) next[j] = wr.v[j];
+    }
 #pragma unroll
     for (int p = 0; p < 4; ++p) {
         if (p >= h.parts) break;
         f64x4 z0 = {0., 0., 0., 0.}, z1 = z0;
         f32x4 part[NCT];
-        if constexpr (PlaneRegs<NCT>::HELD == 1) {
+        if constexpr (kAhead) {
 #pragma unroll
             for (int j = 0; j < NCT; ++j) part[j] = next[j];
-            if (p + 1 < h.parts) fetch_part<RT, NCT>(a, W, np, h, p + 1, next);
-        } else {
-#pragma unroll
-            for (int j = 0; j < NCT; ++j) part[j] = wr.v[p * NCT + j];
+            fetch_parts<RT, NCT, 1>(a, W, np, h, p + 1, next);
         }
 #pragma unroll
         for (int j = 0; j < NCT; ++j) {
             const int c0 = 16 * (4 * j + h.part0 + p);
             if (c0 >= a.dp) break;
-            const f32x4 x = lds4(xrow + c0), y = part[j];                   // (columns beyond d are zeros in xs)
+            const f32x4 x = lds4(xrow + c0), y = kAhead ? part[j] : wr.v[kAhead ? 0 : p * NCT + j];          // (columns beyond d are zeros in xs)
             z0 = mfma64(x[0], y[0], z0);
             z1 = mfma64(x[1], y[1], z1);
             z0 = mfma64(x[2], y[2], z0);
@@ -629,9 +629,9 @@ struct TotalsLds {
 };
 
 // (Three workgroups per CU where 168 registers do: 192 columns, B H = 8, N = 2048, L = 6, P = 5: 75 us for the totals with two, at 180
-// registers, 66 with three.  256 columns would spill 74: 89 us with two, 112 with three.)
+// registers, 66 with three.  256 columns would spill 74: 89 us with two, 112 with three.  64 columns take 115 by themselves.)
 template <typename T, int RT, int NCT, int SIDE>
-__global__ __launch_bounds__(kThreads, RT * NCT <= 4 && NCT < 4 ? 3 : 2) void generic_totals(GArgs a, const T *Xq, const T *Xk, const T *Y, const T *O,
+__global__ __launch_bounds__(kThreads, RT * NCT <= 4 && NCT < 4 && NCT > 1 ? 3 : 2) void generic_totals(GArgs a, const T *Xq, const T *Xk, const T *Y, const T *O,
                                                               const float *den, float *state)
 {
     extern __shared__ __attribute__((aligned(16))) float lds[];
