@@ -24,7 +24,7 @@
 // LDS bank arithmetic as measured on gfx950 (64 banks of 4 bytes, 256 bytes per clock for reads: 16-byte
 // accesses go 16 lanes at a time, 8-byte ones 32 lanes): rows read 16 bytes per lane want a row stride of
 // 4 mod 64 words; tiles read through the transposing 8-byte loads (per 16 lanes 4 rows x 32 bytes, the
-// next 16 lanes 32 bytes further) want 16 mod 32 words.
+// next 16 lanes 32 bytes further) want 16 mod 32 words, or rows at spread_row() under 4 mod 64.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -67,6 +67,7 @@ struct Cfg {
     static constexpr int NTW = NT / CG;                 // column tiles per wavefront
     static constexpr int DW = D / CG;                   // columns per wavefront
     static constexpr int MA = (MT + CG - 1) / CG;       // row tiles whose extra column a wavefront carries
+    static_assert(MT == 1 || MT % CG == 0, "row tiles over the column groups");
     // wavefronts per SIMD the stream and totals kernels are compiled for: shapes with at most two accumulator
     // tiles of statistics and one column tile per wavefront fit 128 registers and leave room for a second workgroup
     // on the CU, whose phases interleave with the first one's (measured: with two column tiles the kernels spill
@@ -77,9 +78,9 @@ struct Cfg {
     // LDS row strides, in bf16 elements (rows stay 16-byte aligned; the pad staggers banks)
     static constexpr int XS = D + 8;                    // [token][d] tiles and W rows, read by rows
     static constexpr int YS = D + 32;                   // [token][d] tiles read through transposing loads
-    static constexpr int PS = LR + 8;                   // [token][L*R] assignment tiles, read by rows
-    static constexpr int PST = LR + 16;                 // ... read through transposing loads only (a compromise:
-                                                        // 16-byte row writes and transposing reads both 2-way at most)
+    static constexpr int PS = LR + 8;                   // [token][L*R] assignment tiles, rows at spread_row() of the token
+    static constexpr int PST = LR + 16;                 // ... rows in order, read through the 16-row transposing loads (16-byte row
+                                                        // writes and transposing reads both 2-way at most)
     static constexpr int STATE = LR * (D + 1);          // floats per saved state: B [LR][D] then A [LR]
     // hashed form of a row (see bit_code()): one float per (table, hyperplane).  In memory a tile of 32 tokens is
     // [table][32 tokens][4 hyperplanes], for P = 6 followed per table by [32 tokens][2 hyperplanes], so that a half
@@ -116,10 +117,19 @@ __device__ __forceinline__ void wait_loads() { __builtin_amdgcn_s_waitcnt(0x0F70
 
 // Hides the value of an index from the optimiser inside a loop body, so that the dozens of addresses
 // derived from it (index + constant) are folded into instruction offsets instead of being hoisted out of
-// the loop as separate loop-invariant registers (which then spill).
-__device__ __forceinline__ int opaque(int x)
+// the loop as separate loop-invariant registers (which then spill).  `step` is the loop's counter: a value that depends on it
+// cannot leave the loop.  (Not as a volatile statement: no load or store is moved across one of those, which left every LDS read
+// where it was written, its latency in front of its use.)
+__device__ __forceinline__ int opaque(int x, int step)
 {
-    asm volatile("" : "+v"(x));
+    asm("" : "+v"(x) : "s"(step));
+    return x;
+}
+// The same for a uniform value: what is added to it is added again in every pass of the loop (one instruction), not kept in a
+// register of its own per sum.
+__device__ __forceinline__ int opaque_uniform(int x, int step)
+{
+    asm("" : "+s"(x) : "s"(step));
     return x;
 }
 
@@ -138,7 +148,7 @@ struct KArgs {
     int scanned;           // totals: their segments are scanned (not added up), which leaves the last one's unread
     int hash_tokens;       // tokens per workgroup of the hashing kernel
     int64_t N, seg_len;
-    float beta;
+    float beta, inv_tables;
     int L_real, P_real;    // the problem's tables and hyperplanes (<= the compiled shape's)
     __host__ __device__ Soft soft() const { return Soft{beta, L_real, P_real}; }
     const bf16raw *Wp;     // (H, LPP, D) bf16, rows in projection-group order
@@ -201,26 +211,32 @@ __device__ __forceinline__ constexpr int il(int c) { return (c & ~12) | ((c & 4)
 typedef __attribute__((ext_vector_type(4))) short s16x4;
 typedef s16x4 __attribute__((address_space(3))) lds_s16x4;
 // IL: the tile's columns are pair-interleaved (the chunk of logical columns 4c.. sits at 4 * swap(c)).
-template <bool IL = false>
+// SPREAD: its rows are at spread_row(): the four rows of a block lie four apart, 16 banks under a stride of 4 mod 64 words, which
+// suits reads by rows and transposing reads alike (64 KB read by transposing loads: 256 cycles; with the rows in order 1024 under
+// that stride, 512 under 8 mod 64 words).
+__device__ __forceinline__ constexpr int spread_row(int r) { return (r & ~15) | ((r & 3) << 2) | ((r >> 2) & 3); }
+template <bool IL = false, bool SPREAD = false>
 __device__ __forceinline__ u32x4 lds_tr8(const bf16raw *M, int stride, int k0a, int k0b, int n0, int ln)
 {
     const int sub = ln & 15;
     const int chunk = IL ? (((sub & 1) << 1) | ((sub >> 1) & 1)) : (sub & 3);
-    const bf16raw *p = M + (sub >> 2) * stride + n0 + 16 * (ln >> 4) + 4 * chunk;
-    const s16x4 a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(p + k0a * stride));
-    const s16x4 b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(p + k0b * stride));
+    const bf16raw *p = M + (SPREAD ? 4 : 1) * (sub >> 2) * stride + n0 + 16 * (ln >> 4) + 4 * chunk;
+    const s16x4 a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(p + (SPREAD ? spread_row(k0a) : k0a) * stride));
+    const s16x4 b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(p + (SPREAD ? spread_row(k0b) : k0b) * stride));
     const u32x2 ua = __builtin_bit_cast(u32x2, a), ub = __builtin_bit_cast(u32x2, b);
     return u32x4{ua.x, ua.y, ub.x, ub.y};
 }
-// k-slots in plain order (rows k0 + 8h + 0..7) or in accumulator order (pairs with acc_operand)
-template <bool IL = false>
+// k-slots in plain order (rows k0 + 8h + 0..7) or in accumulator order (pairs with acc_operand); k0: a multiple of 16
+template <bool IL = false, bool SPREAD = false>
 __device__ __forceinline__ u32x4 lds_tr_plain(const bf16raw *M, int stride, int k0, int n0, int ln, int h)
 {
+    if (SPREAD) return lds_tr8<IL, true>(M + (k0 + 2 * h) * stride, stride, 0, 4, n0, ln);
     return lds_tr8<IL>(M, stride, k0 + 8 * h, k0 + 8 * h + 4, n0, ln);
 }
-template <bool IL = false>
+template <bool IL = false, bool SPREAD = false>
 __device__ __forceinline__ u32x4 lds_tr_acc(const bf16raw *M, int stride, int k0, int n0, int ln, int h)
 {
+    if (SPREAD) return lds_tr8<IL, true>(M + (k0 + h) * stride, stride, 0, 8, n0, ln);
     return lds_tr8<IL>(M, stride, k0 + 4 * h, k0 + 8 + 4 * h, n0, ln);
 }
 
@@ -363,10 +379,31 @@ __device__ __forceinline__ void store_chunk(bf16raw *dst, int row, int ch, u32x4
     }
 }
 
-template <class C, int ROWS, int STRIDE = C::XS, int IL = kPlain>
-__device__ __forceinline__ void store_rows(const RowChunks<C, ROWS> &r, bf16raw *dst)
+// ... of a 32-row tile, every thread's chunk at the byte offset `at` from the tile (its place under STRIDE, worked out once per kernel).
+template <class C, int STRIDE, int IL>
+__device__ __forceinline__ int chunk_offset(int tid)
 {
-    const uint32_t tid = opaque(static_cast<int>(threadIdx.x)) & (kThreads - 1);      // keeps the tile addresses out of long-lived registers
+    const int row = tid / C::CPR, ch = tid % C::CPR;
+    return (row * STRIDE + (IL == kPlain ? 8 * ch : IL == kPairs16 ? 16 * (ch >> 1) + 4 * (ch & 1) : 32 * (ch >> 2) + 16 * (ch & 1) + 4 * ((ch >> 1) & 1))) * 2;
+}
+template <class C, int IL>
+__device__ __forceinline__ void store_tile(const RowChunks<C, kTile> &r, unsigned char *at)
+{
+    static_assert(RowChunks<C, kTile>::N == 1, "one chunk per thread at most");
+    if (!RowChunks<C, kTile>::EVEN && threadIdx.x >= kTile * C::CPR) return;
+    const u32x4 v = r.v[0];
+    if (IL == kPlain) {
+        *reinterpret_cast<u32x4 *>(at) = v;
+    } else {
+        *reinterpret_cast<u32x2 *>(at) = u32x2{v.x, v.y};
+        *reinterpret_cast<u32x2 *>(at + 16) = u32x2{v.z, v.w};
+    }
+}
+
+template <class C, int ROWS, int STRIDE = C::XS, int IL = kPlain>
+__device__ __forceinline__ void store_rows(const RowChunks<C, ROWS> &r, bf16raw *dst, int step)
+{
+    const uint32_t tid = opaque(static_cast<int>(threadIdx.x), step) & (kThreads - 1);      // keeps the tile addresses out of long-lived registers
 #pragma unroll
     for (int k = 0; k < RowChunks<C, ROWS>::N; ++k) {
         const uint32_t c = tid + k * kThreads, row = c / C::CPR, ch = c % C::CPR;
@@ -378,9 +415,9 @@ __device__ __forceinline__ void store_rows(const RowChunks<C, ROWS> &r, bf16raw 
 // rows held in r, from the fp32 sum of squares of the stored elements.  (Rows past the end of a tile hold a copy of
 // the last real row.)
 template <class C, int ROWS>
-__device__ __forceinline__ void store_row_scales(const RowChunks<C, ROWS> &r, float *scale)
+__device__ __forceinline__ void store_row_scales(const RowChunks<C, ROWS> &r, float *scale, int step)
 {
-    const int tid = opaque(static_cast<int>(threadIdx.x));
+    const int tid = opaque(static_cast<int>(threadIdx.x), step);
 #pragma unroll
     for (int k = 0; k < RowChunks<C, ROWS>::N; ++k) {
         const int c = tid + k * kThreads, row = c / C::CPR, ch = c % C::CPR;
@@ -421,9 +458,9 @@ __device__ __forceinline__ void fetch_cotangent(const bf16raw *dO, const bf16raw
 // passes read them back as plain rows.  ge_parts: [kParts][ROWS], see weight_part().
 template <class C, int ROWS, int STRIDE>
 __device__ __forceinline__ void store_cotangent(const CotChunks<C, ROWS> &r, bf16raw *dst, bf16raw *ge_parts, int L_real, int nvalid,
-                                                bf16raw *Gout, float *ge_out, int64_t t0)
+                                                bf16raw *Gout, float *ge_out, int64_t t0, int step)
 {
-    const int tid = opaque(static_cast<int>(threadIdx.x));
+    const int tid = opaque(static_cast<int>(threadIdx.x), step);
     char *gbase = reinterpret_cast<char *>(Gout + t0 * C::D);
 #pragma unroll
     for (int k = 0; k < RowChunks<C, ROWS>::N; ++k) {
@@ -526,11 +563,11 @@ struct Share {
 // 3.., b: bits 0..2), corners pair-interleaved: the 16 corners of high-bit indices (a, a+1), a even, are stored as
 // [a: b 0..3 | a+1: b 0..3 | a: b 4..7 | a+1: b 4..7].
 // valid == false writes zeros (a token past the end of the sequence must not reach the statistics).
-// If mass != null (bucket masses in the same pair-interleaved order), returns sum_r phi[r] * mass[r] over what was written
-// (the read-out of the bucket masses A by this token, i.e. its share of the normaliser).
-template <class C, int SLOTS, int STRIDE>
+// MASS: returns sum_r phi[r] * mass[r] over what was written (bucket masses in the same pair-interleaved order): the read-out of the
+// bucket masses A by this token, i.e. its share of the normaliser.  (As a test of the pointer every use of it was a branch.)
+template <class C, int SLOTS, int STRIDE, bool MASS = false>
 __device__ __forceinline__ float produce(const typename Share<C, SLOTS>::Regs &codes, int slot, int row, const Soft &sf, bool valid,
-                                         bf16raw *ph, const float *mass = nullptr)
+                                         bf16raw *ph, int step, const float *mass = nullptr)
 {
     using Sh = Share<C, SLOTS>;
     static_assert(C::PLO == 3 && C::PHI >= 1, "eight low corners per high-bit index, indices in pairs");
@@ -538,14 +575,14 @@ __device__ __forceinline__ float produce(const typename Share<C, SLOTS>::Regs &c
     // two shares of a table: halves of the high-bit indices if there are two pairs of them, else of the low corners
     constexpr bool kSplitA = Sh::PARTS == 2 && C::PHI >= 2;
     const int part = Sh::part(slot);
-    float dn = 0.f;
-    if (part >= Sh::PARTS) return dn;
+    float dn[4] = {0.f, 0.f, 0.f, 0.f};
+    if (part >= Sh::PARTS) return 0.f;
 #pragma unroll
     for (int i = 0; i < Sh::NTAB; ++i) {
         const int table = Sh::table(slot, i);
         const bool live = valid && (!C::PAD || table < sf.L);     // (a padding table: zero assignments)
-        const int tbase = opaque(table * C::R);                   // one base register, constants folded into offsets
-        bf16raw *prow = ph + opaque(row * STRIDE);
+        const int tbase = opaque(table * C::R, step);                   // one base register, constants folded into offsets
+        bf16raw *prow = ph + opaque(row * STRIDE, step);
         float p[C::P], q[C::P], lo[8], hi[NA];
 #pragma unroll
         for (int t = 0; t < C::P; ++t) code_masses(codes.c[i][t], p[t], q[t]);
@@ -572,11 +609,12 @@ __device__ __forceinline__ float produce(const typename Share<C, SLOTS>::Regs &c
 #pragma unroll
             for (int i = 0; i < 4; ++i) next[i] = *reinterpret_cast<const float4 *>(mass + tbase + abase + a * 8 + 4 * i);
         };
-        if (mass) load_masses(0);
+        if (MASS) load_masses(0);
 #pragma unroll
         for (int a = 0; a < kA; a += 2) {
+            const float ha[2] = {hi[a], hi[a + 1]};
             float4 mq[4];
-            if (mass) {
+            if (MASS) {
 #pragma unroll
                 for (int i = 0; i < 4; ++i) mq[i] = next[i];
                 if (a + 2 < kA) load_masses(a + 2);
@@ -588,19 +626,58 @@ __device__ __forceinline__ float produce(const typename Share<C, SLOTS>::Regs &c
                 const float4 m0 = mq[2 * half], m1 = mq[2 * half + 1];
                 float f[8];
 #pragma unroll
-                for (int b = 0; b < 4; ++b) { f[b] = hi[a] * lo[4 * half + b]; f[4 + b] = hi[a + 1] * lo[4 * half + b]; }
-                if (mass) {
-                    dn = fmaf(f[0], m0.x, dn); dn = fmaf(f[1], m0.y, dn); dn = fmaf(f[2], m0.z, dn); dn = fmaf(f[3], m0.w, dn);
-                    dn = fmaf(f[4], m1.x, dn); dn = fmaf(f[5], m1.y, dn); dn = fmaf(f[6], m1.z, dn); dn = fmaf(f[7], m1.w, dn);
+                for (int b = 0; b < 4; ++b) { f[b] = ha[0] * lo[4 * half + b]; f[4 + b] = ha[1] * lo[4 * half + b]; }
+                if (MASS) {
+                    dn[0] = fmaf(f[0], m0.x, dn[0]); dn[1] = fmaf(f[1], m0.y, dn[1]); dn[2] = fmaf(f[2], m0.z, dn[2]); dn[3] = fmaf(f[3], m0.w, dn[3]);
+                    dn[0] = fmaf(f[4], m1.x, dn[0]); dn[1] = fmaf(f[5], m1.y, dn[1]); dn[2] = fmaf(f[6], m1.z, dn[2]); dn[3] = fmaf(f[7], m1.w, dn[3]);
                 }
                 *reinterpret_cast<u32x4 *>(prow + pos) =
                     u32x4{pack2(f[0], f[1]), pack2(f[2], f[3]), pack2(f[4], f[5]), pack2(f[6], f[7])};
             }
+            if (MASS) asm volatile("" : "+v"(dn[0]), "+v"(dn[1]), "+v"(dn[2]), "+v"(dn[3]));    // (else the sums wait, with all products and masses, for the last pair)
             RACE_SCHED_FENCE();
         }
     }
-    return dn;
+    return (dn[0] + dn[1]) + (dn[2] + dn[3]);
 }
+
+// One table's assignments of 32 tokens by the wavefront that uses them (lane = token ln, half h of the corners: bit 2 is h), into
+// its own columns of ph.
+template <class C, int STRIDE>      // (rows at spread_row())
+__device__ __forceinline__ void produce_table(const float (&c)[C::P], int table, int ln, int h, const Soft &sf, bool valid, bf16raw *ph, int step)
+{
+    static_assert(C::PLO == 3 && C::PHI >= 1, "eight low corners per high-bit index, indices in pairs");
+    constexpr int NA = 1 << C::PHI;
+    const bool live = valid && (!C::PAD || table < sf.L);
+    float p[C::P], q[C::P], lo[4], hi[NA];
+#pragma unroll
+    for (int t = 0; t < C::P; ++t) code_masses(c[t], p[t], q[t]);
+    const float m2 = h ? p[2] : q[2];
+    lo[0] = q[0] * q[1] * m2; lo[1] = p[0] * q[1] * m2; lo[2] = q[0] * p[1] * m2; lo[3] = p[0] * p[1] * m2;
+    hi[0] = live ? 1.f : 0.f;
+#pragma unroll
+    for (int t = 3; t < C::P; ++t) {
+#pragma unroll
+        for (int b = 0; b < (1 << (t - 3)); ++b) {
+            hi[b + (1 << (t - 3))] = hi[b] * p[t];
+            hi[b] = hi[b] * q[t];
+        }
+    }
+    bf16raw *dst = ph + opaque(spread_row(ln) * STRIDE + table * C::R + 8 * h, step);
+#pragma unroll
+    for (int a = 0; a < NA; a += 2) {
+        float f[8];
+#pragma unroll
+        for (int b = 0; b < 4; ++b) { f[b] = hi[a] * lo[b]; f[4 + b] = hi[a + 1] * lo[b]; }
+        *reinterpret_cast<u32x4 *>(dst + 8 * a) = u32x4{pack2(f[0], f[1]), pack2(f[2], f[3]), pack2(f[4], f[5]), pack2(f[6], f[7])};
+    }
+}
+
+// Stores whose lanes are dropped by the address check where they lie past `bytes` (a store under a condition is a branch, behind
+// which the compiler no longer knows how many of the loads issued before it are in flight, and waits for too many).
+typedef __amdgpu_buffer_rsrc_t buffer_t;
+__device__ __forceinline__ buffer_t store_buffer(void *base, int bytes) { return __builtin_amdgcn_make_buffer_rsrc(base, 0, bytes, 0x00020000); }
+__device__ __forceinline__ void buffer_store128(buffer_t b, int offset, u32x4 v) { __builtin_amdgcn_raw_buffer_store_b128(v, b, offset, 0, 0); }
 
 }  // namespace mfma
 }  // namespace race

@@ -17,11 +17,15 @@
 // uses T^T[b][a] = Yw_b . Yr_a (+ the product of the two extra columns), masked to b <= a (b >= a
 // right to left), which goes to LDS as the A operand of  T . phi_writer.
 //
-// Two barriers per tile.  First half: the following tile's rows -> LDS (two buffers), the writer's assignments, the
-// derivative of tanh, the in-tile term, and dX of the previous tile; second half: dphi, the corner softmax backwards, dz,
-// and the update of the statistics.  (With a third barrier between the staging of a tile's own rows and everything that reads
-// them, the projection on two wavefronts and its masses through LDS to the others: 10.4 ms for 16.8 million rows of
-// 128 columns at L = 8, P = 6; now 10.1.)
+// Two barriers per tile.  First half: what the tile needs before its dphi (the derivative of tanh, the writer's assignments, the
+// in-tile term) and dX of the tile before it; second half: dphi, the corner softmax backwards, dz, and the rows of the following
+// tile -> LDS (two buffers).  R = 64: a wavefront builds the assignments of its own table, which nothing else reads, so the update of
+// the statistics belongs to the first half of the following tile, whose vector work runs next to its products.  Loads and stores
+// are unconditional, a tile that does not exist repeating the last one's: behind a branch the compiler no longer knows how
+// many are in flight and waits for the newest, which at the production cost every tile a trip to memory.
+// (Both gradients of 4.2 million rows of 128 columns, L = 8, P = 6: 4.42 ms with the production on four wavefronts, the update in the
+// second half and W read through transposing loads; now 4.10.  The clock gives part of it back: 7880 -> 7060 cycles a tile, 1.87 ->
+// 1.81 GHz on the same box.)
 #pragma once
 #include "mfma_common.h"
 
@@ -47,8 +51,11 @@ struct GradCfg {
     static constexpr int TS = C::L >= kWaves ? 1 : kWaves / C::L;       // wavefronts that share a table's tokens
     static_assert(TS <= 2 && (T16 || TPW == 1), "tables over wavefronts");
     static constexpr int SREGS = T16 ? TPW * C::D / 4 : MTG * C::NT * 16;        // registers of statistics
-    static constexpr int YORDER = T16 ? kPairs32 : kPairs16;
-    // First half of a tile, by role.  Production: `SLOTS` half wavefronts from wavefront 0 on; projection of the reader's rows:
+    // W transposed next to W: dX's operands are reads by rows.  (Transposing reads of W, under its stride for reads by rows, take
+    // four times as long.  R = 16: two workgroups on a CU need the room.)
+    static constexpr bool WT = !T16;
+    static constexpr int YORDER = T16 ? kPairs32 : kPlain;
+    // First half of a tile, by role.  Production (R = 16): `SLOTS` half wavefronts from wavefront 0 on; projection of the reader's rows:
     // 2 PT 16 x 16 tiles; in-tile term: three 16 x 16 tiles; dX of the previous tile: 2 NT pieces.
     static constexpr int SLOTS = C::L >= 16 ? 16 : 8;
     static constexpr int proj_wave(int i, bool causal)
@@ -56,7 +63,7 @@ struct GradCfg {
         if (!causal || C::PT == 4) return i % kWaves;
         return i == 0 ? 0 : 3 + i;
     }
-    static constexpr int tt_wave(int i) { return T16 ? (C::L >= 16 ? 5 + i : 1 + i) : 4 + i; }
+    static constexpr int tt_wave(int i) { return T16 ? (C::L >= 16 ? 5 + i : 1 + i) : i; }
     static constexpr int dx_wave(int i, bool causal) { return T16 && causal && C::L >= 16 ? i : kWaves - 1 - i; }
     static_assert(2 * C::NT <= kWaves, "one piece of dX per wavefront at most");
 };
@@ -70,7 +77,9 @@ struct GradLds {
     static constexpr int XB = UNIT ? 2 : 1;                             // buffers of the reader's rows and of the scales
     static constexpr int wp = 0;                                        // [LPP][XS] bf16
     static constexpr int DZS = C::LPP + 8;                              // bf16 row stride of the dz tile
-    static constexpr int dz = wp + C::LPP * C::XS * 2;                  // [32][DZS] bf16
+    static constexpr int WTS = C::LPP + 8;                              // bf16 row stride of W transposed
+    static constexpr int wt = wp + C::LPP * C::XS * 2;                  // [D][WTS] bf16: W transposed, column c at wt_row(c)
+    static constexpr int dz = wt + (G::WT ? C::D * WTS * 2 : 0);        // [32][DZS] bf16
     static constexpr int sr = dz + kTile * DZS * 2;                     // [2][32] fp32 extra column of reader-Y
     static constexpr int sw = sr + 2 * kTile * 4;                       // [2][32] fp32 extra column of writer-Y
     static constexpr int swp = sw + 2 * kTile * 4;                      // [2][kParts][32] bf16: parts of sw (key side)
@@ -86,8 +95,8 @@ struct GradLds {
     static constexpr int ttop = xr + XB * xr_bytes;                     // [2][64] x 16 B: masked in-tile term as MFMA operands
     static constexpr int yw = ttop + (INTRA ? 2 * 64 * 16 : 0);         // [2][32][YS] writer-Y rows, pair-interleaved columns
     static constexpr int yw_bytes = kTile * C::YS * 2;
-    static constexpr int phw = yw + (INTRA ? 2 * yw_bytes : 0);         // [32][PST] writer assignments
-    static constexpr int mass = phw + (INTRA ? kTile * C::PST * 2 : 0); // R = 16: [kWaves][TPW * 16] fp32: extra column of each wavefront's rows
+    static constexpr int phw = yw + (INTRA ? 2 * yw_bytes : 0);         // [32][PS or PST] writer assignments
+    static constexpr int mass = phw + (INTRA ? kTile * (G::T16 ? C::PST : C::PS) * 2 : 0); // R = 16: [kWaves][TPW * 16] fp32: extra column of each wavefront's rows
     static constexpr int total = mass + (G::T16 ? kWaves * G::TPW * 16 * 4 : 0);
     // where the cotangent of beta is wanted:
     static constexpr int th = total;                                    // [QUADS][32] float4: tanh z
@@ -105,6 +114,10 @@ constexpr int grad_waves_per_simd()
     return (!INTRA && GradCfg<C>::SREGS <= 32 && GradLds<C, UNIT, INTRA>::total <= 80 * 1024) ? 4 : 2;
 }
 
+// Row of W transposed that holds column c: in every 32 columns the first 16 rows are the first halves of the eights, the others
+// the second ones (the order in which dX's tiles take them).
+__device__ __forceinline__ constexpr int wt_row(int c) { return (c & ~31) | ((c & 4) << 2) | ((c >> 1) & 12) | (c & 3); }
+
 template <class C, int SIDE, bool UNIT, bool INTRA>
 __global__ __launch_bounds__(kThreads, (grad_waves_per_simd<C, UNIT, INTRA>()))
 void grad_kernel(KArgs a, const bf16raw *Xr, const bf16raw *V, const bf16raw *G_, bf16raw *dX)
@@ -113,6 +126,7 @@ void grad_kernel(KArgs a, const bf16raw *Xr, const bf16raw *V, const bf16raw *G_
     using G = GradCfg<C>;
     extern __shared__ __attribute__((aligned(256))) unsigned char lds[];
     bf16raw *wp = reinterpret_cast<bf16raw *>(lds + S::wp);
+    bf16raw *wt = reinterpret_cast<bf16raw *>(lds + S::wt);
     bf16raw *dz = reinterpret_cast<bf16raw *>(lds + S::dz);
     float *rad = reinterpret_cast<float *>(lds + S::rad);
     f32x4 *s2t = reinterpret_cast<f32x4 *>(lds + S::s2);
@@ -149,7 +163,11 @@ void grad_kernel(KArgs a, const bf16raw *Xr, const bf16raw *V, const bf16raw *G_
         const bf16raw *src = a.Wp + static_cast<size_t>(head) * C::LPP * C::D;
         for (int c = tid; c < C::LPP * C::CPR; c += kThreads) {
             const int row = c / C::CPR, ch = c % C::CPR;
-            *reinterpret_cast<u32x4 *>(wp + row * C::XS + ch * 8) = *reinterpret_cast<const u32x4 *>(src + row * C::D + ch * 8);
+            const u32x4 v = *reinterpret_cast<const u32x4 *>(src + row * C::D + ch * 8);
+            *reinterpret_cast<u32x4 *>(wp + row * C::XS + ch * 8) = v;
+            const uint32_t vw[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+            for (int e = 0; e < (G::WT ? 8 : 0); ++e) wt[wt_row(8 * ch + e) * S::WTS + row] = static_cast<bf16raw>(vw[e / 2] >> (16 * (e & 1)));
         }
     }
     if (C::L * C::PP < C::LPP) {
@@ -197,7 +215,7 @@ void grad_kernel(KArgs a, const bf16raw *Xr, const bf16raw *V, const bf16raw *G_
 #pragma unroll
             for (int mtc = 0; mtc < C::NT; ++mtc) {
 #pragma unroll
-                for (int v = 0; v < 16; ++v) ST[mr][mtc][v] = st[(r_own + 32 * mr + ln) * C::D + 32 * mtc + acc_row(v, h)];
+                for (int v = 0; v < 16; ++v) ST[mr][mtc][v] = st[(r_own + 32 * mr + ln) * C::D + 32 * mtc + 16 * (v / 8) + 8 * h + v % 8];
             }
             macc[mr] = h == 0 ? st[C::LR * C::D + r_own + 32 * mr + ln] : 0.f;
         }
@@ -209,6 +227,20 @@ void grad_kernel(KArgs a, const bf16raw *Xr, const bf16raw *V, const bf16raw *G_
     auto tile_t0 = [&](int it) { return t_begin + static_cast<int64_t>(kReverse ? ntiles - 1 - it : it) * kTile; };
     auto tile_nv = [&](int64_t t0) { return (t_end - t0 < kTile) ? static_cast<int>(t_end - t0) : kTile; };
 
+    // LDS addresses are a lane's offset under a stride plus a uniform one, added where it is used.  R = 64: the lane's offsets are
+    // worked out here; R = 16, where they would push two workgroups' registers past a CU's: again in every tile.
+    int step = 0;       // (the loop counter of these sums)
+    auto at = [&](int uniform, int lane_offset) __attribute__((always_inline)) { return lds + (opaque_uniform(uniform, step) + lane_offset); };
+    const int at16x_ = (n16 * C::XS + 8 * q16) * 2, at16d_ = (n16 * S::DZS + 8 * q16) * 2;      // 16-row operands
+    const int at_x_ = chunk_offset<C, C::XS, kPlain>(tid), at_yr_ = chunk_offset<C, C::XS, G::YORDER>(tid), at_yw_ = chunk_offset<C, C::YS, G::YORDER>(tid);
+    auto rebuilt_lane = [&]() __attribute__((always_inline)) { return opaque(lane, step); };
+    auto at16 = [&](int stride, int kept) __attribute__((always_inline)) {
+        if (!G::T16) return kept;
+        const int lo = rebuilt_lane();
+        return ((lo & 15) * stride + 8 * (lo >> 4)) * 2;
+    };
+    static_assert(S::DZS == S::WTS, "one offset for both operands of dX");
+    auto operand = [&](const unsigned char *p, int bytes) __attribute__((always_inline)) { return *reinterpret_cast<const u32x4 *>(p + bytes); };
     // rows: requested two tiles ahead, written to LDS one tile ahead (the reader's in the second half of a tile, behind its
     // projection; the others in the first)
     RowChunks<C, kTile> pre_r, pre_v, pre_g;
@@ -227,13 +259,8 @@ void grad_kernel(KArgs a, const bf16raw *Xr, const bf16raw *V, const bf16raw *G_
         fetch_rows<C, kTile>(Xr, t0, tile_nv(t0), pre_r);
     };
     auto stage_y = [&](int it) __attribute__((always_inline)) {
-        if (SIDE == 0) {
-            store_rows<C, kTile, C::XS, G::YORDER>(pre_g, buf_yr(it));
-            if (intra) store_rows<C, kTile, C::YS, G::YORDER>(pre_v, buf_yw(it));
-        } else {
-            store_rows<C, kTile, C::XS, G::YORDER>(pre_v, buf_yr(it));
-            if (intra) store_rows<C, kTile, C::YS, G::YORDER>(pre_g, buf_yw(it));
-        }
+        store_tile<C, G::YORDER>(SIDE == 0 ? pre_g : pre_v, at(S::yr + (it & 1) * S::yr_bytes, G::T16 ? chunk_offset<C, C::XS, G::YORDER>(opaque(tid, step)) : at_yr_));
+        if (intra) store_tile<C, G::YORDER>(SIDE == 0 ? pre_v : pre_g, at(S::yw + (it & 1) * S::yw_bytes, G::T16 ? chunk_offset<C, C::YS, G::YORDER>(opaque(tid, step)) : at_yw_));
         if (tid < kTile) {
             buf_sr(it)[tid] = SIDE == 0 ? pre_ge : 1.f;
             buf_sw(it)[tid] = SIDE == 0 ? 1.f : pre_ge;
@@ -241,14 +268,24 @@ void grad_kernel(KArgs a, const bf16raw *Xr, const bf16raw *V, const bf16raw *G_
         if (SIDE == 1 && intra && tid < kParts * kTile) buf_swp(it)[tid] = weight_part(pre_ge, tid / kTile);
     };
     auto stage_x = [&](int it) __attribute__((always_inline)) {
-        store_rows<C, kTile>(pre_r, buf_xr(it));
-        if (UNIT) store_row_scales<C, kTile>(pre_r, buf_nrm(it));
+        store_tile<C, kPlain>(pre_r, at(S::xr + (UNIT ? it & 1 : 0) * S::xr_bytes, G::T16 ? chunk_offset<C, C::XS, kPlain>(opaque(tid, step)) : at_x_));
+        if (UNIT) store_row_scales<C, kTile>(pre_r, buf_nrm(it), step);
     };
+    // the writer's assignments.  R = 64: every wavefront builds those of its own table, which nothing else reads; R = 16: the first
+    // wavefronts build all of them
     using Sh = Share<C, G::SLOTS>;
     const int slot = 2 * (w & (G::SLOTS / 2 - 1)) + h;
-    const bool produces = intra && w < G::SLOTS / 2;
+    const bool produces = intra && (!G::T16 || w < G::SLOTS / 2);
     typename Sh::Regs pre_w;
-    const uint32_t woff = table_offset<C>(Sh::table(slot, 0), ln);
+    float own_w[C::P];
+    const uint32_t woff = table_offset<C>(G::T16 ? Sh::table(slot, 0) : tl0, ln);
+    auto fetch_w = [&](int it) __attribute__((always_inline)) {
+        if (!produces) return;
+        if constexpr (G::T16) Sh::load(Mw + tile_t0(it) * C::LP, woff, ln, pre_w);
+        else load_table_codes<C>(Mw + tile_t0(it) * C::LP, woff, ln, own_w);
+    };
+    // the loads of a tile that does not exist repeat the last one's (and are not used): see store_buffer()
+    auto existing = [&](int it) { return it < ntiles ? it : ntiles - 1; };
     // the reader's hashed rows: R = 64: token ln of the wavefront's table; R = 16: tokens n16 (and 16 + n16) of its tables
     const int th0 = G::TS == 2 ? w >> 2 : 0;
     const uint32_t roff = table_offset<C>(tl0, G::T16 ? 16 * th0 + n16 : ln);
@@ -268,10 +305,11 @@ void grad_kernel(KArgs a, const bf16raw *Xr, const bf16raw *V, const bf16raw *G_
     if (ntiles > 0) {
         fetch_x(0);
         fetch_y(0);
-        if (produces) Sh::load(Mw + tile_t0(0) * C::LP, woff, ln, pre_w);
+        fetch_w(0);
         stage_x(0);
         stage_y(0);
-        if (ntiles > 1) { fetch_x(1); fetch_y(1); }
+        fetch_x(existing(1));
+        fetch_y(existing(1));
         __syncthreads();
     }
 
@@ -280,19 +318,42 @@ void grad_kernel(KArgs a, const bf16raw *Xr, const bf16raw *V, const bf16raw *G_
     //      (n, q) holds eight consecutive columns of token n and stores them as one 16-byte piece, without a stop in LDS.
     //      (As 32 x 32 tiles on four wavefronts, staged in LDS on their way out, this chain of dependent steps took 1700 of the
     //      3750 cycles of the first half; here every wavefront has a quarter of that.)
-    auto dx_stage = [&](int i, int it) __attribute__((always_inline)) {
-        const int64_t t0 = tile_t0(it);
-        const int lo = opaque(lane), n = lo & 15, q = lo >> 4;       // addresses below are rebuilt per tile, not kept in registers
-        const int c0 = 32 * (i >> 1), tok = 16 * (i & 1) + n;
-        f32x4 x0 = {0.f, 0.f, 0.f, 0.f}, x1 = x0;
+    struct DxOperands { u32x4 d[C::LPP / 32], wa[C::LPP / 32], wb[C::LPP / 32]; };
+    auto dx_load = [&](int i, DxOperands &o) __attribute__((always_inline)) {
+        const unsigned char *d = at(S::dz + 16 * (i & 1) * S::DZS * 2, at16(S::DZS, at16d_));
+        if constexpr (G::WT) {
+            const unsigned char *wc = at(S::wt + 32 * (i >> 1) * S::WTS * 2, at16(S::DZS, at16d_));
+#pragma unroll
+            for (int s = 0; s < C::LPP / 32; ++s) {
+                o.d[s] = operand(d, 64 * s);
+                o.wa[s] = operand(wc, 64 * s);
+                o.wb[s] = operand(wc, 16 * S::WTS * 2 + 64 * s);
+            }
+        } else {
+            const int lo = rebuilt_lane(), chunk = 32 * (i >> 1) + 8 * (lo & 3);
+#pragma unroll
+            for (int s = 0; s < C::LPP / 32; ++s) {
+                const int k = 32 * s + 8 * (lo >> 4);
+                o.d[s] = operand(d, 64 * s);
+                o.wa[s] = lds_tr16(wp, C::XS, k, k + 4, chunk, lo);
+                o.wb[s] = lds_tr16(wp, C::XS, k, k + 4, chunk + 4, lo);
+            }
+        }
+    };
+    auto dx_mma = [&](const DxOperands &o, f32x4 &x0, f32x4 &x1) __attribute__((always_inline)) {
+        x0 = x1 = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int s = 0; s < C::LPP / 32; ++s) {
-            const u32x4 d = lds128(dz + tok * S::DZS + 32 * s + 8 * q);
-            const int k = 32 * s + 8 * q, chunk = c0 + 8 * (lo & 3);
-            x0 = mma16(lds_tr16(wp, C::XS, k, k + 4, chunk, lo), d, x0);
-            x1 = mma16(lds_tr16(wp, C::XS, k, k + 4, chunk + 4, lo), d, x1);
+            x0 = mma16(o.wa[s], o.d[s], x0);
+            x1 = mma16(o.wb[s], o.d[s], x1);
         }
+    };
+    // (tile -1, of the first step, has no rows)
+    auto dx_store = [&](int i, int it, f32x4 x0, f32x4 x1) __attribute__((always_inline)) {
+        const int64_t t0 = tile_t0(it >= 0 ? it : 0);
+        const int c0 = 32 * (i >> 1);
         if (UNIT) {
+            const int lo = opaque(lane, step), n = lo & 15, q = lo >> 4, tok = 16 * (i & 1) + n;
             float cp = 0.f;                              // (z . dz) / |x|^2 of the token, parts in wavefront order
 #pragma unroll
             for (int w8 = 0; w8 < kWaves / G::TS; ++w8) cp += rad[((G::TS == 2 ? 4 * (tok >> 4) : 0) + w8) * kTile + tok];
@@ -303,25 +364,23 @@ void grad_kernel(KArgs a, const bf16raw *Xr, const bf16raw *V, const bf16raw *G_
             x1[0] = fmaf(-cp, bf_lo(xv.z), x1[0]); x1[1] = fmaf(-cp, bf_hi(xv.z), x1[1]);
             x1[2] = fmaf(-cp, bf_lo(xv.w), x1[2]); x1[3] = fmaf(-cp, bf_hi(xv.w), x1[3]);
         }
-        char *dst = reinterpret_cast<char *>(dX + t0 * C::D);
-        if (tok < tile_nv(t0))
-            *reinterpret_cast<u32x4 *>(dst + static_cast<uint32_t>((tok * C::D + c0 + 8 * q) * 2)) =
-                u32x4{pack2(x0[0], x0[1]), pack2(x0[2], x0[3]), pack2(x1[0], x1[1]), pack2(x1[2], x1[3])};
+        buffer_store128(store_buffer(dX + t0 * C::D, it >= 0 ? tile_nv(t0) * C::D * 2 : 0), opaque_uniform((16 * (i & 1) * C::D + c0) * 2, step) + at16(C::D, (n16 * C::D + 8 * q16) * 2),
+                        u32x4{pack2(x0[0], x0[1]), pack2(x0[2], x0[3]), pack2(x1[0], x1[1]), pack2(x1[2], x1[3])});
     };
     // ---- projections of the reader's rows, 16 packed hyperplanes x 16 tokens (tile i of 2 PT), and what the chain rule through
     //      tanh needs of them: tanh z and 1 - tanh^2 z
     constexpr bool kAllProject = 2 * C::PT == kWaves;       // one tile per wavefront, no roles
     auto project = [&](int i, int it) __attribute__((always_inline)) {
-        const int lo = opaque(lane), n = lo & 15, q = lo >> 4;      // (addresses rebuilt per tile, not kept in registers)
-        const bf16raw *wrow = wp + (16 * (i >> 1) + n) * C::XS + 8 * q, *xrow = buf_xr(it) + (16 * (i & 1) + n) * C::XS + 8 * q;
+        const unsigned char *wrow = at(S::wp + 16 * (i >> 1) * C::XS * 2, at16(C::XS, at16x_));
+        const unsigned char *xrow = at(S::xr + (UNIT ? it & 1 : 0) * S::xr_bytes + 16 * (i & 1) * C::XS * 2, at16(C::XS, at16x_));
         f32x4 z = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int s = 0; s < C::D / 32; ++s) z = mma16(lds128(wrow + 32 * s), lds128(xrow + 32 * s), z);
+        for (int s = 0; s < C::D / 32; ++s) z = mma16(operand(wrow, 64 * s), operand(xrow, 64 * s), z);
         return z;
     };
     auto finish_projection = [&](int i, int it, f32x4 z) __attribute__((always_inline)) {
-        const int lo = opaque(lane), tok = 16 * (i & 1) + (lo & 15), quad = 4 * (i >> 1) + (lo >> 4), at = quad * kTile + tok;
-        if (UNIT) z = z * buf_nrm(it)[tok];
+        const int quad = 4 * (i >> 1) + q16, slot16 = opaque_uniform((4 * (i >> 1) * kTile + 16 * (i & 1)) * 16, step) + (q16 * kTile + n16) * 16;
+        if (UNIT) z = z * buf_nrm(it)[16 * (i & 1) + n16];
         f32x4 sv, uv;
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
@@ -330,35 +389,42 @@ void grad_kernel(KArgs a, const bf16raw *Xr, const bf16raw *V, const bf16raw *G_
             uv[v] = z[v] >= 0.f ? ua : -ua;
         }
         if (C::L * C::PP % 16 == 0 || quad < S::QUADS) {
-            s2t[at] = sv;
-            if (a.want_dbeta) tht[at] = uv;
-            if (UNIT) zzt[at] = z;
+            *reinterpret_cast<f32x4 *>(lds + S::s2 + slot16) = sv;
+            if (a.want_dbeta) *reinterpret_cast<f32x4 *>(lds + S::th + slot16) = uv;
+            if (UNIT) *reinterpret_cast<f32x4 *>(lds + S::zz + slot16) = z;
         }
     };
 
     if (G::T16 && w >= 4) lead(true);       // (R = 16: all along; handing the lead back half way through the tables is slower)
     float dbeta_acc = 0.f;    // this lane's share of the cotangent of beta: sum of 2 p_t q_t E_t tanh z_t
-    for (int it = 0; it < ntiles; ++it) {
-        const int64_t t0 = tile_t0(it);
+    // ================ first half of tile `it`: all that it needs before its dphi, and dX of the tile before it
+    // (the reader's hashed rows of this wavefront's tables: used in the second half)
+    constexpr int kTh = G::T16 && G::TS == 1 ? 2 : 1;      // R = 16: halves of the tile's tokens
+    float rc[G::TPW * kTh][C::P];
+    auto first_half = [&](int it) __attribute__((always_inline)) {
+        const int64_t t0 = tile_t0(existing(it));
         const int nvalid = tile_nv(t0);
-        // ================ first half
-        // the reader's hashed rows of this wavefront's tables: used in the second half
-        constexpr int kTh = G::T16 && G::TS == 1 ? 2 : 1;      // R = 16: halves of the tile's tokens
-        float rc[G::TPW * kTh][C::P];
 #pragma unroll
         for (int i = 0; i < G::TPW * kTh; ++i)
             load_table_codes<C>(Mr + t0 * C::LP + (i / kTh) * C::HT + (i % kTh) * 64, roff, ln, rc[i]);      // (16 tokens are 64 floats)
         f32x4 z_own = {0.f, 0.f, 0.f, 0.f};
-        if (kAllProject) z_own = project(w, it);             // (under the staging and the production)
-        if (it + 1 < ntiles) {
-            stage_y(it + 1);
-            if (it + 2 < ntiles) fetch_y(it + 2);
+        constexpr bool kAllDx = 2 * C::NT == kWaves;             // a piece of dX for every wavefront
+        DxOperands dxo;
+        f32x4 x0 = {0.f, 0.f, 0.f, 0.f}, x1 = x0;
+        if (kAllDx) dx_load(my_dx, dxo);
+        if (kAllProject) z_own = project(w, it);             // (under the production)
+        if (kAllDx) dx_mma(dxo, x0, x1);
+        if (!kAllDx && my_dx >= 0) {
+            dx_load(my_dx, dxo);
+            dx_mma(dxo, x0, x1);
+            dx_store(my_dx, it - 1, x0, x1);
         }
-        if (it > 0 && my_dx >= 0) dx_stage(my_dx, it - 1);
         if (produces) {
-            produce<C, G::SLOTS, C::PST>(pre_w, slot, ln, a.soft(), ln < nvalid, phw);
-            if (it + 1 < ntiles) Sh::load(Mw + tile_t0(it + 1) * C::LP, woff, ln, pre_w);
+            if constexpr (G::T16) produce<C, G::SLOTS, C::PST>(pre_w, slot, ln, a.soft(), ln < nvalid, phw, step);
+            else produce_table<C, C::PS>(own_w, tl0, ln, h, a.soft(), ln < nvalid, phw, step);
         }
+        if (kAllDx) dx_store(my_dx, it - 1, x0, x1);
+        fetch_w(existing(it + 1));
         if (kAllProject) {
             finish_projection(w, it, z_own);
         } else {
@@ -371,13 +437,14 @@ void grad_kernel(KArgs a, const bf16raw *Xr, const bf16raw *V, const bf16raw *G_
         if (intra && my_tt >= 0) {
             // T^T[b][a] = Yw_b . Yr_a + sw_b sr_a, one of the three 16 x 16 tiles (b, a) that the mask leaves: the two on the
             // diagonal and one off it; both row tiles keep their columns in the same order, which is all a contraction needs
-            const int lo = opaque(lane), n = lo & 15, q = lo >> 4;
-            const int bt = my_tt < 2 ? my_tt : (kReverse ? 1 : 0), at = my_tt < 2 ? my_tt : 1 - bt;
-            const bf16raw *brow = buf_yw(it) + (16 * bt + n) * C::YS + 8 * q, *arow = buf_yr(it) + (16 * at + n) * C::XS + 8 * q;
+            const int lo = opaque(lane, step), n = lo & 15, q = lo >> 4;
+            const int bt = my_tt < 2 ? my_tt : (kReverse ? 1 : 0), rt = my_tt < 2 ? my_tt : 1 - bt;
+            const bf16raw *brow = buf_yw(it) + (16 * bt + n) * C::YS + 8 * q;
+            const unsigned char *arow = at(S::yr + (it & 1) * S::yr_bytes + 16 * rt * C::XS * 2, at16(C::XS, at16x_));
             f32x4 tt = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int s = 0; s < C::D / 32; ++s) tt = mma16(lds128(brow + 32 * s), lds128(arow + 32 * s), tt);
-            const int ai = 16 * at + n;
+            for (int s = 0; s < C::D / 32; ++s) tt = mma16(lds128(brow + 32 * s), operand(arow, 64 * s), tt);
+            const int ai = 16 * rt + n;
             const float sra = buf_sr(it)[ai];
             const f32x4 swb = *reinterpret_cast<const f32x4 *>(buf_sw(it) + 16 * bt + 4 * q);
 #pragma unroll
@@ -387,10 +454,16 @@ void grad_kernel(KArgs a, const bf16raw *Xr, const bf16raw *V, const bf16raw *G_
             }
             // R = 64: rows 4 q .. of k-step bt belong to lane half q % 2, words 2 (q / 2) .. of its operand;
             // R = 16: k-slots 4 .. 7 of a lane are its rows of the second tile
-            uint32_t *dst = G::T16 ? reinterpret_cast<uint32_t *>(ttop + 64 * at + lo) + 2 * bt
+            uint32_t *dst = G::T16 ? reinterpret_cast<uint32_t *>(ttop + 64 * rt + lo) + 2 * bt
                                    : reinterpret_cast<uint32_t *>(ttop + 64 * bt + 32 * (q & 1) + ai) + 2 * (q >> 1);
             *reinterpret_cast<u32x2 *>(dst) = u32x2{pack2(tt[0], tt[1]), pack2(tt[2], tt[3])};
         }
+    };
+    if (ntiles > 0) first_half(0);
+    for (int it = 0; it < ntiles; ++it) {
+        step = it;
+        const int64_t t0 = tile_t0(it);
+        const int nvalid = tile_nv(t0);
         __syncthreads();
 
         // ================ second half
@@ -446,7 +519,7 @@ void grad_kernel(KArgs a, const bf16raw *Xr, const bf16raw *V, const bf16raw *G_
                 if (intra) {
                     // ---- statistics += Yw^T . phi_writer
                     const u32x4 pb = lds_tr16(phw + r_own + 16 * i, C::PST, 8 * q16, 8 * q16 + 4, tr_ph, lane);
-                    macc[i] += column_sum<SIDE == 1>(SIDE == 1 ? lds128(buf_swp(it) + parts_offset16(kTile, opaque(lane))) : ones16(opaque(lane)), pb);
+                    macc[i] += column_sum<SIDE == 1>(SIDE == 1 ? lds128(buf_swp(it) + parts_offset16(kTile, opaque(lane, step))) : ones16(opaque(lane, step)), pb);
 #pragma unroll
                     for (int ct = 0; ct < C::D / 16; ++ct)
                         SU[i][ct] = mma16(lds_tr16(yw, C::YS, 8 * q16, 8 * q16 + 4, 32 * (ct >> 1) + 8 * (lane & 3) + 4 * (ct & 1), lane), pb, SU[i][ct]);
@@ -496,10 +569,10 @@ void grad_kernel(KArgs a, const bf16raw *Xr, const bf16raw *V, const bf16raw *G_
                 if (intra) {
 #pragma unroll
                     for (int s = 0; s < 2; ++s)
-                        dP = mma(lds_tr_acc<true>(phw, C::PST, 16 * s, r_own + 32 * mr, ln, h), ttop[64 * s + lane], dP);
+                        dP = mma(lds_tr_acc<true, true>(phw, C::PS, 16 * s, r_own + 32 * mr, ln, h), ttop[64 * s + lane], dP);
                 }
                 {
-                    const int yo = opaque(ln * C::XS + 8 * h);       // pair-interleaved columns: one 16-byte read per k-step
+                    const int yo = ln * C::XS + 8 * h;
 #pragma unroll
                     for (int mtc = 0; mtc < C::NT; ++mtc) {
 #pragma unroll
@@ -571,9 +644,16 @@ void grad_kernel(KArgs a, const bf16raw *Xr, const bf16raw *V, const bf16raw *G_
                 radial = sum_halves(radial);
                 if (h == 0) rad[w * kTile + ln] = radial;
             }
+        }
+        stage_y(it + 1);
+        fetch_y(existing(it + 2));
+        stage_x(it + 1);
+        fetch_x(existing(it + 2));
+        __syncthreads();        // dz is visible; this tile's assignments, in-tile term and tanh are dead from here on
+        if constexpr (!G::T16) {
             // ---- statistics += Yw^T . phi_writer
             if (intra) {
-                const int lo = opaque(lane), swp_off = parts_offset32<true>(kTile, lo);
+                const int lo = opaque(lane, step), swp_off = parts_offset32<true>(kTile, lo);
 #pragma unroll
                 for (int s = 0; s < 2; ++s) {
                     const u32x4 gw = SIDE == 1 ? lds128(buf_swp(it) + swp_off + 16 * s) : ones32<true>(lo);   // (SIDE 0: [V | 1])
@@ -582,7 +662,7 @@ void grad_kernel(KArgs a, const bf16raw *Xr, const bf16raw *V, const bf16raw *G_
                     for (int mtc = 0; mtc < C::NT; ++mtc) ay[mtc] = lds_tr_plain<true>(yw, C::YS, 16 * s, 32 * mtc, ln, h);
 #pragma unroll
                     for (int mr = 0; mr < G::MTG; ++mr) {
-                        const u32x4 bp = lds_tr_plain<true>(phw, C::PST, 16 * s, r_own + 32 * mr, ln, h);
+                        const u32x4 bp = lds_tr_plain<true, true>(phw, C::PS, 16 * s, r_own + 32 * mr, ln, h);
                         macc[mr] += column_sum<SIDE == 1>(gw, bp);
 #pragma unroll
                         for (int mtc = 0; mtc < C::NT; ++mtc) ST[mr][mtc] = mma(ay[mtc], bp, ST[mr][mtc]);
@@ -590,13 +670,8 @@ void grad_kernel(KArgs a, const bf16raw *Xr, const bf16raw *V, const bf16raw *G_
                 }
             }
         }
-        if (it + 1 < ntiles) {
-            stage_x(it + 1);
-            if (it + 2 < ntiles) fetch_x(it + 2);
-        }
-        __syncthreads();        // dz is visible; this tile's assignments, in-tile term and tanh are dead from here on
+        first_half(it + 1);
     }
-    if (ntiles > 0 && my_dx >= 0) dx_stage(my_dx, ntiles - 1);
     // ---- cotangent of beta: lanes -> wavefront (shuffles) -> workgroup (LDS, wavefront order) -> one workspace slot
     if (a.want_dbeta) {
 #pragma unroll

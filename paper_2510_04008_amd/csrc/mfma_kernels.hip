@@ -129,15 +129,18 @@ template <class C>
 struct TotalsLds {
     static constexpr int TT = 64;
     static constexpr int y = 0;                                         // [64][YS] accumulated rows
-    static constexpr int ph = y + TT * C::YS * 2;                       // [64][PST] assignments
-    static constexpr int ge = ph + TT * C::PST * 2;                     // [kParts][64] bf16
+    static constexpr int ph = y + TT * C::YS * 2;                       // [64][PS] assignments
+    static constexpr int ge = ph + TT * C::PS * 2;                     // [kParts][64] bf16
     static constexpr int total = ge + kParts * TT * 2;
     static_assert(total <= 160 * 1024, "LDS budget");
 };
 
-// which column group carries the extra column of row tile mt (taking turns spreads the vector work over the wavefronts)
+// The wavefronts of a row group share its row tiles' extra column: the one of column group cg takes the MA tiles that come first in
+// its own order, which starts at tile cg MA.  (Ownership by the tile's number was a branch around every tile's sum: the loads of the
+// products of one tile waited behind those of the one before it.  A single tile is summed by all of them and written by the first.)
+// First bucket row of the mt-th tile in that order:
 template <class C>
-__device__ __forceinline__ bool mass_owner(int mt, int cg) { return mt % C::CG == cg; }
+__device__ __forceinline__ int tile_row(int r_own, int mt, int cg) { return r_own + 32 * ((mt / C::MA + cg) % C::CG * C::MA % C::MT + mt % C::MA); }
 
 // M: the hashed rows of the tensor whose assignments feed the statistics (K forward, Q backward).  QG == 1 also leaves the
 // cotangent rows it forms in memory, rows in Gout (the caller's buffer for dK, which nothing else uses before dK is
@@ -168,7 +171,7 @@ void totals_kernel(KArgs a, const float *M, const bf16raw *Y, const bf16raw *Oin
     if (!QG && unread) return;
 
     f32x16 Sacc[C::MT][C::NTW];
-    float macc[C::MA];                 // extra column of row tiles cg, cg + CG, ...: lane n <-> row, per-half partial sums
+    float macc[C::MA];                 // extra column of the first row tiles: lane n <-> row, per-half partial sums
 #pragma unroll
     for (int i = 0; i < C::MA; ++i) macc[i] = 0.f;
 #pragma unroll
@@ -202,12 +205,12 @@ void totals_kernel(KArgs a, const float *M, const bf16raw *Y, const bf16raw *Oin
     for (int it = 0; it < nsteps; ++it) {
         const int64_t t0 = t_begin + static_cast<int64_t>(it) * TT;
         const int nvalid = step_nv(t0);
-        produce<C, 8, C::PST>(pre_m, slot, row, a.soft(), row < nvalid, ph);
+        produce<C, 8, C::PS>(pre_m, slot, half * kTile + spread_row(ln), a.soft(), row < nvalid, ph, it);
         if (QG) {
             wait_loads();
-            store_cotangent<C, TT, C::YS>(pre_c, ys, ge_lds, a.L_real, nvalid, Gout, ge_out, t0);
+            store_cotangent<C, TT, C::YS>(pre_c, ys, ge_lds, a.L_real, nvalid, Gout, ge_out, t0, it);
         } else {
-            store_rows<C, TT, C::YS>(pre_y, ys);
+            store_rows<C, TT, C::YS>(pre_y, ys, it);
         }
         if (it + 1 < nsteps) fetch(it + 1);
         __syncthreads();
@@ -219,9 +222,8 @@ void totals_kernel(KArgs a, const float *M, const bf16raw *Y, const bf16raw *Oin
             const u32x4 gw = QG ? lds128(ge_lane + 16 * s) : ones32<false>(lane);
 #pragma unroll
             for (int mt = 0; mt < C::MT; ++mt) {
-                const u32x4 ap = lds_tr_plain<true>(ph, C::PST, 16 * s, r_own + 32 * mt, ln, h);
-                if (mass_owner<C>(mt, cg))      // the extra column (bucket mass, or its cotangent): shared out over the column groups
-                    macc[mt / C::CG] += column_sum<QG != 0>(gw, ap);
+                const u32x4 ap = lds_tr_plain<true, true>(ph, C::PS, 16 * s, tile_row<C>(r_own, mt, cg), ln, h);
+                if (mt < C::MA) macc[mt] += column_sum<QG != 0>(gw, ap);      // the extra column (bucket mass, or its cotangent)
 #pragma unroll
                 for (int nt = 0; nt < C::NTW; ++nt) Sacc[mt][nt] = mma(ap, by[nt], Sacc[mt][nt]);
             }
@@ -235,11 +237,11 @@ void totals_kernel(KArgs a, const float *M, const bf16raw *Y, const bf16raw *Oin
         for (int nt = 0; nt < C::NTW; ++nt) {
 #pragma unroll
             for (int v = 0; v < 16; ++v)
-                st[state_b<C>(r_own + 32 * mt + acc_row(v, h), c_own + 32 * nt + ln)] = Sacc[mt][nt][v];
+                st[state_b<C>(tile_row<C>(r_own, mt, cg) + acc_row(v, h), c_own + 32 * nt + ln)] = Sacc[mt][nt][v];
         }
-        if (mass_owner<C>(mt, cg)) {
-            const float tot = sum_halves(macc[mt / C::CG]);
-            if (h == 0) st[state_a<C>(r_own + 32 * mt + ln)] = tot;
+        if (mt < C::MA) {
+            const float tot = sum_halves(macc[mt]);
+            if (h == 0 && (C::MT > 1 || cg == 0)) st[state_a<C>(tile_row<C>(r_own, mt, cg) + ln)] = tot;
         }
     }
 }
@@ -305,7 +307,7 @@ void stream_kernel(KArgs a, const float *Mr, const float *Mw, const bf16raw *Y, 
     const float *st = a.state + (static_cast<size_t>(bh) * a.nseg + (NC ? 0 : seg)) * C::STATE;
 
     f32x16 Sacc[C::MT][C::NTW];
-    float macc[C::MA];                 // bucket masses of row tiles cg, cg + CG, ... (balances the work): lane n <-> row, per-half partial sums
+    float macc[C::MA];                 // bucket masses of the first row tiles: lane n <-> row, per-half partial sums
 #pragma unroll
     for (int i = 0; i < C::MA; ++i) macc[i] = 0.f;
     // (causal: nothing precedes the first segment, right to left the last one, and the scan writes no state for it)
@@ -323,22 +325,19 @@ void stream_kernel(KArgs a, const float *Mr, const float *Mw, const bf16raw *Y, 
             for (int nt = 0; nt < C::NTW; ++nt) {
 #pragma unroll
                 for (int v = 0; v < 16; ++v)
-                    Sacc[mt][nt][v] = st[state_b<C>(r_own + 32 * mt + acc_row(v, h), c_own + 32 * nt + ln)];
+                    Sacc[mt][nt][v] = st[state_b<C>(tile_row<C>(r_own, mt, cg) + acc_row(v, h), c_own + 32 * nt + ln)];
             }
         }
     }
     if (MODE == kForward) {
         // (behind the loads of the statistics, all of which are in flight together)
 #pragma unroll
-        for (int i = 0; i < C::MA; ++i) {
-            const int mt = i * C::CG + cg;
-            if (mt < C::MT && !from_zero) macc[i] = st[state_a<C>(r_own + 32 * mt + ln)];
-        }
+        for (int i = 0; i < C::MA; ++i)
+            if (!from_zero) macc[i] = st[state_a<C>(tile_row<C>(r_own, i, cg) + ln)];
 #pragma unroll
         for (int i = 0; i < C::MA; ++i) {
-            const int mt = i * C::CG + cg;
             macc[i] = h == 0 ? macc[i] : 0.f;
-            if (mt < C::MT && h == 0) mass[r_own + 32 * mt + il(ln)] = macc[i];
+            if (h == 0) mass[tile_row<C>(r_own, i, cg) + il(ln)] = macc[i];
         }
     }
 
@@ -361,7 +360,6 @@ void stream_kernel(KArgs a, const float *Mr, const float *Mw, const bf16raw *Y, 
     };
     if (ntiles > 0) fetch(0);
 
-    const float inv_tables = 1.0f / static_cast<float>(a.L_real);
     // ---- epilogue of one tile: thread = (token, pieces of 4 columns: 4i.. and, for d = 128, 64 + 4i..; consecutive
     //      threads read consecutive 16-byte pieces of the partials): sum, normalise, store
     auto epilogue = [&](int it) __attribute__((always_inline)) {
@@ -370,7 +368,7 @@ void stream_kernel(KArgs a, const float *Mr, const float *Mw, const bf16raw *Y, 
         const float *dnr = dnp + (it & 1) * 256;
         {
         constexpr int NP = C::D / 64;                // pieces of 4 columns per thread
-        const int tok = tid >> 4, c0 = (tid & 15) * 4;
+        const int to = opaque(tid, it), tok = to >> 4, c0 = (to & 15) * 4;      // (addresses rebuilt per tile, not kept in registers)
         float acc[NP][4];
 #pragma unroll
         for (int c = 0; c < NP; ++c) acc[c][0] = acc[c][1] = acc[c][2] = acc[c][3] = 0.f;
@@ -392,12 +390,12 @@ void stream_kernel(KArgs a, const float *Mr, const float *Mw, const bf16raw *Y, 
         }
         if (tok < nvalid) {
             const float scale = (MODE == kForward) ? (e > 0.f ? __builtin_amdgcn_rcpf(e) : 0.f) : 1.0f;   // e = 0: hard hash, empty buckets
-            bf16raw *dst = Out + (t0 + tok) * C::D + c0;
+            char *dst = reinterpret_cast<char *>(Out + t0 * C::D);
 #pragma unroll
             for (int c = 0; c < NP; ++c)
-                *reinterpret_cast<u32x2 *>(dst + 64 * c) =
+                *reinterpret_cast<u32x2 *>(dst + static_cast<uint32_t>((tok * C::D + c0 + 64 * c) * 2)) =
                     u32x2{pack2(acc[c][0] * scale, acc[c][1] * scale), pack2(acc[c][2] * scale, acc[c][3] * scale)};
-            if (MODE == kForward && (tid & 15) == 0) den_out[t0 + tok] = e * inv_tables;
+            if (MODE == kForward && (to & 15) == 0) (den_out + t0)[static_cast<uint32_t>(tok)] = e * a.inv_tables;
         }
     }
     };
@@ -407,12 +405,12 @@ void stream_kernel(KArgs a, const float *Mr, const float *Mw, const bf16raw *Y, 
         // ---- first half: this tile's rows and assignments -> LDS, then the previous tile's output (its stores are issued when
         //      nothing loaded is waited for any more; in front of the production every tile waited for them to complete)
         if (kOutputFirst && it > 0) epilogue(it - 1);
-        if (intra) store_rows<C, kTile, C::YS>(pre_y, ytile);
+        if (intra) store_rows<C, kTile, C::YS>(pre_y, ytile, it);
         if (side == 0) {
-            const float dnl = produce<C, 8, C::PS>(pre_m, slot, ln, a.soft(), true, phr, MODE == kForward ? mass : nullptr);
-            if (MODE == kForward) dnp[(it & 1) * 256 + w * 64 + lane] = dnl;      // this lane's tables' share of the normaliser
+            const float dnl = produce<C, 8, C::PS, MODE == kForward>(pre_m, slot, spread_row(ln), a.soft(), true, phr, it, mass);
+            if (MODE == kForward) dnp[(it & 1) * 256 + w * 64 + opaque(lane, it)] = dnl;      // this lane's tables' share of the normaliser
         } else if (intra) {
-            produce<C, 8, C::PS>(pre_m, slot, ln, a.soft(), ln < nvalid, phw);
+            produce<C, 8, C::PS>(pre_m, slot, spread_row(ln), a.soft(), ln < nvalid, phw, it);
         }
         if (!kOutputFirst && it > 0) epilogue(it - 1);
         __syncthreads();
@@ -428,12 +426,12 @@ void stream_kernel(KArgs a, const float *Mr, const float *Mw, const bf16raw *Y, 
         for (int mt = 0; mt < C::MT; ++mt) {
 #pragma unroll
             for (int s = 0; s < 2; ++s) {
-                const int rr = r_own + 32 * mt + 16 * s + 8 * h;      // pair-interleaved corners: one 16-byte read
-                const u32x4 ar = lds128(phr + ln * C::PS + rr);
+                const int rr = tile_row<C>(r_own, mt, cg) + 16 * s + 8 * h;      // pair-interleaved corners: one 16-byte read
+                const u32x4 ar = lds128(phr + spread_row(ln) * C::PS + rr);
 #pragma unroll
                 for (int nt = 0; nt < C::NTW; ++nt) out[nt] = mma(acc_operand(Sacc[mt][nt], s), ar, out[nt]);
                 if (intra) {
-                    const u32x4 aw = lds128(phw + ln * C::PS + rr);
+                    const u32x4 aw = lds128(phw + spread_row(ln) * C::PS + rr);
                     sct = mma(aw, ar, sct);
                 }
                 RACE_SCHED_FENCE();
@@ -458,6 +456,21 @@ void stream_kernel(KArgs a, const float *Mr, const float *Mw, const bf16raw *Y, 
                     out[nt] = mma(lds_tr_acc(ytile, C::YS, 16 * s, c_own + 32 * nt, ln, h), ak, out[nt]);
             }
         }
+        // the next tile's loads fly during the reduction and the update (few registers are live there)
+        if (it + 1 < ntiles) fetch(it + 1);
+
+        // ---- reduction over the bucket-row groups: partial read-outs through LDS, 16 bytes per store
+        //      (a lane holds four consecutive columns of its token in registers 4k .. 4k+3), under the products of the update
+        const int rbase = opaque((rg * kTile + ln) * S::RS + c_own + 4 * h, it);
+#pragma unroll
+        for (int nt = 0; nt < C::NTW; ++nt) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                *reinterpret_cast<float4 *>(red + rbase + 32 * nt + 8 * k) =
+                    float4{out[nt][4 * k], out[nt][4 * k + 1], out[nt][4 * k + 2], out[nt][4 * k + 3]};
+        }
+        // in-tile part of the normaliser: row sums of the masked kernel values (partial over this row group)
+        if (MODE == kForward && cg == 0 && h == 0) red[(rg * kTile + ln) * S::RS + C::D] = rowsum;
         if (intra) {
             // ---- statistics += phi_writer^T . Y  (the read-out above used the old statistics)
 #pragma unroll
@@ -467,36 +480,20 @@ void stream_kernel(KArgs a, const float *Mr, const float *Mw, const bf16raw *Y, 
                 for (int nt = 0; nt < C::NTW; ++nt) by[nt] = lds_tr_plain(ytile, C::YS, 16 * s, c_own + 32 * nt, ln, h);
 #pragma unroll
                 for (int mt = 0; mt < C::MT; ++mt) {
-                    const u32x4 ap = lds_tr_plain<true>(phw, C::PS, 16 * s, r_own + 32 * mt, ln, h);
-                    if (MODE == kForward && mass_owner<C>(mt, cg)) macc[mt / C::CG] += column_sum<false>(ones32<false>(opaque(lane)), ap);
+                    const u32x4 ap = lds_tr_plain<true, true>(phw, C::PS, 16 * s, tile_row<C>(r_own, mt, cg), ln, h);
+                    if (MODE == kForward && mt < C::MA) macc[mt] += column_sum<false>(ones32<false>(opaque(lane, it)), ap);
 #pragma unroll
                     for (int nt = 0; nt < C::NTW; ++nt) Sacc[mt][nt] = mma(ap, by[nt], Sacc[mt][nt]);
                     RACE_SCHED_FENCE();
                 }
             }
         }
-        // the next tile's loads fly during the reduction and the output of this tile (few registers are live there)
-        if (it + 1 < ntiles) fetch(it + 1);
-
-        // ---- reduction over the bucket-row groups: partial read-outs through LDS, 16 bytes per store
-        //      (a lane holds four consecutive columns of its token in registers 4k .. 4k+3)
-        const int rbase = opaque((rg * kTile + ln) * S::RS + c_own + 4 * h);
-#pragma unroll
-        for (int nt = 0; nt < C::NTW; ++nt) {
-#pragma unroll
-            for (int k = 0; k < 4; ++k)
-                *reinterpret_cast<float4 *>(red + rbase + 32 * nt + 8 * k) =
-                    float4{out[nt][4 * k], out[nt][4 * k + 1], out[nt][4 * k + 2], out[nt][4 * k + 3]};
-        }
         if (MODE == kForward) {
-            // in-tile part of the normaliser: row sums of the masked kernel values (partial over this row group)
-            if (cg == 0 && h == 0) red[(rg * kTile + ln) * S::RS + C::D] = rowsum;
             // masses after this tile, for the next tile's read-out
 #pragma unroll
-            for (int mt = 0; mt < C::MT; ++mt) {
-                if (!mass_owner<C>(mt, cg)) continue;
-                const float tot = sum_halves(macc[mt / C::CG]);
-                if (h == 0) mass[r_own + 32 * mt + il(ln)] = tot;
+            for (int mt = 0; mt < C::MA; ++mt) {
+                const float tot = sum_halves(macc[mt]);
+                if (h == 0) mass[tile_row<C>(r_own, mt, cg) + il(ln)] = tot;
             }
         }
         __syncthreads();
@@ -598,7 +595,7 @@ __global__ __launch_bounds__(kThreads) void hash_tap_kernel(KArgs a, const bf16r
             if (Share<C, 8>::part(slot) == 0 && table < a.L_real && ln < nvalid)
                 codes[(static_cast<size_t>(bh) * a.N + t0 + ln) * a.L_real + table] = static_cast<uint8_t>(code);
         }
-        produce<C, 8, C::PS>(r, slot, ln, sf, true, ph);
+        produce<C, 8, C::PS>(r, slot, ln, sf, true, ph, 0);
     }
     __syncthreads();
     if (phi) {
@@ -662,6 +659,7 @@ KArgs make_kargs(const Plan &p, char *ws)
     KArgs a;
     a.H = p.H; a.nseg = p.nseg; a.N = p.N; a.seg_len = p.seg_len; a.beta = p.beta;
     a.L_real = p.L; a.P_real = p.P;
+    a.inv_tables = 1.0f / static_cast<float>(p.L);
     a.Wp = reinterpret_cast<const bf16raw *>(ws + p.off_W);
     a.state = reinterpret_cast<float *>(ws + p.off_stateA);
     a.Mq = reinterpret_cast<float *>(ws + p.off_massQ);
