@@ -7,7 +7,7 @@
 // wavefront holds an eighth of them as 32x32 MFMA accumulator tiles (stream kernels: a quarter of the
 // bucket rows x half of the columns; grad kernel: an eighth of the bucket rows x all columns, transposed).
 // Per tile the workgroup
-//   1. turns the hashed rows of the tile's queries and keys (hash_kernel) into soft assignments phi (vector ALU), written
+//   1. turns the hashed rows of the tile's queries and keys (bit_code()) into soft assignments phi (vector ALU), written
 //      as bf16 tiles to LDS;
 //   2. contracts them with the register-resident statistics and with each other (MFMA).
 // Two barriers per tile: whatever goes to LDS for a tile is written in the first half (next to the output of the previous
@@ -540,21 +540,98 @@ __device__ __forceinline__ void load_table_codes(const float *Mt, uint32_t lane_
 }
 
 // Production: SLOTS half wavefronts share the tables of a tile of 32 tokens (lane = token).  Half wavefront `slot` takes
-// tables slot, slot + SLOTS, ...; with fewer tables than slots, two share a table (the lower and upper half of its
+// tables NTAB slot .. NTAB slot + NTAB - 1; with fewer tables than slots, two share a table (the lower and upper half of its
 // 16-byte pieces) and the rest are idle.
 template <class C, int SLOTS>
 struct Share {
     static constexpr int NTAB = C::L >= SLOTS ? C::L / SLOTS : 1;
     static constexpr int PARTS = C::L >= SLOTS ? 1 : 2;
     static_assert(C::L >= SLOTS ? C::L % SLOTS == 0 : SLOTS % C::L == 0, "tables over half wavefronts");
-    __device__ static __forceinline__ int table(int slot, int i) { return PARTS == 1 ? slot + i * SLOTS : slot % C::L; }
+    __device__ static __forceinline__ int table(int slot, int i) { return PARTS == 1 ? slot * NTAB + i : slot % C::L; }
     __device__ static __forceinline__ int part(int slot) { return PARTS == 1 ? 0 : slot / C::L; }       // >= PARTS: idle
     typedef Codes<C, NTAB> Regs;
     // Mt: the tile's hashed rows; lane_off: table_offset() of table(slot, 0)
     __device__ static __forceinline__ void load(const float *Mt, uint32_t lane_off, int ln, Regs &r)
     {
 #pragma unroll
-        for (int i = 0; i < NTAB; ++i) load_table_codes<C>(Mt + i * SLOTS * C::HT, lane_off, ln, r.c[i]);
+        for (int i = 0; i < NTAB; ++i) load_table_codes<C>(Mt + i * C::HT, lane_off, ln, r.c[i]);
+    }
+};
+
+// Hashed rows formed where they are used: the tables of a wavefront's two half wavefronts (slots 2 a and 2 a + 1 of Share) are at most
+// 16 packed rows of W, projected as two 16 x 16 tiles of 16 tokens whose rows 4 q + v are, for q = 2 h + i, quad i of the hyperplanes
+// (P = 6) or table i (P = 4) of half wavefront h.  Swapping rows of 16 lanes between the two tiles then leaves every lane with all
+// projections of its token and tables.  W stays in registers, the rows come from an LDS tile [tokens][XS].
+template <class C, int SLOTS>
+struct Hasher {
+    using Sh = Share<C, SLOTS>;
+    u32x4 w[C::D / 32];
+    __device__ __forceinline__ void load(const bf16raw *Wp, int a, int lane)
+    {
+        const int m = lane & 15, q = m >> 2, hh = q >> 1, i = q & 1;
+        const int row = C::PP == 8 ? Sh::table(2 * a + hh, 0) * 8 + 4 * i + (m & 3) : Sh::table(2 * a + hh, i < Sh::NTAB ? i : 0) * 4 + (m & 3);
+#pragma unroll
+        for (int s = 0; s < C::D / 32; ++s) w[s] = *reinterpret_cast<const u32x4 *>(Wp + row * C::D + 32 * s + 8 * (lane >> 4));
+    }
+    // the tile's rows as operands; row_of: where a token's row begins
+    struct Rows { u32x4 x[2][C::D / 32]; };
+    template <class RowOf>
+    __device__ __forceinline__ static void fetch(RowOf row_of, int lane, Rows &r)
+    {
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            const bf16raw *row = row_of(16 * t + (lane & 15)) + 8 * (lane >> 4);
+#pragma unroll
+            for (int s = 0; s < C::D / 32; ++s) r.x[t][s] = *reinterpret_cast<const u32x4 *>(row + 32 * s);
+        }
+    }
+    // x: an LDS tile [tokens][XS]; M: where the tile's hashed rows go (null: nowhere)
+    template <bool UNIT>
+    __device__ __forceinline__ void run(const bf16raw *x, int slot, int lane, const Soft &sf, float *M, typename Sh::Regs &r) const
+    {
+        Rows rows;
+        fetch([&](int token) __attribute__((always_inline)) { return x + token * C::XS; }, lane, rows);
+        run_rows<UNIT>(rows, slot, lane, sf, M, r);
+    }
+    template <bool UNIT>
+    __device__ __forceinline__ void run_rows(const Rows &rows, int slot, int lane, const Soft &sf, float *M, typename Sh::Regs &r) const
+    {
+        const int ln = lane & 31;
+        f32x4 z[2];
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            const u32x4 (&xv)[C::D / 32] = rows.x[t];
+            z[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int s = 0; s < C::D / 32; ++s) z[t] = mma16(w[s], xv[s], z[t]);
+            if (UNIT) {
+                // 1 / max(|x|, 1e-12), from the fp32 sum of squares of the stored elements
+                float ss = 0.f;
+#pragma unroll
+                for (int s = 0; s < C::D / 32; ++s) ss = dot2(xv[s].x, xv[s].x, dot2(xv[s].y, xv[s].y, dot2(xv[s].z, xv[s].z, dot2(xv[s].w, xv[s].w, ss))));
+                z[t] = z[t] * __builtin_amdgcn_rsqf(fmaxf(sum_rows(ss), 1e-24f));
+            }
+        }
+        float zz[2][4];
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const auto s = __builtin_amdgcn_permlane16_swap(__float_as_uint(z[0][v]), __float_as_uint(z[1][v]), false, false);
+            zz[0][v] = __uint_as_float(s[0]);
+            zz[1][v] = __uint_as_float(s[1]);
+        }
+#pragma unroll
+        for (int i = 0; i < Sh::NTAB; ++i) {
+            const int table = Sh::table(slot, i);
+#pragma unroll
+            for (int t = 0; t < C::P; ++t) {
+                const float code = bit_code(C::PP == 8 ? zz[t / 4][t % 4] : zz[i][t], sf.beta);      // (worked out in any case: no branch)
+                r.c[i][t] = !C::PAD || (table < sf.L && t < sf.P) ? code : 0.f;
+            }
+            if (!M || Sh::part(slot) > 0) continue;
+            float *dst = M + table * C::HT;
+            *reinterpret_cast<float4 *>(dst + 4 * ln) = float4{r.c[i][0], r.c[i][1], r.c[i][2], r.c[i][3]};
+            if (C::P == 6) *reinterpret_cast<float2 *>(dst + 4 * kTile + 2 * ln) = float2{r.c[i][4], r.c[i][5]};
+        }
     }
 };
 

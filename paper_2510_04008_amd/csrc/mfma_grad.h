@@ -9,7 +9,7 @@
 //       dphi_K(j)[r] = dS[r,:] . [V_j | 1]
 // followed in both cases by the chain rule through the corner softmax, tanh and W:  dx = W^T dz.
 // "reader" is the tensor whose gradient is produced, "writer" the tensor that feeds the statistics.  The assignments of
-// both are rebuilt from their hashed rows (hash_kernel); the chain rule through tanh needs tanh z and its derivative as
+// both are rebuilt from their hashed rows; the chain rule through tanh needs tanh z and its derivative as
 // well, for which the reader's rows are projected here, a 16 x 16 tile per wavefront.
 //
 // The statistics are held transposed, tiles S^T[head column][bucket row], so that a tile's accumulator
@@ -225,17 +225,22 @@ void grad_kernel(KArgs a, const bf16raw *Xr, const bf16raw *V, const bf16raw *G_
     const int64_t t_end = (t_begin + a.seg_len < a.N) ? t_begin + a.seg_len : a.N;
     const int ntiles = static_cast<int>((t_end - t_begin + kTile - 1) / kTile);
     auto tile_t0 = [&](int it) { return t_begin + static_cast<int64_t>(kReverse ? ntiles - 1 - it : it) * kTile; };
+    // the loads of a tile that does not exist repeat the last one's (and are not used): see store_buffer()
+    const int64_t t_last = t_begin + static_cast<int64_t>(ntiles - 1) * kTile;
+    auto existing_t0 = [&](int it) { const int64_t t = tile_t0(it); return kReverse ? (t > t_begin ? t : t_begin) : (t < t_last ? t : t_last); };
     auto tile_nv = [&](int64_t t0) { return (t_end - t0 < kTile) ? static_cast<int>(t_end - t0) : kTile; };
 
-    // LDS addresses are a lane's offset under a stride plus a uniform one, added where it is used.  R = 64: the lane's offsets are
-    // worked out here; R = 16, where they would push two workgroups' registers past a CU's: again in every tile.
+    // LDS addresses are a lane's offset under a stride plus a uniform one, added where it is used.  The lane's offsets are worked out
+    // here, or, where they would push two workgroups' registers past a CU's (R = 16) or spill (the unit-norm option beside 128
+    // registers of statistics), again in every tile.
+    constexpr bool kRebuild = G::T16 || (UNIT && G::SREGS == 128);
     int step = 0;       // (the loop counter of these sums)
     auto at = [&](int uniform, int lane_offset) __attribute__((always_inline)) { return lds + (opaque_uniform(uniform, step) + lane_offset); };
     const int at16x_ = (n16 * C::XS + 8 * q16) * 2, at16d_ = (n16 * S::DZS + 8 * q16) * 2;      // 16-row operands
     const int at_x_ = chunk_offset<C, C::XS, kPlain>(tid), at_yr_ = chunk_offset<C, C::XS, G::YORDER>(tid), at_yw_ = chunk_offset<C, C::YS, G::YORDER>(tid);
     auto rebuilt_lane = [&]() __attribute__((always_inline)) { return opaque(lane, step); };
     auto at16 = [&](int stride, int kept) __attribute__((always_inline)) {
-        if (!G::T16) return kept;
+        if (!kRebuild) return kept;
         const int lo = rebuilt_lane();
         return ((lo & 15) * stride + 8 * (lo >> 4)) * 2;
     };
@@ -246,7 +251,7 @@ void grad_kernel(KArgs a, const bf16raw *Xr, const bf16raw *V, const bf16raw *G_
     RowChunks<C, kTile> pre_r, pre_v, pre_g;
     float pre_ge = 0.f;
     auto fetch_y = [&](int it) __attribute__((always_inline)) {
-        const int64_t t0 = tile_t0(it);
+        const int64_t t0 = existing_t0(it);
         const int nv = tile_nv(t0);
         if (SIDE == 1 || intra) fetch_rows<C, kTile>(V, t0, nv, pre_v);
         if (SIDE == 0 || intra) {
@@ -255,12 +260,12 @@ void grad_kernel(KArgs a, const bf16raw *Xr, const bf16raw *V, const bf16raw *G_
         }
     };
     auto fetch_x = [&](int it) __attribute__((always_inline)) {
-        const int64_t t0 = tile_t0(it);
+        const int64_t t0 = existing_t0(it);
         fetch_rows<C, kTile>(Xr, t0, tile_nv(t0), pre_r);
     };
     auto stage_y = [&](int it) __attribute__((always_inline)) {
-        store_tile<C, G::YORDER>(SIDE == 0 ? pre_g : pre_v, at(S::yr + (it & 1) * S::yr_bytes, G::T16 ? chunk_offset<C, C::XS, G::YORDER>(opaque(tid, step)) : at_yr_));
-        if (intra) store_tile<C, G::YORDER>(SIDE == 0 ? pre_v : pre_g, at(S::yw + (it & 1) * S::yw_bytes, G::T16 ? chunk_offset<C, C::YS, G::YORDER>(opaque(tid, step)) : at_yw_));
+        store_tile<C, G::YORDER>(SIDE == 0 ? pre_g : pre_v, at(S::yr + (it & 1) * S::yr_bytes, kRebuild ? chunk_offset<C, C::XS, G::YORDER>(opaque(tid, step)) : at_yr_));
+        if (intra) store_tile<C, G::YORDER>(SIDE == 0 ? pre_v : pre_g, at(S::yw + (it & 1) * S::yw_bytes, kRebuild ? chunk_offset<C, C::YS, G::YORDER>(opaque(tid, step)) : at_yw_));
         if (tid < kTile) {
             buf_sr(it)[tid] = SIDE == 0 ? pre_ge : 1.f;
             buf_sw(it)[tid] = SIDE == 0 ? 1.f : pre_ge;
@@ -268,7 +273,7 @@ void grad_kernel(KArgs a, const bf16raw *Xr, const bf16raw *V, const bf16raw *G_
         if (SIDE == 1 && intra && tid < kParts * kTile) buf_swp(it)[tid] = weight_part(pre_ge, tid / kTile);
     };
     auto stage_x = [&](int it) __attribute__((always_inline)) {
-        store_tile<C, kPlain>(pre_r, at(S::xr + (UNIT ? it & 1 : 0) * S::xr_bytes, G::T16 ? chunk_offset<C, C::XS, kPlain>(opaque(tid, step)) : at_x_));
+        store_tile<C, kPlain>(pre_r, at(S::xr + (UNIT ? it & 1 : 0) * S::xr_bytes, kRebuild ? chunk_offset<C, C::XS, kPlain>(opaque(tid, step)) : at_x_));
         if (UNIT) store_row_scales<C, kTile>(pre_r, buf_nrm(it), step);
     };
     // the writer's assignments.  R = 64: every wavefront builds those of its own table, which nothing else reads; R = 16: the first
@@ -281,11 +286,9 @@ void grad_kernel(KArgs a, const bf16raw *Xr, const bf16raw *V, const bf16raw *G_
     const uint32_t woff = table_offset<C>(G::T16 ? Sh::table(slot, 0) : tl0, ln);
     auto fetch_w = [&](int it) __attribute__((always_inline)) {
         if (!produces) return;
-        if constexpr (G::T16) Sh::load(Mw + tile_t0(it) * C::LP, woff, ln, pre_w);
-        else load_table_codes<C>(Mw + tile_t0(it) * C::LP, woff, ln, own_w);
+        if constexpr (G::T16) Sh::load(Mw + existing_t0(it) * C::LP, woff, ln, pre_w);
+        else load_table_codes<C>(Mw + existing_t0(it) * C::LP, woff, ln, own_w);
     };
-    // the loads of a tile that does not exist repeat the last one's (and are not used): see store_buffer()
-    auto existing = [&](int it) { return it < ntiles ? it : ntiles - 1; };
     // the reader's hashed rows: R = 64: token ln of the wavefront's table; R = 16: tokens n16 (and 16 + n16) of its tables
     const int th0 = G::TS == 2 ? w >> 2 : 0;
     const uint32_t roff = table_offset<C>(tl0, G::T16 ? 16 * th0 + n16 : ln);
@@ -308,8 +311,8 @@ void grad_kernel(KArgs a, const bf16raw *Xr, const bf16raw *V, const bf16raw *G_
         fetch_w(0);
         stage_x(0);
         stage_y(0);
-        fetch_x(existing(1));
-        fetch_y(existing(1));
+        fetch_x(1);
+        fetch_y(1);
         __syncthreads();
     }
 
@@ -348,9 +351,8 @@ void grad_kernel(KArgs a, const bf16raw *Xr, const bf16raw *V, const bf16raw *G_
             x1 = mma16(o.wb[s], o.d[s], x1);
         }
     };
-    // (tile -1, of the first step, has no rows)
     auto dx_store = [&](int i, int it, f32x4 x0, f32x4 x1) __attribute__((always_inline)) {
-        const int64_t t0 = tile_t0(it >= 0 ? it : 0);
+        const int64_t t0 = tile_t0(it);
         const int c0 = 32 * (i >> 1);
         if (UNIT) {
             const int lo = opaque(lane, step), n = lo & 15, q = lo >> 4, tok = 16 * (i & 1) + n;
@@ -364,7 +366,7 @@ void grad_kernel(KArgs a, const bf16raw *Xr, const bf16raw *V, const bf16raw *G_
             x1[0] = fmaf(-cp, bf_lo(xv.z), x1[0]); x1[1] = fmaf(-cp, bf_hi(xv.z), x1[1]);
             x1[2] = fmaf(-cp, bf_lo(xv.w), x1[2]); x1[3] = fmaf(-cp, bf_hi(xv.w), x1[3]);
         }
-        buffer_store128(store_buffer(dX + t0 * C::D, it >= 0 ? tile_nv(t0) * C::D * 2 : 0), opaque_uniform((16 * (i & 1) * C::D + c0) * 2, step) + at16(C::D, (n16 * C::D + 8 * q16) * 2),
+        buffer_store128(store_buffer(dX + t0 * C::D, tile_nv(t0) * C::D * 2), opaque_uniform((16 * (i & 1) * C::D + c0) * 2, step) + at16(C::D, (n16 * C::D + 8 * q16) * 2),
                         u32x4{pack2(x0[0], x0[1]), pack2(x0[2], x0[3]), pack2(x1[0], x1[1]), pack2(x1[2], x1[3])});
     };
     // ---- projections of the reader's rows, 16 packed hyperplanes x 16 tokens (tile i of 2 PT), and what the chain rule through
@@ -401,20 +403,25 @@ void grad_kernel(KArgs a, const bf16raw *Xr, const bf16raw *V, const bf16raw *G_
     // (the reader's hashed rows of this wavefront's tables: used in the second half)
     constexpr int kTh = G::T16 && G::TS == 1 ? 2 : 1;      // R = 16: halves of the tile's tokens
     float rc[G::TPW * kTh][C::P];
-    auto first_half = [&](int it) __attribute__((always_inline)) {
-        const int64_t t0 = tile_t0(existing(it));
+    auto first_half = [&](int it, bool first) __attribute__((always_inline)) {
+        const int64_t t0 = existing_t0(it);
         const int nvalid = tile_nv(t0);
 #pragma unroll
         for (int i = 0; i < G::TPW * kTh; ++i)
             load_table_codes<C>(Mr + t0 * C::LP + (i / kTh) * C::HT + (i % kTh) * 64, roff, ln, rc[i]);      // (16 tokens are 64 floats)
         f32x4 z_own = {0.f, 0.f, 0.f, 0.f};
-        constexpr bool kAllDx = 2 * C::NT == kWaves;             // a piece of dX for every wavefront
+        // (R = 64, a piece of dX for every wavefront: its products run under the production)
+        constexpr bool kAllDx = 2 * C::NT == kWaves && !G::T16;
         DxOperands dxo;
         f32x4 x0 = {0.f, 0.f, 0.f, 0.f}, x1 = x0;
-        if (kAllDx) dx_load(my_dx, dxo);
+        if (kAllDx && !first) dx_load(my_dx, dxo);
         if (kAllProject) z_own = project(w, it);             // (under the production)
-        if (kAllDx) dx_mma(dxo, x0, x1);
-        if (!kAllDx && my_dx >= 0) {
+        if (kAllDx && !first) dx_mma(dxo, x0, x1);
+        if (G::T16) {
+            stage_y(it + 1);
+            fetch_y(it + 2);
+        }
+        if (!kAllDx && !first && my_dx >= 0) {
             dx_load(my_dx, dxo);
             dx_mma(dxo, x0, x1);
             dx_store(my_dx, it - 1, x0, x1);
@@ -423,8 +430,8 @@ void grad_kernel(KArgs a, const bf16raw *Xr, const bf16raw *V, const bf16raw *G_
             if constexpr (G::T16) produce<C, G::SLOTS, C::PST>(pre_w, slot, ln, a.soft(), ln < nvalid, phw, step);
             else produce_table<C, C::PS>(own_w, tl0, ln, h, a.soft(), ln < nvalid, phw, step);
         }
-        if (kAllDx) dx_store(my_dx, it - 1, x0, x1);
-        fetch_w(existing(it + 1));
+        if (kAllDx && !first) dx_store(my_dx, it - 1, x0, x1);
+        fetch_w(it + 1);
         if (kAllProject) {
             finish_projection(w, it, z_own);
         } else {
@@ -459,7 +466,7 @@ void grad_kernel(KArgs a, const bf16raw *Xr, const bf16raw *V, const bf16raw *G_
             *reinterpret_cast<u32x2 *>(dst) = u32x2{pack2(tt[0], tt[1]), pack2(tt[2], tt[3])};
         }
     };
-    if (ntiles > 0) first_half(0);
+    if (ntiles > 0) first_half(0, true);
     for (int it = 0; it < ntiles; ++it) {
         step = it;
         const int64_t t0 = tile_t0(it);
@@ -645,11 +652,14 @@ void grad_kernel(KArgs a, const bf16raw *Xr, const bf16raw *V, const bf16raw *G_
                 if (h == 0) rad[w * kTile + ln] = radial;
             }
         }
-        stage_y(it + 1);
-        fetch_y(existing(it + 2));
+        if (!G::T16) {          // (not before every wavefront has updated its statistics with the rows that lie there)
+            stage_y(it + 1);
+            fetch_y(it + 2);
+        }
         stage_x(it + 1);
-        fetch_x(existing(it + 2));
+        fetch_x(it + 2);
         __syncthreads();        // dz is visible; this tile's assignments, in-tile term and tanh are dead from here on
+        if (G::T16 && it + 1 == ntiles) break;
         if constexpr (!G::T16) {
             // ---- statistics += Yw^T . phi_writer
             if (intra) {
@@ -670,7 +680,16 @@ void grad_kernel(KArgs a, const bf16raw *Xr, const bf16raw *V, const bf16raw *G_
                 }
             }
         }
-        first_half(it + 1);
+        first_half(it + 1, false);
+    }
+    // (R = 64 comes past the end of the last tile and forms its dX there: with the loop left in the middle the statistics of the long
+    // sequences are spilled, and both gradients take 4 % more)
+    if (G::T16 && ntiles > 0 && my_dx >= 0) {
+        DxOperands dxo;
+        f32x4 x0, x1;
+        dx_load(my_dx, dxo);
+        dx_mma(dxo, x0, x1);
+        dx_store(my_dx, ntiles - 1, x0, x1);
     }
     // ---- cotangent of beta: lanes -> wavefront (shuffles) -> workgroup (LDS, wavefront order) -> one workspace slot
     if (a.want_dbeta) {

@@ -1,8 +1,9 @@
 // bf16 MFMA kernel family for RACE Attention on gfx950 (see mfma_common.h for the execution shape).
 //
 // Kernels
-//   hash_kernel      projection and per-bit soft-hash masses of every row of Q and K, once per call: the "hashed rows"
-//                    (one float per token, table and hyperplane) that every later pass rebuilds phi from.
+//   hashed rows      projection and per-bit soft-hash masses of every row of Q and K, once per call: one float per token, table and
+//                    hyperplane that every later pass rebuilds phi from.  The totals of the forward pass form K's, its replay
+//                    Q's (Hasher); hash_kernel forms Q's for a backward pass without the forward's workspace.
 //   totals_kernel    statistics of every segment from a zero start, of (phi_K, [V | 1]) (Algorithm 1, step 5) or, for the
 //                    backward pass, of (phi_Q, read-out cotangents); an exclusive prefix (forward) or suffix (backward)
 //                    scan over segments (scan_states) turns them into segment-start states.
@@ -14,6 +15,7 @@
 #include <hip/hip_runtime.h>
 
 #include "internal.h"
+#include <algorithm>
 #include <cstring>
 
 #include "mfma_common.h"
@@ -31,92 +33,46 @@ template <class C>
 __device__ __forceinline__ int state_a(int r) { return C::LR * C::D + r; }
 
 // ================================================================ hash_kernel
-// z^T (32 packed rows of W) x (32 tokens): lane (n, h) ends up with packed rows 8 (v / 4) + 4 h + v % 4 of token n in register
-// v, i.e. with natural order (row = table * PP + t) the quads t = 4 h' .. 4 h' + 3 of whole tables.
-template <class C>
-struct WRows { u32x4 w[C::D / 16]; };             // this lane's row of a group, as A operands
-template <class C>
-__device__ __forceinline__ void load_w_rows(const bf16raw *Wp, int g, int ln, int h, WRows<C> &r)
-{
-#pragma unroll
-    for (int s = 0; s < C::D / 16; ++s) r.w[s] = *reinterpret_cast<const u32x4 *>(Wp + (g * 32 + ln) * C::D + 16 * s + 8 * h);
-}
-template <class C>
-__device__ __forceinline__ f32x16 project(const WRows<C> &w, const u32x4 (&x)[C::D / 16])
-{
-    // two accumulators halve the chain of dependent MFMAs
-    f32x16 z0 = {0}, z1 = {0};
-#pragma unroll
-    for (int s = 0; s < C::D / 16; s += 2) {
-        z0 = mma(w.w[s], x[s], z0);
-        z1 = mma(w.w[s + 1], x[s + 1], z1);
-    }
-    return z0 + z1;
-}
-// 1 / max(|x|, 1e-12) of the row whose elements 16 s + 8 h .. + 7 the two lane halves hold (fp32 sum of squares)
-template <class C>
-__device__ __forceinline__ float row_scale(const u32x4 (&x)[C::D / 16])
-{
-    float ss = 0.f;
-#pragma unroll
-    for (int s = 0; s < C::D / 16; ++s) ss = dot2(x[s].x, x[s].x, dot2(x[s].y, x[s].y, dot2(x[s].z, x[s].z, dot2(x[s].w, x[s].w, ss))));
-    ss += __shfl_xor(ss, 32, 64);
-    return __builtin_amdgcn_rsqf(fmaxf(ss, 1e-24f));
-}
-
-// Algorithm 1, steps 2-4 up to the per-bit masses, for every row of Q (blockIdx.z + first == 0) or K (== 1): one float per
-// (table, hyperplane), see bit_code().  Bound by memory: every wavefront streams tiles of 32 rows on its own (no LDS, no
-// barrier): its rows of W stay in registers, a row of X is 16-byte pieces straight from memory (the second group's
-// wavefront finds them in L1), the results leave as contiguous pieces of a table's 32 tokens, and the next tile's rows are
-// requested before the current one's arithmetic.  (Through LDS tiles with three barriers a step, 64 rows a step:
-// 3.4 ms for 33.5 million rows of 128 columns at L = 8, P = 6.)
+// Algorithm 1, steps 2-4 up to the per-bit masses, for every row of a tensor (blockIdx.z: of one or the other): one float per (table,
+// hyperplane), see bit_code().  For calls whose passes do not hash for themselves: see hash_in_passes(), and race_attn_bwd, whose
+// pass over Q would be the forward's.  The same arithmetic as theirs (Hasher), the rows straight from memory: no LDS, no barrier.
 constexpr int kHashThreads = 256;
 constexpr int kHashTokens = 512;        // most tokens per workgroup (amortises the load of W)
-template <class C> constexpr int hash_tiles() { return 4 / C::NG; }        // tiles a workgroup's wavefronts take at a time
 
 template <class C, bool UNIT>
-__global__ __launch_bounds__(kHashThreads) void hash_kernel(KArgs a, const bf16raw *Xq, const bf16raw *Xk, int first)
+__global__ __launch_bounds__(kHashThreads) void hash_kernel(KArgs a, const bf16raw *X, float *M, const bf16raw *X1, float *M1)
 {
-    const int which = static_cast<int>(blockIdx.z) + first;
-    const int bh = blockIdx.y, head = bh % a.H;
-    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, ln = lane & 31, h = lane >> 5;
-    const int g = w % C::NG;
-    const bf16raw *X = (which ? Xk : Xq) + static_cast<size_t>(bh) * a.N * C::D;
+    if (blockIdx.z) { X = X1; M = M1; }
+    const int bh = blockIdx.y;
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, h = lane >> 5;
+    X += static_cast<size_t>(bh) * a.N * C::D;
     const int64_t all_tiles = (a.N + kTile - 1) / kTile;
-    float *M = (which ? a.Mk : a.Mq) + static_cast<size_t>(bh) * all_tiles * kTile * C::LP;
-    WRows<C> wr;
-    load_w_rows<C>(a.Wp + static_cast<size_t>(head) * C::LPP * C::D, g, ln, h, wr);
+    M += static_cast<size_t>(bh) * all_tiles * kTile * C::LP;
+    // a wavefront hashes all tables of its tiles: what two or four of them share in the passes
+    constexpr int kShares = Share<C, 8>::PARTS == 2 ? 2 : 4, kTiles = kHashThreads / 64;
+    Hasher<C, 8> hasher[kShares];
+#pragma unroll
+    for (int i = 0; i < kShares; ++i) hasher[i].load(a.Wp + static_cast<size_t>(bh % a.H) * C::LPP * C::D, i, lane);
     const int64_t t_first = static_cast<int64_t>(blockIdx.x) * (a.hash_tokens / kTile);
     const int64_t t_end = (t_first + a.hash_tokens / kTile < all_tiles) ? t_first + a.hash_tokens / kTile : all_tiles;
-    const Soft sf = a.soft();
-    // (rows past the end repeat the last one: finite values in the padding of the last tile)
-    auto fetch = [&](int64_t tile, u32x4 (&x)[C::D / 16]) __attribute__((always_inline)) {
-        const int64_t t = tile * kTile + ln;
-        const bf16raw *src = X + (t < a.N ? t : a.N - 1) * C::D + 8 * h;
-#pragma unroll
-        for (int s = 0; s < C::D / 16; ++s) x[s] = *reinterpret_cast<const u32x4 *>(src + 16 * s);
+    using Rows = typename Hasher<C, 8>::Rows;
+    auto fetch = [&](int64_t tile, Rows &rows) __attribute__((always_inline)) {
+        // (rows past the end repeat the last one: finite values in the padding of the last tile)
+        Hasher<C, 8>::fetch([&](int token) __attribute__((always_inline)) {
+            const int64_t t = tile * kTile + token;
+            return X + (t < a.N ? t : a.N - 1) * C::D;
+        }, lane, rows);
     };
-    int64_t tile = t_first + w / C::NG;
-    u32x4 x[C::D / 16];
-    if (tile < t_end) fetch(tile, x);
-    for (; tile < t_end; tile += hash_tiles<C>()) {
-        f32x16 z = project<C>(wr, x);
-        if (UNIT) z = z * row_scale<C>(x);
-        if (tile + hash_tiles<C>() < t_end) fetch(tile + hash_tiles<C>(), x);
-        float *Mt = M + tile * (kTile * C::LP);
+    int64_t tile = t_first + w;
+    Rows rows;
+    if (tile < t_end) fetch(tile, rows);
+    for (; tile < t_end; tile += kTiles) {
+        const Rows now = rows;
+        if (tile + kTiles < t_end) fetch(tile + kTiles, rows);
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            // this lane's quad of registers 4 k .. 4 k + 3: hyperplanes 4 (quad % (PP / 4)) .. of a table
-            const int quad = g * 8 + 2 * k + h, table = C::PP == 8 ? quad >> 1 : quad, t0 = C::PP == 8 ? 4 * h : 0;
-            if (table >= C::L) continue;
-            const bool real_table = !C::PAD || table < sf.L;
-            float c[4];
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-                c[e] = (real_table && (!C::PAD || t0 + e < sf.P)) ? bit_code(z[4 * k + e], sf.beta) : 0.f;
-            float *dst = Mt + table * C::HT;
-            if (C::PP == 4 || h == 0) *reinterpret_cast<float4 *>(dst + 4 * ln) = float4{c[0], c[1], c[2], c[3]};
-            else *reinterpret_cast<float2 *>(dst + 4 * kTile + 2 * ln) = float2{c[0], c[1]};
+        for (int i = 0; i < kShares; ++i) {
+            typename Share<C, 8>::Regs codes;
+            hasher[i].template run_rows<UNIT>(now, 2 * i + h, lane, a.soft(), M + tile * (kTile * C::LP), codes);
         }
     }
 }
@@ -131,24 +87,28 @@ struct TotalsLds {
     static constexpr int y = 0;                                         // [64][YS] accumulated rows
     static constexpr int ph = y + TT * C::YS * 2;                       // [64][PS] assignments
     static constexpr int ge = ph + TT * C::PS * 2;                     // [kParts][64] bf16
-    static constexpr int total = ge + kParts * TT * 2;
-    static_assert(total <= 160 * 1024, "LDS budget");
+    static constexpr int x = ge + kParts * TT * 2;                      // [64][XS] rows of K (HASH)
+    static constexpr int total = x, total_hash = x + TT * C::XS * 2;
+    static_assert(total_hash <= 160 * 1024, "LDS budget");
 };
 
 // The wavefronts of a row group share its row tiles' extra column: the one of column group cg takes the MA tiles that come first in
 // its own order, which starts at tile cg MA.  (Ownership by the tile's number was a branch around every tile's sum: the loads of the
-// products of one tile waited behind those of the one before it.  A single tile is summed by all of them and written by the first.)
+// products of one tile waited behind those of the one before it.  A single tile is the first one's.)
 // First bucket row of the mt-th tile in that order:
 template <class C>
 __device__ __forceinline__ int tile_row(int r_own, int mt, int cg) { return r_own + 32 * ((mt / C::MA + cg) % C::CG * C::MA % C::MT + mt % C::MA); }
 
-// M: the hashed rows of the tensor whose assignments feed the statistics (K forward, Q backward).  QG == 1 also leaves the
+// HASH (QG == 0): hashes the rows of K (X) itself and leaves the hashed rows in memory (M; null: nobody reads them): the pass over K that
+// hashed it before, and the pass over its hashed rows here, are one.  Next to the products' latencies the projection and the
+// exponentials cost less than their own kernel at the memory's rate (see hash_in_passes()).  Else M are the hashed rows of K or,
+// QG == 1, of Q.  QG == 1 also leaves the
 // cotangent rows it forms in memory, rows in Gout (the caller's buffer for dK, which nothing else uses before dK is
 // written, tile behind tile of its own reading) and the extra column in a.ge: the passes behind it then read 260 bytes a token instead of dO,
 // O and Den, and do not form the rows again (35 of 750 vector instructions a tile and wavefront).
-template <class C, int QG>
-__global__ __launch_bounds__(kThreads, C::STREAM_WAVES_PER_SIMD)
-void totals_kernel(KArgs a, const float *M, const bf16raw *Y, const bf16raw *Oin, const float *den_in, bf16raw *Gout)
+template <class C, int QG, bool HASH, bool UNIT>
+__global__ __launch_bounds__(kThreads, (C::MT * C::NTW <= 2 ? 4 : 2))      // (two workgroups on a CU where their registers fit it)
+void totals_kernel(KArgs a, float *M, const bf16raw *X, const bf16raw *Y, const bf16raw *Oin, const float *den_in, bf16raw *Gout)
 {
     using S = TotalsLds<C>;
     constexpr int TT = S::TT;
@@ -156,19 +116,23 @@ void totals_kernel(KArgs a, const float *M, const bf16raw *Y, const bf16raw *Oin
     bf16raw *ys = reinterpret_cast<bf16raw *>(lds + S::y);
     bf16raw *ph = reinterpret_cast<bf16raw *>(lds + S::ph);
     bf16raw *ge_lds = reinterpret_cast<bf16raw *>(lds + S::ge);
+    bf16raw *xs = reinterpret_cast<bf16raw *>(lds + S::x);
 
     const int seg = blockIdx.x, bh = blockIdx.y;
     const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, ln = lane & 31, h = lane >> 5;
     const int rg = w % C::RG, cg = w / C::RG;
     const int r_own = rg * C::LRW, c_own = cg * C::DW;
     const size_t base = static_cast<size_t>(bh) * a.N * C::D;
-    M += static_cast<size_t>(bh) * ((a.N + kTile - 1) / kTile) * (kTile * C::LP); Y += base;
+    if (M) M += static_cast<size_t>(bh) * ((a.N + kTile - 1) / kTile) * (kTile * C::LP);
+    Y += base;
+    if (HASH) X += base;
     float *ge_out = a.ge + static_cast<size_t>(bh) * a.N;
     if (QG) { Oin += base; Gout += base; den_in += static_cast<size_t>(bh) * a.N; }
     float *st = a.state + (static_cast<size_t>(bh) * a.nseg + seg) * C::STATE;
     // causal: the totals of the last segment (backward: of the first) are in no other segment's start state
+    // (the last segment's rows of K are hashed all the same)
     const bool unread = a.scanned && seg == (QG ? 0 : a.nseg - 1);
-    if (!QG && unread) return;
+    if (!QG && !HASH && unread) return;
 
     f32x16 Sacc[C::MT][C::NTW];
     float macc[C::MA];                 // extra column of the first row tiles: lane n <-> row, per-half partial sums
@@ -189,22 +153,43 @@ void totals_kernel(KArgs a, const float *M, const bf16raw *Y, const bf16raw *Oin
     const uint32_t lane_off = table_offset<C>(Share<C, 8>::table(slot, 0), ln);
     const bf16raw *ge_lane = ge_lds + parts_offset32<false>(TT, lane);
     typename Share<C, 8>::Regs pre_m;
-    RowChunks<C, TT> pre_y;
+    RowChunks<C, TT> pre_y, pre_x;
     CotChunks<C, TT> pre_c;
     auto fetch = [&](int it) {
         const int64_t t0 = t_begin + static_cast<int64_t>(it) * TT;
         const int nv = step_nv(t0);
         // (the second half of the last step may lie past the end: it reads the first half's tile, and its tokens are not valid)
         const int64_t tile = t0 / kTile + (half && nv > kTile ? 1 : 0);
-        Share<C, 8>::load(M + tile * (kTile * C::LP), lane_off, ln, pre_m);
+        if (!HASH) Share<C, 8>::load(M + tile * (kTile * C::LP), lane_off, ln, pre_m);
         if (QG) fetch_cotangent<C, TT>(Y, Oin, den_in, t0, nv, pre_c);
         else fetch_rows<C, TT>(Y, t0, nv, pre_y);
     };
-    if (nsteps > 0) fetch(0);
+    // rows of K: requested two steps ahead, in LDS one step ahead
+    auto fetch_x = [&](int it) {
+        const int64_t t0 = t_begin + static_cast<int64_t>(it < nsteps ? it : nsteps - 1) * TT;
+        fetch_rows<C, TT>(X, t0, step_nv(t0), pre_x);
+    };
+    Hasher<C, 8> hasher;
+    if (nsteps > 0) {
+        if (HASH) {
+            fetch_x(0);
+            hasher.load(a.Wp + static_cast<size_t>(bh % a.H) * C::LPP * C::D, w % 4, lane);
+        }
+        fetch(0);
+        if (HASH) {
+            store_rows<C, TT, C::XS>(pre_x, xs, 0);
+            fetch_x(1);
+            __syncthreads();
+        }
+    }
 
     for (int it = 0; it < nsteps; ++it) {
         const int64_t t0 = t_begin + static_cast<int64_t>(it) * TT;
         const int nvalid = step_nv(t0);
+        if constexpr (HASH) {
+            const bool exists = half * kTile < nvalid;
+            hasher.template run<UNIT>(xs + half * kTile * C::XS, slot, lane, a.soft(), exists && M ? M + (t0 / kTile + half) * (kTile * C::LP) : nullptr, pre_m);
+        }
         produce<C, 8, C::PS>(pre_m, slot, half * kTile + spread_row(ln), a.soft(), row < nvalid, ph, it);
         if (QG) {
             wait_loads();
@@ -214,6 +199,8 @@ void totals_kernel(KArgs a, const float *M, const bf16raw *Y, const bf16raw *Oin
         }
         if (it + 1 < nsteps) fetch(it + 1);
         __syncthreads();
+        // (two workgroups on a CU leave 128 registers, which (128, 4, 8) would pass with the rows of W kept)
+        if (HASH && C::D == 128 && C::MT * C::NTW == 2) hasher.load(a.Wp + static_cast<size_t>(bh % a.H) * C::LPP * C::D, w % 4, opaque(lane, it));
 #pragma unroll
         for (int s = 0; s < TT / 16; ++s) {
             u32x4 by[C::NTW];
@@ -223,10 +210,14 @@ void totals_kernel(KArgs a, const float *M, const bf16raw *Y, const bf16raw *Oin
 #pragma unroll
             for (int mt = 0; mt < C::MT; ++mt) {
                 const u32x4 ap = lds_tr_plain<true, true>(ph, C::PS, 16 * s, tile_row<C>(r_own, mt, cg), ln, h);
-                if (mt < C::MA) macc[mt] += column_sum<QG != 0>(gw, ap);      // the extra column (bucket mass, or its cotangent)
+                if (mt < C::MA && (C::MT > 1 || cg == 0)) macc[mt] += column_sum<QG != 0>(gw, ap);      // the extra column (bucket mass, or its cotangent)
 #pragma unroll
                 for (int nt = 0; nt < C::NTW; ++nt) Sacc[mt][nt] = mma(ap, by[nt], Sacc[mt][nt]);
             }
+        }
+        if (HASH) {
+            store_rows<C, TT, C::XS>(pre_x, xs, it);
+            fetch_x(it + 2);
         }
         __syncthreads();
     }
@@ -253,29 +244,35 @@ void totals_kernel(KArgs a, const float *M, const bf16raw *Y, const bf16raw *Oin
 // "reader" = tensor whose assignments read the statistics (Q forward, K for dV), "writer" = tensor
 // whose assignments feed them (K forward, Q for dV), Y = rows accumulated (V forward, the
 // cotangent rows for dV).
-template <class C>
+template <class C, bool NC>
 struct StreamLds {
+    // half wavefronts that share the production of a side: half of the workgroup.  (All of it where there is no writer's side: 182
+    // instead of 169 us for the forward pass at B H = 64, N = 16384, (64, 4, 16).)
+    static constexpr int SLOTS = 8;
     static constexpr int y = 0;                                         // [32][YS] bf16: accumulated rows
-    static constexpr int mass = y + kTile * C::YS * 2;                  // [LR] fp32: bucket masses A before this tile, pair-interleaved
-    static constexpr int dnp = mass + C::LR * 4;                        // [2][4][2][32] fp32: mass read-outs per reader wavefront and lane
-                                                                        // half, two buffers used by alternate tiles
-    static constexpr int phr = (dnp + 2 * 4 * 2 * kTile * 4 + 255) & ~255;   // [32][PS] reader assignments
+    static constexpr int mass = y + (NC ? 0 : kTile * C::YS * 2);       // [LR] fp32: bucket masses A before this tile, pair-interleaved
+    static constexpr int dnp = mass + C::LR * 4;                        // [2][SLOTS / 2][32] fp32: mass read-outs per reader wavefront,
+                                                                        // two buffers used by alternate tiles
+    static constexpr int phr = (dnp + SLOTS * kTile * 4 + 255) & ~255;  // [32][PS] reader assignments
     static constexpr int phw = phr + kTile * C::PS * 2;                 // [32][PS] writer assignments
     // reduction over the bucket-row groups, in bytes of its own: a tile's sums are formed next to the production of the
     // following tile
     static constexpr int RS = C::D + 4;                                 // fp32 row stride: D numerators, 1 normaliser part
-    static constexpr int red = (phw + kTile * C::PS * 2 + 255) & ~255;  // [RG][32][RS] fp32
+    static constexpr int red = (phw + (NC ? 0 : kTile * C::PS * 2) + 255) & ~255;  // [RG][32][RS] fp32
     static constexpr int total = red + C::RG * kTile * RS * 4;
-    static_assert(total <= 160 * 1024, "LDS budget");
+    static constexpr int x = total, total_hash = x + kTile * C::XS * 2;  // [32][XS] rows of Q (HASH)
+    static_assert(total_hash <= 160 * 1024 && (C::STREAM_WAVES_PER_SIMD < 4 || total_hash <= 80 * 1024), "LDS budget");
 };
 
 // NC: not causal (the in-tile term and the update are compiled out).
-// Mr, Mw: the hashed rows of the reader and the writer tensor.
-template <class C, int MODE, bool NC>
+// Mr, Mw: the hashed rows of the reader and the writer tensor.  HASH (kForward): hashes the reader's rows itself (X: Q) and leaves them
+// in Mr, see hash_in_passes().
+template <class C, int MODE, bool NC, bool HASH, bool UNIT>
 __global__ __launch_bounds__(kThreads, C::STREAM_WAVES_PER_SIMD)
-void stream_kernel(KArgs a, const float *Mr, const float *Mw, const bf16raw *Y, bf16raw *Out, float *den_out)
+void stream_kernel(KArgs a, float *Mr, const float *Mw, const bf16raw *X, const bf16raw *Y, bf16raw *Out, float *den_out)
 {
-    using S = StreamLds<C>;
+    using S = StreamLds<C, NC>;
+    using Sh = Share<C, S::SLOTS>;
     extern __shared__ __attribute__((aligned(256))) unsigned char lds[];
     bf16raw *ytile = reinterpret_cast<bf16raw *>(lds + S::y);
     float *mass = reinterpret_cast<float *>(lds + S::mass);
@@ -283,6 +280,7 @@ void stream_kernel(KArgs a, const float *Mr, const float *Mw, const bf16raw *Y, 
     bf16raw *phr = reinterpret_cast<bf16raw *>(lds + S::phr);
     bf16raw *phw = reinterpret_cast<bf16raw *>(lds + S::phw);
     float *red = reinterpret_cast<float *>(lds + S::red);
+    bf16raw *xs = reinterpret_cast<bf16raw *>(lds + S::x);
 
     constexpr bool kReverse = (MODE == kGradV);
     // Without the in-tile term half of the wavefronts have nothing to produce.  They finish the output under the others' production
@@ -302,6 +300,7 @@ void stream_kernel(KArgs a, const float *Mr, const float *Mw, const bf16raw *Y, 
     const size_t mbase = static_cast<size_t>(bh) * ((a.N + kTile - 1) / kTile) * (kTile * C::LP);
     Mr += mbase; Mw += mbase;
     Y += base; Out += base;
+    if (HASH) X += base;
     if (MODE == kForward) den_out += static_cast<size_t>(bh) * a.N;
     // statistics at the start of the segment (not causal: the totals, which the scan leaves in the first segment's place)
     const float *st = a.state + (static_cast<size_t>(bh) * a.nseg + (NC ? 0 : seg)) * C::STATE;
@@ -348,24 +347,46 @@ void stream_kernel(KArgs a, const float *Mr, const float *Mw, const bf16raw *Y, 
     auto tile_nv = [&](int64_t t0) { return (t_end - t0 < kTile) ? static_cast<int>(t_end - t0) : kTile; };
 
     // production: wavefronts 0-3 build the reader's assignments, 4-7 the writer's; a lane's token is ln, its tables by slot
-    const int side = w / 4, slot = 2 * (w % 4) + h;
-    const uint32_t lane_off = table_offset<C>(Share<C, 8>::table(slot, 0), ln);
+    constexpr int kHalf = S::SLOTS / 2;
+    const int side = w / kHalf, slot = 2 * (w % kHalf) + h;
+    const uint32_t lane_off = table_offset<C>(Sh::table(slot, 0), ln);
     // loads run one tile ahead of the arithmetic
-    typename Share<C, 8>::Regs pre_m;
+    typename Sh::Regs pre_m;
     RowChunks<C, kTile> pre_y;
     auto fetch = [&](int it) {
         const int64_t t0 = tile_t0(it);
-        if (side == 0 || intra) Share<C, 8>::load((side == 0 ? Mr : Mw) + t0 * C::LP, lane_off, ln, pre_m);
+        if (HASH ? side == 1 && intra : side == 0 || intra) Sh::load((side == 0 ? Mr : Mw) + t0 * C::LP, lane_off, ln, pre_m);
         if (intra) fetch_rows<C, kTile>(Y, t0, tile_nv(t0), pre_y);
     };
-    if (ntiles > 0) fetch(0);
+    // the reader's rows, in LDS at the end of the tile before theirs: requested behind its read-out, or, where a tile is that and little
+    // more (not causal: 210 instead of 169 us at B H = 64, N = 16384, (64, 4, 16)), a tile earlier
+    RowChunks<C, kTile> pre_x;
+    auto fetch_x = [&](int it) {
+        const int64_t t0 = tile_t0(it < ntiles ? it : ntiles - 1);
+        fetch_rows<C, kTile>(X, t0, tile_nv(t0), pre_x);
+    };
+    // (the rows of W stay in registers; at (64, 4, 16), causal, whose 128 are full, they are read again for every tile)
+    constexpr bool kReloadW = HASH && !NC && C::STREAM_WAVES_PER_SIMD == 4 && C::LR == 256;
+    Hasher<C, S::SLOTS> hasher;
+    const bf16raw *Wp = a.Wp + static_cast<size_t>(bh % a.H) * C::LPP * C::D;
+    if (ntiles > 0) {
+        if (HASH) {
+            fetch_x(0);
+            hasher.load(Wp, w % kHalf, lane);
+        }
+        fetch(0);
+        if (HASH) {
+            store_rows<C, kTile>(pre_x, xs, 0);
+            if (NC) fetch_x(1);
+        }
+    }
 
     // ---- epilogue of one tile: thread = (token, pieces of 4 columns: 4i.. and, for d = 128, 64 + 4i..; consecutive
     //      threads read consecutive 16-byte pieces of the partials): sum, normalise, store
     auto epilogue = [&](int it) __attribute__((always_inline)) {
         const int64_t t0 = tile_t0(it);
         const int nvalid = tile_nv(t0);
-        const float *dnr = dnp + (it & 1) * 256;
+        const float *dnr = dnp + (it & 1) * (kHalf * kTile);
         {
         constexpr int NP = C::D / 64;                // pieces of 4 columns per thread
         const int to = opaque(tid, it), tok = to >> 4, c0 = (to & 15) * 4;      // (addresses rebuilt per tile, not kept in registers)
@@ -374,7 +395,7 @@ void stream_kernel(KArgs a, const float *Mr, const float *Mw, const bf16raw *Y, 
         for (int c = 0; c < NP; ++c) acc[c][0] = acc[c][1] = acc[c][2] = acc[c][3] = 0.f;
         float e = 0.f;
 #pragma unroll
-        for (int gg = 0; gg < 4; ++gg) {              // row groups (at most four) and the four reader wavefronts
+        for (int gg = 0; gg < kHalf; ++gg) {          // row groups (at most four) and the reader wavefronts
             const float *src = red + (gg * kTile + tok) * S::RS;
             if (gg < C::RG) {
 #pragma unroll
@@ -384,7 +405,7 @@ void stream_kernel(KArgs a, const float *Mr, const float *Mw, const bf16raw *Y, 
                 }
             }
             if (MODE == kForward) {
-                const float dpart = dnr[gg * 64 + tok] + dnr[gg * 64 + 32 + tok];
+                const float dpart = dnr[gg * 32 + tok];
                 e += gg < C::RG ? src[C::D] + dpart : dpart;
             }
         }
@@ -399,7 +420,7 @@ void stream_kernel(KArgs a, const float *Mr, const float *Mw, const bf16raw *Y, 
         }
     }
     };
-    __syncthreads();        // the bucket masses are in place
+    __syncthreads();        // the bucket masses and the first tile's reader rows are in place
     for (int it = 0; it < ntiles; ++it) {
         const int nvalid = tile_nv(tile_t0(it));
         // ---- first half: this tile's rows and assignments -> LDS, then the previous tile's output (its stores are issued when
@@ -407,15 +428,20 @@ void stream_kernel(KArgs a, const float *Mr, const float *Mw, const bf16raw *Y, 
         if (kOutputFirst && it > 0) epilogue(it - 1);
         if (intra) store_rows<C, kTile, C::YS>(pre_y, ytile, it);
         if (side == 0) {
-            const float dnl = produce<C, 8, C::PS, MODE == kForward>(pre_m, slot, spread_row(ln), a.soft(), true, phr, it, mass);
-            if (MODE == kForward) dnp[(it & 1) * 256 + w * 64 + opaque(lane, it)] = dnl;      // this lane's tables' share of the normaliser
+            if constexpr (HASH) hasher.template run<UNIT>(xs, slot, lane, a.soft(), Mr + tile_t0(it) * C::LP, pre_m);
+            const float dnl = produce<C, S::SLOTS, C::PS, MODE == kForward>(pre_m, slot, spread_row(ln), a.soft(), true, phr, it, mass);
+            if (MODE == kForward) {
+                // this wavefront's tables' share of the normaliser
+                const float both = sum_halves(dnl);
+                if (h == 0) dnp[(it & 1) * (kHalf * kTile) + w * kTile + opaque(ln, it)] = both;
+            }
         } else if (intra) {
-            produce<C, 8, C::PS>(pre_m, slot, spread_row(ln), a.soft(), ln < nvalid, phw, it);
+            produce<C, S::SLOTS, C::PS>(pre_m, slot, spread_row(ln), a.soft(), ln < nvalid, phw, it);
         }
         if (!kOutputFirst && it > 0) epilogue(it - 1);
         __syncthreads();
 
-        if (!kOutputFirst && side == 1) lead(true);
+        if (!kOutputFirst && w >= 4) lead(true);
         // ---- contraction with the register-resident statistics (own bucket rows x own columns)
         f32x16 out[C::NTW];     // read-out, transposed: lane = reader token, register v = column acc_row(v, h) of the tile
         f32x16 sct = {0};       // in-tile kernel values, transposed: row = writer token, lane = reader token
@@ -437,7 +463,9 @@ void stream_kernel(KArgs a, const float *Mr, const float *Mw, const bf16raw *Y, 
                 RACE_SCHED_FENCE();
             }
         }
-        if (!kOutputFirst && side == 1) lead(false);
+        if (!kOutputFirst && w >= 4) lead(false);
+        if (HASH && !NC) fetch_x(it + 1);
+        if (kReloadW) hasher.load(Wp, w % kHalf, opaque(lane, it));
         if (intra) {
             // mask (writer token j = row, reader token i = lane), row sums, and (mask o kernel) . Y
 #pragma unroll
@@ -481,7 +509,7 @@ void stream_kernel(KArgs a, const float *Mr, const float *Mw, const bf16raw *Y, 
 #pragma unroll
                 for (int mt = 0; mt < C::MT; ++mt) {
                     const u32x4 ap = lds_tr_plain<true, true>(phw, C::PS, 16 * s, tile_row<C>(r_own, mt, cg), ln, h);
-                    if (MODE == kForward && mt < C::MA) macc[mt] += column_sum<false>(ones32<false>(opaque(lane, it)), ap);
+                    if (MODE == kForward && mt < C::MA && (C::MT > 1 || cg == 0)) macc[mt] += column_sum<false>(ones32<false>(opaque(lane, it)), ap);
 #pragma unroll
                     for (int nt = 0; nt < C::NTW; ++nt) Sacc[mt][nt] = mma(ap, by[nt], Sacc[mt][nt]);
                     RACE_SCHED_FENCE();
@@ -493,8 +521,12 @@ void stream_kernel(KArgs a, const float *Mr, const float *Mw, const bf16raw *Y, 
 #pragma unroll
             for (int mt = 0; mt < C::MA; ++mt) {
                 const float tot = sum_halves(macc[mt]);
-                if (h == 0) mass[tile_row<C>(r_own, mt, cg) + il(ln)] = tot;
+                if (h == 0 && (C::MT > 1 || cg == 0)) mass[tile_row<C>(r_own, mt, cg) + il(ln)] = tot;
             }
+        }
+        if (HASH) {
+            store_rows<C, kTile>(pre_x, xs, it);
+            if (NC) fetch_x(it + 2);
         }
         __syncthreads();
     }
@@ -553,45 +585,32 @@ __global__ __launch_bounds__(kTapThreads) void bucket_tap_kernel(const float *st
     else A[dst * a_stride] = run;
 }
 
-// Debug tap: hard codes and phi from the production step itself.
+// Debug tap: hard codes and phi from the passes' own hashing and production.
 template <class C, bool UNIT>
 __global__ __launch_bounds__(kThreads) void hash_tap_kernel(KArgs a, const bf16raw *X, uint8_t *codes, float *phi)
 {
     extern __shared__ __attribute__((aligned(256))) unsigned char lds[];
     bf16raw *ph = reinterpret_cast<bf16raw *>(lds);                             // [32][PS]
-    float *zt = reinterpret_cast<float *>(lds + kTile * C::PS * 2);             // [LPP][32] projections
-    const int bh = blockIdx.y, head = bh % a.H;
+    const int bh = blockIdx.y;
     const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, ln = lane & 31, h = lane >> 5;
     const int64_t t0 = static_cast<int64_t>(blockIdx.x) * kTile;
     const int nvalid = (a.N - t0 < kTile) ? static_cast<int>(a.N - t0) : kTile;
     const Soft sf = a.soft();
-    if (w < C::NG) {
-        WRows<C> wr;
-        load_w_rows<C>(a.Wp + static_cast<size_t>(head) * C::LPP * C::D, w, ln, h, wr);
-        u32x4 x[C::D / 16];
-        const bf16raw *src = X + (static_cast<size_t>(bh) * a.N + t0 + (ln < nvalid ? ln : nvalid - 1)) * C::D + 8 * h;
-#pragma unroll
-        for (int s = 0; s < C::D / 16; ++s) x[s] = *reinterpret_cast<const u32x4 *>(src + 16 * s);
-        f32x16 z = project<C>(wr, x);
-        if (UNIT) z = z * row_scale<C>(x);
-#pragma unroll
-        for (int v = 0; v < 16; ++v) zt[(w * 32 + acc_row(v, h)) * kTile + ln] = z[v];
-    }
-    __syncthreads();
     if (w < 4) {
         const int slot = 2 * w + h;
+        X += (static_cast<size_t>(bh) * a.N + t0) * C::D;
+        Hasher<C, 8> hasher;
+        hasher.load(a.Wp + static_cast<size_t>(bh % a.H) * C::LPP * C::D, w, lane);
         typename Share<C, 8>::Regs r;
+        typename Hasher<C, 8>::Rows rows;
+        Hasher<C, 8>::fetch([&](int token) { return X + (token < nvalid ? token : nvalid - 1) * C::D; }, lane, rows);
+        hasher.template run_rows<UNIT>(rows, slot, lane, sf, nullptr, r);
 #pragma unroll
         for (int i = 0; i < Share<C, 8>::NTAB; ++i) {
             const int table = Share<C, 8>::table(slot, i);
             unsigned code = 0;
 #pragma unroll
-            for (int t = 0; t < C::P; ++t) {
-                const float z = zt[(table * C::PP + t) * kTile + ln];
-                const bool real = !C::PAD || (table < sf.L && t < sf.P);
-                r.c[i][t] = real ? bit_code(z, sf.beta) : 0.f;
-                code |= (t < a.P_real && z >= 0.f ? 1u : 0u) << t;
-            }
+            for (int t = 0; t < C::P; ++t) code |= (t < a.P_real && (__float_as_uint(r.c[i][t]) >> 31) == 0 ? 1u : 0u) << t;      // (clear sign: z >= 0)
             if (Share<C, 8>::part(slot) == 0 && table < a.L_real && ln < nvalid)
                 codes[(static_cast<size_t>(bh) * a.N + t0 + ln) * a.L_real + table] = static_cast<uint8_t>(code);
         }
@@ -672,44 +691,71 @@ KArgs make_kargs(const Plan &p, char *ws)
     return a;
 }
 
-// Hashed rows of Q (first == 0) and/or K: `count` tensors starting with `first`.
+// Where the forward's passes hash the rows they read: wherever their workgroups fill a good part of the chip, or have few tiles each.
+// Hashing is then work next to the latencies of a tile, 0.9 to 1.2 us of it over both passes; a kernel of its own, which spreads any
+// problem over the chip, takes 4 us and the memory's time, (4 d + 8 L P) bytes a token and head, for it.  The two meet at 150
+// workgroups of 32-token tiles at 512 bucket rows, and at 220 to 280 at 256 and 64, of which a CU takes two.  (Training steps of 4.2
+// million rows of 128 columns, L = 8, P = 6, 512 workgroups: 10.55 -> 10.16 ms; 64 columns, L = 16, P = 4, not causal, 1 million rows, 512
+// workgroups: 1105 -> 1045 us; a prompt of 120 044 rows and its state, 252 workgroups: 241 -> 218 us.  With 8 to 96 workgroups of 32
+// tiles, a caller's chunk of 1024: 69 -> 89, 314 -> 342, 252 -> 270, 267 -> 286 us.)
+bool hash_in_passes(const Plan &p)
+{
+    const int64_t tiles = (std::min(p.seg_len, p.N) + kTile - 1) / kTile;
+    return static_cast<int64_t>(p.BH) * p.nseg >= 160 * mfma_workgroups_per_cu(p) || tiles <= 4;
+}
+
+// Hashed rows of X, and of X1 if there is one.
 template <class C>
-hipError_t launch_hash(const Plan &p, KArgs a, const void *Q, const void *K, int first, int count, hipStream_t st)
+hipError_t launch_hash(const Plan &p, KArgs a, const void *X, float *M, const void *X1, float *M1, hipStream_t st)
 {
     auto kern = p.unit_qk ? hash_kernel<C, true> : hash_kernel<C, false>;
-    // short sequences: fewer tokens per workgroup, down to one step, until there are four workgroups per CU
+    // short sequences: fewer tokens per workgroup, down to a tile per wavefront, until there are four workgroups per CU
     a.hash_tokens = kHashTokens;
-    while (a.hash_tokens > kTile * hash_tiles<C>() && static_cast<int64_t>(p.BH) * count * ((p.N + a.hash_tokens - 1) / a.hash_tokens) < 1024)
+    while (a.hash_tokens > kTile * kHashThreads / 64 && static_cast<int64_t>(p.BH) * (X1 ? 2 : 1) * ((p.N + a.hash_tokens - 1) / a.hash_tokens) < 1024)
         a.hash_tokens /= 2;
     ProfileScope prof("hash_rows", st);
-    hipLaunchKernelGGL(kern, dim3(static_cast<unsigned>((p.N + a.hash_tokens - 1) / a.hash_tokens), p.BH, count), dim3(kHashThreads), 0, st, a,
-                       static_cast<const bf16raw *>(Q), static_cast<const bf16raw *>(K), first);
+    hipLaunchKernelGGL(kern, dim3(static_cast<unsigned>((p.N + a.hash_tokens - 1) / a.hash_tokens), p.BH, X1 ? 2 : 1), dim3(kHashThreads), 0, st, a,
+                       static_cast<const bf16raw *>(X), M, static_cast<const bf16raw *>(X1), M1);
     return hipGetLastError();
 }
 
+// X: rows of K to be hashed into M (or null: M are the hashed rows; and M null: nobody reads them)
 template <class C, int QG>
-hipError_t launch_totals(const Plan &p, KArgs a, const float *M, const void *Y, const void *O, const float *den_in, void *Gout,
+hipError_t launch_totals(const Plan &p, KArgs a, float *M, const void *X, const void *Y, const void *O, const float *den_in, void *Gout,
                          hipStream_t st)
 {
-    auto kern = totals_kernel<C, QG>;
-    RACE_TRY(allow_lds(kern, TotalsLds<C>::total));
+    auto kern = totals_kernel<C, QG, false, false>;
+    if (!QG && X) kern = p.unit_qk ? totals_kernel<C, QG, QG == 0, QG == 0> : totals_kernel<C, QG, QG == 0, false>;
+    const int lds = X ? TotalsLds<C>::total_hash : TotalsLds<C>::total;
+    RACE_TRY(allow_lds(kern, lds));
     ProfileScope prof(QG ? "stream_totals_qg" : "stream_totals_kv", st);
-    hipLaunchKernelGGL(kern, dim3(p.nseg, p.BH), dim3(kThreads), TotalsLds<C>::total, st, a, M,
+    hipLaunchKernelGGL(kern, dim3(p.nseg, p.BH), dim3(kThreads), lds, st, a, M, static_cast<const bf16raw *>(X),
                        static_cast<const bf16raw *>(Y), static_cast<const bf16raw *>(O), den_in, static_cast<bf16raw *>(Gout));
     return hipGetLastError();
 }
 
-template <class C, int MODE>
-hipError_t launch_stream(const Plan &p, KArgs a, const float *Mr, const float *Mw, const void *Y, void *Out, float *den_out,
-                         hipStream_t st)
+// X: rows of Q to be hashed into Mr (or null: Mr are the hashed rows)
+template <class C, int MODE, bool NC>
+hipError_t launch_stream_nc(const Plan &p, KArgs a, float *Mr, const float *Mw, const void *X, const void *Y, void *Out, float *den_out,
+                            hipStream_t st)
 {
     static const char *const names[] = {"stream_forward", "stream_grad_v"};
-    auto kern = p.causal ? stream_kernel<C, MODE, false> : stream_kernel<C, MODE, true>;
-    RACE_TRY(allow_lds(kern, StreamLds<C>::total));
+    constexpr bool kFwd = MODE == kForward;
+    auto kern = stream_kernel<C, MODE, NC, false, false>;
+    if (kFwd && X) kern = p.unit_qk ? stream_kernel<C, MODE, NC, kFwd, kFwd> : stream_kernel<C, MODE, NC, kFwd, false>;
+    const int lds = X ? StreamLds<C, NC>::total_hash : StreamLds<C, NC>::total;
+    RACE_TRY(allow_lds(kern, lds));
     ProfileScope prof(names[MODE], st);
-    hipLaunchKernelGGL(kern, dim3(p.nseg, p.BH), dim3(kThreads), StreamLds<C>::total, st, a, Mr, Mw,
+    hipLaunchKernelGGL(kern, dim3(p.nseg, p.BH), dim3(kThreads), lds, st, a, Mr, Mw, static_cast<const bf16raw *>(X),
                        static_cast<const bf16raw *>(Y), static_cast<bf16raw *>(Out), den_out);
     return hipGetLastError();
+}
+template <class C, int MODE>
+hipError_t launch_stream(const Plan &p, KArgs a, float *Mr, const float *Mw, const void *X, const void *Y, void *Out, float *den_out,
+                         hipStream_t st)
+{
+    return p.causal ? launch_stream_nc<C, MODE, false>(p, a, Mr, Mw, X, Y, Out, den_out, st)
+                    : launch_stream_nc<C, MODE, true>(p, a, Mr, Mw, X, Y, Out, den_out, st);
 }
 
 template <class C>
@@ -717,10 +763,11 @@ hipError_t fwd_t(const Plan &p, const void *Q, const void *K, const void *V, voi
 {
     KArgs a = make_kargs<C>(p, ws);
     a.scanned = p.causal;
-    RACE_TRY((launch_hash<C>(p, a, Q, K, 0, 2, st)));
-    RACE_TRY((launch_totals<C, 0>(p, a, a.Mk, V, nullptr, nullptr, nullptr, st)));
+    const bool in_passes = hash_in_passes(p);
+    if (!in_passes) RACE_TRY((launch_hash<C>(p, a, Q, a.Mq, K, a.Mk, st)));
+    RACE_TRY((launch_totals<C, 0>(p, a, a.Mk, in_passes ? K : nullptr, V, nullptr, nullptr, nullptr, st)));
     RACE_TRY(scan_states("segment_scan", a.state, p.nseg, p.BH, C::STATE, p.causal ? kScanPrefixOpen : kScanTotal, st));
-    RACE_TRY((launch_stream<C, kForward>(p, a, a.Mq, a.Mk, V, O, den, st)));
+    RACE_TRY((launch_stream<C, kForward>(p, a, a.Mq, a.Mk, in_passes ? Q : nullptr, V, O, den, st)));
     return hipSuccess;
 }
 
@@ -752,15 +799,16 @@ hipError_t bwd_t(const Plan &p, const void *Q, const void *K, const void *V, con
     // these behind: its scan is in place and its streaming pass only reads them); then the statistics of
     // (phi_Q, read-out cotangents) at segment ends
     if (!p.fwd_state_kept) {
-        RACE_TRY((launch_hash<C>(p, a, Q, K, 0, 2, st)));
-        RACE_TRY((launch_totals<C, 0>(p, a, a.Mk, V, nullptr, nullptr, nullptr, st)));
+        const bool in_passes = hash_in_passes(p);
+        RACE_TRY((launch_hash<C>(p, a, Q, a.Mq, in_passes ? nullptr : K, a.Mk, st)));
+        RACE_TRY((launch_totals<C, 0>(p, a, a.Mk, in_passes ? K : nullptr, V, nullptr, nullptr, nullptr, st)));
         RACE_TRY(scan_states("segment_scan", a.state, p.nseg, p.BH, C::STATE, p.causal ? kScanPrefixOpen : kScanTotal, st));
     }
     a.want_dbeta = b.want_dbeta = dbeta != nullptr;
     // dK's buffer holds the cotangent rows until dK itself is written
-    RACE_TRY((launch_totals<C, 1>(p, b, a.Mq, dO, O, den, dK, st)));
+    RACE_TRY((launch_totals<C, 1>(p, b, a.Mq, nullptr, dO, O, den, dK, st)));
     RACE_TRY(scan_states("segment_scan", b.state, p.nseg, p.BH, C::STATE, p.causal ? kScanSuffixOpen : kScanTotal, st));
-    RACE_TRY((launch_stream<C, kGradV>(p, b, a.Mk, a.Mq, dK, dV, nullptr, st)));
+    RACE_TRY((launch_stream<C, kGradV>(p, b, a.Mk, a.Mq, nullptr, dK, dV, nullptr, st)));
     RACE_TRY((launch_grad<C, 0>(p, a, Q, V, dK, dQ, st)));
     RACE_TRY((launch_grad<C, 1>(p, b, K, V, dK, dK, st)));
     if (dbeta) RACE_TRY(reduce_dbeta(p, a.dbeta_part, dbeta, st));
@@ -772,8 +820,9 @@ hipError_t buckets_t(const Plan &p, const void *K, const void *V, float *A, floa
                      char *ws, hipStream_t st)
 {
     KArgs a = make_kargs<C>(p, ws);
-    RACE_TRY((launch_hash<C>(p, a, nullptr, K, 1, 1, st)));
-    RACE_TRY((launch_totals<C, 0>(p, a, a.Mk, V, nullptr, nullptr, nullptr, st)));
+    const bool in_passes = hash_in_passes(p);
+    if (!in_passes) RACE_TRY((launch_hash<C>(p, a, K, a.Mk, nullptr, nullptr, st)));
+    RACE_TRY((launch_totals<C, 0>(p, a, in_passes ? nullptr : a.Mk, in_passes ? K : nullptr, V, nullptr, nullptr, nullptr, st)));
     const int per = p.LR * (C::D + 1), groups = tap_groups(p.nseg), elements = kTapThreads / groups;
     hipLaunchKernelGGL(bucket_tap_kernel<C>, dim3((per + elements - 1) / elements, p.BH), dim3(kTapThreads), 0, st, a.state,
                        p.nseg, groups, p.L, p.P, A, Bsum, a_stride, b_stride);
@@ -784,7 +833,7 @@ template <class C>
 hipError_t hash_t(const Plan &p, const void *X, uint8_t *codes, float *phi, char *ws, hipStream_t st)
 {
     KArgs a = make_kargs<C>(p, ws);
-    const size_t lds = static_cast<size_t>(kTile) * C::PS * 2 + static_cast<size_t>(C::LPP) * kTile * 4;
+    const size_t lds = static_cast<size_t>(kTile) * C::PS * 2;
     auto kern = p.unit_qk ? hash_tap_kernel<C, true> : hash_tap_kernel<C, false>;
     RACE_TRY(allow_lds(kern, lds));
     hipLaunchKernelGGL(kern, dim3(static_cast<unsigned>((p.N + kTile - 1) / kTile), p.BH), dim3(kThreads), lds, st, a,
