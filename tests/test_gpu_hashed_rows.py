@@ -1,0 +1,51 @@
+"""The rows of Q and K are hashed either inside the forward's passes or by a kernel of their own in front of them, by a rule on the
+number of workgroups and of their tiles.  Both run the same arithmetic: a batch that takes one way has, sequence by sequence and bit
+for bit, the results of its sequences alone, which take the other; and both agree with the oracle at the edges of the tiles."""
+import pytest
+import torch
+
+import paper_2510_04008_amd as ra
+from paper_2510_04008_amd import synth
+from paper_2510_04008_amd.synth import Workload
+
+from parity_util import check_case, desc_of
+
+pytestmark = pytest.mark.gpu
+
+# exact and padded, one and several tables a half wavefront, tables shared by two of them
+SHAPES = [(128, 8, 6), (64, 16, 4), (64, 6, 5), (64, 3, 2), (128, 12, 3), (128, 7, 3), (128, 4, 4)]
+
+
+@pytest.mark.parametrize("causal,unit", [(True, False), (True, True), (False, False), (False, True)])
+@pytest.mark.parametrize("shape", SHAPES, ids=str)
+def test_both_ways_are_bit_identical(shape, causal, unit):
+    d, L, P = shape
+    # 6 tiles a workgroup, the last one ragged: 320 workgroups hash in the passes, 8 do not
+    B, H, N = 40, 8, 165
+    w = Workload("rows", B, H, N, d, L, P, 4.0, causal, "bf16", chunk=192, unit_qk=unit)
+    tensors = [t.cuda() if not t.is_cuda else t for t in synth.make_inputs(w, "cuda")]
+    seeds = synth.projection_seeds(w)
+
+    def run(desc, Q, K, V, dO):
+        assert ra.race_attn_kernel_family(desc) == 2
+        ws = torch.empty(ra.race_attn_workspace_bytes(desc), dtype=torch.uint8, device="cuda")
+        O, den = ra.race_attn_fwd(desc, Q, K, V, seeds, workspace=ws)
+        grads = ra.race_attn_bwd_saved(desc, Q, K, V, O, den, dO, seeds, ws, want_dbeta=True)
+        state = ra.race_attn_state_init(desc, K, V, seeds)
+        torch.cuda.synchronize()
+        return (O, den) + tuple(grads) + (state,)
+
+    whole = run(desc_of(w), *tensors)
+    one = desc_of(Workload("row", 1, H, N, d, L, P, 4.0, causal, "bf16", chunk=192, unit_qk=unit))
+    for b in (0, B - 1):
+        alone = run(one, *[t[b:b + 1].contiguous() for t in tensors])
+        for name, x, y in zip(("O", "den", "dQ", "dK", "dV", "dbeta", "state"), whole, alone):
+            assert torch.equal(x[b:b + 1], y), (name, b)
+
+
+@pytest.mark.parametrize("N,chunk", [(31, 0), (97, 96), (128, 128), (129, 160), (300, 320)])
+@pytest.mark.parametrize("shape", SHAPES, ids=str)
+def test_tile_edges_against_the_oracle(shape, N, chunk):
+    d, L, P = shape
+    for causal in (True, False):
+        check_case(Workload("rows-%d-%d" % (N, chunk), 1, 2, N, d, L, P, 2.0, causal, "bf16", normalize_qk=True, chunk=chunk), saved=True)
