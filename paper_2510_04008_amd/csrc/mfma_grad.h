@@ -231,11 +231,14 @@ void grad_kernel(KArgs a, const bf16raw *Xr, const bf16raw *V, const bf16raw *G_
     auto tile_nv = [&](int64_t t0) { return (t_end - t0 < kTile) ? static_cast<int>(t_end - t0) : kTile; };
 
     // LDS addresses are a lane's offset under a stride plus a uniform one, added where it is used.  The lane's offsets are worked out
-    // here, or, where they would push two workgroups' registers past a CU's (R = 16) or spill (the unit-norm option beside 128
-    // registers of statistics), again in every tile.
-    constexpr bool kRebuild = G::T16 || (UNIT && G::SREGS == 128);
+    // here, or, where they would push two workgroups' registers past a CU's (R = 16, causal) or spill (the unit-norm option beside 128
+    // registers of statistics), again in every tile.  R = 16, not causal, has registers to spare and few instructions a tile: there
+    // the uniform parts are the instructions' own offsets.  (dQ at 32 workgroups of up to 32 tiles, (128, 4, 4): 59.7 -> 55.8 us; a step
+    // of B H = 64, N = 16384, (64, 4, 16): 1031 -> 1016 us.)
+    constexpr bool kRebuild = (G::T16 && INTRA) || (UNIT && G::SREGS == 128);
+    constexpr bool kFold = G::T16 && !INTRA;
     int step = 0;       // (the loop counter of these sums)
-    auto at = [&](int uniform, int lane_offset) __attribute__((always_inline)) { return lds + (opaque_uniform(uniform, step) + lane_offset); };
+    auto at = [&](int uniform, int lane_offset) __attribute__((always_inline)) { return lds + ((kFold ? uniform : opaque_uniform(uniform, step)) + lane_offset); };
     const int at16x_ = (n16 * C::XS + 8 * q16) * 2, at16d_ = (n16 * S::DZS + 8 * q16) * 2;      // 16-row operands
     const int at_x_ = chunk_offset<C, C::XS, kPlain>(tid), at_yr_ = chunk_offset<C, C::XS, G::YORDER>(tid), at_yw_ = chunk_offset<C, C::YS, G::YORDER>(tid);
     auto rebuilt_lane = [&]() __attribute__((always_inline)) { return opaque(lane, step); };

@@ -381,6 +381,9 @@ void stream_kernel(KArgs a, float *Mr, const float *Mw, const bf16raw *X, const 
         }
     }
 
+    // (NC: half of the work, and registers to keep the addresses in that the causal passes rebuild in every tile: 37.2 -> 36.3 us for
+    // the forward pass and 30.4 -> 29.7 for dV at 32 workgroups of 32 tiles, (128, 4, 4))
+    auto step = [&](int it) { return NC ? 0 : it; };
     // ---- epilogue of one tile: thread = (token, pieces of 4 columns: 4i.. and, for d = 128, 64 + 4i..; consecutive
     //      threads read consecutive 16-byte pieces of the partials): sum, normalise, store
     auto epilogue = [&](int it) __attribute__((always_inline)) {
@@ -389,7 +392,7 @@ void stream_kernel(KArgs a, float *Mr, const float *Mw, const bf16raw *X, const 
         const float *dnr = dnp + (it & 1) * (kHalf * kTile);
         {
         constexpr int NP = C::D / 64;                // pieces of 4 columns per thread
-        const int to = opaque(tid, it), tok = to >> 4, c0 = (to & 15) * 4;      // (addresses rebuilt per tile, not kept in registers)
+        const int to = opaque(tid, step(it)), tok = to >> 4, c0 = (to & 15) * 4;      // (addresses rebuilt per tile, not kept in registers)
         float acc[NP][4];
 #pragma unroll
         for (int c = 0; c < NP; ++c) acc[c][0] = acc[c][1] = acc[c][2] = acc[c][3] = 0.f;
@@ -429,14 +432,14 @@ void stream_kernel(KArgs a, float *Mr, const float *Mw, const bf16raw *X, const 
         if (intra) store_rows<C, kTile, C::YS>(pre_y, ytile, it);
         if (side == 0) {
             if constexpr (HASH) hasher.template run<UNIT>(xs, slot, lane, a.soft(), Mr + tile_t0(it) * C::LP, pre_m);
-            const float dnl = produce<C, S::SLOTS, C::PS, MODE == kForward>(pre_m, slot, spread_row(ln), a.soft(), true, phr, it, mass);
+            const float dnl = produce<C, S::SLOTS, C::PS, MODE == kForward>(pre_m, slot, spread_row(ln), a.soft(), true, phr, step(it), mass);
             if (MODE == kForward) {
                 // this wavefront's tables' share of the normaliser
                 const float both = sum_halves(dnl);
-                if (h == 0) dnp[(it & 1) * (kHalf * kTile) + w * kTile + opaque(ln, it)] = both;
+                if (h == 0) dnp[(it & 1) * (kHalf * kTile) + w * kTile + opaque(ln, step(it))] = both;
             }
         } else if (intra) {
-            produce<C, S::SLOTS, C::PS>(pre_m, slot, spread_row(ln), a.soft(), ln < nvalid, phw, it);
+            produce<C, S::SLOTS, C::PS>(pre_m, slot, spread_row(ln), a.soft(), ln < nvalid, phw, step(it));
         }
         if (!kOutputFirst && it > 0) epilogue(it - 1);
         __syncthreads();
@@ -489,7 +492,7 @@ void stream_kernel(KArgs a, float *Mr, const float *Mw, const bf16raw *X, const 
 
         // ---- reduction over the bucket-row groups: partial read-outs through LDS, 16 bytes per store
         //      (a lane holds four consecutive columns of its token in registers 4k .. 4k+3), under the products of the update
-        const int rbase = opaque((rg * kTile + ln) * S::RS + c_own + 4 * h, it);
+        const int rbase = opaque((rg * kTile + ln) * S::RS + c_own + 4 * h, step(it));
 #pragma unroll
         for (int nt = 0; nt < C::NTW; ++nt) {
 #pragma unroll
@@ -516,7 +519,7 @@ void stream_kernel(KArgs a, float *Mr, const float *Mw, const bf16raw *X, const 
                 }
             }
         }
-        if (MODE == kForward) {
+        if (MODE == kForward && intra) {
             // masses after this tile, for the next tile's read-out
 #pragma unroll
             for (int mt = 0; mt < C::MA; ++mt) {
