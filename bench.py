@@ -42,7 +42,7 @@ def kernel_shares(w):
     """Algorithmic work per token-head credited to each kernel, (flops, HBM bytes); the flops add up to 3 Proj + 6 U and
     the bytes to 12 d s + 8.  The segment-total and scan kernels exist only because the sequence is cut into segments
     and get 0.  Bytes: every tensor of the problem statement is credited once per pass, to the kernel that first
-    needs it (forward: Q, K to the hashing kernel, V, O, den to the streaming pass; backward: dO, O, den, dV to the
+    needs it (forward: Q, K to the hashing kernel, where there is one, V, O, den to the streaming pass; backward: dO, O, den, dV to the
     dV pass, Q, dQ to the dQ pass, K, V, dK to the dK pass)."""
     proj, U, _ = algorithmic_counts(w)
     s = 2 if w.dtype == "bf16" else 4
@@ -58,6 +58,17 @@ def kernel_shares(w):
         "simple_fwd_replay": (proj + 2 * U, 4 * ds + 4),
         "simple_grads": (2 * proj + 4 * U, 8 * ds + 4),
     }
+
+
+def launched_shares(w, launched):
+    """kernel_shares() for the kernels of a step: where no kernel of its own hashes the rows, its share goes to the passes
+    that do: K's half to the totals of (phi_K, [V | 1]), Q's to the output."""
+    shares = kernel_shares(w)
+    if "hash_rows" not in launched:
+        flops, nbytes = shares.pop("hash_rows")
+        for name in ("stream_totals_kv", "stream_forward"):
+            shares[name] = (shares[name][0] + flops / 2, shares[name][1] + nbytes / 2)
+    return shares
 
 
 def source_hash() -> str:
@@ -236,7 +247,7 @@ def main() -> int:
     roofline = None
     kernels = {}
     if prof:
-        shares = kernel_shares(w)
+        shares = launched_shares(w, prof)
         table, table_note = measured_traffic(w) if family == 2 else (None, "no counter summary for the generic kernels")
         mfma = family == 2
         flop_peak = PEAK_BF16_FLOPS if mfma else PEAK_FP32_VECTOR_FLOPS
