@@ -1509,6 +1509,8 @@ hipError_t hash_impl(const Plan &p, const T *X, uint8_t *codes, float *phi, char
 
 hipError_t scan_states(const char *name, float *state, int nseg, int BH, size_t stride, int mode, hipStream_t st)
 {
+    // (one segment: its total is where it belongs, and an open scan would neither read nor write a state)
+    if (nseg == 1 && (mode == kScanTotal || mode == kScanPrefixOpen || mode == kScanSuffixOpen)) return hipSuccess;
     ProfileScope prof(name, st);
     int groups = 1;
     while (groups < 16 && groups * kScanRun < nseg) groups *= 2;

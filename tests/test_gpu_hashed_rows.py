@@ -49,3 +49,21 @@ def test_tile_edges_against_the_oracle(shape, N, chunk):
     d, L, P = shape
     for causal in (True, False):
         check_case(Workload("rows-%d-%d" % (N, chunk), 1, 2, N, d, L, P, 2.0, causal, "bf16", normalize_qk=True, chunk=chunk), saved=True)
+
+
+@pytest.mark.parametrize("causal", [True, False])
+@pytest.mark.parametrize("N", [5, 32, 165])        # (of one token alone dQ and dK are zero, a difference of roundings)
+@pytest.mark.parametrize("shape,dtype", [((128, 8, 6), "bf16"), ((64, 16, 4), "bf16"), ((128, 4, 4), "bf16"), ((32, 3, 3), "bf16"), ((64, 4, 4), "f32")], ids=str)
+def test_one_segment_reads_nothing_that_was_not_written(shape, dtype, N, causal):
+    # (a call of one segment leaves out the scans and, causal, the totals; the workspace is full of NaN)
+    d, L, P = shape
+    w = Workload("one", 1, 2, N, d, L, P, 2.0, causal, dtype, chunk=192, normalize_qk=True)
+    check_case(w, saved=True)
+    Q, K, V, dO = [t.cuda() for t in synth.make_inputs(w, "cuda")]
+    seeds, desc, out = synth.projection_seeds(w), desc_of(w), []
+    for fill in (0, 255):
+        ws = torch.full((ra.race_attn_workspace_bytes(desc),), fill, dtype=torch.uint8, device="cuda")
+        O, den = ra.race_attn_fwd(desc, Q, K, V, seeds, workspace=ws)
+        out.append((O, den) + tuple(ra.race_attn_bwd_saved(desc, Q, K, V, O, den, dO, seeds, ws)))
+    for x, y in zip(*out):
+        assert torch.isfinite(x).all() and torch.equal(x, y)
