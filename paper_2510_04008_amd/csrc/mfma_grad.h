@@ -106,8 +106,9 @@ struct GradLds {
 
 // Wavefronts per SIMD the gradient kernel is compiled for: four (128 registers, two workgroups per CU, whose phases
 // interleave) where the statistics do not change, 32 registers hold a wavefront's share of them and the tiles fit 80 KB.
-// The causal variants are compiled for two.  Those of (128, 4, 4) fit a CU twice all the same, at 120 to 127 registers; (128, 4, 8)
-// takes 133 to 136 and (64, 4, 16) 139 to 144.  (Kernels that wanted 139 spilled when they were held to 128 and took 1.6 times as long.)
+// The causal variants are compiled for two.  Those of (128, 4, 4) fit a CU twice all the same, at 122 to 127 registers (at 129, dK with the
+// unit-norm option, B H = 64, N = 4096: 92 us instead of 72); (128, 4, 8) takes 132 to 137 and (64, 4, 16) 140 to 147.  (Kernels that
+// wanted 139 spilled when they were held to 128 and took 1.6 times as long.)
 template <class C, bool UNIT, bool INTRA>
 constexpr int grad_waves_per_simd()
 {
@@ -384,8 +385,9 @@ void grad_kernel(KArgs a, const bf16raw *Xr, const bf16raw *V, const bf16raw *G_
         return z;
     };
     auto finish_projection = [&](int i, int it, f32x4 z) __attribute__((always_inline)) {
-        const int quad = 4 * (i >> 1) + q16, slot16 = opaque_uniform((4 * (i >> 1) * kTile + 16 * (i & 1)) * 16, step) + (q16 * kTile + n16) * 16;
-        if (UNIT) z = z * buf_nrm(it)[16 * (i & 1) + n16];
+        const int lo = kRebuild ? rebuilt_lane() : lane, n = lo & 15, q = lo >> 4;
+        const int quad = 4 * (i >> 1) + q, slot16 = opaque_uniform((4 * (i >> 1) * kTile + 16 * (i & 1)) * 16, step) + (q * kTile + n) * 16;
+        if (UNIT) z = z * buf_nrm(it)[16 * (i & 1) + n];
         f32x4 sv, uv;
 #pragma unroll
         for (int v = 0; v < 4; ++v) {

@@ -34,12 +34,24 @@ def _kernels(data, elf):
             at = body + (desc + 3) // 4 * 4
 
 
-def test_no_kernel_of_the_passes_uses_scratch():
+def _library():
     if not os.path.exists(build.LIB):
         pytest.skip("the library is not built")
     with open(build.LIB, "rb") as f:
-        data = f.read()
+        return f.read()
+
+
+def test_no_kernel_of_the_passes_uses_scratch():
+    data = _library()
     # (the decoding step of large tables is not among them: it holds its rows in registers up to 32 at a time, and some outside)
     kernels = [k for elf in _code_objects(data) for k in _kernels(data, elf) if "decode_step" not in k[".name"]]
     assert len(kernels) > 100
     assert [k[".name"] for k in kernels if k[".private_segment_fixed_size"] or k[".vgpr_spill_count"]] == []
+
+
+def test_gradient_kernels_that_fit_a_cu_twice():
+    # 512 threads: two wavefronts per SIMD and workgroup, of 512 registers a SIMD
+    data = _library()
+    kernels = [k for elf in _code_objects(data) for k in _kernels(data, elf) if "grad_kernelINS0_3CfgILi128ELi4ELi4E" in k[".name"]]
+    assert len(kernels) == 8            # dQ and dK, with and without the unit-norm option, causal or not
+    assert [(k[".name"], k[".vgpr_count"]) for k in kernels if k[".vgpr_count"] > 128] == []
