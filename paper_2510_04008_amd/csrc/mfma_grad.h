@@ -107,7 +107,7 @@ struct GradLds {
 // Wavefronts per SIMD the gradient kernel is compiled for: four (128 registers, two workgroups per CU, whose phases
 // interleave) where the statistics do not change, 32 registers hold a wavefront's share of them and the tiles fit 80 KB.
 // The causal variants are compiled for two.  Those of (128, 4, 4) fit a CU twice all the same, at 122 to 127 registers (at 129, dK with the
-// unit-norm option, B H = 64, N = 4096: 92 us instead of 72); (128, 4, 8) takes 132 to 137 and (64, 4, 16) 140 to 147.  (Kernels that
+// unit-norm option, B H = 64, N = 4096: 92 us instead of 72); (128, 4, 8) takes 135 to 141 and (64, 4, 16) 142 to 150.  (Kernels that
 // wanted 139 spilled when they were held to 128 and took 1.6 times as long.)
 template <class C, bool UNIT, bool INTRA>
 constexpr int grad_waves_per_simd()
@@ -408,6 +408,11 @@ void grad_kernel(KArgs a, const bf16raw *Xr, const bf16raw *V, const bf16raw *G_
     // (the reader's hashed rows of this wavefront's tables: used in the second half)
     constexpr int kTh = G::T16 && G::TS == 1 ? 2 : 1;      // R = 16: halves of the tile's tokens
     float rc[G::TPW * kTh][C::P];
+    // A tile's first half follows the second half of the tile before it in the loop's body.  (The causal kernels of 32 registers of
+    // statistics whose other registers leave a CU no room for a second workgroup have it in order: dQ and dK at B H = 64, N = 4096, (128,
+    // 8, 4): 83.2 and 85.8 against 81.7 and 83.2 us; (64, 16, 4): 106.8 and 109.5 against 105.0 and 107.4.  (128, 4, 4) needs 130
+    // registers that way and has the CU for itself.)
+    constexpr bool kRotate = !G::T16 || !INTRA || G::TS == 2 || G::SREGS > 32;
     auto first_half = [&](int it, bool first) __attribute__((always_inline)) {
         const int64_t t0 = existing_t0(it);
         const int nvalid = tile_nv(t0);
@@ -471,9 +476,10 @@ void grad_kernel(KArgs a, const bf16raw *Xr, const bf16raw *V, const bf16raw *G_
             *reinterpret_cast<u32x2 *>(dst) = u32x2{pack2(tt[0], tt[1]), pack2(tt[2], tt[3])};
         }
     };
-    if (ntiles > 0) first_half(0, true);
+    if (kRotate && ntiles > 0) first_half(0, true);
     for (int it = 0; it < ntiles; ++it) {
         step = it;
+        if (!kRotate) first_half(it, it == 0);
         const int64_t t0 = tile_t0(it);
         const int nvalid = tile_nv(t0);
         __syncthreads();
@@ -664,7 +670,7 @@ void grad_kernel(KArgs a, const bf16raw *Xr, const bf16raw *V, const bf16raw *G_
         stage_x(it + 1);
         fetch_x(it + 2);
         __syncthreads();        // dz is visible; this tile's assignments, in-tile term and tanh are dead from here on
-        if (G::T16 && it + 1 == ntiles) break;
+        if (kRotate && G::T16 && it + 1 == ntiles) break;
         if constexpr (!G::T16) {
             // ---- statistics += Yw^T . phi_writer
             if (intra) {
@@ -685,7 +691,7 @@ void grad_kernel(KArgs a, const bf16raw *Xr, const bf16raw *V, const bf16raw *G_
                 }
             }
         }
-        first_half(it + 1, false);
+        if (kRotate) first_half(it + 1, false);
     }
     // (R = 64 comes past the end of the last tile and forms its dX there: with the loop left in the middle the statistics of the long
     // sequences are spilled, and both gradients take 4 % more)
