@@ -36,45 +36,59 @@ __device__ __forceinline__ int state_a(int r) { return C::LR * C::D + r; }
 // Algorithm 1, steps 2-4 up to the per-bit masses, for every row of a tensor (blockIdx.z: of one or the other): one float per (table,
 // hyperplane), see bit_code().  For calls whose passes do not hash for themselves: see hash_in_passes(), and race_attn_bwd, whose
 // pass over Q would be the forward's.  The same arithmetic as theirs (Hasher), the rows straight from memory: no LDS, no barrier.
+// Bound by the latency of one tile where there are few, by memory where there are many.  (Q and K of two sequences of 2000 tokens, (128, 8,
+// 6), all shares of a tile in one wavefront: 6.3 us, each in its own 4.8; of eight of 5000, (128, 8, 4), in shares of the passes' eight half
+// wavefronts 12.3, of four 9.8.)
 constexpr int kHashThreads = 256;
 constexpr int kHashTokens = 512;        // most tokens per workgroup (amortises the load of W)
+// Half wavefronts that share a tile's tables here, so that a wavefront's 16 rows of an MFMA tile are 16 packed rows of W (in the passes,
+// which share eight ways, (4, 8) and (4, 4) fill half of them).
+template <class C> constexpr int hash_slots() { return C::P == 6 ? C::L : C::L / 2; }
+template <class C> constexpr int hash_shares() { return hash_slots<C>() / 2; }
 
-template <class C, bool UNIT>
-__global__ __launch_bounds__(kHashThreads) void hash_kernel(KArgs a, const bf16raw *X, float *M, const bf16raw *X1, float *M1)
+// This wavefront's SHARES shares, from `share` on, of tiles first, first + stride, ... < end of one (batch, head) (X, M: its first
+// row's; Wp: its head's), the next tile's rows requested before a tile's arithmetic.
+template <class C, bool UNIT, int SHARES>
+__device__ __forceinline__ void hash_tiles(const KArgs &a, const bf16raw *X, const bf16raw *Wp, float *M, int share, int64_t first, int64_t end,
+                                           int stride, int lane)
 {
-    if (blockIdx.z) { X = X1; M = M1; }
-    const int bh = blockIdx.y;
-    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, h = lane >> 5;
-    X += static_cast<size_t>(bh) * a.N * C::D;
-    const int64_t all_tiles = (a.N + kTile - 1) / kTile;
-    M += static_cast<size_t>(bh) * all_tiles * kTile * C::LP;
-    // a wavefront hashes all tables of its tiles: what two or four of them share in the passes
-    constexpr int kShares = Share<C, 8>::PARTS == 2 ? 2 : 4, kTiles = kHashThreads / 64;
-    Hasher<C, 8> hasher[kShares];
+    using Hash = Hasher<C, hash_slots<C>()>;
+    Hash hasher[SHARES];
 #pragma unroll
-    for (int i = 0; i < kShares; ++i) hasher[i].load(a.Wp + static_cast<size_t>(bh % a.H) * C::LPP * C::D, i, lane);
-    const int64_t t_first = static_cast<int64_t>(blockIdx.x) * (a.hash_tokens / kTile);
-    const int64_t t_end = (t_first + a.hash_tokens / kTile < all_tiles) ? t_first + a.hash_tokens / kTile : all_tiles;
-    using Rows = typename Hasher<C, 8>::Rows;
-    auto fetch = [&](int64_t tile, Rows &rows) __attribute__((always_inline)) {
+    for (int i = 0; i < SHARES; ++i) hasher[i].load(Wp, share + i, lane);
+    auto fetch = [&](int64_t tile, typename Hash::Rows &rows) __attribute__((always_inline)) {
         // (rows past the end repeat the last one: finite values in the padding of the last tile)
-        Hasher<C, 8>::fetch([&](int token) __attribute__((always_inline)) {
+        Hash::fetch([&](int token) __attribute__((always_inline)) {
             const int64_t t = tile * kTile + token;
             return X + (t < a.N ? t : a.N - 1) * C::D;
         }, lane, rows);
     };
-    int64_t tile = t_first + w;
-    Rows rows;
-    if (tile < t_end) fetch(tile, rows);
-    for (; tile < t_end; tile += kTiles) {
-        const Rows now = rows;
-        if (tile + kTiles < t_end) fetch(tile + kTiles, rows);
+    typename Hash::Rows rows;
+    if (first < end) fetch(first, rows);
+    for (int64_t tile = first; tile < end; tile += stride) {
+        const typename Hash::Rows now = rows;
+        if (tile + stride < end) fetch(tile + stride, rows);
 #pragma unroll
-        for (int i = 0; i < kShares; ++i) {
-            typename Share<C, 8>::Regs codes;
-            hasher[i].template run_rows<UNIT>(now, 2 * i + h, lane, a.soft(), M + tile * (kTile * C::LP), codes);
+        for (int i = 0; i < SHARES; ++i) {
+            typename Hash::Sh::Regs codes;
+            hasher[i].template run_rows<UNIT>(now, 2 * (share + i) + (lane >> 5), lane, a.soft(), M + tile * (kTile * C::LP), codes);
         }
     }
+}
+
+template <class C, bool UNIT, int SHARES>
+__global__ __launch_bounds__(kHashThreads) void hash_kernel(KArgs a, const bf16raw *X, float *M, const bf16raw *X1, float *M1)
+{
+    if (blockIdx.z) { X = X1; M = M1; }
+    const int bh = blockIdx.y;
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int64_t all_tiles = (a.N + kTile - 1) / kTile;
+    const int64_t t_first = static_cast<int64_t>(blockIdx.x) * (a.hash_tokens / kTile);
+    const int64_t t_end = (t_first + a.hash_tokens / kTile < all_tiles) ? t_first + a.hash_tokens / kTile : all_tiles;
+    constexpr int kParties = hash_shares<C>() / SHARES;         // wavefronts on a tile
+    hash_tiles<C, UNIT, SHARES>(a, X + static_cast<size_t>(bh) * a.N * C::D, a.Wp + static_cast<size_t>(bh % a.H) * C::LPP * C::D,
+                                M + static_cast<size_t>(bh) * all_tiles * kTile * C::LP, SHARES * (w % kParties), t_first + w / kParties, t_end,
+                                kHashThreads / 64 / kParties, lane);
 }
 
 // ================================================================ totals_kernel
@@ -715,11 +729,15 @@ bool wants_totals(const Plan &p) { return !p.causal || p.nseg > 1; }
 template <class C>
 hipError_t launch_hash(const Plan &p, KArgs a, const void *X, float *M, const void *X1, float *M1, hipStream_t st)
 {
-    auto kern = p.unit_qk ? hash_kernel<C, true> : hash_kernel<C, false>;
-    // short sequences: fewer tokens per workgroup, down to a tile per wavefront, until there are four workgroups per CU
-    a.hash_tokens = kHashTokens;
-    while (a.hash_tokens > kTile * kHashThreads / 64 && static_cast<int64_t>(p.BH) * (X1 ? 2 : 1) * ((p.N + a.hash_tokens - 1) / a.hash_tokens) < 1024)
-        a.hash_tokens /= 2;
+    constexpr int kShares = hash_shares<C>();
+    const int64_t rows = static_cast<int64_t>(p.BH) * (X1 ? 2 : 1);
+    // too few tiles for the chip: a wavefront per share of a tile, else one per tile, with fewer tokens per workgroup, down to a tile per
+    // wavefront, until there are four workgroups per CU
+    const bool split = rows * ((p.N + kTile - 1) / kTile) <= 1024;
+    auto kern = p.unit_qk ? hash_kernel<C, true, kShares> : hash_kernel<C, false, kShares>;
+    if (split) kern = p.unit_qk ? hash_kernel<C, true, 1> : hash_kernel<C, false, 1>;
+    a.hash_tokens = split ? kTile * kHashThreads / 64 / kShares : kHashTokens;
+    while (!split && a.hash_tokens > kTile * kHashThreads / 64 && rows * ((p.N + a.hash_tokens - 1) / a.hash_tokens) < 1024) a.hash_tokens /= 2;
     ProfileScope prof("hash_rows", st);
     hipLaunchKernelGGL(kern, dim3(static_cast<unsigned>((p.N + a.hash_tokens - 1) / a.hash_tokens), p.BH, X1 ? 2 : 1), dim3(kHashThreads), 0, st, a,
                        static_cast<const bf16raw *>(X), M, static_cast<const bf16raw *>(X1), M1);

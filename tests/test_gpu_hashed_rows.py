@@ -67,3 +67,29 @@ def test_one_segment_reads_nothing_that_was_not_written(shape, dtype, N, causal)
         out.append((O, den) + tuple(ra.race_attn_bwd_saved(desc, Q, K, V, O, den, dO, seeds, ws)))
     for x, y in zip(*out):
         assert torch.isfinite(x).all() and torch.equal(x, y)
+
+
+@pytest.mark.parametrize("unit", [False, True])
+@pytest.mark.parametrize("shape", SHAPES + [(128, 6, 5)], ids=str)
+def test_hashing_kernel_by_tiles_and_by_shares_of_a_tile(shape, unit):
+    # eight sequences of 66 tiles, the last one ragged, of Q and K: a wavefront a tile; one of them: a wavefront a share of a tile
+    d, L, P = shape
+    w = Workload("shares", 8, 1, 2100, d, L, P, 2.0, True, "bf16", chunk=1056, unit_qk=unit)
+    Q, K, V, dO = synth.make_inputs(w, "cuda")
+    seeds = synth.projection_seeds(w)
+
+    def run(desc, *T):
+        ws = torch.empty(ra.race_attn_workspace_bytes(desc), dtype=torch.uint8, device="cuda")
+        ra.race_attn_profile_enable(True)
+        O, den = ra.race_attn_fwd(desc, T[0], T[1], T[2], seeds, workspace=ws)
+        torch.cuda.synchronize()
+        names = set(ra.race_attn_profile_read())
+        ra.race_attn_profile_enable(False)
+        assert "hash_rows" in names
+        return (O, den) + tuple(ra.race_attn_bwd_saved(desc, T[0], T[1], T[2], O, den, T[3], seeds, ws))
+
+    whole = run(desc_of(w), Q, K, V, dO)
+    one = desc_of(Workload("share", 1, 1, 2100, d, L, P, 2.0, True, "bf16", chunk=1056, unit_qk=unit))
+    for b in (0, 7):
+        for x, y in zip(whole, run(one, *[t[b:b + 1].contiguous() for t in (Q, K, V, dO)])):
+            assert torch.equal(x[b:b + 1], y), b
