@@ -93,3 +93,34 @@ def test_hashing_kernel_by_tiles_and_by_shares_of_a_tile(shape, unit):
     for b in (0, 7):
         for x, y in zip(whole, run(one, *[t[b:b + 1].contiguous() for t in (Q, K, V, dO)])):
             assert torch.equal(x[b:b + 1], y), b
+
+
+@pytest.mark.parametrize("causal,unit", [(True, False), (True, True), (False, False)])
+@pytest.mark.parametrize("shape", SHAPES + [(128, 6, 5)], ids=str)
+def test_both_ways_are_bit_identical_over_several_segments(shape, causal, unit):
+    d, L, P = shape
+    # three segments: five tiles (an odd one in the last 64-token step of the totals), five, and two, the last ragged, whose totals
+    # nobody reads where the sequence is causal; 960 workgroups hash in the passes, 24 do not
+    B, H, N = 40, 8, 357
+    w = Workload("rows", B, H, N, d, L, P, 4.0, causal, "bf16", chunk=160, unit_qk=unit)
+    Q, K, V, dO = synth.make_inputs(w, "cuda")
+    seeds = synth.projection_seeds(w)
+
+    def run(desc, Q, K, V, dO, in_passes):
+        ws = torch.empty(ra.race_attn_workspace_bytes(desc), dtype=torch.uint8, device="cuda")
+        ra.race_attn_profile_enable(True)
+        O, den = ra.race_attn_fwd(desc, Q, K, V, seeds, workspace=ws)
+        torch.cuda.synchronize()
+        names = set(ra.race_attn_profile_read())
+        ra.race_attn_profile_enable(False)
+        assert ("hash_rows" not in names) == in_passes and "stream_totals_kv" in names
+        saved = ra.race_attn_bwd_saved(desc, Q, K, V, O, den, dO, seeds, ws, want_dbeta=True)
+        again = ra.race_attn_bwd(desc, Q, K, V, O, den, dO, seeds)
+        return (O, den) + tuple(saved) + tuple(again) + (ra.race_attn_state_init(desc, K, V, seeds),)
+
+    whole = run(desc_of(w), Q, K, V, dO, True)
+    one = desc_of(Workload("row", 1, H, N, d, L, P, 4.0, causal, "bf16", chunk=160, unit_qk=unit))
+    for b in (0, B - 1):
+        alone = run(one, *[t[b:b + 1].contiguous() for t in (Q, K, V, dO)], False)
+        for name, x, y in zip(("O", "den", "dQ", "dK", "dV", "dbeta", "dQ recomputed", "dK recomputed", "dV recomputed", "state"), whole, alone):
+            assert torch.equal(x[b:b + 1], y), (name, b)
