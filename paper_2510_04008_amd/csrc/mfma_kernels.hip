@@ -144,8 +144,8 @@ void totals_kernel(KArgs a, float *M, const bf16raw *X, const bf16raw *Y, const 
     if (QG) { Oin += base; Gout += base; den_in += static_cast<size_t>(bh) * a.N; }
     float *st = a.state + (static_cast<size_t>(bh) * a.nseg + seg) * C::STATE;
     // causal: the totals of the last segment (backward: of the first) are in no other segment's start state
-    // (the last segment's rows of K are hashed all the same, and nothing else is done for it: a forward call of B H = 255, N = 2500, few
-    // segments, (128, 8, 6), 550 us when it ran the whole loop, 489; B H = 80, N = 4000: 271, 265)
+    // (the last segment's rows of K are hashed all the same, and nothing else is done for it: a forward call of B H = 80, N = 4000, three
+    // segments, (128, 8, 6), 271 us when it ran the whole loop, 265; N = 1500, B H = 128, two, 173 and 166)
     const bool unread = a.scanned && seg == (QG ? 0 : a.nseg - 1);
     if (!QG && unread) {
         if (HASH) {
@@ -797,9 +797,11 @@ hipError_t fwd_t(const Plan &p, const void *Q, const void *K, const void *V, voi
 {
     KArgs a = make_kargs<C>(p, ws);
     a.scanned = p.causal;
-    const bool in_passes = hash_in_passes(p);
+    // (no totals, no pass over K to hash it in: a step of B H = 512, N = 500, (128, 8, 6), takes 653 us with one that also sums, 630
+    // with one that only hashes, 612 with the kernel)
+    const bool in_passes = wants_totals(p) && hash_in_passes(p);
     if (!in_passes) RACE_TRY((launch_hash<C>(p, a, Q, a.Mq, K, a.Mk, st)));
-    if (in_passes || wants_totals(p)) RACE_TRY((launch_totals<C, 0>(p, a, a.Mk, in_passes ? K : nullptr, V, nullptr, nullptr, nullptr, st)));
+    if (wants_totals(p)) RACE_TRY((launch_totals<C, 0>(p, a, a.Mk, in_passes ? K : nullptr, V, nullptr, nullptr, nullptr, st)));
     RACE_TRY(scan_states("segment_scan", a.state, p.nseg, p.BH, C::STATE, p.causal ? kScanPrefixOpen : kScanTotal, st));
     RACE_TRY((launch_stream<C, kForward>(p, a, a.Mq, a.Mk, in_passes ? Q : nullptr, V, O, den, st)));
     return hipSuccess;
@@ -833,9 +835,9 @@ hipError_t bwd_t(const Plan &p, const void *Q, const void *K, const void *V, con
     // these behind: its scan is in place and its streaming pass only reads them); then the statistics of
     // (phi_Q, read-out cotangents) at segment ends
     if (!p.fwd_state_kept) {
-        const bool in_passes = hash_in_passes(p);
+        const bool in_passes = wants_totals(p) && hash_in_passes(p);
         RACE_TRY((launch_hash<C>(p, a, Q, a.Mq, in_passes ? nullptr : K, a.Mk, st)));
-        if (in_passes || wants_totals(p)) RACE_TRY((launch_totals<C, 0>(p, a, a.Mk, in_passes ? K : nullptr, V, nullptr, nullptr, nullptr, st)));
+        if (wants_totals(p)) RACE_TRY((launch_totals<C, 0>(p, a, a.Mk, in_passes ? K : nullptr, V, nullptr, nullptr, nullptr, st)));
         RACE_TRY(scan_states("segment_scan", a.state, p.nseg, p.BH, C::STATE, p.causal ? kScanPrefixOpen : kScanTotal, st));
     }
     a.want_dbeta = b.want_dbeta = dbeta != nullptr;

@@ -20,7 +20,8 @@ SHAPES = [(128, 8, 6), (64, 16, 4), (64, 6, 5), (64, 3, 2), (128, 12, 3), (128, 
 @pytest.mark.parametrize("shape", SHAPES, ids=str)
 def test_both_ways_are_bit_identical(shape, causal, unit):
     d, L, P = shape
-    # 6 tiles a workgroup, the last one ragged: 320 workgroups hash in the passes, 8 do not
+    # 6 tiles a workgroup, the last one ragged: not causal, 320 workgroups hash in the passes, 8 do not; causal, one segment, the kernel
+    # hashes for both (several segments: below)
     B, H, N = 40, 8, 165
     w = Workload("rows", B, H, N, d, L, P, 4.0, causal, "bf16", chunk=192, unit_qk=unit)
     tensors = [t.cuda() if not t.is_cuda else t for t in synth.make_inputs(w, "cuda")]
@@ -124,3 +125,22 @@ def test_both_ways_are_bit_identical_over_several_segments(shape, causal, unit):
         alone = run(one, *[t[b:b + 1].contiguous() for t in (Q, K, V, dO)], False)
         for name, x, y in zip(("O", "den", "dQ", "dK", "dV", "dbeta", "dQ recomputed", "dK recomputed", "dV recomputed", "state"), whole, alone):
             assert torch.equal(x[b:b + 1], y), (name, b)
+
+
+@pytest.mark.parametrize("BH,N", [(8, 100), (256, 128), (320, 165)])
+@pytest.mark.parametrize("shape", [(128, 8, 6), (64, 16, 4), (128, 4, 4)], ids=str)
+def test_one_causal_segment_launches_no_totals_of_its_own(shape, BH, N):
+    d, L, P = shape
+    w = Workload("one", BH // 8, 8, N, d, L, P, 2.0, True, "bf16", chunk=192)
+    Q, K, V, dO = synth.make_inputs(w, "cuda")
+    seeds, desc = synth.projection_seeds(w), desc_of(w)
+    ws = torch.empty(ra.race_attn_workspace_bytes(desc), dtype=torch.uint8, device="cuda")
+    launched = []
+    O, den = ra.race_attn_fwd(desc, Q, K, V, seeds, workspace=ws)
+    for call in (lambda: ra.race_attn_fwd(desc, Q, K, V, seeds, O, den, ws), lambda: ra.race_attn_bwd(desc, Q, K, V, O, den, dO, seeds, workspace=ws)):
+        ra.race_attn_profile_enable(True)
+        call()
+        torch.cuda.synchronize()
+        launched.append(set(ra.race_attn_profile_read()))
+        ra.race_attn_profile_enable(False)
+    assert launched == [{"hash_rows", "stream_forward"}, {"hash_rows", "stream_totals_qg", "stream_grad_v", "grad_q", "grad_k"}]
