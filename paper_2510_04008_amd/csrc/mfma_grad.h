@@ -106,8 +106,8 @@ struct GradLds {
 
 // Wavefronts per SIMD the gradient kernel is compiled for: four (128 registers, two workgroups per CU, whose phases
 // interleave) where the statistics do not change, 32 registers hold a wavefront's share of them and the tiles fit 80 KB.
-// The causal variants are compiled for two.  Those of (128, 4, 4) fit a CU twice all the same, at 122 to 127 registers (at 129, dK with the
-// unit-norm option, B H = 64, N = 4096: 92 us instead of 72); (128, 4, 8) takes 135 to 141 and (64, 4, 16) 142 to 150.  (Kernels that
+// The causal variants are compiled for two.  Those of (128, 4, 4) fit a CU twice all the same, at 123 to 128 registers (at 129, dK with the
+// unit-norm option, B H = 64, N = 4096: 92 us instead of 74); (128, 4, 8) takes 136 to 143 and (64, 4, 16) 140 to 149.  (Kernels that
 // wanted 139 spilled when they were held to 128 and took 1.6 times as long.)
 template <class C, bool UNIT, bool INTRA>
 constexpr int grad_waves_per_simd()
@@ -385,7 +385,12 @@ void grad_kernel(KArgs a, const bf16raw *Xr, const bf16raw *V, const bf16raw *G_
         return z;
     };
     auto finish_projection = [&](int i, int it, f32x4 z) __attribute__((always_inline)) {
-        const int lo = kRebuild ? rebuilt_lane() : lane, n = lo & 15, q = lo >> 4;
+        int n = n16, q = q16;
+        if constexpr (INTRA && UNIT && SIDE == 1 && G::TS == 2) {       // (129 registers with this address kept: see grad_waves_per_simd())
+            const int lo = rebuilt_lane();
+            n = lo & 15;
+            q = lo >> 4;
+        }
         const int quad = 4 * (i >> 1) + q, slot16 = opaque_uniform((4 * (i >> 1) * kTile + 16 * (i & 1)) * 16, step) + (q * kTile + n) * 16;
         if (UNIT) z = z * buf_nrm(it)[16 * (i & 1) + n];
         f32x4 sv, uv;
@@ -408,11 +413,10 @@ void grad_kernel(KArgs a, const bf16raw *Xr, const bf16raw *V, const bf16raw *G_
     // (the reader's hashed rows of this wavefront's tables: used in the second half)
     constexpr int kTh = G::T16 && G::TS == 1 ? 2 : 1;      // R = 16: halves of the tile's tokens
     float rc[G::TPW * kTh][C::P];
-    // A tile's first half follows the second half of the tile before it in the loop's body.  (The causal kernels of 32 registers of
-    // statistics whose other registers leave a CU no room for a second workgroup have it in order: dQ and dK at B H = 64, N = 4096, (128,
-    // 8, 4): 83.2 and 85.8 against 81.7 and 83.2 us; (64, 16, 4): 106.8 and 109.5 against 105.0 and 107.4.  (128, 4, 4) needs 130
-    // registers that way and has the CU for itself.)
-    constexpr bool kRotate = !G::T16 || !INTRA || G::TS == 2 || G::SREGS > 32;
+    // A tile's first half follows the second half of the tile before it in the loop's body.  (The causal kernels of (128, 8, 4) have it in
+    // order: dQ and dK at B H = 64, N = 4096, 83.2 and 85.8 against 81.7 and 83.2 us.  (128, 4, 4) needs 130 registers that way and has the
+    // CU for itself; (64, 16, 4) with the unit-norm option takes 2 to 3 % more, (128, 16, 4) 2 %.)
+    constexpr bool kRotate = !G::T16 || !INTRA || G::TS == 2 || G::TPW > 1;
     auto first_half = [&](int it, bool first) __attribute__((always_inline)) {
         const int64_t t0 = existing_t0(it);
         const int nvalid = tile_nv(t0);
@@ -476,10 +480,12 @@ void grad_kernel(KArgs a, const bf16raw *Xr, const bf16raw *V, const bf16raw *G_
             *reinterpret_cast<u32x2 *>(dst) = u32x2{pack2(tt[0], tt[1]), pack2(tt[2], tt[3])};
         }
     };
-    if (kRotate && ntiles > 0) first_half(0, true);
+    if constexpr (kRotate) {
+        if (ntiles > 0) first_half(0, true);
+    }
     for (int it = 0; it < ntiles; ++it) {
         step = it;
-        if (!kRotate) first_half(it, it == 0);
+        if constexpr (!kRotate) first_half(it, it == 0);
         const int64_t t0 = tile_t0(it);
         const int nvalid = tile_nv(t0);
         __syncthreads();
@@ -691,7 +697,7 @@ void grad_kernel(KArgs a, const bf16raw *Xr, const bf16raw *V, const bf16raw *G_
                 }
             }
         }
-        if (kRotate) first_half(it + 1, false);
+        if constexpr (kRotate) first_half(it + 1, false);
     }
     // (R = 64 comes past the end of the last tile and forms its dX there: with the loop left in the middle the statistics of the long
     // sequences are spilled, and both gradients take 4 % more)
