@@ -717,22 +717,27 @@ KArgs make_kargs(const Plan &p, char *ws)
     return a;
 }
 
-// Where the forward's passes hash the rows they read: wherever their workgroups fill a good part of the chip, or have few tiles each.
-// Hashing is then work next to the latencies of a tile, 0.9 to 1.2 us of it over both passes; a kernel of its own, which spreads any
-// problem over the chip, takes 4 us and the memory's time, (4 d + 8 L P) bytes a token and head, for it.  The two meet at 150
-// workgroups of 32-token tiles at 512 bucket rows, and at 220 to 280 at 256 and 64, of which a CU takes two.  (Training steps of 4.2
-// million rows of 128 columns, L = 8, P = 6, 512 workgroups: 10.55 -> 10.16 ms; 64 columns, L = 16, P = 4, not causal, 1 million rows, 512
-// workgroups: 1105 -> 1045 us; a prompt of 120 044 rows and its state, 252 workgroups: 241 -> 218 us.  With 8 to 96 workgroups of 32
-// tiles, a caller's chunk of 1024: 69 -> 89, 314 -> 342, 252 -> 270, 267 -> 286 us.)
-bool hash_in_passes(const Plan &p)
-{
-    const int64_t tiles = (std::min(p.seg_len, p.N) + kTile - 1) / kTile;
-    return static_cast<int64_t>(p.BH) * p.nseg >= 160 * mfma_workgroups_per_cu(p) || tiles <= 4;
-}
-
 // Whether anything reads the key and value totals of the forward pass: the only segment of a causal sequence starts from zeros.  (A step of
 // two heads of 302 tokens, (128, 4, 4), without them and the two scans: 94.7 -> 89.9 us.)
 bool wants_totals(const Plan &p) { return !p.causal || p.nseg > 1; }
+
+// Whether the passes that read rows hash them as well.  That is work next to the latencies of a tile: 1.1 us a tile over both passes.  A
+// kernel of its own spreads any problem over the chip; it takes its launch, launch_us, and the memory's time, (4 d + 8 L P) bytes a token
+// and head: 1.1 us for a tile each of as many workgroups as 145 000 over those bytes, 142 to 227.  Kernel minus passes, forward calls in a
+// graph, us, (128, 8, 6), causal, at 16, 64, 128, 192, 256 workgroups: 2 tiles +0.6 +0.8 +4.1 +4.1 +6.2; 4 tiles -0.9 +0.2 +4.7 +4.0 +4.7; 8
+// tiles -3.3 +0.8 +4.3 +4.5 +7.2; 32 tiles -16 -10 -3 +10 +17; (64, 16, 4) of 32 tiles -22 -18 -12 -4 -1, (128, 4, 4) -20 -15 -9 -4 +3.
+// (128, 8, 4) fits a CU twice where it does not hash and once where it does: its passes' time goes by rounds of 256 workgroups.  (Not
+// causal, 32 tiles, 288 and 512 workgroups: 154 and 214 us with the kernel, 186 and 208 in the passes.)
+bool hashing_pays(const Plan &p, double launch_us)
+{
+    const int64_t tiles = (std::min(p.seg_len, p.N) + kTile - 1) / kTile, groups = static_cast<int64_t>(p.BH) * p.nseg;
+    const int64_t rounds = p.LRc == 128 ? (groups + 255) / 256 : 1;
+    const double tile_us = 1.1 * static_cast<double>(tiles), row_bytes = 4.0 * p.d + 8.0 * p.Lc * p.Pc;
+    return tile_us * static_cast<double>(rounds) <= launch_us + tile_us * static_cast<double>(groups) * row_bytes / 145e3;
+}
+
+// The forward pass (its totals K's rows, its replay Q's), and the totals of the taps and of a decoding state.
+bool hash_in_passes(const Plan &p) { return hashing_pays(p, 3.5); }
 
 // Hashed rows of X, and of X1 if there is one.
 template <class C>
@@ -835,7 +840,9 @@ hipError_t bwd_t(const Plan &p, const void *Q, const void *K, const void *V, con
     // these behind: its scan is in place and its streaming pass only reads them); then the statistics of
     // (phi_Q, read-out cotangents) at segment ends
     if (!p.fwd_state_kept) {
-        const bool in_passes = wants_totals(p) && hash_in_passes(p);
+        // (no pass over Q comes that could hash it, and the kernel for it is launched in any case: K's rows leave it where the memory's
+        // time alone is more than a pass's work)
+        const bool in_passes = wants_totals(p) && hashing_pays(p, 0.0);
         RACE_TRY((launch_hash<C>(p, a, Q, a.Mq, in_passes ? nullptr : K, a.Mk, st)));
         if (wants_totals(p)) RACE_TRY((launch_totals<C, 0>(p, a, a.Mk, in_passes ? K : nullptr, V, nullptr, nullptr, nullptr, st)));
         RACE_TRY(scan_states("segment_scan", a.state, p.nseg, p.BH, C::STATE, p.causal ? kScanPrefixOpen : kScanTotal, st));

@@ -144,3 +144,23 @@ def test_one_causal_segment_launches_no_totals_of_its_own(shape, BH, N):
         launched.append(set(ra.race_attn_profile_read()))
         ra.race_attn_profile_enable(False)
     assert launched == [{"hash_rows", "stream_forward"}, {"hash_rows", "stream_totals_qg", "stream_grad_v", "grad_q", "grad_k"}]
+
+
+@pytest.mark.parametrize("shape,BH,N,chunk,in_passes", [
+    ((64, 16, 4), 6, 6000, 0, True), ((128, 4, 4), 6, 6000, 0, True),           # a workgroup for nearly every CU
+    ((128, 8, 6), 4, 1000, 128, False), ((128, 8, 6), 16, 1000, 128, True),     # four tiles each: 32 workgroups, 128
+    ((128, 8, 6), 4, 1000, 64, True),                                           # two tiles each
+    ((128, 8, 4), 36, 8192, 1024, False), ((128, 8, 4), 64, 8192, 1024, True),  # one round of workgroups and a bit, two rounds
+], ids=str)
+def test_where_rows_are_hashed(shape, BH, N, chunk, in_passes):
+    d, L, P = shape
+    w = Workload("where", 1, BH, N, d, L, P, 2.0, True, "bf16", chunk=chunk)
+    Q, K, V, _ = synth.make_inputs(w, "cuda")
+    desc = desc_of(w)
+    ws = torch.empty(ra.race_attn_workspace_bytes(desc), dtype=torch.uint8, device="cuda")
+    ra.race_attn_profile_enable(True)
+    ra.race_attn_fwd(desc, Q, K, V, synth.projection_seeds(w), workspace=ws)
+    torch.cuda.synchronize()
+    names = set(ra.race_attn_profile_read())
+    ra.race_attn_profile_enable(False)
+    assert ("hash_rows" not in names) == in_passes
