@@ -60,14 +60,18 @@ def kernel_shares(w):
     }
 
 
-def launched_shares(w, launched):
-    """kernel_shares() for the kernels of a step: where no kernel of its own hashes the rows, its share goes to the passes
-    that do: K's half to the totals of (phi_K, [V | 1]), Q's to the output."""
+def launched_shares(w, launches, recompute=False):
+    """kernel_shares() for the kernels of a step (launches: of each in a step), per launch.  Where the forward pass launches no kernel of
+    its own for the hashing, that kernel's share goes to the passes that hash: K's half to the totals of (phi_K, [V | 1]), Q's to
+    the output.  A backward pass without the forward's workspace (recompute) launches the kernel in any case: for Q's rows where
+    the forward's totals hash K's."""
     shares = kernel_shares(w)
-    if "hash_rows" not in launched:
+    if launches.get("hash_rows", 0) <= (1 if recompute else 0):
         flops, nbytes = shares.pop("hash_rows")
         for name in ("stream_totals_kv", "stream_forward"):
             shares[name] = (shares[name][0] + flops / 2, shares[name][1] + nbytes / 2)
+        if recompute:
+            shares["hash_rows"] = (flops / 2, nbytes / 2)
     return shares
 
 
@@ -247,7 +251,7 @@ def main() -> int:
     roofline = None
     kernels = {}
     if prof:
-        shares = launched_shares(w, prof)
+        shares = launched_shares(w, {name: n / args.steps for name, (_, n) in prof.items()}, args.bwd_recompute)
         table, table_note = measured_traffic(w) if family == 2 else (None, "no counter summary for the generic kernels")
         mfma = family == 2
         flop_peak = PEAK_BF16_FLOPS if mfma else PEAK_FP32_VECTOR_FLOPS

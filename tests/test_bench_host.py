@@ -27,6 +27,22 @@ def test_kernel_credits_add_up_to_the_algorithmic_counts():
         assert shares["stream_totals_kv"] == shares["stream_totals_qg"] == shares["segment_scan"] == (0.0, 0.0)
 
 
+def test_credits_follow_the_kernels_that_hash():
+    for w in (synth.C2, synth.C3, synth.C5, synth.G44):
+        proj, U, nbytes = bench.algorithmic_counts(w)
+        once = {k: 2 if k == "segment_scan" else 1 for k in MFMA_KERNELS}
+        by_kernel, in_passes = bench.launched_shares(w, once), bench.launched_shares(w, {k: n for k, n in once.items() if k != "hash_rows"})
+        assert by_kernel == bench.kernel_shares(w) and "hash_rows" not in in_passes
+        for shares in (by_kernel, in_passes):
+            assert sum(shares[k][0] for k in MFMA_KERNELS if k in shares) == 3 * proj + 6 * U
+            assert sum(shares[k][1] for k in MFMA_KERNELS if k in shares) == nbytes
+        # a recomputing backward pass launches the kernel once: for Q alone where the forward hashed in its passes, else it is the second
+        again = bench.launched_shares(w, once, recompute=True)
+        assert again.pop("hash_rows") == (proj / 2, 2 * w.d * (2 if w.dtype == "bf16" else 4) / 2)
+        assert again == in_passes
+        assert bench.launched_shares(w, dict(once, hash_rows=2), recompute=True) == by_kernel
+
+
 def test_headline_counts_are_the_published_ones():
     proj, U, nbytes = bench.algorithmic_counts(synth.C5)
     assert (proj, U, nbytes) == (24576, 132096, 3080) and 3 * proj + 6 * U == 866304
