@@ -17,9 +17,9 @@
 //   C/D      : column n, rows 8*(v/4) + 4h + v%4 for register v = 0..15.
 // An accumulator tile is fed back as a B operand without touching LDS: registers 8s..8s+7 of the
 // tile, packed to bf16, are the B operand of k-step s if k-slot (h, e) is taken to mean row
-// 16s + 8*(e/4) + 4h + e%4.  The other operand must use the same k order; tiles that are contracted
-// against such operands keep their feature dimension "pair-interleaved" in LDS (il()): inside every
-// group of 16 features the two middle blocks of 4 are swapped, so that the 8 features a lane needs
+// 16s + 8*(e/4) + 4h + e%4.  The other operand must use the same k order; assignment tiles, which are contracted
+// against such operands, keep their bucket rows "pair-interleaved" in LDS (il()): inside every
+// group of 16 the two middle blocks of 4 are swapped, so that the 8 a lane needs
 // are one aligned 16-byte read.
 // LDS bank arithmetic as measured on gfx950 (64 banks of 4 bytes, 256 bytes per clock for reads: 16-byte
 // accesses go 16 lanes at a time, 8-byte ones 32 lanes): rows read 16 bytes per lane want a row stride of
@@ -92,7 +92,7 @@ struct Cfg {
     static_assert(L == 4 || L % 8 == 0, "tables over the eight half wavefronts of a side");
     static_assert(RG >= 1 && LR % (32 * RG) == 0 && NT % CG == 0 && NTW >= 1, "bucket rows and columns over the wavefronts");
     static_assert(D % 64 == 0 && P >= 4, "shape (assignments are written for pairs of high-bit indices)");
-    static_assert(4 % NG == 0 && NG <= 4 && PT <= 4, "groups of packed rows must divide four wavefronts");
+    static_assert(PT <= 4, "tiles of packed rows over the wavefronts that project them");
 };
 
 // Scheduling fence: keeps the instruction scheduler from hoisting the loads and conversions of later
@@ -151,7 +151,7 @@ struct KArgs {
     float beta, inv_tables;
     int L_real, P_real;    // the problem's tables and hyperplanes (<= the compiled shape's)
     __host__ __device__ Soft soft() const { return Soft{beta, L_real, P_real}; }
-    const bf16raw *Wp;     // (H, LPP, D) bf16, rows in projection-group order
+    const bf16raw *Wp;     // (H, LPP, D) bf16, rows table by table (see Cfg::PP)
     float *state;          // (BH, nseg, STATE) fp32
     float *Mq, *Mk;        // (BH, ceil(N / 32), 32 * L * P) fp32: the hashed rows of Q and K, tile by tile (see Cfg::HT)
     float *ge;             // (BH, N) fp32: extra column of the read-out cotangents (backward only)
@@ -199,7 +199,7 @@ __device__ __forceinline__ float dot2(uint32_t a, uint32_t b, float c)
 constexpr uint32_t kOnePair = 0x3F803F80u;     // (1.0, 1.0)
 // row of accumulator register v for lane half h
 __device__ __forceinline__ int acc_row(int v, int h) { return 8 * (v >> 2) + 4 * h + (v & 3); }
-// pair-interleaved position of feature c: bits 2 and 3 of the index swapped
+// pair-interleaved position of bucket row c: bits 2 and 3 of the index swapped
 __device__ __forceinline__ constexpr int il(int c) { return (c & ~12) | ((c & 4) << 1) | ((c & 8) >> 1); }
 
 // ---------------------------------------------------------------- transposing operand reads
@@ -361,38 +361,26 @@ __device__ __forceinline__ void fetch_rows(const bf16raw *X, int64_t t0, int nva
     }
 }
 
-// Column order of a row-major tile: as they are; pair-interleaved in groups of 16 (il()); or in groups of 32, where the
-// eight features {4q .. 4q+3, 16 + 4q .. 16 + 4q+3} that a lane of a 16 x 16 x 32 product holds in two accumulator tiles are
-// neighbours (position 8 q + 4 (c / 16) + c % 4).
-enum Order { kPlain = 0, kPairs16 = 1, kPairs32 = 2 };
-// One 16-byte chunk (columns 8ch .. 8ch+7) into row-major tile `dst` with row stride STRIDE; in either interleaved order the
-// chunk's two blocks of 4 land 8 positions apart.
-template <int STRIDE, int IL>
-__device__ __forceinline__ void store_chunk(bf16raw *dst, int row, int ch, u32x4 v)
-{
-    if (IL) {
-        bf16raw *p = dst + row * STRIDE + (IL == kPairs16 ? 16 * (ch >> 1) + 4 * (ch & 1) : 32 * (ch >> 2) + 16 * (ch & 1) + 4 * ((ch >> 1) & 1));
-        *reinterpret_cast<u32x2 *>(p) = u32x2{v.x, v.y};
-        *reinterpret_cast<u32x2 *>(p + 8) = u32x2{v.z, v.w};
-    } else {
-        *reinterpret_cast<u32x4 *>(dst + row * STRIDE + ch * 8) = v;
-    }
-}
+// Column order of a row-major tile: as they are; or, in groups of 32, the eight features {4q .. 4q+3, 16 + 4q .. 16 + 4q+3} that a lane
+// of a 16 x 16 x 32 product holds in two accumulator tiles as neighbours (position 8 q + 4 (c / 16) + c % 4; a 16-byte chunk's two
+// blocks of 4 land 8 positions apart).
+enum Order { kPlain = 0, kPairs32 = 1 };
 
-// ... of a 32-row tile, every thread's chunk at the byte offset `at` from the tile (its place under STRIDE, worked out once per kernel).
-template <class C, int STRIDE, int IL>
+// A 32-row tile, every thread's chunk (columns 8 ch .. 8 ch + 7 of its row) at the byte offset `at` from the tile (its place under STRIDE,
+// worked out once per kernel).
+template <class C, int STRIDE, int ORDER>
 __device__ __forceinline__ int chunk_offset(int tid)
 {
     const int row = tid / C::CPR, ch = tid % C::CPR;
-    return (row * STRIDE + (IL == kPlain ? 8 * ch : IL == kPairs16 ? 16 * (ch >> 1) + 4 * (ch & 1) : 32 * (ch >> 2) + 16 * (ch & 1) + 4 * ((ch >> 1) & 1))) * 2;
+    return (row * STRIDE + (ORDER == kPlain ? 8 * ch : 32 * (ch >> 2) + 16 * (ch & 1) + 4 * ((ch >> 1) & 1))) * 2;
 }
-template <class C, int IL>
+template <class C, int ORDER>
 __device__ __forceinline__ void store_tile(const RowChunks<C, kTile> &r, unsigned char *at)
 {
     static_assert(RowChunks<C, kTile>::N == 1, "one chunk per thread at most");
     if (!RowChunks<C, kTile>::EVEN && threadIdx.x >= kTile * C::CPR) return;
     const u32x4 v = r.v[0];
-    if (IL == kPlain) {
+    if (ORDER == kPlain) {
         *reinterpret_cast<u32x4 *>(at) = v;
     } else {
         *reinterpret_cast<u32x2 *>(at) = u32x2{v.x, v.y};
@@ -400,14 +388,15 @@ __device__ __forceinline__ void store_tile(const RowChunks<C, kTile> &r, unsigne
     }
 }
 
-template <class C, int ROWS, int STRIDE = C::XS, int IL = kPlain>
+// Rows, chunk by chunk, into a tile of row stride STRIDE, columns as they are.
+template <class C, int ROWS, int STRIDE = C::XS>
 __device__ __forceinline__ void store_rows(const RowChunks<C, ROWS> &r, bf16raw *dst, int step)
 {
     const uint32_t tid = opaque(static_cast<int>(threadIdx.x), step) & (kThreads - 1);      // keeps the tile addresses out of long-lived registers
 #pragma unroll
     for (int k = 0; k < RowChunks<C, ROWS>::N; ++k) {
         const uint32_t c = tid + k * kThreads, row = c / C::CPR, ch = c % C::CPR;
-        if (RowChunks<C, ROWS>::EVEN || row < ROWS) store_chunk<STRIDE, IL>(dst, row, ch, r.v[k]);
+        if (RowChunks<C, ROWS>::EVEN || row < ROWS) *reinterpret_cast<u32x4 *>(dst + static_cast<int>(row) * STRIDE + static_cast<int>(ch) * 8) = r.v[k];
     }
 }
 
@@ -478,7 +467,7 @@ __device__ __forceinline__ void store_cotangent(const CotChunks<C, ROWS> &r, bf1
             dot = dot2(out[e], ow[e], dot);
         }
         const u32x4 v = {out[0], out[1], out[2], out[3]};
-        if (row < ROWS) store_chunk<STRIDE, kPlain>(dst, row, ch, v);
+        if (row < ROWS) *reinterpret_cast<u32x4 *>(dst + row * STRIDE + ch * 8) = v;
         if (row < nvalid) *reinterpret_cast<u32x4 *>(gbase + static_cast<uint32_t>((row * C::D + ch * 8) * 2)) = v;
         // the CPR threads of one row are consecutive lanes
 #pragma unroll

@@ -88,12 +88,12 @@ struct GradLds {
     static constexpr int QUADS = C::L * C::PP / 4;
     static constexpr int s2 = (rad + (UNIT ? kWaves * kTile * 4 : 0) + 15) & ~15;     // [QUADS][32] float4: 1 - tanh^2 z of four hyperplanes
     static constexpr int zz = s2 + QUADS * kTile * 16;                  // [QUADS][32] float4: z
-    static constexpr int yr = zz + (UNIT ? QUADS * kTile * 16 : 0);     // [2][32][XS] reader-Y rows, pair-interleaved columns
+    static constexpr int yr = zz + (UNIT ? QUADS * kTile * 16 : 0);     // [2][32][XS] reader-Y rows, columns in YORDER
     static constexpr int yr_bytes = kTile * C::XS * 2;
     static constexpr int xr = yr + 2 * yr_bytes;                        // [XB][32][XS] reader rows
     static constexpr int xr_bytes = kTile * C::XS * 2;
     static constexpr int ttop = xr + XB * xr_bytes;                     // [2][64] x 16 B: masked in-tile term as MFMA operands
-    static constexpr int yw = ttop + (INTRA ? 2 * 64 * 16 : 0);         // [2][32][YS] writer-Y rows, pair-interleaved columns
+    static constexpr int yw = ttop + (INTRA ? 2 * 64 * 16 : 0);         // [2][32][YS] writer-Y rows, columns in YORDER
     static constexpr int yw_bytes = kTile * C::YS * 2;
     static constexpr int phw = yw + (INTRA ? 2 * yw_bytes : 0);         // [32][PS or PST] writer assignments
     static constexpr int mass = phw + (INTRA ? kTile * (G::T16 ? C::PST : C::PS) * 2 : 0); // R = 16: [kWaves][TPW * 16] fp32: extra column of each wavefront's rows
@@ -251,7 +251,7 @@ void grad_kernel(KArgs a, const bf16raw *Xr, const bf16raw *V, const bf16raw *G_
     static_assert(S::DZS == S::WTS, "one offset for both operands of dX");
     auto operand = [&](const unsigned char *p, int bytes) __attribute__((always_inline)) { return *reinterpret_cast<const u32x4 *>(p + bytes); };
     // rows: requested two tiles ahead, written to LDS one tile ahead (the reader's in the second half of a tile, behind its
-    // projection; the others in the first)
+    // projection; the others there as well for R = 64, in the first half for R = 16)
     RowChunks<C, kTile> pre_r, pre_v, pre_g;
     float pre_ge = 0.f;
     auto fetch_y = [&](int it) __attribute__((always_inline)) {

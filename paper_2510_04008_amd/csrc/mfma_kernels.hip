@@ -2,8 +2,8 @@
 //
 // Kernels
 //   hashed rows      projection and per-bit soft-hash masses of every row of Q and K, once per call: one float per token, table and
-//                    hyperplane that every later pass rebuilds phi from.  The totals of the forward pass form K's, its replay
-//                    Q's (Hasher); hash_kernel forms Q's for a backward pass without the forward's workspace.
+//                    hyperplane that every later pass rebuilds phi from.  Formed by hash_kernel or, by a rule on the sizes
+//                    (hashing_pays()), in the passes of the forward: the totals form K's, the replay Q's (Hasher).
 //   totals_kernel    statistics of every segment from a zero start, of (phi_K, [V | 1]) (Algorithm 1, step 5) or, for the
 //                    backward pass, of (phi_Q, read-out cotangents); an exclusive prefix (forward) or suffix (backward)
 //                    scan over segments (scan_states) turns them into segment-start states.
@@ -34,7 +34,7 @@ __device__ __forceinline__ int state_a(int r) { return C::LR * C::D + r; }
 
 // ================================================================ hash_kernel
 // Algorithm 1, steps 2-4 up to the per-bit masses, for every row of a tensor (blockIdx.z: of one or the other): one float per (table,
-// hyperplane), see bit_code().  For calls whose passes do not hash for themselves: see hash_in_passes(), and race_attn_bwd, whose
+// hyperplane), see bit_code().  For calls whose passes do not hash for themselves: see hashing_pays(), and race_attn_bwd, whose
 // pass over Q would be the forward's.  The same arithmetic as theirs (Hasher), the rows straight from memory: no LDS, no barrier.
 // Bound by the latency of one tile where there are few, by memory where there are many.  (Q and K of two sequences of 2000 tokens, (128, 8,
 // 6), all shares of a tile in one wavefront: 6.3 us, each in its own 4.8; of eight of 5000, (128, 8, 4), in shares of the passes' eight half
@@ -115,8 +115,10 @@ __device__ __forceinline__ int tile_row(int r_own, int mt, int cg) { return r_ow
 
 // HASH (QG == 0): hashes the rows of K (X) itself and leaves the hashed rows in memory (M; null: nobody reads them): the pass over K that
 // hashed it before, and the pass over its hashed rows here, are one.  Next to the products' latencies the projection and the
-// exponentials cost less than their own kernel at the memory's rate (see hash_in_passes()).  Else M are the hashed rows of K or,
-// QG == 1, of Q.  QG == 1 also leaves the
+// exponentials cost less than their own kernel at the memory's rate (see hashing_pays()), also at (128, 4, 16) and (64, 6, 8), where they
+// take the second workgroup's place on a CU (160 to 164 registers, 118 to 122 without; held to 128 the first spills, the second's LDS is
+// past 80 KB with the rows of K).  B H = 64, N = 8192, causal, us, kernel for Q and K, totals, replay: 108 + 59 + 191, in the passes 100 + 235;
+// (64, 6, 8) 67 + 64 + 209, 91 + 215.  Else M are the hashed rows of K or, QG == 1, of Q.  QG == 1 also leaves the
 // cotangent rows it forms in memory, rows in Gout (the caller's buffer for dK, which nothing else uses before dK is
 // written, tile behind tile of its own reading) and the extra column in a.ge: the passes behind it then read 260 bytes a token instead of dO,
 // O and Den, and do not form the rows again (35 of 750 vector instructions a tile and wavefront).
@@ -289,7 +291,7 @@ struct StreamLds {
 
 // NC: not causal (the in-tile term and the update are compiled out).
 // Mr, Mw: the hashed rows of the reader and the writer tensor.  HASH (kForward): hashes the reader's rows itself (X: Q) and leaves them
-// in Mr, see hash_in_passes().
+// in Mr, see hashing_pays().
 template <class C, int MODE, bool NC, bool HASH, bool UNIT>
 __global__ __launch_bounds__(kThreads, C::STREAM_WAVES_PER_SIMD)
 void stream_kernel(KArgs a, float *Mr, const float *Mw, const bf16raw *X, const bf16raw *Y, bf16raw *Out, float *den_out)
